@@ -295,7 +295,8 @@ def main():
             ms = timed(lambda: B.quaternary_gemm(qa, qw, 4096, 4096, 4096, fmt, acc_out=acc), 3 if fmt == B.RTN_CODE_BITPLANE else 10)
             ta, _ = B.ternarize_pack(x1, 0.33, 0.66, fmt)
             tw, _ = B.ternarize_pack(x2, 0.33, 0.66, fmt)
-            mt = timed(lambda: B.ternary_gemm(ta, tw, 4096, 4096, 4096, fmt=fmt, acc_out=acc, want_acc=True),
+            mt = timed(lambda: B.ternary_gemm(ta, tw, 4096, 4096, 4096, fmt=fmt, acc_out=acc, want_acc=True,
+                                              path=B.RTN_PATH_POPC if fmt == B.RTN_CODE_BITPLANE else B.RTN_PATH_AUTO),
                        3 if fmt == B.RTN_CODE_BITPLANE else 10)
             rowsq[name] = dict(quaternary_us=round(ms * 1e3, 1), quaternary_tmacs=round(macs / ms / 1e9, 1),
                                ternary_us=round(mt * 1e3, 1), ternary_tmacs=round(macs / mt / 1e9, 1),
@@ -389,8 +390,9 @@ def main():
                                         garg(case["beta_w"]), sa, sw)
                         y = torch.empty((M, NK), dtype=torch.float32, device=dev)
                         reps = 2 if name == "popcount" else 5
+                        path = B.RTN_PATH_POPC if name == "popcount" else B.RTN_PATH_AUTO
                         for _ in range(2):
-                            B.ternary_gemm(ca, cw, M, NK, NK, fmt=fmt, ep=ep, y_out=y)
+                            B.ternary_gemm(ca, cw, M, NK, NK, fmt=fmt, path=path, ep=ep, y_out=y)
                         # the better of two timing passes: a pass now and then catches a stall of tens
                         # of milliseconds that has nothing to do with the kernels (same launches, no
                         # allocation inside)
@@ -399,7 +401,7 @@ def main():
                             e0, e1, e2 = ev(enable_timing=True), ev(enable_timing=True), ev(enable_timing=True)
                             e0.record()
                             for _ in range(reps):
-                                B.ternary_gemm(ca, cw, M, NK, NK, fmt=fmt, ep=ep, y_out=y)
+                                B.ternary_gemm(ca, cw, M, NK, NK, fmt=fmt, path=path, ep=ep, y_out=y)
                             e1.record()
                             for _ in range(reps):
                                 B.ternarize_pack(xa, -0.5, 0.5, fmt, codes=ca, sum_t=sa)   # into the resident buffers

@@ -84,10 +84,11 @@ typedef enum { RTN_ROWS_K_CONTIG = 0, RTN_NCHW = 1 } rtn_layout;
 typedef enum { RTN_PAD_TRUE_ZERO = 0, RTN_PAD_CODE_ZERO = 1 } rtn_pad_mode;
 
 /* Contraction strategy.  MFMA_I8: int8 matrix cores on RTN_CODE_I8 codes.
- * POPC: Eq.8 (AND / XOR / popcount) on RTN_CODE_BITPLANE codes.
+ * POPC: Eq.8 (AND / XOR / popcount, on the vector ALU) on RTN_CODE_BITPLANE codes.
  * MFMA_FP4: FP4 matrix cores with fp32 accumulation on RTN_CODE_FP4 codes (every
  * product is exact and the sums are integers below 2^24, so D is the same integer).
- * AUTO picks the one that matches the code format.                           */
+ * AUTO picks the fastest one for the code format: the matrix cores for all three (bit
+ * planes are expanded to FP4 in registers, on their way into the matrix instruction).  */
 typedef enum { RTN_PATH_AUTO = 0, RTN_PATH_MFMA_I8 = 1, RTN_PATH_POPC = 2, RTN_PATH_MFMA_FP4 = 3 } rtn_path;
 
 /* Four-term reparameterization applied to an accumulator D (Eq.9 with a weight

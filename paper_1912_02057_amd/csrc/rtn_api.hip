@@ -192,6 +192,8 @@ int rtn_ternary_gemm(rtn_code_format fmt, rtn_path path, const void* a_codes, co
     if (fmt != RTN_CODE_I8 && fmt != RTN_CODE_BITPLANE && fmt != RTN_CODE_FP4) return RTN_ERR_UNSUPPORTED;
     if (path != RTN_PATH_AUTO && path != RTN_PATH_MFMA_I8 && path != RTN_PATH_POPC && path != RTN_PATH_MFMA_FP4)
         return RTN_ERR_UNSUPPORTED;
+    // bit planes run on the matrix cores too, unless the caller asks for the popcount pattern
+    const bool planes_mfma = fmt == RTN_CODE_BITPLANE && path == RTN_PATH_AUTO;
     if (path == RTN_PATH_AUTO)
         path = fmt == RTN_CODE_I8 ? RTN_PATH_MFMA_I8 : (fmt == RTN_CODE_FP4 ? RTN_PATH_MFMA_FP4 : RTN_PATH_POPC);
     if ((path == RTN_PATH_MFMA_I8) != (fmt == RTN_CODE_I8)) return RTN_ERR_UNSUPPORTED;
@@ -227,7 +229,7 @@ int rtn_ternary_gemm(rtn_code_format fmt, rtn_path path, const void* a_codes, co
         p.acc = acc_out;
         p.y = y_out;
         p.ep = e;
-        he = rtn::launch_gemm_popc(p, st);
+        he = planes_mfma ? rtn::launch_gemm_planes(p, st) : rtn::launch_gemm_popc(p, st);
     }
     return he == hipSuccess ? RTN_OK : hip_fail(he);
 }

@@ -177,6 +177,8 @@ struct PopcArgs {
     EpiArgs ep;
 };
 hipError_t launch_gemm_popc(const PopcArgs& a, hipStream_t st);
+// the same contraction with the planes expanded to FP4 in registers for the matrix cores
+hipError_t launch_gemm_planes(const PopcArgs& a, hipStream_t st);
 
 // The quaternary comparison system (values 0..3): quantize + pack of rows, and the bit-serial
 // dot product on bit planes.  The matrix-core forms go through launch_gemm_mfma.

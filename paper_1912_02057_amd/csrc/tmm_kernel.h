@@ -200,6 +200,130 @@ __device__ __forceinline__ void wait_groups(int groups)
         wait_vm<3 * DPS>();
 }
 
+// Output tile of this workgroup (false: none).  Workgroups are dealt to the 8 XCDs round-robin by
+// blockIdx; give each XCD (and so each L2) one contiguous run of tiles, P-tile index fastest, so
+// tiles that share operand rows and conv halo pixels share an L2.  Within that run, tiles are
+// visited in bands of up to 8 P-tiles, P fastest, so the 32 co-resident tiles of an XCD form an
+// 8 x 4 patch of the output (12 operand row-blocks per K-step instead of 18 for a 16 x 2 strip).
+__device__ __forceinline__ bool block_tile(const TmmParams& prm, int& tileP, int& tileQ)
+{
+    const int chunk = (int)(gridDim.x >> 3);  // grid is padded to a multiple of 8
+    const int bid = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
+    if (bid >= prm.ntiles) return false;
+    const int band = (int)fastdiv((uint32_t)bid, prm.div_band);  // band = 8 * tilesQ tiles
+    const int inband = bid - band * prm.band_tiles;
+    const int bandw = prm.tilesP - band * 8 < 8 ? prm.tilesP - band * 8 : 8;
+    tileQ = bandw == 8 ? (inband >> 3) : inband / bandw;
+    tileP = band * 8 + inband - tileQ * bandw;
+    return true;
+}
+
+// The GEMM's epilogue on a wave's TP x TQ accumulator tiles at rows p0 + wrow, columns q0 + wcol:
+//   y = aw*(aa*D + ba*Sw) + bw*r2 with r2 = aa*Sa + K*ba per row m (Eq.9 with a weight offset),
+// ReLU and BN, one rounding to fp32; `tab` is LDS for [3][BP] doubles and may lie over the
+// operand stages.  value(acc) is the integer D as the accumulator's type.  SUMS: the side sums
+// exist (not for the weight-only form, whose beta_a and beta_w are 0).
+// The element loops exist in straight-line variants -- (interior / ragged tile) x (acc only / y
+// only / both), and y without ReLU and BN on interior tiles, which needs 4 fp64 operations per
+// output instead of 6 and fewer registers -- picked once per block.  The GEMM keeps plain
+// stores: its tiles finish together, and the cache absorbs that burst faster than HBM takes it.
+template <int BP, int TP, int TQ, bool SUMS, class Acc, class Value>
+__device__ __forceinline__ void gemm_epilogue(const TmmParams& prm, double* tab, int p0, int q0, int wrow, int wcol,
+                                              bool full_tile, const Acc& acc, Value value)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const EpiArgs& ep = prm.ep;
+    const bool has_bn = ep.bn_scale != nullptr;
+    // ReLU and BN are applied with neutral parameters when only the other is asked for:
+    // max(v, -inf) = v and 1*v + 0 = v exactly, so the element code has no selects.
+    const double relu_floor = __builtin_canonicalize(ep.relu ? 0.0 : -__builtin_inf());
+    __syncthreads();  // all waves are done with the operand stages
+    if (prm.y) {
+        for (int t = tid; t < BP; t += 256) {
+            const int m = p0 + t;
+            double aa = 0.0, ba = 0.0, r2 = 0.0;
+            if (m < prm.RP) {
+                aa = pval(ep.alpha_a, m);
+                ba = pval(ep.beta_a, m);
+                if (SUMS) r2 = aa * (double)ep.sum_ta[m] + (double)prm.Klogical * ba;
+            }
+            tab[t] = aa;
+            tab[BP + t] = ba;
+            tab[2 * BP + t] = r2;
+        }
+    }
+    __syncthreads();
+    const int64_t N = prm.RQ;
+    auto run = [&](auto full, auto want_acc, auto want_y, auto want_tail) {
+        constexpr bool FULL = decltype(full)::value, ACC = decltype(want_acc)::value, Y = decltype(want_y)::value;
+        constexpr bool TAIL = decltype(want_tail)::value;
+        // per lane: its TQ output columns, their factors and base pointers.  Set up
+        // inside each variant so that a variant holds only what it uses.
+        bool nok[TQ];
+        double aw[TQ], bw[TQ], bs[TQ], bh[TQ], sw[TQ];
+        int32_t* accp[TQ];
+        float* yp[TQ];
+#pragma unroll
+        for (int j = 0; j < TQ; ++j) {
+            const int ncol = q0 + wcol + j * 32 + (lane & 31);
+            nok[j] = FULL || ncol < prm.RQ;
+            aw[j] = bw[j] = bh[j] = sw[j] = 0.0;
+            bs[j] = 1.0;
+            if (Y && nok[j]) {
+                aw[j] = pval(ep.alpha_w, ncol);
+                bw[j] = pval(ep.beta_w, ncol);
+                if (SUMS) sw[j] = (double)ep.sum_tw[ncol];
+                if (TAIL && has_bn) {
+                    bs[j] = ep.bn_scale[ncol];
+                    bh[j] = ep.bn_shift ? (double)ep.bn_shift[ncol] : 0.0;
+                }
+            }
+            accp[j] = ACC ? prm.acc + (nok[j] ? ncol : 0) : nullptr;
+            yp[j] = Y ? prm.y + (nok[j] ? ncol : 0) : nullptr;
+        }
+#pragma unroll
+        for (int i = 0; i < TP; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int t = wrow + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                const int m = p0 + t;
+                const bool mok = FULL || m < prm.RP;
+                double aa = 0.0, ba = 0.0, r2 = 0.0;
+                if (Y) {
+                    aa = tab[t];
+                    ba = tab[BP + t];
+                    r2 = tab[2 * BP + t];
+                }
+                const int64_t rowoff = (int64_t)m * N;
+#pragma unroll
+                for (int j = 0; j < TQ; ++j) {
+                    if (FULL || (mok && nok[j])) {
+                        const auto D = value(acc[i][j][r]);
+                        if (ACC) accp[j][rowoff] = (int)D;
+                        if (Y) {
+                            double v = aw[j] * (aa * (double)D + ba * sw[j]) + bw[j] * r2;
+                            if (TAIL) v = bs[j] * __builtin_fmax(v, relu_floor) + bh[j];
+                            yp[j][rowoff] = (float)v;
+                        }
+                    }
+                }
+                // keep the scheduler from hoisting every later load up here (every 4 rows let the
+                // 256 x 256 tile spill: 60 against 54 us at 4096^3 with ReLU and BN)
+                if ((r & 1) == 1) __builtin_amdgcn_sched_barrier(0);
+            }
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    if (!prm.y)
+        full_tile ? run(yes, yes, no, no) : run(no, yes, no, no);
+    else if (prm.acc)
+        full_tile ? run(yes, yes, yes, yes) : run(no, yes, yes, yes);
+    else if (!full_tile)
+        run(no, no, yes, yes);
+    else
+        ep.relu || has_bn ? run(yes, no, yes, yes) : run(yes, no, yes, no);
+}
+
 // MINW = waves per SIMD the register allocation must leave room for.
 //
 // HC != 0 selects the halo variant of the conv (stride 1, KH = 2 pad + 1,
@@ -247,20 +371,8 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, lives in an SGPR
     const int wp = wave / WGQ, wq = wave % WGQ;
-    // Workgroups are dealt to the 8 XCDs round-robin by blockIdx; give each XCD
-    // (and so each L2) one contiguous run of tiles, P-tile index fastest, so
-    // tiles that share operand rows and conv halo pixels share an L2.
-    const int chunk = (int)(gridDim.x >> 3);  // grid is padded to a multiple of 8
-    const int bid = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
-    if (bid >= prm.ntiles) return;
-    // Within that run, tiles are visited in bands of up to 8 P-tiles, P fastest,
-    // so the 32 co-resident tiles of an XCD form an 8 x 4 patch of the output
-    // (12 operand row-blocks per K-step instead of 18 for a 16 x 2 strip).
-    const int band = (int)fastdiv((uint32_t)bid, prm.div_band);  // band = 8 * tilesQ tiles
-    const int inband = bid - band * prm.band_tiles;
-    const int bandw = prm.tilesP - band * 8 < 8 ? prm.tilesP - band * 8 : 8;
-    const int tileQ = bandw == 8 ? (inband >> 3) : inband / bandw;
-    const int tileP = band * 8 + inband - tileQ * bandw;
+    int tileP, tileQ;
+    if (!block_tile(prm, tileP, tileQ)) return;
     const int p0 = tileP * BP, q0 = tileQ * BQ;
     const ConvGeom& g = prm.g;
     // Wave priority falls along a block's life: the waves that still have to get
@@ -672,8 +784,6 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     // read: 92 us plain, 75 us with the hint).  An output that fits is stored about twice
     // as fast without the hint, and the kernel after it is not slowed (51 MB: 25 us
     // against 39 us for the pair).  The launch code decides (prm.nt_out).
-    // The GEMM keeps plain stores: its 256 tiles finish together, and the cache
-    // absorbs that burst faster than HBM takes it.
     // (a tag type, not a run-time test at the store: the compiler merges the two arms of such
     // a test into one plain store)
     const bool nt_out = CONV && prm.nt_out;
@@ -684,9 +794,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
             *ptr = value;
     };
     const EpiArgs& ep = prm.ep;
-    const bool has_bn = ep.bn_scale != nullptr;
-    // ReLU and BN are applied unconditionally with neutral parameters when off:
-    // max(v, -inf) = v and 1*v + 0 = v exactly, so the element code has no selects.
+    // ReLU and BN with neutral parameters when off, as in gemm_epilogue
     const double relu_floor = __builtin_canonicalize(ep.relu ? 0.0 : -__builtin_inf());
     double* tab = (double*)(smem + (CONV ? toff : 0));
     const bool full_tile = p0 + BP <= prm.RP && q0 + BQ <= prm.RQ;
@@ -710,90 +818,14 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
         }
     };
     auto dispatch = [&](auto&& run) {
-        if constexpr (CONV) {
-            if (nt_out) {
-                dispatch3(run, std::true_type{});
-                return;
-            }
-        }
-        dispatch3(run, std::false_type{});
+        if (nt_out)
+            dispatch3(run, std::true_type{});
+        else
+            dispatch3(run, std::false_type{});
     };
-    if (!CONV) {
-        __syncthreads();  // all waves are done with the operand stages
-        // y = aw*(aa*D + ba*Sw) + bw*r2 with r2 = aa*Sa + K*ba per row m; tab = [3][BP]
-        if (prm.y) {
-            for (int t = tid; t < BP; t += 256) {
-                const int m = p0 + t;
-                double aa = 0.0, ba = 0.0, r2 = 0.0;
-                if (m < prm.RP) {
-                    aa = pval(ep.alpha_a, m);
-                    ba = pval(ep.beta_a, m);
-                    if (DT != 1) r2 = aa * (double)ep.sum_ta[m] + (double)prm.Klogical * ba;
-                }
-                tab[t] = aa;
-                tab[BP + t] = ba;
-                tab[2 * BP + t] = r2;
-            }
-        }
-        __syncthreads();
-        const int64_t N = prm.RQ;
-        dispatch([&](auto full, auto want_acc, auto want_y, auto nt) {
-            constexpr bool FULL = decltype(full)::value, ACC = decltype(want_acc)::value,
-                           Y = decltype(want_y)::value;
-            // per lane: its TQ output columns, their factors and base pointers.  Set up
-            // inside each variant so that a variant holds only what it uses.
-            bool nok[TQ];
-            double aw[TQ], bw[TQ], bs[TQ], bh[TQ], sw[TQ];
-            int32_t* accp[TQ];
-            float* yp[TQ];
-#pragma unroll
-            for (int j = 0; j < TQ; ++j) {
-                const int ncol = q0 + wq * WQ + j * 32 + (lane & 31);
-                nok[j] = FULL || ncol < prm.RQ;
-                aw[j] = bw[j] = bh[j] = sw[j] = 0.0;
-                bs[j] = 1.0;
-                if (Y && nok[j]) {
-                    aw[j] = pval(ep.alpha_w, ncol);
-                    bw[j] = pval(ep.beta_w, ncol);
-                    if (DT != 1) sw[j] = (double)ep.sum_tw[ncol];
-                    if (has_bn) {
-                        bs[j] = ep.bn_scale[ncol];
-                        bh[j] = ep.bn_shift ? (double)ep.bn_shift[ncol] : 0.0;
-                    }
-                }
-                accp[j] = ACC ? prm.acc + (nok[j] ? ncol : 0) : nullptr;
-                yp[j] = Y ? prm.y + (nok[j] ? ncol : 0) : nullptr;
-            }
-#pragma unroll
-            for (int i = 0; i < TP; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int t = wp * WP + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    const int m = p0 + t;
-                    const bool mok = FULL || m < prm.RP;
-                    double aa = 0.0, ba = 0.0, r2 = 0.0;
-                    if (Y) {
-                        aa = tab[t];
-                        ba = tab[BP + t];
-                        r2 = tab[2 * BP + t];
-                    }
-                    const int64_t rowoff = (int64_t)m * N;
-#pragma unroll
-                    for (int j = 0; j < TQ; ++j) {
-                        if (FULL || (mok && nok[j])) {
-                            const auto D = acc[i][j][r];
-                            if (ACC) put(nt, (int)D, accp[j] + rowoff);
-                            if (Y) {
-                                double v = aw[j] * (aa * (double)D + ba * sw[j]) + bw[j] * r2;
-                                v = __builtin_fmax(v, relu_floor);
-                                put(nt, (float)(bs[j] * v + bh[j]), yp[j] + rowoff);
-                            }
-                        }
-                    }
-                    // keep the scheduler from hoisting every later load up here
-                    if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-                }
-        });
+    if constexpr (!CONV) {
+        gemm_epilogue<BP, TP, TQ, DT != 1>(prm, (double*)smem, p0, q0, wp * WP, wq * WQ, full_tile, acc,
+                                            [](auto d) { return d; });
     } else {
         // y = g1[o]*D + c2[o]*Sa[m] + Cst[class(m)][o],  g1 = aa*aw, c2 = aa*bw;
         // tab = [4 + ncls][BP]: g1, c2, bn scale, bn shift, then the class constants.
@@ -979,7 +1011,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
                             }
                         }
                     }
-                    if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+                    if ((r & 1) == 1) __builtin_amdgcn_sched_barrier(0);
                 }
         });
     }
@@ -998,6 +1030,19 @@ inline bool halo_eligible(const TmmParams& prm, int hc)
     const ConvGeom& g = prm.g;
     return g.stride == 1 && g.KH == 2 * g.pad + 1 && g.KW == 2 * g.pad + 1 && g.Cpad == hc && g.OH == g.H &&
            g.OW == g.W;
+}
+
+// Fills in the tile counts of a BP x BQ tiling; the grid size, or 0 if it is out of range.
+inline unsigned tile_grid(TmmParams& prm, int bp, int bq)
+{
+    prm.tilesP = (prm.RP + bp - 1) / bp;
+    const int64_t tilesQ = ((int64_t)prm.RQ + bq - 1) / bq;
+    const int64_t blocks = (int64_t)prm.tilesP * tilesQ;
+    if (blocks <= 0 || blocks > 0x7fffff00 || tilesQ * 8 > 0x7fffffff) return 0;
+    prm.ntiles = (int)blocks;
+    prm.band_tiles = (int)(8 * tilesQ);
+    prm.div_band = make_fastdiv((uint32_t)prm.band_tiles);
+    return (unsigned)((blocks + 7) / 8 * 8);
 }
 
 template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0>
@@ -1028,15 +1073,8 @@ hipError_t launch_cfg(TmmParams& prm, hipStream_t st)
         if (e != hipSuccess) return e;
         attr_done = true;
     }
-    prm.tilesP = (prm.RP + BP - 1) / BP;
-    const int64_t tilesQ = ((int64_t)prm.RQ + BQ - 1) / BQ;
-    const int64_t blocks = (int64_t)prm.tilesP * tilesQ;
-    if (blocks <= 0 || blocks > 0x7fffff00) return hipErrorInvalidValue;
-    prm.ntiles = (int)blocks;
-    if (tilesQ * 8 > 0x7fffffff) return hipErrorInvalidValue;
-    prm.band_tiles = (int)(8 * tilesQ);
-    prm.div_band = make_fastdiv((uint32_t)prm.band_tiles);
-    const unsigned grid = (unsigned)((blocks + 7) / 8 * 8);
+    const unsigned grid = tile_grid(prm, BP, BQ);
+    if (!grid) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), (size_t)smem, st, prm);
     return hipGetLastError();
 }

@@ -1,0 +1,192 @@
+// Ternary GEMM on bit planes (RTN_CODE_BITPLANE) with the FP4 matrix cores.
+//
+// The operands stay in the paper's 2-bit storage in memory, in L2 and in LDS -- 0.25 byte per
+// code -- and become FP4 nibbles only in registers, right before the MFMA.  The kernel the
+// method's own pattern gives (AND / XOR / popcount, k_gemm_popc) is bound by the vector ALU: about
+// 12 instructions per 64 products of a lane, 407 us at M = N = K = 4096.  Here a
+// fragment of 32 codes costs 10 vector instructions once and feeds TP or TQ MFMAs:
+//
+//   * E2M1 is (sign, exponent 2 bits, mantissa): sign bit over the *upper* exponent bit is +-2.0
+//     (0x4, 0xC), and those are adjacent bits.  So mask and sign bits are interleaved into 2-bit
+//     fields (two bit-selects per 16 codes, one plane shifted by 1) and a dword of 8 nibbles is
+//     one AND, every second one after a shift by 2.  Both operands are 2 t, D is the sum / 4,
+//     exact: |sum| <= 4 * 2^22 = 2^24.
+//   * a zero may carry a sign (-0.0): it adds nothing.  Both operands use the stored sign bit
+//     (1 <=> +1) as the number's sign, i.e. both are negated, which their product undoes.
+//   * which k a nibble position stands for is the same in both operands, so the order of a
+//     fragment's codes is free: lane half h takes 16-byte chunk 2 g + h of a row, and its four
+//     dwords are four k-slices.
+//
+// A stage is 64 bytes of each plane of every tile row (512 codes, 8 MFMA k-slices), loaded global
+// -> LDS directly, two stages, one barrier per stage.  EB = bytes a lane loads at once: 16, or 4
+// when the rows' byte length is not a multiple of 16 (an odd number of plane words); what lies
+// behind a row's end is read from the zero page.
+//
+// M = N = K = 4096: 56.6 us against 407 us for k_gemm_popc (and 38.5 us for the FP4 GEMM, which has
+// nothing to expand).  Bound by instruction issue beside the MFMAs: per k-slice a wave of the
+// 256 x 256 tile runs 80 expanding instructions for 16 MFMAs.  A wave tile of 128 x 128 halves that
+// share against 64 x 64, hence the largest tile as soon as it gives every CU a block.
+#include "tmm_kernel.h"
+
+namespace rtn {
+
+namespace {
+
+__device__ __forceinline__ unsigned bitsel(unsigned m, unsigned a, unsigned b) { return (a & m) | (b & ~m); }
+
+// 32 codes of one row (mask and sign dword) as an FP4 fragment of values +-2, 0
+__device__ __forceinline__ v8i planes_to_fp4(unsigned m, unsigned s)
+{
+    const unsigned lo = bitsel(0x55555555u, m, s << 1), hi = bitsel(0x55555555u, m >> 1, s);
+    return v8i{(int)(lo & 0xccccccccu), (int)((lo << 2) & 0xccccccccu), (int)(hi & 0xccccccccu),
+               (int)((hi << 2) & 0xccccccccu), 0, 0, 0, 0};
+}
+
+template <int BP, int BQ, int WGP, int WGQ, int MINW, int EB>
+__global__ __launch_bounds__(256, MINW) void k_gemm_planes(TmmParams prm, const int8_t* Psign, const int8_t* Qsign)
+{
+    constexpr int WP = BP / WGP, WQ = BQ / WGQ, TP = WP / 32, TQ = WQ / 32;
+    constexpr int ROWS = 2 * (BP + BQ);          // LDS rows of a stage: P mask, P sign, Q mask, Q sign
+    constexpr int STAGE = ROWS * 64;
+    constexpr int RPL = EB, NL = ROWS / (4 * RPL);  // rows a wave's load covers (64 EB / 64), loads per wave
+    static_assert(EB == 16 || EB == 4, "16- or 4-byte lanes");
+    static_assert(BP % 64 == 0 && BQ % 64 == 0 && NL >= 1, "tile too small");
+
+    extern __shared__ __attribute__((aligned(16))) int8_t smem[];
+    const unsigned lds0 = (unsigned)(uintptr_t)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wp = wave / WGQ, wq = wave % WGQ;
+    int tileP, tileQ;
+    if (!block_tile(prm, tileP, tileQ)) return;
+    const int p0 = tileP * BP, q0 = tileQ * BQ;
+    const unsigned rowb = (unsigned)prm.ldP;  // bytes of a plane row (both operands)
+
+    // ---- loader: load j of a wave covers stage rows RPL * (wave + 4 j) .. + RPL - 1 ----------
+    const int lpos = (lane * EB) & 63;  // byte position within the 64-byte LDS row
+    auto issue = [&](int st) {
+        const unsigned dst0 = lds0 + (unsigned)((st & 1) * STAGE);
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            const int rr = RPL * (wave + 4 * j);          // first row of this load (wave-uniform)
+            const int row = rr + lane * EB / 64;
+            const bool isP = rr < 2 * BP;
+            const int r0 = isP ? rr : rr - 2 * BP, half = isP ? BP : BQ;
+            const bool sgn = r0 >= half;
+            const int8_t* base = isP ? (sgn ? Psign : prm.P) : (sgn ? Qsign : prm.Q);
+            int gr = (isP ? p0 : q0) + (r0 - (sgn ? half : 0)) + lane * EB / 64;
+            const int lim = (isP ? prm.RP : prm.RQ) - 1;
+            gr = gr < lim ? gr : lim;  // rows past the end: any valid row, never stored
+            const unsigned kb = (unsigned)st * 64 + (unsigned)((((lpos >> 4) ^ swz(row)) << 4) + (lpos & 15));
+            const int8_t* src = kb < rowb ? base + (int64_t)gr * rowb + kb : (const int8_t*)g_zero16;
+            const unsigned dst = dst0 + (unsigned)rr * 64;
+            if constexpr (EB == 16)
+                dma16(src, dst);
+            else
+                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(dst), "v"(src) : "memory");
+        }
+    };
+
+    v16f acc[TP][TQ];
+#pragma unroll
+    for (int i = 0; i < TP; ++i)
+#pragma unroll
+        for (int j = 0; j < TQ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+    const int nst = prm.nk;
+    issue(0);
+    for (int st = 0; st < nst; ++st) {
+        // this wave's loads of stage st have landed; after the barrier everybody's have, and
+        // every wave is done with the other stage, which the next loads overwrite
+        wait_vm<0>();
+        wait_lgkm0();
+        block_barrier();
+        if (st + 1 < nst) issue(st + 1);
+        const int8_t* sb = smem + (st & 1) * STAGE;
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            v4i pm[TP], ps[TP], qm[TQ], qs[TQ];
+            const int ch = 2 * g + (lane >> 5);
+#pragma unroll
+            for (int t = 0; t < TP; ++t) {
+                const int row = wp * WP + t * 32 + (lane & 31);
+                const int o = row * 64 + ((ch ^ swz(row)) << 4);
+                pm[t] = *(const v4i*)(sb + o);
+                ps[t] = *(const v4i*)(sb + BP * 64 + o);
+            }
+#pragma unroll
+            for (int t = 0; t < TQ; ++t) {
+                const int row = wq * WQ + t * 32 + (lane & 31);
+                const int o = 2 * BP * 64 + row * 64 + ((ch ^ swz(row)) << 4);
+                qm[t] = *(const v4i*)(sb + o);
+                qs[t] = *(const v4i*)(sb + BQ * 64 + o);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v8i fp[TP], fq[TQ];
+#pragma unroll
+                for (int t = 0; t < TP; ++t) fp[t] = planes_to_fp4((unsigned)pm[t][e], (unsigned)ps[t][e]);
+#pragma unroll
+                for (int t = 0; t < TQ; ++t) fq[t] = planes_to_fp4((unsigned)qm[t][e], (unsigned)qs[t][e]);
+#pragma unroll
+                for (int i = 0; i < TP; ++i)
+#pragma unroll
+                    for (int j = 0; j < TQ; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp[i], fq[j], acc[i][j], 4, 4, 0, 0, 0, 0);
+            }
+        }
+    }
+    const bool full_tile = p0 + BP <= prm.RP && q0 + BQ <= prm.RQ;
+    gemm_epilogue<BP, TP, TQ, true>(prm, (double*)smem, p0, q0, wp * WP, wq * WQ, full_tile, acc,
+                                    [](float s) { return 0.25f * s; });
+}
+
+template <int BP, int BQ, int WGP, int WGQ, int MINW, int EB>
+hipError_t launch_planes(TmmParams& prm, const int8_t* ps, const int8_t* qs, hipStream_t st)
+{
+    constexpr int smem = 2 * 2 * (BP + BQ) * 64;  // two stages; the epilogue's [3][BP] doubles fit in one
+    static_assert(3 * BP * 8 <= smem, "epilogue table over the stages");
+    auto kern = k_gemm_planes<BP, BQ, WGP, WGQ, MINW, EB>;
+    static bool attr_done = false;
+    if (!attr_done) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        if (e != hipSuccess) return e;
+        attr_done = true;
+    }
+    const unsigned grid = tile_grid(prm, BP, BQ);
+    if (!grid) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), (size_t)smem, st, prm, ps, qs);
+    return hipGetLastError();
+}
+
+template <int EB>
+hipError_t launch_planes_eb(TmmParams& prm, const int8_t* ps, const int8_t* qs, hipStream_t st)
+{
+    auto tiles = [&](int bp, int bq) { return (((int64_t)prm.RP + bp - 1) / bp) * (((int64_t)prm.RQ + bq - 1) / bq); };
+    if (tiles(256, 256) >= 256) return launch_planes<256, 256, 2, 2, 1, EB>(prm, ps, qs, st);
+    if (tiles(128, 128) >= 192) return launch_planes<128, 128, 2, 2, 2, EB>(prm, ps, qs, st);
+    return launch_planes<64, 64, 2, 2, 4, EB>(prm, ps, qs, st);
+}
+
+}  // namespace
+
+hipError_t launch_gemm_planes(const PopcArgs& a, hipStream_t st)
+{
+    TmmParams prm = {};
+    prm.P = (const int8_t*)a.a_mask;
+    prm.Q = (const int8_t*)a.w_mask;
+    prm.RP = (int)a.M;
+    prm.RQ = (int)a.N;
+    prm.ldP = a.words * 8;
+    prm.nk = (int)((a.words + 7) / 8);
+    prm.Klogical = (int)a.K;
+    prm.acc = a.acc;
+    prm.y = a.y;
+    prm.ep = a.ep;
+    const int8_t *ps = (const int8_t*)a.a_sign, *qs = (const int8_t*)a.w_sign;
+    return a.words % 2 == 0 ? launch_planes_eb<16>(prm, ps, qs, st) : launch_planes_eb<4>(prm, ps, qs, st);
+}
+
+}  // namespace rtn

@@ -206,6 +206,27 @@ def test_gemm_popc_vs_oracle(M, N, K):
     T.assert_y_close(got["y"].cpu().numpy(), ref["y"], "popc y")
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 65, 64), (64, 64, 512), (65, 70, 513), (130, 129, 576), (200, 136, 1088),
+                                   (128 * 14, 128 * 14, 192), (256 * 16 + 1, 256 * 16 - 1, 200)])
+@pytest.mark.parametrize("path", [B.RTN_PATH_AUTO, B.RTN_PATH_POPC], ids=["auto", "popc"])
+def test_gemm_planes_paths_vs_fp4(M, N, K, path):
+    """Bit planes through the matrix cores (AUTO: one, an odd and an even number of plane words, tails of
+    the 512-code stage, each tile size's edges) and through the popcount pattern.  Integers must be
+    those of the FP4 path, which is pinned against the oracle; y is one fp32 rounding of the same fp64
+    formula in two associations, so at most one ulp (2^-23) apart where the terms do not cancel."""
+    _say("gemm planes path=%d M=%d N=%d K=%d" % (path, M, N, K))
+    case = wl.gemm_case(M, N, K, p_zero=0.4, seed=M + K)
+    want = T.hip_gemm(case, fmt=B.RTN_CODE_FP4, relu=True)
+    ca, sa = B.ternarize_pack(T.dev(case["xa"]), -0.5, 0.5, B.RTN_CODE_BITPLANE)
+    cw, sw = B.ternarize_pack(T.dev(case["xw"]), -0.5, 0.5, B.RTN_CODE_BITPLANE)
+    ep = B.Epilogue(T.gran_arg(case["alpha_a"]), T.gran_arg(case["beta_a"]), T.gran_arg(case["alpha_w"]),
+                    T.gran_arg(case["beta_w"]), sa, sw, relu=True)
+    acc, y = B.ternary_gemm(ca, cw, M, N, K, fmt=B.RTN_CODE_BITPLANE, path=path, ep=ep, want_acc=True)
+    torch.cuda.synchronize()
+    assert torch.equal(acc, want["D"])
+    T.assert_y_close(y.cpu().numpy(), want["y"].cpu().numpy(), "planes y")
+
+
 def test_standalone_epilogue_gemm():
     _say("standalone epilogue (gemm form)")
     case = wl.gemm_case(100, 90, 300, seed=4, table4=True)
