@@ -289,14 +289,14 @@ int rtn_ternary_weight_conv2d(const float *x, const void *w_codes, int64_t Nb, i
  * (the offline preparation of the weights the paper's "Inference" paragraph describes:
  * everything that depends only on the trained filters is stored ahead of time).
  *   rtn_weight_gemm_prepare: the codes [N][rtn_padded_k(K)] as bf16 values.
- *   rtn_weight_conv2d_prepare: the codes [O][KH][KW][rtn_padded_k(C)] as bf16 values,
- *   then the per-filter epilogue table (alpha_w and the BN affine; nullable BN as above).
+ *   rtn_weight_conv2d_prepare: the codes [O][KH][KW][rtn_padded_k(C)] as bf16 values in
+ *   the order the matrix instruction takes them, then the per-filter epilogue table (alpha_w and the BN affine; nullable BN as above).
  * prepared: DEVICE, 16-byte aligned, at least rtn_weight_*_prepared_bytes(...) bytes;
  * it is only read by the *_prepared calls below, so one buffer serves any number of
  * calls, batch sizes and image sizes.  Those calls compute exactly what
  * rtn_ternary_weight_gemm / rtn_ternary_weight_conv2d compute (same kernels, same
- * bits); their workspace (same size functions as above) then holds only the split
- * activations.  The conv takes alpha_w and the BN affine from the prepared table. */
+ * bits); their workspace (same size functions as above) then holds only the GEMM's split
+ * activations (the conv splits in registers).  The conv takes alpha_w and the BN affine from the prepared table. */
 size_t rtn_weight_gemm_prepared_bytes(int64_t N, int64_t K);
 int rtn_weight_gemm_prepare(const void *w_codes, int64_t N, int64_t K, void *prepared,
                             size_t prepared_bytes, void *stream);

@@ -147,7 +147,8 @@ hipError_t launch_wgemm(const WGemmArgs& a, hipStream_t st);
 hipError_t launch_wgemm_prepare(const int8_t* w, int64_t N, int64_t Kpad, void* prepared, hipStream_t st);
 
 // conv form: x fp32 NCHW, w int8 [O][KH][KW][Cpad] (g.Cpad in elements), y fp32 NCHW;
-// workspace: 3 activation planes + weights as bf16, then the epilogue table
+// workspace (one-call form): weights as bf16, then the epilogue table, behind room for 3
+// activation planes, which is not used
 struct WConvArgs {
     const float* x;
     const int8_t* w;
@@ -165,6 +166,7 @@ hipError_t launch_conv_mfma(const ConvArgs& a, hipStream_t st);
 // Tile configuration override for tuning and tests (-1 = heuristic).
 int tile_config_count();
 void force_tile_config(int index);
+int forced_tile_config();
 
 hipError_t launch_conv_class_consts(const ConvArgs& a, double* cst, hipStream_t st);
 

@@ -31,7 +31,7 @@
 //   TERN conv whose epilogue ternarizes its output for the next layer (1), also after
 //        the residual add and second ReLU of a block tail (2);
 //   DT   1: bf16 operands with fp32 accumulators (v_mfma_f32_32x32x16_bf16) for the
-//        weight-only ternary GEMM / conv, whose fp32 activations are split exactly
+//        weight-only ternary GEMM, whose fp32 activations are split exactly
 //        into three bf16 terms laid along K;
 //        2: codes stored as FP4 (E2M1) nibbles, two per byte, multiplied by
 //        v_mfma_f32_32x32x64_f8f6f4 with fp32 accumulators.  -1, 0, +1 are exact in
@@ -75,11 +75,9 @@ struct TmmParams {
     const float* res;
     int relu_out;
     int nt_out;  // conv: store the fp32 / int32 outputs with the non-temporal hint
-    // bf16 operands (DT = 1): the weight rows (GEMM: Q, conv: P) are wwrap bytes long and
-    // are walked again from the start each time the K offset passes their end; the
-    // conv's three activation planes lie qplane bytes apart
+    // bf16 operands (DT = 1): the weight rows (Q) are wwrap bytes long and are walked again
+    // from the start each time the K offset passes their end
     unsigned wwrap;
-    int64_t qplane;
 };
 
 // Launch of tile configuration `cfg` (the numbering rtn_set_tile_config() documents) of the
@@ -89,9 +87,8 @@ struct TmmParams {
 // (CONV, TERN, DT) triple per translation unit.
 template <bool CONV, int TERN, int DT>
 hipError_t tmm_launch_index_raw(int cfg, TmmParams& prm, hipStream_t st);
-// The bf16-operand variants of the weight-only path: variant 0 = 64x64, 1 = 128x128,
-// 2 = the largest (conv: 128x256, GEMM: 256x256), conv only: 3 = 64x256.
-hipError_t tmm_launch_bf16(bool conv, int variant, TmmParams& prm, hipStream_t st);
+// The bf16-operand variants of the weight-only GEMM: 0 = 64x64, 1 = 128x128, 2 = 256x256.
+hipError_t tmm_launch_bf16(int variant, TmmParams& prm, hipStream_t st);
 
 namespace {
 
@@ -351,7 +348,7 @@ __device__ __forceinline__ void gemm_epilogue(const TmmParams& prm, double* tab,
 template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0>
 __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
 {
-    static_assert(DT != 1 || (TERN == 0 && HC == 0), "bf16 operands: plain GEMM and plain conv only");
+    static_assert(DT != 1 || !CONV, "bf16 operands: GEMM only");
     static_assert(!TERN || CONV, "the ternarizing epilogue belongs to the conv");
     static_assert(WGP * WGQ == 4, "4 waves per block");
     constexpr bool HALO = HC != 0;
@@ -439,13 +436,11 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     int is_kh = 0, is_kw = 0;
     const int8_t* zero_page = (const int8_t*)g_zero16;
 
-    int64_t l_plane = 0;  // DT = 1 conv: byte offset of the activation plane being walked
     int64_t l_koff = 0;   // conv: running byte offset of the step being issued within the window
     const int64_t l_rowskip = CONV ? (int64_t)(g.W - g.KW) * g.Cpad : 0;
     auto issue_begin = [&](int kt) {
         is_sbase = lds0 + (unsigned)(roff + (kt % NS) * STAGE);
         is_koffP = (int64_t)kt * 64;
-        if (CONV && DT == 1) is_koffP = (int64_t)((unsigned)is_koffP % prm.wwrap);
         if (CONV && !HALO) {
             // byte offset of tap (kh, kw), channel chunk cc from a pixel's tap (0, 0):
             // (kh W + kw) Cpad + cc, kept as a running sum (scalar multiplies in this loop cost
@@ -453,7 +448,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
             // tap to the next tap of the row, and + (W - KW) Cpad at the end of a window row
             is_kh = l_kh;
             is_kw = l_kw;
-            is_koffQ = l_koff + l_plane;
+            is_koffQ = l_koff;
             l_koff += 64;
             l_cc += 64;
             if (l_cc == g.Cpad) {
@@ -462,11 +457,6 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
                     l_kw = 0;
                     ++l_kh;
                     l_koff += l_rowskip;
-                    if (DT == 1 && l_kh == g.KH) {
-                        l_kh = 0;
-                        l_koff = 0;
-                        l_plane += prm.qplane;
-                    }
                 }
             }
         } else {

@@ -1,6 +1,6 @@
 // Host side of the matrix-core contraction: tile choice and the launch functions of the
-// GEMM, the conv and the weight-only forms, plus the small kernels around them -- the
-// conv's per-layer epilogue table, the fp32 -> 3 x bf16 splits and the int8 -> bf16
+// GEMM, the conv and the weight-only GEMM, plus the small kernels around them -- the
+// conv's per-layer epilogue table, the fp32 -> 3 x bf16 split and the int8 -> bf16
 // weight copy.  The contraction kernel itself is in tmm_kernel.h.
 #include <cstdlib>
 
@@ -102,6 +102,7 @@ int pick_tile(int64_t rp, int64_t rq, bool conv)
 
 int tile_config_count() { return kNumTileConfigs; }
 void force_tile_config(int index) { g_forced_tile = index; }
+int forced_tile_config() { return g_forced_tile; }
 
 hipError_t launch_conv_class_consts(const ConvArgs& a, double* cst, hipStream_t st)
 {
@@ -194,117 +195,6 @@ __global__ __launch_bounds__(256) void k_codes_to_bf16(const int8_t* codes, int6
     dst[1] = make_uint4(o[4], o[5], o[6], o[7]);
 }
 
-// The same split for an NCHW activation tensor, written channel-innermost as the conv
-// reads it: out[plane][pixel][Cpad] bf16, plane 0 = hi, 1 = mid, 2 = lo, planes
-// `plane_elems` apart, channels C .. Cpad-1 zero.  A block transposes 64 pixels x 64
-// channels through LDS: lanes run along pixels for the fp32 reads (256 contiguous
-// bytes per channel) and along channels for the stores (128 contiguous bytes per pixel
-// and plane).  LDS rows are 33 dwords (two bf16 per dword), so both phases are free of
-// bank conflicts.
-__global__ __launch_bounds__(256) void k_split_nchw_bf16x3(const float* x, int64_t Nb, int C, int Cpad, int HW,
-                                                           int64_t plane_elems, uint16_t* out)
-{
-    __shared__ unsigned tile[3][64][33];
-    const int64_t npix = Nb * HW;
-    const int64_t pix0 = (int64_t)blockIdx.x * 64;
-    const int c0 = (int)blockIdx.y * 64;
-    const int tid = threadIdx.x;
-    {
-        const int p = tid & 63, cg = tid >> 6;  // this thread: pixel p, channels c0 + 16 cg .. + 15
-        const int64_t pix = pix0 + p;
-        const bool pok = pix < npix;
-        const int64_t nb = pok ? pix / HW : 0;
-        const int q = pok ? (int)(pix - nb * HW) : 0;
-#pragma unroll
-        for (int e = 0; e < 16; e += 2) {
-            unsigned w[3] = {0, 0, 0};
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const int c = c0 + 16 * cg + e + s;
-                const float v = (pok && c < C) ? x[(nb * C + c) * HW + q] : 0.0f;
-                const unsigned h = bf16_rn(v);
-                const float r1 = v - __uint_as_float(h << 16);
-                const unsigned md = bf16_rn(r1);
-                const float r2 = r1 - __uint_as_float(md << 16);
-                const unsigned lo = bf16_rn(r2);
-                w[0] |= h << (16 * s);
-                w[1] |= md << (16 * s);
-                w[2] |= lo << (16 * s);
-            }
-#pragma unroll
-            for (int pl = 0; pl < 3; ++pl) tile[pl][p][8 * cg + e / 2] = w[pl];
-        }
-    }
-    __syncthreads();
-    // 3 planes x 64 pixels x 8 sixteen-byte parts = 1536 stores, 6 per thread
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        const int u = tid + 256 * i;
-        const int pl = u >> 9, p = (u >> 3) & 63, part = u & 7;
-        const int64_t pix = pix0 + p;
-        if (pix >= npix) continue;
-        const unsigned* src = &tile[pl][p][4 * part];
-        *(uint4*)(out + pl * plane_elems + pix * Cpad + c0 + 8 * part) = make_uint4(src[0], src[1], src[2], src[3]);
-    }
-}
-
-// table position behind wn bf16 weights
-static double* wconv_table(uint16_t* wb, int64_t wn) { return (double*)(((uintptr_t)(wb + wn) + 15) & ~(uintptr_t)15); }
-
-hipError_t launch_wconv_prepare(const int8_t* w, const ConvGeom& g0, const EpiArgs& ep, void* prepared, hipStream_t st)
-{
-    uint16_t* wb = (uint16_t*)prepared;
-    const int64_t wn = (int64_t)g0.O * g0.KH * g0.KW * g0.Cpad;
-    hipLaunchKernelGGL(k_codes_to_bf16, dim3((unsigned)((wn / 16 + 255) / 256)), dim3(256), 0, st, w, wn / 16, wb);
-    ConvArgs c = {};
-    c.g = g0;
-    c.ep = ep;
-    return launch_conv_class_consts(c, wconv_table(wb, wn), st);  // g1 = alpha_w, BN rows; the class constants are 0
-}
-
-hipError_t launch_wconv(const WConvArgs& a, hipStream_t st)
-{
-    const ConvGeom& g0 = a.g;  // Cpad in elements here
-    const int64_t npix = (int64_t)g0.Nb * g0.H * g0.W;
-    const int64_t plane = npix * g0.Cpad;
-    uint16_t* a3 = (uint16_t*)a.workspace;
-    uint16_t* wb = a.prepared ? (uint16_t*)a.prepared : a3 + 3 * plane;
-    const int64_t wn = (int64_t)g0.O * g0.KH * g0.KW * g0.Cpad;
-    double* tab = wconv_table(wb, wn);
-    hipLaunchKernelGGL(k_split_nchw_bf16x3, dim3((unsigned)((npix + 63) / 64), (unsigned)(g0.Cpad / 64)), dim3(256), 0,
-                       st, a.x, (int64_t)g0.Nb, g0.C, g0.Cpad, g0.H * g0.W, plane, a3);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess && !a.prepared) e = launch_wconv_prepare(a.w, g0, a.ep, wb, st);
-    if (e != hipSuccess) return e;
-    TmmParams prm = {};
-    prm.g = g0;
-    prm.g.Cpad = g0.Cpad * 2;  // bytes per pixel row: the kernel's K bookkeeping is in bytes
-    prm.P = (const int8_t*)wb;
-    prm.Q = (const int8_t*)a3;
-    prm.RP = g0.O;
-    prm.RQ = (int)((int64_t)g0.Nb * g0.OH * g0.OW);
-    prm.ldP = (int64_t)g0.KH * g0.KW * g0.Cpad * 2;
-    prm.wwrap = (unsigned)prm.ldP;
-    prm.qplane = plane * 2;
-    prm.nk = (int)(3 * prm.ldP / 64);
-    prm.Klogical = g0.C * g0.KH * g0.KW;
-    prm.y = a.y;
-    prm.cst_cls = tab;
-    prm.ep = a.ep;
-    const int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(g0.O, prm.RQ, true);
-    const int bp = kTileBP[cfg];
-    e = hipErrorInvalidValue;
-    if (cfg == 13 || cfg == 4 || cfg == 19)
-        e = tmm_launch_bf16(true, 2, prm, st);
-    else if (bp >= 128)
-        e = tmm_launch_bf16(true, 1, prm, st);
-    else if (cfg == 3 || cfg == 7 || cfg == 9 || cfg == 14 || cfg == 15)
-        e = tmm_launch_bf16(true, 3, prm, st);
-    // the smallest tile also serves a table too large for the others (wide pad, tiny image)
-    if (e == hipErrorInvalidValue) e = tmm_launch_bf16(true, 0, prm, st);
-    return e;
-}
-
 hipError_t launch_wgemm_prepare(const int8_t* w, int64_t N, int64_t Kpad, void* prepared, hipStream_t st)
 {
     const int64_t nw = N * Kpad / 16;
@@ -335,7 +225,7 @@ hipError_t launch_wgemm(const WGemmArgs& a, hipStream_t st)
     prm.y = a.y;
     prm.ep = a.ep;
     const int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(a.M, a.N, false);
-    return tmm_launch_bf16(false, kTileBP[cfg] >= 256 ? 2 : (kTileBP[cfg] >= 128 ? 1 : 0), prm, st);
+    return tmm_launch_bf16(kTileBP[cfg] >= 256 ? 2 : (kTileBP[cfg] >= 128 ? 1 : 0), prm, st);
 }
 
 hipError_t launch_conv_mfma(const ConvArgs& a, hipStream_t st)

@@ -1295,6 +1295,25 @@ def test_weight_conv_tile_configs(cfg, tile_reset):
     _wconv_check(wl.ConvShape("u", 128, 12, 136, 3, 1, 1), 3, seed=cfg + 9, Wx=10, what="wconv cfg %d rect" % cfg)
 
 
+WCONV_EDGES = [  # shape, width: runs of input pixels, single taps, channel and filter tails, every window kind
+    (wl.ConvShape("tails", 17, 9, 33, 3, 1, 1), 9), (wl.ConvShape("k5", 70, 13, 40, 5, 1, 2), 11),
+    (wl.ConvShape("k5s2", 33, 14, 65, 5, 2, 2), 15), (wl.ConvShape("k3s5", 16, 23, 31, 3, 5, 0), 23),
+    (wl.ConvShape("k3p2", 20, 8, 32, 3, 1, 2), 8), (wl.ConvShape("k2", 24, 7, 20, 2, 1, 1), 7),
+    (wl.ConvShape("k7", 9, 12, 18, 7, 2, 2), 12), (wl.ConvShape("wide", 18, 4, 40, 3, 1, 1), 400),
+    (wl.ConvShape("k1s2", 50, 9, 70, 1, 2, 0), 8), (wl.ConvShape("tiny", 40, 1, 5, 3, 1, 1), 2),
+    (wl.ConvShape("s2", 32, 56, 48, 3, 2, 1), 56),
+]
+
+
+@pytest.mark.parametrize("edge", WCONV_EDGES, ids=lambda e: e[0].name)
+def test_weight_conv_edges_every_tile(edge, tile_reset):
+    shape, W = edge
+    for cfg in (-1, 0, 1, 7, 11, 13):
+        _say("weight-only conv edge %s W=%d cfg %d" % (shape, W, cfg))
+        B.set_tile_config(cfg)
+        _wconv_check(shape, 5, seed=31 + W, Wx=W, relu=True, bn=True, what="%s cfg %d" % (shape.name, cfg))
+
+
 def test_weight_conv_exact_on_ternary_activations():
     _say("weight-only conv on ternary activations")
     shape = wl.ConvShape("e", 64, 10, 96, 3, 1, 1)
