@@ -3,6 +3,8 @@
 Argument marshalling only: torch tensors supply device memory and the current
 HIP stream; every step of the path runs in the library's kernels.  There is no
 CPU fallback -- if librtn.so is missing or cannot be loaded this raises.
+The calls a pass makes go through the extension module _native (csrc/binding_native.cpp),
+which checks and marshals in native code; the offline ones through ctypes.
 """
 import ctypes as C
 import os
@@ -135,6 +137,19 @@ def lib():
     return _lib
 
 
+_native_module = None
+
+
+def _native():
+    """The extension module (built by build.py).  Raises if it is not there."""
+    global _native_module
+    if _native_module is None:
+        lib()
+        from . import _native as m
+        _native_module = m
+    return _native_module
+
+
 def _check(rc, where):
     if rc != RTN_OK:
         raise RtnError(rc, where)
@@ -181,29 +196,29 @@ def ternarize_pack(x, lo, hi, fmt=RTN_CODE_I8, layout=None, want_sum=True, codes
     Returns (codes, sum_t).  codes: int8 [rows,Kpad] / [N,H,W,Cpad]; for FP4 uint8
     [rows,Kpad/2] / [N,H,W,Cpad/2] (two nibbles per byte); for bit planes
     uint64-as-int64 [2, rows, Kpad/64] / [2, N,H,W, Cpad/64]."""
+    shape = x.shape
     if layout is None:
-        layout = RTN_NCHW if x.dim() == 4 else RTN_ROWS_K_CONTIG
+        layout = RTN_NCHW if len(shape) == 4 else RTN_ROWS_K_CONTIG
     if layout == RTN_ROWS_K_CONTIG:
-        d = (x.shape[0], x.shape[1], 1, 1)
-        lead = (x.shape[0],)
+        d = (shape[0], shape[1], 1, 1)
+        lead = (shape[0],)
     else:
-        d = tuple(x.shape)
-        lead = (x.shape[0], x.shape[2], x.shape[3])
-    kp = padded_k(d[1], fmt)
-    cshape = {RTN_CODE_I8: lead + (kp,), RTN_CODE_FP4: lead + (kp // 2,),
-              RTN_CODE_BITPLANE: (2,) + lead + (kp // 64,)}[fmt]
-    cdtype = {RTN_CODE_I8: torch.int8, RTN_CODE_FP4: torch.uint8, RTN_CODE_BITPLANE: torch.int64}[fmt]
+        d = shape
+        lead = (shape[0], shape[2], shape[3])
+    kp = -(-d[1] // 128) * 128 if fmt == RTN_CODE_FP4 else -(-d[1] // 64) * 64
+    if fmt == RTN_CODE_I8:
+        cshape, cdtype = lead + (kp,), torch.int8
+    elif fmt == RTN_CODE_FP4:
+        cshape, cdtype = lead + (kp // 2,), torch.uint8
+    else:
+        cshape, cdtype = (2,) + lead + (kp // 64,), torch.int64
     if codes is not None:
         assert tuple(codes.shape) == cshape and codes.dtype == cdtype and codes.is_cuda and codes.is_contiguous()
     else:
         codes = torch.empty(cshape, dtype=cdtype, device=x.device)
     if sum_t is None and want_sum:
         sum_t = torch.empty(lead, dtype=torch.int32, device=x.device)
-    glo, ghi = _Gran(lo), _Gran(hi)
-    assert glo.gran == ghi.gran
-    rc = lib().rtn_ternarize_pack(_dev(x, torch.float32), layout, d[0], d[1], d[2], d[3], glo.ptr,
-                                  ghi.ptr, glo.gran, fmt, C.c_void_p(codes.data_ptr()),
-                                  None if sum_t is None else _dev(sum_t, torch.int32), _stream())
+    rc = _native().pack(x, layout, d[0], d[1], d[2], d[3], lo, hi, fmt, codes, sum_t)
     _check(rc, "rtn_ternarize_pack")
     return codes, sum_t
 
@@ -224,6 +239,7 @@ class Epilogue:
                              int(bool(relu)),
                              None if bn_scale is None else _dev(bn_scale, torch.float32),
                              None if bn_shift is None else _dev(bn_shift, torch.float32))
+        self.addr = C.addressof(self.s)
 
     def ref(self):
         return C.cast(C.pointer(self.s), C.c_void_p)
@@ -233,17 +249,11 @@ def ternary_gemm(a_codes, w_codes, M, N, K, fmt=RTN_CODE_I8, path=RTN_PATH_AUTO,
                  want_acc=False, acc_out=None, y_out=None):
     """Returns (acc or None, y or None)."""
     dev = a_codes.device
-    if fmt != RTN_CODE_BITPLANE:
-        _check_codes(a_codes, M, K, fmt, "a_codes")
-        _check_codes(w_codes, N, K, fmt, "w_codes")
     if want_acc and acc_out is None:
         acc_out = torch.empty((M, N), dtype=torch.int32, device=dev)
     if ep is not None and y_out is None:
         y_out = torch.empty((M, N), dtype=torch.float32, device=dev)
-    rc = lib().rtn_ternary_gemm(fmt, path, C.c_void_p(a_codes.data_ptr()), C.c_void_p(w_codes.data_ptr()),
-                                M, N, K, None if acc_out is None else _dev(acc_out, torch.int32),
-                                None if ep is None else ep.ref(),
-                                None if y_out is None else _dev(y_out, torch.float32), None, 0, _stream())
+    rc = _native().gemm(fmt, path, a_codes, w_codes, M, N, K, acc_out, None if ep is None else ep.addr, y_out)
     _check(rc, "rtn_ternary_gemm")
     return acc_out, y_out
 
@@ -287,22 +297,17 @@ def ternary_conv2d(a_codes, w_codes, Nb, Cc, H, W, O, KH, KW, stride, pad, pad_m
                    ep=None, want_acc=False, acc_out=None, y_out=None, workspace=None,
                    fmt=RTN_CODE_I8, path=RTN_PATH_AUTO):
     """a_codes: int8 [Nb,H,W,Cpad]; w_codes: int8 [O,KH,KW,Cpad].  Returns (acc, y) in NCHW."""
-    dev = a_codes.device
-    _check_codes(a_codes, Nb * H * W, Cc, fmt, "a_codes")
-    _check_codes(w_codes, O * KH * KW, Cc, fmt, "w_codes")
-    OH, OW = conv_out_hw(H, W, KH, KW, stride, pad)
-    if want_acc and acc_out is None:
-        acc_out = torch.empty((Nb, O, OH, OW), dtype=torch.int32, device=dev)
-    if ep is not None and y_out is None:
-        y_out = torch.empty((Nb, O, OH, OW), dtype=torch.float32, device=dev)
+    if (want_acc and acc_out is None) or (ep is not None and y_out is None):
+        dev = a_codes.device
+        OH, OW = conv_out_hw(H, W, KH, KW, stride, pad)
+        if want_acc and acc_out is None:
+            acc_out = torch.empty((Nb, O, OH, OW), dtype=torch.int32, device=dev)
+        if ep is not None and y_out is None:
+            y_out = torch.empty((Nb, O, OH, OW), dtype=torch.float32, device=dev)
     if ep is not None and workspace is None:
         workspace = conv2d_prepare_constants(Cc, O, KH, KW, pad, ep)
-    rc = lib().rtn_ternary_conv2d_implicit_gemm(
-        fmt, path, C.c_void_p(a_codes.data_ptr()), C.c_void_p(w_codes.data_ptr()), Nb, Cc, H, W, O, KH, KW,
-        stride, pad, pad_mode, None if acc_out is None else _dev(acc_out, torch.int32),
-        None if ep is None else ep.ref(), None if y_out is None else _dev(y_out, torch.float32),
-        None if workspace is None else C.c_void_p(workspace.data_ptr()),
-        0 if workspace is None else workspace.numel() * workspace.element_size(), _stream())
+    rc = _native().conv2d(fmt, path, a_codes, w_codes, Nb, Cc, H, W, O, KH, KW, stride, pad, pad_mode, acc_out,
+                          None if ep is None else ep.addr, y_out, workspace)
     _check(rc, "rtn_ternary_conv2d_implicit_gemm")
     return acc_out, y_out
 
@@ -314,26 +319,15 @@ def ternary_conv2d_ternarize(a_codes, w_codes, Nb, Cc, H, W, O, KH, KW, stride, 
     """The conv with the ternarizing epilogue.  lo/hi: python floats or cuda float32
     vectors (one per output channel).  residual / relu_out / y_out: the block-tail
     form (fp32 NCHW tensors).  Returns int8 codes [Nb,OH,OW,padded_k(O)]."""
-    OH, OW = conv_out_hw(H, W, KH, KW, stride, pad)
-    _check_codes(a_codes, Nb * H * W, Cc, fmt, "a_codes")
-    _check_codes(w_codes, O * KH * KW, Cc, fmt, "w_codes")
-    if codes_out is not None:
-        _check_codes(codes_out, Nb * OH * OW, O, fmt, "codes_out")
     if codes_out is None:
+        OH, OW = conv_out_hw(H, W, KH, KW, stride, pad)
         codes_out = (torch.empty((Nb, OH, OW, padded_k(O)), dtype=torch.int8, device=a_codes.device)
                      if fmt == RTN_CODE_I8 else
                      torch.empty((Nb, OH, OW, padded_k(O, fmt) // 2), dtype=torch.uint8, device=a_codes.device))
     if workspace is None:
         workspace = conv2d_prepare_constants(Cc, O, KH, KW, pad, ep)
-    glo, ghi = _Gran(lo), _Gran(hi)
-    assert glo.gran == ghi.gran
-    rc = lib().rtn_ternary_conv2d_ternarize(
-        fmt, path, C.c_void_p(a_codes.data_ptr()), C.c_void_p(w_codes.data_ptr()), Nb, Cc, H, W, O, KH, KW,
-        stride, pad, pad_mode, ep.ref(), None if residual is None else _dev(residual, torch.float32),
-        int(bool(relu_out)), glo.ptr, ghi.ptr, glo.gran,
-        None if y_out is None else _dev(y_out, torch.float32),
-        _dev(codes_out, torch.int8 if fmt == RTN_CODE_I8 else torch.uint8),
-        C.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(), _stream())
+    rc = _native().conv2d_ternarize(fmt, path, a_codes, w_codes, Nb, Cc, H, W, O, KH, KW, stride, pad, pad_mode, ep.addr,
+                                    residual, relu_out, lo, hi, y_out, codes_out, workspace)
     _check(rc, "rtn_ternary_conv2d_ternarize")
     return codes_out
 
@@ -357,14 +351,8 @@ def ternary_weight_gemm(x, w_codes, M, N, K, alpha_w, relu=False, bn_scale=None,
     if workspace is None:
         workspace = torch.empty(lib().rtn_weight_gemm_workspace_bytes(M, N, K), dtype=torch.uint8,
                                 device=x.device)
-    ga = _Gran(alpha_w)
-    fn = lib().rtn_ternary_weight_gemm if prepared is None else lib().rtn_ternary_weight_gemm_prepared
-    wsrc = w_codes if prepared is None else prepared
-    rc = fn(
-        _dev(x, torch.float32), C.c_void_p(wsrc.data_ptr()), M, N, K, ga.ptr, ga.gran, int(bool(relu)),
-        None if bn_scale is None else _dev(bn_scale, torch.float32),
-        None if bn_shift is None else _dev(bn_shift, torch.float32), _dev(y_out, torch.float32),
-        C.c_void_p(workspace.data_ptr()), workspace.numel(), _stream())
+    rc = _native().weight_gemm(x, w_codes if prepared is None else prepared, prepared is not None, M, N, K, alpha_w, relu,
+                               bn_scale, bn_shift, y_out, workspace)
     _check(rc, "rtn_ternary_weight_gemm")
     return y_out
 
@@ -389,17 +377,14 @@ def ternary_weight_conv2d(x, w_codes, O, KH, KW, stride, pad, alpha_w=None, relu
     [O,KH,KW,Cpad]; or w_codes None and prepared = weight_conv2d_prepare(...), which already
     holds alpha_w and the BN affine.  Returns y float32 [Nb,O,OH,OW]."""
     Nb, Cc, H, W = x.shape
-    OH, OW = conv_out_hw(H, W, KH, KW, stride, pad)
     if y_out is None:
+        OH, OW = conv_out_hw(H, W, KH, KW, stride, pad)
         y_out = torch.empty((Nb, O, OH, OW), dtype=torch.float32, device=x.device)
     if workspace is None:
         workspace = torch.empty(lib().rtn_weight_conv2d_workspace_bytes(Nb, Cc, H, W, O, KH, KW, pad),
                                 dtype=torch.uint8, device=x.device)
     if prepared is not None:
-        rc = lib().rtn_ternary_weight_conv2d_prepared(
-            _dev(x, torch.float32), C.c_void_p(prepared.data_ptr()), Nb, Cc, H, W, O, KH, KW, stride, pad,
-            int(bool(relu)), _dev(y_out, torch.float32), C.c_void_p(workspace.data_ptr()), workspace.numel(),
-            _stream())
+        rc = _native().weight_conv2d_prepared(x, prepared, Nb, Cc, H, W, O, KH, KW, stride, pad, relu, y_out, workspace)
         _check(rc, "rtn_ternary_weight_conv2d_prepared")
         return y_out
     ga = _Gran(alpha_w)
@@ -423,11 +408,7 @@ def activation_backward(a, grad_out, lo, hi, gamma, want_grad_in=True, grad_in=N
     if workspace is None:
         workspace = torch.empty(lib().rtn_activation_backward_workspace_bytes(n), dtype=torch.uint8,
                                 device=a.device)
-    glo, ghi, gg = _Gran(lo), _Gran(hi), _Gran(gamma)
-    rc = lib().rtn_activation_backward(_dev(a, torch.float32), _dev(grad_out, torch.float32), n, glo.ptr, ghi.ptr,
-                                       gg.ptr, None if grad_in is None else _dev(grad_in, torch.float32),
-                                       _dev(sums, torch.float64), C.c_void_p(workspace.data_ptr()),
-                                       workspace.numel(), _stream())
+    rc = _native().activation_backward(a, grad_out, n, lo, hi, gamma, grad_in, sums, workspace)
     _check(rc, "rtn_activation_backward")
     return grad_in, sums
 
@@ -453,11 +434,7 @@ def weight_backward(w, grad_out, lo, hi, k_w, b_w, alpha, want_grad_w=True, grad
         grad_w = torch.empty_like(w)
     if sums is None:
         sums = torch.empty((O, 3), dtype=torch.float64, device=w.device)
-    glo, ghi = _Gran(lo), _Gran(hi)
-    rc = lib().rtn_weight_backward(_dev(w, torch.float32), _dev(grad_out, torch.float32), O, K, glo.ptr, ghi.ptr,
-                                   _dev(k_w, torch.float32), _dev(b_w, torch.float32), _dev(alpha, torch.float32),
-                                   None if grad_w is None else _dev(grad_w, torch.float32),
-                                   _dev(sums, torch.float64), _stream())
+    rc = _native().weight_backward(w, grad_out, O, K, lo, hi, k_w, b_w, alpha, grad_w, sums)
     _check(rc, "rtn_weight_backward")
     return grad_w, sums
 
@@ -514,17 +491,14 @@ def quaternary_gemm(a_codes, w_codes, M, N, K, fmt=RTN_CODE_I8, path=RTN_PATH_AU
 def ternary_depthwise_conv2d(a_codes, w_codes, Nb, Cc, H, W, KH, KW, stride, pad, pad_mode=RTN_PAD_TRUE_ZERO, ep=None,
                              want_acc=False, acc_out=None, y_out=None):
     """a_codes int8 [Nb,H,W,Cpad]; w_codes int8 [C, padded_k(KH*KW)].  Returns (acc, y) in NCHW."""
-    _check_codes(a_codes, Nb * H * W, Cc, RTN_CODE_I8, "a_codes")
-    _check_codes(w_codes, Cc, KH * KW, RTN_CODE_I8, "w_codes")
-    OH, OW = conv_out_hw(H, W, KH, KW, stride, pad)
-    dev = a_codes.device
-    if want_acc and acc_out is None:
-        acc_out = torch.empty((Nb, Cc, OH, OW), dtype=torch.int32, device=dev)
-    if ep is not None and y_out is None:
-        y_out = torch.empty((Nb, Cc, OH, OW), dtype=torch.float32, device=dev)
-    rc = lib().rtn_ternary_depthwise_conv2d(
-        C.c_void_p(a_codes.data_ptr()), C.c_void_p(w_codes.data_ptr()), Nb, Cc, H, W, KH, KW, stride, pad, pad_mode,
-        None if acc_out is None else _dev(acc_out, torch.int32), None if ep is None else ep.ref(),
-        None if y_out is None else _dev(y_out, torch.float32), _stream())
+    if (want_acc and acc_out is None) or (ep is not None and y_out is None):
+        OH, OW = conv_out_hw(H, W, KH, KW, stride, pad)
+        dev = a_codes.device
+        if want_acc and acc_out is None:
+            acc_out = torch.empty((Nb, Cc, OH, OW), dtype=torch.int32, device=dev)
+        if ep is not None and y_out is None:
+            y_out = torch.empty((Nb, Cc, OH, OW), dtype=torch.float32, device=dev)
+    rc = _native().depthwise(a_codes, w_codes, Nb, Cc, H, W, KH, KW, stride, pad, pad_mode, acc_out,
+                             None if ep is None else ep.addr, y_out)
     _check(rc, "rtn_ternary_depthwise_conv2d")
     return acc_out, y_out

@@ -6,6 +6,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_1912_02057_amd import binding as B
 
@@ -421,3 +422,21 @@ def test_bench_refuses_more_than_one_gpu():
                        text=True, timeout=300)
     assert r.returncode == 2
     assert "ONE GPU" in (r.stdout + r.stderr)
+
+
+def test_binding_native_calls_refuse_host_tensors_and_wrong_types():
+    """The extension module checks before any launch: host tensors, wrong types, mixed thresholds."""
+    x = torch.zeros(4, 64)
+    with pytest.raises(AssertionError):
+        B.ternarize_pack(x, -0.5, 0.5, codes=None, want_sum=False)
+    with pytest.raises(AssertionError):
+        B._native().pack(x, 0, 4, 64, 1, 1, -0.5, torch.zeros(4), 0, x, None)
+    i8 = torch.zeros(64, 64, dtype=torch.int8)
+    with pytest.raises(ValueError):
+        B.ternary_gemm(i8, i8, 64, 64, 64, want_acc=False, acc_out=i8)
+    with pytest.raises(ValueError):
+        B.ternary_conv2d(i8, i8, 1, 64, 8, 8, 64, 1, 1, 1, 0, acc_out=i8)
+    with pytest.raises(TypeError):
+        B._native().gemm(1, 2, 3)
+    with pytest.raises(TypeError):
+        B._native().weight_gemm(None, i8, False, 1, 1, 1, "a", 0, None, None, None, None)
