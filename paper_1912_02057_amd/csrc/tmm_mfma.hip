@@ -81,8 +81,19 @@ hipError_t launch_index(int cfg, TmmParams& prm, hipStream_t st)
 // The conv rules come from timing the ResNet-18 layer shapes at batch 256: a
 // grid that fits the chip in one round beats a finer one that needs a second,
 // and the short-K layers prefer more resident blocks over a deeper ring.
-int pick_tile(int64_t rp, int64_t rq, bool conv)
+// Small grids: a K-step (64 bytes) of a block costs about 0.5 us with the 128 x 128 tile and
+// 0.3 us with the 64 x 64 one whatever the ring depth (12 stages: no faster than 4), so the finer
+// tile wins while its blocks run side by side, one or two per CU.  Beyond that the operand
+// traffic of the small tile counts, the more the longer K is.  us, 128 x 128 -> 64 x 64 tile:
+//   conv, FP4, 256 filters on one 14 x 14 image (16 blocks, 18 steps)  13.3 -> 8.1
+//   GEMM, FP4, 128 x 1024 x 4096 (32 blocks, 32 steps)                 10.1 -> 7.0
+//   GEMM, int8, 512 x 4096 x 4096 (512 blocks, 64 steps)               20.1 -> 18.4
+//   weight-only GEMM, 512 x 4096 x 4096 (512 blocks, 384 steps)        98.4 -> 103.4, not taken
+//   GEMM, FP4, 1000 x 4000 x 1000 (1008 blocks, 8 steps)                9.5 -> 8.1
+//   GEMM, FP4, 768 x 4096 x 4096 (768 blocks, 32 steps)                12.3 -> 15.6, not taken
+int pick_tile(int64_t rp, int64_t rq, int nk, bool conv)
 {
+    if (nblocks(rp, rq, 64, 64) <= (nk > 64 ? 256 : (nk > 12 ? 512 : 1024))) return 0;
     if (rp <= 64) return nblocks(rp, rq, 64, 256) >= 512 ? 7 : 0;
     if (conv) {
         const int64_t t256 = nblocks(rp, rq, 128, 256), t128 = nblocks(rp, rq, 128, 128);
@@ -126,7 +137,7 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t st)
     prm.acc = a.acc;
     prm.y = a.y;
     prm.ep = a.ep;
-    const int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(a.M, a.N, false);
+    const int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(a.M, a.N, prm.nk, false);
     return a.fp4 ? launch_index<false, 0, 2>(cfg, prm, st) : launch_index<false>(cfg, prm, st);
 }
 
@@ -224,7 +235,7 @@ hipError_t launch_wgemm(const WGemmArgs& a, hipStream_t st)
     prm.Klogical = (int)a.K;
     prm.y = a.y;
     prm.ep = a.ep;
-    const int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(a.M, a.N, false);
+    const int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(a.M, a.N, prm.nk, false);
     return tmm_launch_bf16(kTileBP[cfg] >= 256 ? 2 : (kTileBP[cfg] >= 128 ? 1 : 0), prm, st);
 }
 
@@ -257,7 +268,7 @@ hipError_t launch_conv_mfma(const ConvArgs& a, hipStream_t st)
         const int64_t out_bytes = (int64_t)g.Nb * g.O * g.OH * g.OW * 4 * ((a.acc ? 1 : 0) + (a.y ? 1 : 0));
         prm.nt_out = out_bytes > (int64_t)128 << 20;
     }
-    int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(g.O, prm.RQ, true);
+    int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(g.O, prm.RQ, prm.nk, true);
     // a 64-filter layer with a centred stride-1 window: the variant that keeps the
     // tile's input pixel run in LDS (measured faster there; on par or slower elsewhere)
     if (g_forced_tile < 0 && cfg == 7 && halo_eligible(prm, 64)) cfg = 15;

@@ -447,6 +447,19 @@ def test_all_tile_configs_fp4(cfg, tile_reset):
             T.assert_y_close(cgot["y"].cpu().numpy(), cref["y"], "conv fp4 cfg %d" % cfg)
 
 
+@pytest.mark.parametrize("M,N,K,fmt", [
+    (2047, 2043, 70, FP4), (2049, 2048, 70, FP4),    # 1024 and 1056 small tiles, few K-steps
+    (1403, 1470, 833, B.RTN_CODE_I8), (1472, 1473, 833, B.RTN_CODE_I8),  # 506 and 552, 14 K-steps
+    (129, 130, 8200, FP4)])                          # 9 tiles, 65 K-steps
+def test_small_grid_tile_choice(M, N, K, fmt):
+    """The library's own choice on both sides of each line of the small-tile rule."""
+    _say("tile choice %d x %d x %d" % (M, N, K))
+    case = wl.gemm_case(M, N, K, seed=M + N)
+    ref, got = T.oracle_gemm(case), T.hip_gemm(case, fmt=fmt)
+    assert (got["D"].cpu().numpy() == ref["D"]).all()
+    T.assert_y_close(got["y"].cpu().numpy(), ref["y"], "tile choice")
+
+
 FP4_HALO_SHAPES = HALO_SHAPES + [
     ("h256", 256, 10, 136, 3, 1, 1, 3, None),      # 128 bytes per pixel: two K-steps per tap
     ("h200r", 200, 7, 130, 3, 1, 1, 9, 10),        # C padded to 256, ragged in O and pixels
