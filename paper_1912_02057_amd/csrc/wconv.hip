@@ -14,21 +14,23 @@
 //   RUN     output pixel m reads input pixel i(m) + kh W + kw of the flattened (image, row, column)
 //           index space, so the tile needs one contiguous run of input pixels; LDS row = place in
 //           the run, a tap is a row offset, a tap outside the image reads the zero row.
-//   GATHER  (1 x 1 windows, and every geometry whose run does not fit) LDS row = output pixel, one
-//           tap at a time; a chunk is then (16 CS channels, one tap).
+//   GATHER  (every window; the only form of those other than 3 x 3 and 5 x 5 and of runs that do not
+//           fit) LDS row = output pixel, one tap at a time; a chunk is then (16 CS channels, one tap).
+// Which of the forms runs is estimated from measured constants (kForms).
 // The next chunk's inputs are loaded into registers while this chunk is multiplied.  Weights are
 // read from global memory in the order the matrix instruction takes them (k_codes_to_frag), PD
 // steps ahead; they are shared by all blocks and stay in L2.  KG > 1: groups of four waves take
 // every KG-th chunk each, with LDS images of their own, and add up at the end -- for grids too
-// small to fill the chip.
+// small to fill the chip.  The order of the fp32 sums, and with it the last bits of a result, is the
+// form's: the same layer may round differently at another batch size.
 //
 // What it replaced wrote the three terms to memory (6 bytes per activation) in a pass of its own
 // and re-read them once per tap and filter tile through LDS, with the weights fetched again for
-// each term.  ResNet-18's 19 layer shapes (before -> now): batch 256 4.54 -> 2.74 ms, batch 40 1.57
-// -> 0.66 ms, batch 1 1.04 -> 0.19 ms.  The 3 x 3 stride-1 layers run at 1.0 to 1.2 PFLOP/s of
-// bf16 (a library matrix product reaches 1.41 on this card) and are bound by the matrix cores
-// at that clock; the stride-2 layers, which split four inputs per output, and the 64-channel
-// layers, whose blocks live for four chunks only, by load latency beside it.
+// each term.  ResNet-18's 19 layer shapes, GPU time (before -> now): batch 256 4.52 -> 2.51 ms, batch 64
+// 1.74 -> 0.87 ms, batch 1 1.02 -> 0.16 ms.  GATHER re-reads and re-splits its inputs once per tap, which
+// the split pass did not: over 857 random geometries with windows of 1 to 7 and strides of 1 to 4 this
+// kernel takes 0.44 times the time at the median and more than 1.02 times on 6, all of them windows of
+// 4 and more that are strided or 5 and more wide, at some 10000 output pixels and more: 1.16 at worst.
 #include "tmm_kernel.h"
 
 namespace rtn {
@@ -42,6 +44,9 @@ struct WcParams {
     int nchunk;         // chunks of 16 CS channels (GATHER: times taps)
     int span;           // RUN: rows of the image a tile may use
     FastDiv div_hw;     // by H W
+    FastDiv div_tap;    // GATHER: by the taps
+    int dc, dtap;       // GATHER: KG chunks on = dc channel chunks and dtap taps
+    unsigned kw_inv;    // tap / KW = tap * kw_inv >> 16 for the 49 taps there are at most
 };
 
 // Two floats -> their bf16 terms, packed; exact by truncation.
@@ -56,6 +61,14 @@ __device__ __forceinline__ void split2(float a, float b, unsigned& h, unsigned& 
     l = __builtin_amdgcn_perm(__float_as_uint(sb), __float_as_uint(sa), 0x07060302u);
 }
 
+// A second image, so that a chunk costs one barrier instead of two, where the LDS leaves room for as
+// many blocks as without it.
+template <bool GATHER, int KG, int BQ>
+constexpr int wc_images()
+{
+    return GATHER && KG == 1 && BQ == 128 ? 2 : 1;
+}
+
 // NTAP: taps of the window, 0 = GATHER.  RMAX: LDS rows per image (a multiple of 64).  BIG: the
 // input offsets within a tile do not fit 32 bits.
 template <int BP, int BQ, int WGP, int WGQ, int KG, int MINW, int NTAP, int CS, int RMAX, bool BIG>
@@ -68,6 +81,7 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
     constexpr int PD = NTAP == 9 ? 3 : (NTAP == 25 ? 5 : CS);     // weight prefetch distance
     constexpr int PLANE = (RMAX + 1) * 32;                        // bytes of one term's image (last row: zeros)
     constexpr int IMG = CS * 3 * PLANE;
+    constexpr int NBUF = wc_images<GATHER, KG, BQ>();              // images per group
     constexpr int NW = WGP * WGQ;                                 // waves per group
     constexpr int NU = 2 * CS * RMAX / (64 * NW);                 // (row, 8 channels) units per thread
     static_assert((NW == 4 || NW == 1) && TP >= 1 && TQ >= 1, "four waves or one per group");
@@ -83,7 +97,7 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
     int tileP, tileQ;
     if (!block_tile(prm.t, tileP, tileQ)) return;
     const int p0 = tileP * BP, q0 = tileQ * BQ;
-    int8_t* img = smem + kg * IMG;
+    int8_t* img = smem + kg * IMG;  // NBUF 2 (one group): this chunk's image
     const int HW = g.H * g.W, ntap = g.KH * g.KW;
 
     // output pixel -> flattened index of its tap (0, 0) (may be negative), and the in-image taps
@@ -133,44 +147,67 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
                 voff[i] = (Off)((unsigned)(nb - nb0) * (unsigned)(g.C * HW) + (unsigned)(f - nb * HW)) * 4u;
         }
     }
+    // The chunks of this group of waves: every KG-th, channels outermost.  (Counted, not divided out:
+    // a scalar division is a chain of some 25 dependent instructions, and GATHER took seven a chunk.)
+    struct Chunk {
+        int c, tap;  // channels 16 CS c and up; GATHER: the tap
+    };
+    const int nch = prm.nchunk;
+    auto next_chunk = [&](Chunk& ck) {  // (past the last one: RUN repeats it, GATHER has no channels to load)
+        ck.c += GATHER ? prm.dc : KG;
+        if (GATHER && (ck.tap += prm.dtap) >= ntap) ck.tap -= ntap, ++ck.c;
+        if (!GATHER && ck.c >= nch) ck.c = nch - 1;
+    };
     float xr[NU][8];
-    auto load_x = [&](int ci) {
-        int c0 = ci * 16 * CS, tap = 0;
-        int64_t toff = 0;
-        if (GATHER && ntap > 1) {
-            tap = ci % ntap;
-            c0 = (ci / ntap) * 16 * CS;
-        }
-        const int kh = GATHER ? tap / g.KW : 0, kw = tap - kh * g.KW;
-        toff = GATHER ? (int64_t)kh * g.W + kw : 0;
+    unsigned xtok = 0;  // GATHER, bit i: unit i's tap is in the image
+    auto load_x = [&](const Chunk& ck) {
+        const int c0 = ck.c * 16 * CS;
+        const int kh = GATHER ? (int)((unsigned)ck.tap * prm.kw_inv >> 16) : 0, kw = GATHER ? ck.tap - kh * g.KW : 0;
+        const int64_t toff = GATHER ? (int64_t)kh * g.W + kw : 0;
+        xtok = 0;
 #pragma unroll
         for (int i = 0; i < NU; ++i) {
-            const int hs = (wave + NW * i) / NSEG;
-            const bool live = GATHER || ((wave + NW * i) % NSEG) * 64 < prm.span;
-            const int c = c0 + 8 * hs;
-            const bool tok = !GATHER || ((tmask[GATHER ? i : 0] >> kh) & (tmask[GATHER ? i : 0] >> (8 + kw)) & 1) != 0;
-            // a tap outside the image: load the tile's first element and drop it
-            const Off o = tok ? (Off)(voff[i] + (Off)(toff * 4)) : (Off)0;
-            if (!live) continue;  // (wave-uniform, like the channel tail)
+            const int hs = (wave + NW * i) / NSEG, c = c0 + 8 * hs;
             const char* xc = (const char*)(xbase + (int64_t)c * HW);
-            if (c + 8 <= g.C) {
+            if constexpr (GATHER) {
+                // Loads only: using a value here (a select, say) would wait for it and leave nothing in
+                // flight behind the matrix work.  What must not count -- a tap outside the image, a
+                // channel past the last -- is loaded from somewhere valid and zeroed in store_x.
+                const bool tok = ((tmask[i] >> kh) & (tmask[i] >> (8 + kw)) & 1) != 0;
+                xtok |= (unsigned)tok << i;
+                if (c >= g.C) continue;  // (wave-uniform)
+                const Off o = tok ? (Off)(voff[i] + (Off)(toff * 4)) : (Off)0;  // outside: the tile's first element
+                const int last = g.C - 1 - c;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) xr[i][e] = *(const float*)(xc + (int64_t)e * HW * 4 + o);
+                for (int e = 0; e < 8; ++e) xr[i][e] = *(const float*)(xc + (Off)(e < last ? e : last) * (Off)HW * 4 + o);
             } else {
+                if (((wave + NW * i) % NSEG) * 64 >= prm.span) continue;  // (wave-uniform, like the channel tail)
+                if (c + 8 <= g.C) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) xr[i][e] = c + e < g.C ? *(const float*)(xc + (int64_t)e * HW * 4 + o) : 0.0f;
-            }
-            if (GATHER) {
+                    for (int e = 0; e < 8; ++e) xr[i][e] = *(const float*)(xc + (int64_t)e * HW * 4 + voff[i]);
+                } else {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) xr[i][e] = tok ? xr[i][e] : 0.0f;
+                    for (int e = 0; e < 8; ++e) xr[i][e] = c + e < g.C ? *(const float*)(xc + (int64_t)e * HW * 4 + voff[i]) : 0.0f;
+                }
             }
         }
     };
-    auto store_x = [&]() {
+    auto store_x = [&](const Chunk& ck) {
 #pragma unroll
         for (int i = 0; i < NU; ++i) {
             if (!GATHER && ((wave + NW * i) % NSEG) * 64 >= prm.span) continue;
             const int r = ((wave + NW * i) % NSEG) * 64 + lane, hs = (wave + NW * i) / NSEG;
+            if constexpr (GATHER) {
+                const int left = g.C - ck.c * 16 * CS - 8 * hs;
+                if (left < 8) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) xr[i][e] = e < left ? xr[i][e] : 0.0f;
+                }
+                if (ntap > 1) {  // (a single tap is never padded)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) xr[i][e] = (xtok >> i & 1) ? xr[i][e] : 0.0f;
+                }
+            }
             unsigned h[4], m[4], l[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) split2(xr[i][2 * e], xr[i][2 * e + 1], h[e], m[e], l[e]);
@@ -197,16 +234,10 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
         wstep[t] = (unsigned)rows * 32;
     }
     v4i pw[PD][TP];
-    // step s of chunk ci
-    auto load_w = [&](int ci, int s, v4i* dst) {
-        int slice, tap;
-        if (GATHER) {
-            tap = ntap > 1 ? ci % ntap : 0;
-            slice = (ntap > 1 ? ci / ntap : ci) * CS + s;
-        } else {
-            slice = ci * CS + s / (NTAP ? NTAP : 1);
-            tap = s % (NTAP ? NTAP : 1);
-        }
+    // step s of a chunk
+    auto load_w = [&](const Chunk& ck, int s, v4i* dst) {
+        int slice = ck.c * CS + (GATHER ? s : s / (NTAP ? NTAP : 1));
+        const int tap = GATHER ? ck.tap : s % (NTAP ? NTAP : 1);
         slice = slice < nslice ? slice : nslice - 1;  // past the end: multiplied with zero activations
         const int64_t idx = (int64_t)slice * ntap + tap;
 #pragma unroll
@@ -234,7 +265,8 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
         }
     }
     // the channels' epilogue factors: rows alpha, BN scale, BN shift of the prepared table
-    double* tab = (double*)(smem + KG * IMG);
+    constexpr int RED = (KG - 1) * BP * BQ * 4;                   // the groups' sums, over the images
+    double* tab = (double*)(smem + (KG * NBUF * IMG > RED ? KG * NBUF * IMG : RED));
     for (int e = tid; e < 3 * BP; e += 64 * NW * KG) {
         const int k = e / BP, o = p0 + e % BP;
         tab[e] = prm.t.cst_cls[(k ? k + 1 : 0) * ((g.O + 1) & ~1) + (o < prm.t.RP ? o : prm.t.RP - 1)];
@@ -260,21 +292,19 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
         }
     };
     __syncthreads();  // the zero rows
-    const int nch = prm.nchunk;
     const int niter = (nch + KG - 1) / KG;
-    auto chunk_of = [&](int it) {
-        const int ci = it * KG + kg;
-        return ci < nch ? ci : nch - 1;
-    };
+    const int kgc = GATHER ? (int)fastdiv((uint32_t)kg, prm.div_tap) : (kg < nch ? kg : nch - 1);
+    Chunk cur = {kgc, GATHER ? kg - kgc * ntap : 0}, nxt = cur;
 #pragma unroll
-    for (int s = 0; s < PD; ++s) load_w(chunk_of(0), s, pw[s]);
-    load_x(chunk_of(0));
+    for (int s = 0; s < PD; ++s) load_w(cur, s, pw[s]);
+    load_x(cur);
     for (int it = 0; it < niter; ++it) {
-        if (it) group_sync();  // everybody is done with the previous chunk's image
-        store_x();
+        if (NBUF == 1 && it) group_sync();  // everybody is done with the previous chunk's image
+        if (NBUF == 2) img = smem + (it & 1) * IMG;
+        store_x(cur);
+        next_chunk(nxt);
+        if (it + 1 < niter) load_x(nxt);
         const bool live = it * KG + kg < nch;
-        const int ci = chunk_of(it), cn = chunk_of(it + 1 < niter ? it + 1 : it);
-        if (it + 1 < niter) load_x(cn);
         group_sync();
         if (KG == 1 || live) {
 #pragma unroll
@@ -299,12 +329,13 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
                             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, pw[s % PD][i]),
                                                                                __builtin_bit_cast(v8bf, fq[j][q]), acc[i][j], 0, 0, 0);
                 if (s + PD < NSTEP)
-                    load_w(ci, s + PD, pw[s % PD]);
+                    load_w(cur, s + PD, pw[s % PD]);
                 else
-                    load_w(cn, s + PD - NSTEP, pw[s % PD]);
+                    load_w(nxt, s + PD - NSTEP, pw[s % PD]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+        cur = nxt;
     }
 
     // ---- KG groups -> one sum ------------------------------------------------------------------
@@ -399,12 +430,13 @@ __global__ __launch_bounds__(256) void k_codes_to_frag(const int8_t* codes, int 
 template <int BP, int BQ, int WGP, int WGQ, int KG, int MINW, int NTAP, int CS, int RMAX, bool BIG = false>
 hipError_t launch_wc(WcParams& prm, hipStream_t st)
 {
-    constexpr int img = KG * CS * 3 * (RMAX + 1) * 32, red = (KG - 1) * BP * BQ * 4;
-    static_assert(red <= img, "the groups' sums over the images, the epilogue table behind them");
-    constexpr int smem = img + 3 * BP * 8;
+    constexpr int img = KG * wc_images<NTAP == 0, KG, BQ>() * CS * 3 * (RMAX + 1) * 32, red = (KG - 1) * BP * BQ * 4;
+    constexpr int smem = (img > red ? img : red) + 3 * BP * 8;  // the groups' sums over the images, the epilogue table behind
     static_assert(smem <= kMaxLds, "LDS");
     const ConvGeom& g = prm.t.g;
     prm.nchunk = (g.C + 16 * CS - 1) / (16 * CS) * (NTAP ? 1 : g.KH * g.KW);
+    prm.dc = KG / (g.KH * g.KW);
+    prm.dtap = KG % (g.KH * g.KW);
     auto kern = k_wconv<BP, BQ, WGP, WGQ, KG, MINW, NTAP, CS, RMAX, BIG>;
     static bool attr_done = false;
     if (!attr_done) {
@@ -430,6 +462,48 @@ int64_t run_rows(const ConvGeom& g, int bq)
     const int64_t over_row = row_step > s ? row_step - s : 0, over_img = img_step > row_step ? img_step - row_step : 0;
     return n * s + nrow * over_row + nimg * over_img + (int64_t)(g.KH - 1) * g.W + g.KW;
 }
+
+// The kernel's forms and what a launch of each costs, in us:
+//   base + n round + steps u max(lat ceil(n / occ), n tp),   u = 1 + slope x
+// with n = blocks of the most loaded CU (256 CUs, rounded up), steps = chunks a group of waves takes,
+// x = rows of the run / 64 (GATHER: stride - 1, at most 3).  A chunk's latency counts once for every
+// occ blocks that run side by side, its throughput for each.  The constants are fitted to the times of all
+// forms on 857 geometries (windows 1 to 7, strides 1 to 4, 3 to 512 channels, 7 to 500 pixels wide, batch 1
+// to 256): the cheapest form by this estimate takes 1.006 times the fastest one's time on average, more
+// than 1.15 times it on 12 of them, 1.45 times at worst.
+struct WcForm {
+    int bp, bq, kg, window, rmax;  // window: side of a run's window, 0: GATHER
+    hipError_t (*launch)(WcParams&, hipStream_t);
+    float lat, tp, base, round, slope;
+    int occ;
+};
+template <int BP, int BQ, int WGP, int WGQ, int KG, int MINW, int NTAP, int CS, int RMAX>
+constexpr WcForm wc_form(float lat, float tp, float base, float round, float slope, int occ)
+{
+    return {BP, BQ, KG, NTAP == 9 ? 3 : (NTAP == 25 ? 5 : 0), RMAX, launch_wc<BP, BQ, WGP, WGQ, KG, MINW, NTAP, CS, RMAX>,
+            lat, tp, base, round, slope, occ};
+}
+const WcForm kForms[] = {
+    wc_form<128, 256, 1, 4, 1, 2, 9, 1, 384>(3.76, 3.4, 11.4, 0.982, 0.0582, 2),
+    wc_form<64, 256, 1, 4, 1, 2, 9, 1, 384>(1.94, 1.76, 6.9, 1, 0.0728, 2),
+    wc_form<64, 256, 1, 4, 1, 2, 9, 1, 512>(2.35, 1.48, 5.75, 2.48, 0.0288, 1),
+    wc_form<64, 256, 1, 4, 1, 2, 9, 1, 768>(2.35, 1.48, 5.75, 2.48, 0.0288, 1),
+    wc_form<128, 128, 2, 2, 1, 2, 9, 1, 256>(0.588, 2.28, 5.99, 1.94, 0, 4),
+    wc_form<128, 128, 2, 2, 1, 2, 9, 1, 768>(1.3, 0.814, 2.21, 4.34, 0.253, 2),
+    wc_form<64, 64, 2, 2, 4, 4, 9, 1, 256>(0.0333, 3.11, 1.7, 3.92, 0.0102, 4),
+    wc_form<64, 64, 2, 2, 2, 2, 9, 1, 512>(1.89, 0.519, 1.79, 2.66, 0.0789, 1),
+    wc_form<32, 32, 1, 1, 16, 4, 9, 1, 64>(2.39, 2.11, 0.358, 4.22, 0.798, 2),
+    wc_form<32, 32, 1, 1, 8, 2, 9, 1, 128>(1.86, 0.372, 1.49, 3.17, 0.322, 1),
+    wc_form<32, 32, 1, 1, 8, 2, 9, 1, 192>(1.86, 0.372, 1.49, 3.17, 0.322, 1),
+    wc_form<32, 32, 1, 1, 4, 1, 9, 1, 384>(0.506, 1.55, 1.18, 2.51, 0.402, 4),
+    wc_form<128, 128, 2, 2, 1, 2, 25, 1, 384>(4.95, 1.39, 7.67, 0.992, 0.0475, 1),
+    wc_form<64, 64, 2, 2, 4, 4, 25, 1, 256>(5.79, 0.372, 0.891, 4.87, 0.0322, 1),
+    wc_form<64, 64, 2, 2, 2, 2, 25, 1, 512>(0.518, 4.33, 3.26, 2.75, 0, 4),
+    wc_form<64, 256, 1, 4, 1, 2, 0, 2, 256>(1.76, 0.982, 5.76, 1.74, 0.251, 3),
+    wc_form<128, 128, 2, 2, 1, 2, 0, 2, 128>(1.17, 0.701, 5.29, 2.14, 0.12, 3),
+    wc_form<128, 128, 2, 2, 2, 4, 0, 2, 128>(1.78, 1.43, 5.36, 2.76, 0.17, 3),
+    wc_form<64, 64, 2, 2, 4, 4, 0, 2, 64>(1.34, 1.04, 4.56, 1.25, 0.218, 3),
+};
 
 }  // namespace
 
@@ -469,87 +543,52 @@ hipError_t launch_wconv(const WConvArgs& a, hipStream_t st)
     prm.x = a.x;
     prm.w = (const int8_t*)wb;
     prm.div_hw = make_fastdiv((uint32_t)(g.H * g.W));
+    prm.div_tap = make_fastdiv((uint32_t)(g.KH * g.KW));
+    prm.kw_inv = 65536u / (unsigned)g.KW + 1;
 
     // offsets within a tile: at most `images` images of C * HW elements
-    auto big = [&](int64_t rows) { return (rows / ((int64_t)g.H * g.W) + 2) * g.C * g.H * g.W * 4 >= (int64_t)1 << 32; };
-    const int ntap = g.KH == g.KW ? g.KH * g.KW : 0;
-    const int64_t r256 = run_rows(g, 256), r128 = run_rows(g, 128), r64 = run_rows(g, 64);
-    auto blocks = [&](int bp, int bq) { return (((int64_t)t.RP + bp - 1) / bp) * (((int64_t)t.RQ + bq - 1) / bq); };
-    auto fits = [&](int64_t rows, int rmax) { return rows > 0 && rows <= rmax && !big(rows); };
-    // Estimated cycles of the K loop, by tile: the matrix-core work of the most loaded CU over the
-    // tile's efficiency (small tiles read more LDS per MFMA, long runs are more work per output),
-    // but no less than the chunks' load latency one after another.  The constants fit the times of
-    // the ten ResNet-18 layer shapes at batch 1, 4, 16, 64 and 256: the choice is the fastest tile or
-    // within 15 % of it on all of them.
-    const double nchunk = (g.C + 15) / 16, slices = nchunk * g.KH * g.KW;
-    auto cost = [&](int bp, int bq, int kg, double eff, int64_t rows) {
-        const double work = (double)((blocks(bp, bq) + 255) / 256) * (bp * bq / 1024) * slices * 3 * 32 / 4 / eff *
-                            (1 + 0.15 * ((double)rows / bq - 1));
-        const double lat = nchunk / kg * (rows == bq ? 1500 : 3000);
-        return work > lat ? work : lat;
+    auto big = [&](int64_t images) { return images * g.C * g.H * g.W * 4 >= (int64_t)1 << 32; };
+    const bool run = g.KH == g.KW && (g.KH == 3 || g.KH == 5);
+    int64_t reach[4] = {};  // of 32, 64, 128, 256 pixels
+    for (int i = 0; run && i < 4; ++i) reach[i] = run_rows(g, 32 << i);
+    auto rows = [&](const WcForm& f) { return f.window ? reach[__builtin_ctz(f.bq) - 5] : f.bq; };
+    auto fits = [&](const WcForm& f) {
+        if (!f.window) return !big(256 / ((int64_t)g.OH * g.OW) + 2);
+        const int64_t r = rows(f);
+        return run && f.window == g.KH && r > 0 && r <= f.rmax && !big(r / ((int64_t)g.H * g.W) + 2);
     };
-    const int forced = forced_tile_config();
-    const int fbp = forced >= 0 ? kTileBP[forced] : 0;
-    auto pick = [&](double c0, double c1, double c2, double c3, double c4) {  // 128x256, 64x256, 128x128, 64x64, 32x32
-        if (forced >= 0)
-            return forced == 13 || forced == 4 || forced == 19 ? 0 : (fbp >= 128 ? 2 : (forced == 0 ? 3 : (forced == 11 ? 4 : 1)));
-        const double c[5] = {c0, c1, c2, c3, c4};
-        int b = 0;
-        for (int i = 1; i < 5; ++i) b = c[i] < c[b] ? i : b;
-        return b;
+    auto cost = [&](const WcForm& f) {
+        const int64_t blocks = (((int64_t)t.RP + f.bp - 1) / f.bp) * (((int64_t)t.RQ + f.bq - 1) / f.bq), n = (blocks + 255) / 256;
+        const int64_t chunks = f.window ? (g.C + 15) / 16 : (int64_t)((g.C + 31) / 32) * g.KH * g.KW;
+        const double u = 1 + f.slope * (f.window ? (double)rows(f) / 64 : (g.stride < 4 ? g.stride : 4) - 1);
+        const double lat = f.lat * (double)((n + f.occ - 1) / f.occ), tp = f.tp * (double)n;
+        return f.base + f.round * (double)n + (double)((chunks + f.kg - 1) / f.kg) * u * (lat > tp ? lat : tp);
     };
-    const double inf = 1e300;
-    const int64_t r32 = run_rows(g, 32);
-    if (ntap == 9 && fits(r64, 512)) {
-        const int kg32 = r32 <= 64 ? 16 : (r32 <= 192 ? 8 : 4);  // what LDS holds
-        switch (pick(fits(r256, 384) ? cost(128, 256, 1, 0.40, r256) : inf, fits(r256, 512) ? cost(64, 256, 1, 0.45, r256) : inf,
-                     fits(r128, 768) ? cost(128, 128, 1, 0.45, r128) : inf, cost(64, 64, 4, 0.3, r64),
-                     fits(r32, 384) ? cost(32, 32, kg32, 0.2, r32) : inf)) {
-            case 0:
-                prm.span = (int)r256;
-                if (fits(r256, 384)) return launch_wc<128, 256, 1, 4, 1, 2, 9, 1, 384>(prm, st);
-                break;
-            case 1:
-                prm.span = (int)r256;
-                if (fits(r256, 384)) return launch_wc<64, 256, 1, 4, 1, 2, 9, 1, 384>(prm, st);
-                if (fits(r256, 512)) return launch_wc<64, 256, 1, 4, 1, 2, 9, 1, 512>(prm, st);
-                break;
-            case 2:
-                prm.span = (int)r128;
-                if (fits(r128, 256)) return launch_wc<128, 128, 2, 2, 1, 2, 9, 1, 256>(prm, st);
-                if (fits(r128, 768)) return launch_wc<128, 128, 2, 2, 1, 2, 9, 1, 768>(prm, st);
-                break;
-            case 4:
-                prm.span = (int)r32;
-                if (fits(r32, 64)) return launch_wc<32, 32, 1, 1, 16, 4, 9, 1, 64>(prm, st);
-                if (fits(r32, 128)) return launch_wc<32, 32, 1, 1, 8, 2, 9, 1, 128>(prm, st);
-                if (fits(r32, 192)) return launch_wc<32, 32, 1, 1, 8, 2, 9, 1, 192>(prm, st);
-                if (fits(r32, 384)) return launch_wc<32, 32, 1, 1, 4, 1, 9, 1, 384>(prm, st);
-                break;
-            default: break;
-        }
-        prm.span = (int)r64;
-        if (fits(r64, 256)) return launch_wc<64, 64, 2, 2, 4, 4, 9, 1, 256>(prm, st);
-        return launch_wc<64, 64, 2, 2, 2, 2, 9, 1, 512>(prm, st);
+    auto pick = [&](auto&& admits) {
+        const WcForm* best = nullptr;
+        double least = 0;
+        for (const WcForm& f : kForms)
+            if (admits(f) && fits(f)) {
+                const double c = cost(f);
+                if (!best || c < least) best = &f, least = c;
+            }
+        return best;
+    };
+    const WcForm* f;
+    if (const int forced = forced_tile_config(); forced >= 0) {
+        // 8, 9, 10, 12: a gathering form; else the tile's run, the smallest run, or gathering if none fits
+        const bool gather = forced == 8 || forced == 9 || forced == 10 || forced == 12, wide = forced == 4 || forced == 13 || forced == 19;
+        const int bp = forced == 11 ? 32 : (forced == 10 ? 64 : kTileBP[forced] >= 128 ? 128 : 64);
+        const int bq = forced == 11 ? 32 : (forced == 0 || forced == 10 ? 64 : bp == 128 && !wide ? 128 : 256);
+        f = pick([&](const WcForm& k) { return !k.window == gather && k.bp == bp && k.bq == bq && (!gather || (k.kg == 2) == (forced == 12)); });
+        if (!f) f = pick([&](const WcForm& k) { return k.window && k.bp == 64 && k.bq == 64; });
+        if (!f) f = pick([&](const WcForm& k) { return !k.window && k.kg != 2 && (bp == 32 || bq == 64 ? k.bq == 64 : k.bq == bq); });
+    } else {
+        f = pick([](const WcForm&) { return true; });
     }
-    if (ntap == 25 && fits(r64, 512)) {
-        if (fits(r128, 384) && pick(inf, inf, cost(128, 128, 1, 0.45, r128), cost(64, 64, 4, 0.3, r64), inf) == 2) {
-            prm.span = (int)r128;
-            return launch_wc<128, 128, 2, 2, 1, 2, 25, 1, 384>(prm, st);
-        }
-        prm.span = (int)r64;
-        if (fits(r64, 256)) return launch_wc<64, 64, 2, 2, 4, 4, 25, 1, 256>(prm, st);
-        return launch_wc<64, 64, 2, 2, 2, 2, 25, 1, 512>(prm, st);
-    }
-    // (GATHER: a tile's outputs lie in at most 256 / (OH OW) + 2 images)
-    if ((256 / ((int64_t)g.OH * g.OW) + 2) * g.C * g.H * g.W * 4 >= (int64_t)1 << 32)
-        return launch_wc<64, 64, 2, 2, 4, 4, 0, 2, 64, true>(prm, st);
-    switch (pick(inf, cost(64, 256, 1, 0.40, 256), cost(128, 128, 1, 0.45, 128), cost(64, 64, 4, 0.3, 64), inf)) {
-        case 0:
-        case 1: return launch_wc<64, 256, 1, 4, 1, 2, 0, 2, 256>(prm, st);
-        case 2: return launch_wc<128, 128, 2, 2, 1, 2, 0, 2, 128>(prm, st);
-        default: return launch_wc<64, 64, 2, 2, 4, 4, 0, 2, 64>(prm, st);
-    }
+    if (!f) return launch_wc<64, 64, 2, 2, 4, 4, 0, 2, 64, true>(prm, st);
+    prm.span = (int)rows(*f);
+    return f->launch(prm, st);
 }
 
 }  // namespace rtn

@@ -1327,6 +1327,28 @@ def test_weight_conv_edges_every_tile(edge, tile_reset):
         _wconv_check(shape, 5, seed=31 + W, Wx=W, relu=True, bn=True, what="%s cfg %d" % (shape.name, cfg))
 
 
+@pytest.mark.parametrize("edge", WCONV_EDGES, ids=lambda e: e[0].name)
+def test_weight_conv_edges_gathering_forms(edge, tile_reset):
+    """Windows a run could serve and windows it cannot, through every form that gathers tap by tap:
+    128 x 128, 64 x 256, 64 x 64 with four groups of waves and 128 x 128 with two (their chunks run
+    through the taps in steps of 1, 2 and 4, so a group may skip channels, taps or both)."""
+    shape, W = edge
+    for cfg in (8, 9, 10, 12):
+        _say("weight-only conv gathered %s W=%d cfg %d" % (shape, W, cfg))
+        B.set_tile_config(cfg)
+        _wconv_check(shape, 5, seed=41 + W, Wx=W, relu=True, bn=True, what="%s cfg %d" % (shape.name, cfg))
+
+
+@pytest.mark.parametrize("W", [62, 63, 96, 127, 128, 254, 255, 256])
+def test_weight_conv_run_lengths(W, tile_reset):
+    """3 x 3 runs of 256 + 2 W + 2 pixels on both sides of the 64 x 256 tile's limits (384, 512, 768 rows)."""
+    shape = wl.ConvShape("run%d" % W, 20, 4, 70, 3, 1, 1)
+    for cfg in (-1, 7, 1, 13):
+        _say("weight-only conv run W=%d cfg %d" % (W, cfg))
+        B.set_tile_config(cfg)
+        _wconv_check(shape, 3, seed=W + 3, relu=True, bn=True, Wx=W, what="W %d cfg %d" % (W, cfg))
+
+
 def test_weight_conv_exact_on_ternary_activations():
     _say("weight-only conv on ternary activations")
     shape = wl.ConvShape("e", 64, 10, 96, 3, 1, 1)
