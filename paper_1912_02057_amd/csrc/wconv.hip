@@ -69,7 +69,7 @@ constexpr int wc_images()
     return GATHER && KG == 1 && BQ == 128 ? 2 : 1;
 }
 
-// NTAP: taps of the window, 0 = GATHER.  RMAX: LDS rows per image (a multiple of 64).  BIG: the
+// NTAP: taps of the window, 0 = GATHER.  RMAX: LDS rows per image (a multiple of 64).  BIG (GATHER): the
 // input offsets within a tile do not fit 32 bits.
 template <int BP, int BQ, int WGP, int WGQ, int KG, int MINW, int NTAP, int CS, int RMAX, bool BIG>
 __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams prm)
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
     constexpr int NU = 2 * CS * RMAX / (64 * NW);                 // (row, 8 channels) units per thread
     static_assert((NW == 4 || NW == 1) && TP >= 1 && TQ >= 1, "four waves or one per group");
     static_assert(NSTEP % PD == 0 && RMAX % 64 == 0 && (2 * CS * RMAX) % (64 * NW) == 0 && (!GATHER || RMAX == BQ), "chunk shape");
-    static_assert(NTAP == 0 || NTAP == 9 || NTAP == 25, "window");
+    static_assert(NTAP == 0 || (!BIG && (NTAP == 9 || NTAP == 25)), "window");
 
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
@@ -141,10 +141,7 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
             int f = imin < total_px - r ? imin + r : total_px - 1;
             f = f < 0 ? 0 : f;
             const int nb = (int)fastdiv((uint32_t)f, prm.div_hw);
-            if (BIG)
-                voff[i] = (Off)(((int64_t)(nb - nb0) * g.C * HW + (f - nb * HW)) * 4);
-            else
-                voff[i] = (Off)((unsigned)(nb - nb0) * (unsigned)(g.C * HW) + (unsigned)(f - nb * HW)) * 4u;
+            voff[i] = (Off)((unsigned)(nb - nb0) * (unsigned)(g.C * HW) + (unsigned)(f - nb * HW)) * 4u;
         }
     }
     // The chunks of this group of waves: every KG-th, channels outermost.  (Counted, not divided out:

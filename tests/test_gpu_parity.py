@@ -1349,6 +1349,31 @@ def test_weight_conv_run_lengths(W, tile_reset):
         _wconv_check(shape, 3, seed=W + 3, relu=True, bn=True, Wx=W, what="W %d cfg %d" % (W, cfg))
 
 
+@pytest.mark.parametrize("Nb,H,k,stride,pad", [(66, 65, 2, 64, 0), (5, 33, 3, 40, 1)], ids=["beyond4GiB", "padded"])
+def test_weight_conv_wide_offsets(Nb, H, k, stride, pad):
+    """Images so large that a tile's inputs may lie 4 GiB apart: the gathering form with 64-bit offsets
+    (one output pixel per image; in the first case the tile's last images really are beyond 4 GiB)."""
+    C, O = 4096, 33
+    _say("weight-only conv, wide offsets: %d images of %d x %d x %d, window %d" % (Nb, C, H, H, k))
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(H)
+    x = torch.randn((Nb, C, H, H), generator=g, device=T.DEV)
+    w = torch.randn((O * k * k, C), generator=g, device=T.DEV)          # [O][KH][KW][C]: the rows of the code tensor
+    cw, _ = B.ternarize_pack(w, -0.6, 0.6, want_sum=False)
+    aw = torch.rand(O, generator=g, device=T.DEV) + 0.5
+    y = B.ternary_weight_conv2d(x, cw, O, k, k, stride, pad, aw)
+    torch.cuda.synchronize()
+    assert y.shape == (Nb, O, 1, 1)
+    win = torch.nn.functional.pad(x[:, :, :k - pad, :k - pad], (pad, 0, pad, 0)).permute(0, 2, 3, 1).reshape(Nb, -1)
+    win = win.cpu().numpy().astype(np.float64)
+    tw = cw[:, :C].cpu().numpy().astype(np.float64).reshape(O, -1)
+    a = aw.cpu().numpy().astype(np.float64)
+    ref, scale = (win @ tw.T) * a, (np.abs(win) @ np.abs(tw).T) * a
+    tol = (4.0 * np.sqrt(3.0 * C * k * k) + 8.0) * 2.0 ** -24 * scale + 1.2e-7 * np.abs(ref)   # as _wconv_check
+    err = np.abs(y.cpu().numpy().reshape(Nb, O) - ref)
+    assert (err <= tol).all(), float((err / tol).max())
+
+
 def test_weight_conv_exact_on_ternary_activations():
     _say("weight-only conv on ternary activations")
     shape = wl.ConvShape("e", 64, 10, 96, 3, 1, 1)
