@@ -227,6 +227,40 @@ def test_gemm_planes_paths_vs_fp4(M, N, K, path):
     T.assert_y_close(y.cpu().numpy(), want["y"].cpu().numpy(), "planes y")
 
 
+@pytest.mark.parametrize("n", [200, 1801, 4101])
+@pytest.mark.parametrize("fmt", [B.RTN_CODE_I8, B.RTN_CODE_FP4, B.RTN_CODE_BITPLANE, None], ids=["i8", "fp4", "planes", "weight_only"])
+def test_gemm_nan_does_not_depend_on_the_tile(fmt, n):
+    """Without ReLU and BN a NaN in one column's factor (weight only: a NaN and an infinity in x) comes
+    out as NaN wherever it lies -- interior tiles and ragged ones, with the accumulators and without --
+    and touches nothing else.  The sizes take the 64, 128 and 256 wide tiles."""
+    _say("gemm nan fmt=%s n=%d" % (fmt, n))
+    K = 70
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(n)
+    x, w = torch.randn((n, K), generator=g, device=T.DEV), torch.randn((n, K), generator=g, device=T.DEV)
+    fac = torch.rand(n, generator=g, device=T.DEV) + 0.5
+    bad = [3, n // 2, n - 1]
+    if fmt is None:
+        cw, _ = B.ternarize_pack(w, -0.5, 0.5, want_sum=False)
+        want = B.ternary_weight_gemm(x, cw, n, n, K, fac)
+        x[bad[0], 5], x[bad[1], 7], x[bad[2], 0] = float("nan"), float("inf"), float("-inf")
+        outs = [B.ternary_weight_gemm(x, cw, n, n, K, fac)]
+        at = (bad, slice(None))
+    else:
+        (ca, sa), (cw, sw) = B.ternarize_pack(x, -0.5, 0.5, fmt), B.ternarize_pack(w, -0.5, 0.5, fmt)
+        run = lambda f, acc: B.ternary_gemm(ca, cw, n, n, K, fmt=fmt, ep=B.Epilogue(1.1, 0.1, f, None, sa, sw), want_acc=acc)[1]
+        want = run(fac, False)
+        fbad = fac.clone()
+        fbad[bad] = float("nan")
+        outs = [run(fbad, False), run(fbad, True)]
+        at = (slice(None), bad)
+    torch.cuda.synchronize()
+    for y in outs:
+        assert bool(torch.isnan(y[at]).all())
+        y[at] = want[at]
+        assert torch.equal(y, want)
+
+
 def test_standalone_epilogue_gemm():
     _say("standalone epilogue (gemm form)")
     case = wl.gemm_case(100, 90, 300, seed=4, table4=True)
