@@ -96,11 +96,12 @@ struct Gran {
 const rtn_epilogue* epilogue(PyObject* o)  // address of an Epilogue's struct, or None
 {
     if (o == Py_None) return nullptr;
-    return (const rtn_epilogue*)PyLong_AsVoidPtr(o);
+    const void* p = PyLong_AsVoidPtr(o);
+    if (!p && PyErr_Occurred()) throw PyError();
+    return (const rtn_epilogue*)p;
 }
 
-// torch's current stream.  Arguments are evaluated in no particular order: on a host without a GPU
-// the argument checks, which no host tensor passes, must be what raises.
+// torch's current stream.  On a host without a GPU the library's own checks must be what raises.
 void* stream()
 {
     try {
@@ -111,6 +112,14 @@ void* stream()
     }
 }
 
+// The interpreter's lock is given up around a call into the library, as ctypes gives it up: a launch that
+// loads its code object or waits for room in the queue must not stop every other Python thread.  The
+// arguments are converted before (the caller's frame keeps them alive meanwhile).
+struct Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 // Runs `f` on the arguments; a C++ exception or a wrong argument count becomes a Python error.
 template <class F>
 PyObject* call(Py_ssize_t want, Py_ssize_t n, F f)
@@ -120,9 +129,7 @@ PyObject* call(Py_ssize_t want, Py_ssize_t n, F f)
         return nullptr;
     }
     try {
-        const int rc = f();
-        if (PyErr_Occurred()) return nullptr;
-        return PyLong_FromLong(rc);
+        return PyLong_FromLong(f());
     } catch (const PyError&) {
         return nullptr;
     } catch (const std::exception& e) {
@@ -138,9 +145,15 @@ PyObject* pack(PyObject*, Args a, Py_ssize_t n)
     return call(11, n, [&] {
         const Gran lo(a[6], "lo"), hi(a[7], "hi");
         if (lo.gran != hi.gran) fail(PyExc_AssertionError, "%s: lo and hi must both be scalars or both vectors", "ternarize_pack");
-        return rtn_ternarize_pack((const float*)dev(a[0], c10::kFloat, "x"), (rtn_layout)integer(a[1]), integer(a[2]), integer(a[3]),
-                                  integer(a[4]), integer(a[5]), lo.ptr, hi.ptr, lo.gran, (rtn_code_format)integer(a[8]),
-                                  raw(a[9], "codes"), (int32_t*)dev(a[10], c10::kInt, "sum_t"), stream());
+        const float* x = (const float*)dev(a[0], c10::kFloat, "x");
+        const rtn_layout layout = (rtn_layout)integer(a[1]);
+        const int64_t d0 = integer(a[2]), d1 = integer(a[3]), d2 = integer(a[4]), d3 = integer(a[5]);
+        const rtn_code_format fmt = (rtn_code_format)integer(a[8]);
+        void* out = raw(a[9], "codes");
+        int32_t* sum = (int32_t*)dev(a[10], c10::kInt, "sum_t");
+        void* st = stream();
+        const Unlocked u;
+        return rtn_ternarize_pack(x, layout, d0, d1, d2, d3, lo.ptr, hi.ptr, lo.gran, fmt, out, sum, st);
     });
 }
 
@@ -149,12 +162,17 @@ PyObject* gemm(PyObject*, Args a, Py_ssize_t n)
 {
     return call(10, n, [&] {
         const rtn_code_format fmt = (rtn_code_format)integer(a[0]);
+        const rtn_path path = (rtn_path)integer(a[1]);
         const int64_t M = integer(a[4]), N = integer(a[5]), K = integer(a[6]);
         const bool planes = fmt == RTN_CODE_BITPLANE;
         const void* ac = planes ? raw(a[2], "a_codes") : codes(a[2], M, K, fmt, "a_codes");
         const void* wc = planes ? raw(a[3], "w_codes") : codes(a[3], N, K, fmt, "w_codes");
-        return rtn_ternary_gemm(fmt, (rtn_path)integer(a[1]), ac, wc, M, N, K, (int32_t*)dev(a[7], c10::kInt, "acc_out"), epilogue(a[8]),
-                                (float*)dev(a[9], c10::kFloat, "y_out"), nullptr, 0, stream());
+        int32_t* acc = (int32_t*)dev(a[7], c10::kInt, "acc_out");
+        const rtn_epilogue* ep = epilogue(a[8]);
+        float* y = (float*)dev(a[9], c10::kFloat, "y_out");
+        void* st = stream();
+        const Unlocked u;
+        return rtn_ternary_gemm(fmt, path, ac, wc, M, N, K, acc, ep, y, nullptr, 0, st);
     });
 }
 
@@ -163,15 +181,20 @@ PyObject* conv2d(PyObject*, Args a, Py_ssize_t n)
 {
     return call(18, n, [&] {
         const rtn_code_format fmt = (rtn_code_format)integer(a[0]);
+        const rtn_path path = (rtn_path)integer(a[1]);
         const int64_t Nb = integer(a[4]), C = integer(a[5]), H = integer(a[6]), W = integer(a[7]), O = integer(a[8]);
-        const int KH = (int)integer(a[9]), KW = (int)integer(a[10]);
+        const int KH = (int)integer(a[9]), KW = (int)integer(a[10]), stride = (int)integer(a[11]), pad = (int)integer(a[12]);
+        const rtn_pad_mode mode = (rtn_pad_mode)integer(a[13]);
         const void* ac = codes(a[2], Nb * H * W, C, fmt, "a_codes");
         const void* wc = codes(a[3], O * KH * KW, C, fmt, "w_codes");
-        return rtn_ternary_conv2d_implicit_gemm(fmt, (rtn_path)integer(a[1]), ac, wc, Nb, C, H, W, O, KH, KW, (int)integer(a[11]),
-                                                (int)integer(a[12]), (rtn_pad_mode)integer(a[13]),
-                                                (int32_t*)dev(a[14], c10::kInt, "acc_out"), epilogue(a[15]),
-                                                (float*)dev(a[16], c10::kFloat, "y_out"), raw(a[17], "workspace"),
-                                                raw_bytes(a[17], "workspace"), stream());
+        int32_t* acc = (int32_t*)dev(a[14], c10::kInt, "acc_out");
+        const rtn_epilogue* ep = epilogue(a[15]);
+        float* y = (float*)dev(a[16], c10::kFloat, "y_out");
+        void* ws = raw(a[17], "workspace");
+        const size_t wsb = raw_bytes(a[17], "workspace");
+        void* st = stream();
+        const Unlocked u;
+        return rtn_ternary_conv2d_implicit_gemm(fmt, path, ac, wc, Nb, C, H, W, O, KH, KW, stride, pad, mode, acc, ep, y, ws, wsb, st);
     });
 }
 
@@ -181,19 +204,26 @@ PyObject* conv2d_ternarize(PyObject*, Args a, Py_ssize_t n)
 {
     return call(22, n, [&] {
         const rtn_code_format fmt = (rtn_code_format)integer(a[0]);
+        const rtn_path path = (rtn_path)integer(a[1]);
         const int64_t Nb = integer(a[4]), C = integer(a[5]), H = integer(a[6]), W = integer(a[7]), O = integer(a[8]);
         const int KH = (int)integer(a[9]), KW = (int)integer(a[10]), stride = (int)integer(a[11]), pad = (int)integer(a[12]);
+        const rtn_pad_mode mode = (rtn_pad_mode)integer(a[13]);
         const void* ac = codes(a[2], Nb * H * W, C, fmt, "a_codes");
         const void* wc = codes(a[3], O * KH * KW, C, fmt, "w_codes");
         const int64_t OH = stride > 0 ? (H + 2 * pad - KH) / stride + 1 : 0, OW = stride > 0 ? (W + 2 * pad - KW) / stride + 1 : 0;
         void* co = codes(a[20], Nb * OH * OW, O, fmt, "codes_out");
         const Gran lo(a[17], "lo"), hi(a[18], "hi");
         if (lo.gran != hi.gran) fail(PyExc_AssertionError, "%s: lo and hi must both be scalars or both vectors", "ternary_conv2d_ternarize");
-        return rtn_ternary_conv2d_ternarize(fmt, (rtn_path)integer(a[1]), ac, wc, Nb, C, H, W, O, KH, KW, stride, pad,
-                                            (rtn_pad_mode)integer(a[13]), epilogue(a[14]),
-                                            (const float*)dev(a[15], c10::kFloat, "residual"), truth(a[16]), lo.ptr, hi.ptr, lo.gran,
-                                            (float*)dev(a[19], c10::kFloat, "y_out"), co, raw(a[21], "workspace"),
-                                            raw_bytes(a[21], "workspace"), stream());
+        const rtn_epilogue* ep = epilogue(a[14]);
+        const float* res = (const float*)dev(a[15], c10::kFloat, "residual");
+        const int relu_out = truth(a[16]);
+        float* y = (float*)dev(a[19], c10::kFloat, "y_out");
+        void* ws = raw(a[21], "workspace");
+        const size_t wsb = raw_bytes(a[21], "workspace");
+        void* st = stream();
+        const Unlocked u;
+        return rtn_ternary_conv2d_ternarize(fmt, path, ac, wc, Nb, C, H, W, O, KH, KW, stride, pad, mode, ep, res, relu_out, lo.ptr, hi.ptr,
+                                            lo.gran, y, co, ws, wsb, st);
     });
 }
 
@@ -202,12 +232,16 @@ PyObject* depthwise(PyObject*, Args a, Py_ssize_t n)
 {
     return call(14, n, [&] {
         const int64_t Nb = integer(a[2]), C = integer(a[3]), H = integer(a[4]), W = integer(a[5]);
-        const int KH = (int)integer(a[6]), KW = (int)integer(a[7]);
+        const int KH = (int)integer(a[6]), KW = (int)integer(a[7]), stride = (int)integer(a[8]), pad = (int)integer(a[9]);
+        const rtn_pad_mode mode = (rtn_pad_mode)integer(a[10]);
         const void* ac = codes(a[0], Nb * H * W, C, RTN_CODE_I8, "a_codes");
         const void* wc = codes(a[1], C, KH * KW, RTN_CODE_I8, "w_codes");
-        return rtn_ternary_depthwise_conv2d(ac, wc, Nb, C, H, W, KH, KW, (int)integer(a[8]), (int)integer(a[9]), (rtn_pad_mode)integer(a[10]),
-                                            (int32_t*)dev(a[11], c10::kInt, "acc_out"), epilogue(a[12]),
-                                            (float*)dev(a[13], c10::kFloat, "y_out"), stream());
+        int32_t* acc = (int32_t*)dev(a[11], c10::kInt, "acc_out");
+        const rtn_epilogue* ep = epilogue(a[12]);
+        float* y = (float*)dev(a[13], c10::kFloat, "y_out");
+        void* st = stream();
+        const Unlocked u;
+        return rtn_ternary_depthwise_conv2d(ac, wc, Nb, C, H, W, KH, KW, stride, pad, mode, acc, ep, y, st);
     });
 }
 
@@ -217,9 +251,17 @@ PyObject* weight_gemm(PyObject*, Args a, Py_ssize_t n)
     return call(12, n, [&] {
         const Gran al(a[6], "alpha_w");
         auto fn = truth(a[2]) ? rtn_ternary_weight_gemm_prepared : rtn_ternary_weight_gemm;
-        return fn((const float*)dev(a[0], c10::kFloat, "x"), raw(a[1], "w_codes"), integer(a[3]), integer(a[4]), integer(a[5]), al.ptr, al.gran,
-                  truth(a[7]), (const float*)dev(a[8], c10::kFloat, "bn_scale"), (const float*)dev(a[9], c10::kFloat, "bn_shift"),
-                  (float*)dev(a[10], c10::kFloat, "y_out"), raw(a[11], "workspace"), raw_bytes(a[11], "workspace"), stream());
+        const float* x = (const float*)dev(a[0], c10::kFloat, "x");
+        const void* w = raw(a[1], "w_codes");
+        const int64_t M = integer(a[3]), N = integer(a[4]), K = integer(a[5]);
+        const int relu = truth(a[7]);
+        const float *bs = (const float*)dev(a[8], c10::kFloat, "bn_scale"), *bh = (const float*)dev(a[9], c10::kFloat, "bn_shift");
+        float* y = (float*)dev(a[10], c10::kFloat, "y_out");
+        void* ws = raw(a[11], "workspace");
+        const size_t wsb = raw_bytes(a[11], "workspace");
+        void* st = stream();
+        const Unlocked u;
+        return fn(x, w, M, N, K, al.ptr, al.gran, relu, bs, bh, y, ws, wsb, st);
     });
 }
 
@@ -227,10 +269,17 @@ PyObject* weight_gemm(PyObject*, Args a, Py_ssize_t n)
 PyObject* weight_conv2d_prepared(PyObject*, Args a, Py_ssize_t n)
 {
     return call(14, n, [&] {
-        return rtn_ternary_weight_conv2d_prepared(
-            (const float*)dev(a[0], c10::kFloat, "x"), raw(a[1], "prepared"), integer(a[2]), integer(a[3]), integer(a[4]), integer(a[5]),
-            integer(a[6]), (int)integer(a[7]), (int)integer(a[8]), (int)integer(a[9]), (int)integer(a[10]), truth(a[11]),
-            (float*)dev(a[12], c10::kFloat, "y_out"), raw(a[13], "workspace"), raw_bytes(a[13], "workspace"), stream());
+        const float* x = (const float*)dev(a[0], c10::kFloat, "x");
+        const void* w = raw(a[1], "prepared");
+        const int64_t Nb = integer(a[2]), C = integer(a[3]), H = integer(a[4]), W = integer(a[5]), O = integer(a[6]);
+        const int KH = (int)integer(a[7]), KW = (int)integer(a[8]), stride = (int)integer(a[9]), pad = (int)integer(a[10]);
+        const int relu = truth(a[11]);
+        float* y = (float*)dev(a[12], c10::kFloat, "y_out");
+        void* ws = raw(a[13], "workspace");
+        const size_t wsb = raw_bytes(a[13], "workspace");
+        void* st = stream();
+        const Unlocked u;
+        return rtn_ternary_weight_conv2d_prepared(x, w, Nb, C, H, W, O, KH, KW, stride, pad, relu, y, ws, wsb, st);
     });
 }
 
@@ -239,9 +288,15 @@ PyObject* activation_backward(PyObject*, Args a, Py_ssize_t n)
 {
     return call(9, n, [&] {
         const Gran lo(a[3], "lo"), hi(a[4], "hi"), ga(a[5], "gamma");
-        return rtn_activation_backward((const float*)dev(a[0], c10::kFloat, "a"), (const float*)dev(a[1], c10::kFloat, "grad_out"),
-                                       integer(a[2]), lo.ptr, hi.ptr, ga.ptr, (float*)dev(a[6], c10::kFloat, "grad_in"),
-                                       (double*)dev(a[7], c10::kDouble, "sums"), raw(a[8], "workspace"), raw_bytes(a[8], "workspace"), stream());
+        const float *x = (const float*)dev(a[0], c10::kFloat, "a"), *g = (const float*)dev(a[1], c10::kFloat, "grad_out");
+        const int64_t count = integer(a[2]);
+        float* gi = (float*)dev(a[6], c10::kFloat, "grad_in");
+        double* sums = (double*)dev(a[7], c10::kDouble, "sums");
+        void* ws = raw(a[8], "workspace");
+        const size_t wsb = raw_bytes(a[8], "workspace");
+        void* st = stream();
+        const Unlocked u;
+        return rtn_activation_backward(x, g, count, lo.ptr, hi.ptr, ga.ptr, gi, sums, ws, wsb, st);
     });
 }
 
@@ -250,10 +305,15 @@ PyObject* weight_backward(PyObject*, Args a, Py_ssize_t n)
 {
     return call(11, n, [&] {
         const Gran lo(a[4], "lo"), hi(a[5], "hi");
-        return rtn_weight_backward((const float*)dev(a[0], c10::kFloat, "w"), (const float*)dev(a[1], c10::kFloat, "grad_out"), integer(a[2]),
-                                   integer(a[3]), lo.ptr, hi.ptr, (const float*)dev(a[6], c10::kFloat, "k_w"),
-                                   (const float*)dev(a[7], c10::kFloat, "b_w"), (const float*)dev(a[8], c10::kFloat, "alpha"),
-                                   (float*)dev(a[9], c10::kFloat, "grad_w"), (double*)dev(a[10], c10::kDouble, "sums"), stream());
+        const float *w = (const float*)dev(a[0], c10::kFloat, "w"), *g = (const float*)dev(a[1], c10::kFloat, "grad_out");
+        const int64_t O = integer(a[2]), K = integer(a[3]);
+        const float *kw = (const float*)dev(a[6], c10::kFloat, "k_w"), *bw = (const float*)dev(a[7], c10::kFloat, "b_w"),
+                    *al = (const float*)dev(a[8], c10::kFloat, "alpha");
+        float* gw = (float*)dev(a[9], c10::kFloat, "grad_w");
+        double* sums = (double*)dev(a[10], c10::kDouble, "sums");
+        void* st = stream();
+        const Unlocked u;
+        return rtn_weight_backward(w, g, O, K, lo.ptr, hi.ptr, kw, bw, al, gw, sums, st);
     });
 }
 

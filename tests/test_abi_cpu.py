@@ -440,3 +440,53 @@ def test_binding_native_calls_refuse_host_tensors_and_wrong_types():
         B._native().gemm(1, 2, 3)
     with pytest.raises(TypeError):
         B._native().weight_gemm(None, i8, False, 1, 1, 1, "a", 0, None, None, None, None)
+
+
+STUB = r"""
+#include <unistd.h>
+static volatile int in_call;
+int busy(void) { return in_call; }
+#define SLOW(name) int name() { in_call = 1; usleep(300000); in_call = 0; return -1; }
+SLOW(rtn_ternarize_pack) SLOW(rtn_ternary_gemm) SLOW(rtn_ternary_conv2d_implicit_gemm) SLOW(rtn_ternary_conv2d_ternarize)
+SLOW(rtn_ternary_depthwise_conv2d) SLOW(rtn_ternary_weight_gemm) SLOW(rtn_ternary_weight_gemm_prepared)
+SLOW(rtn_ternary_weight_conv2d_prepared) SLOW(rtn_activation_backward) SLOW(rtn_weight_backward)
+unsigned long rtn_codes_bytes() { return 0; }
+"""
+
+GIL_PROBE = r"""
+import ctypes, sys, threading
+stub = ctypes.PyDLL(sys.argv[1], ctypes.RTLD_GLOBAL)      # found before librtn; its own calls keep the lock
+sys.path.insert(0, sys.argv[2])
+import torch
+from paper_1912_02057_amd import _native as n
+ran = set()
+now = [None]
+def watch():                                            # sees a call in progress only if that call gave the lock up
+    while now[0] != "end":
+        if stub.busy():
+            ran.add(now[0])
+threading.Thread(target=watch, daemon=True).start()
+N = None
+calls = dict(pack=(N, 0, 1, 1, 1, 1, 0., 1., 0, N, N), weight_gemm=(N, N, 0, 1, 1, 1, 1., 0, N, N, N, N),
+             weight_conv2d_prepared=(N, N, 1, 1, 1, 1, 1, 1, 1, 1, 0, 0, N, N), activation_backward=(N, N, 1, 0., 1., 1., N, N, N),
+             weight_backward=(N, N, 1, 1, 0., 1., N, N, N, N, N))
+for name, args in calls.items():
+    now[0] = name
+    assert getattr(n, name)(*args) == -1, name
+now[0] = "end"
+print("held:", sorted(set(calls) - ran))
+"""
+
+
+def test_binding_native_calls_give_up_the_interpreter_lock(tmp_path):
+    """A call that blocks in the library must leave other Python threads running, as through ctypes.  The library
+    is stood in for by one whose entry points sleep."""
+    import subprocess
+    import sys
+    (tmp_path / "stub.c").write_text(STUB)
+    so = str(tmp_path / "stub.so")
+    subprocess.run(["gcc", "-w", "-shared", "-fPIC", str(tmp_path / "stub.c"), "-o", so], check=True)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", GIL_PROBE, so, root], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    assert "held: []" in r.stdout, r.stdout
