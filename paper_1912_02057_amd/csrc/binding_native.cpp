@@ -52,7 +52,7 @@ void* dev(PyObject* o, c10::ScalarType type, const char* what, bool nullable = t
         fail(PyExc_AssertionError, "%s: a contiguous device tensor of the documented type is required", what);
     return t.data_ptr();
 }
-// Any tensor's storage, unchecked (workspaces, bit planes).
+// Any tensor's storage, unchecked (workspaces, prepared weights).
 void* raw(PyObject* o, const char* what) { return o == Py_None ? nullptr : tensor(o, what).data_ptr(); }
 size_t raw_bytes(PyObject* o, const char* what) { return o == Py_None ? 0 : tensor(o, what).nbytes(); }
 
@@ -67,7 +67,9 @@ void* codes(PyObject* o, int64_t rows, int64_t K, rtn_code_format fmt, const cha
                      (long long)rows, (long long)K, (int)fmt, need);
         throw PyError();
     }
-    if ((fmt == RTN_CODE_FP4 && t.scalar_type() != c10::kByte) || (fmt == RTN_CODE_I8 && t.scalar_type() != c10::kChar))
+    const c10::ScalarType type = t.scalar_type();
+    if ((fmt == RTN_CODE_FP4 && type != c10::kByte) || (fmt == RTN_CODE_I8 && type != c10::kChar) ||
+        (fmt == RTN_CODE_BITPLANE && type != c10::kLong && type != c10::kUInt64))
         fail(PyExc_ValueError, "%s: dtype does not match the code format", what);
     return t.data_ptr();
 }
@@ -164,9 +166,7 @@ PyObject* gemm(PyObject*, Args a, Py_ssize_t n)
         const rtn_code_format fmt = (rtn_code_format)integer(a[0]);
         const rtn_path path = (rtn_path)integer(a[1]);
         const int64_t M = integer(a[4]), N = integer(a[5]), K = integer(a[6]);
-        const bool planes = fmt == RTN_CODE_BITPLANE;
-        const void* ac = planes ? raw(a[2], "a_codes") : codes(a[2], M, K, fmt, "a_codes");
-        const void* wc = planes ? raw(a[3], "w_codes") : codes(a[3], N, K, fmt, "w_codes");
+        const void *ac = codes(a[2], M, K, fmt, "a_codes"), *wc = codes(a[3], N, K, fmt, "w_codes");
         int32_t* acc = (int32_t*)dev(a[7], c10::kInt, "acc_out");
         const rtn_epilogue* ep = epilogue(a[8]);
         float* y = (float*)dev(a[9], c10::kFloat, "y_out");

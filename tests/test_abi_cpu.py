@@ -442,6 +442,13 @@ def test_binding_native_calls_refuse_host_tensors_and_wrong_types():
         B._native().weight_gemm(None, i8, False, 1, 1, 1, "a", 0, None, None, None, None)
 
 
+def test_binding_checks_bit_planes():
+    """Bit planes are checked before any launch like the other formats (a host tensor here)."""
+    planes = torch.zeros(2, 64, 1, dtype=torch.int64)
+    with pytest.raises(ValueError):
+        B.ternary_gemm(planes, planes, 64, 64, 64, fmt=B.RTN_CODE_BITPLANE, acc_out=torch.zeros(64, 64, dtype=torch.int32))
+
+
 STUB = r"""
 #include <unistd.h>
 static volatile int in_call;

@@ -261,6 +261,22 @@ def test_gemm_nan_does_not_depend_on_the_tile(fmt, n):
         assert torch.equal(y, want)
 
 
+def test_gemm_refuses_planes_of_another_size_or_format():
+    """Bit planes are checked like the other formats before their address goes to the library: too few
+    rows, another format's tensor, a view that is not contiguous."""
+    _say("gemm refuses wrong bit planes")
+    x = torch.randn((64, 100), device=T.DEV)
+    P = B.RTN_CODE_BITPLANE
+    good, short = B.ternarize_pack(x, -0.5, 0.5, P)[0], B.ternarize_pack(x[:32].contiguous(), -0.5, 0.5, P)[0]
+    for bad in (short, B.ternarize_pack(x, -0.5, 0.5, B.RTN_CODE_I8)[0], good.transpose(1, 2)):
+        for pair in ((bad, good), (good, bad)):
+            with pytest.raises(ValueError):
+                B.ternary_gemm(*pair, 64, 64, 100, fmt=P, want_acc=True)
+    acc, _ = B.ternary_gemm(good, good.view(torch.uint64), 64, 64, 100, fmt=P, want_acc=True)
+    t = (x > 0.5).int() - (x < -0.5).int()
+    assert torch.equal(acc.cpu(), t.cpu() @ t.cpu().T)
+
+
 def test_standalone_epilogue_gemm():
     _say("standalone epilogue (gemm form)")
     case = wl.gemm_case(100, 90, 300, seed=4, table4=True)
