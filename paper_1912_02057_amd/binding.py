@@ -239,7 +239,11 @@ class Epilogue:
                              int(bool(relu)),
                              None if bn_scale is None else _dev(bn_scale, torch.float32),
                              None if bn_shift is None else _dev(bn_shift, torch.float32))
-        self.addr = C.addressof(self.s)
+
+    @property
+    def addr(self):
+        """Address of the struct that `s` is now (kept, it would dangle once `s` is replaced)."""
+        return C.addressof(self.s)
 
     def ref(self):
         return C.cast(C.pointer(self.s), C.c_void_p)

@@ -449,6 +449,15 @@ def test_binding_checks_bit_planes():
         B.ternary_gemm(planes, planes, 64, 64, 64, fmt=B.RTN_CODE_BITPLANE, acc_out=torch.zeros(64, 64, dtype=torch.int32))
 
 
+def test_epilogue_address_follows_its_struct():
+    """Calls must read the struct an Epilogue holds at the time of the call, also after it was replaced."""
+    import ctypes
+    ep = B.Epilogue(1.0, 0.5, 2.0, None, None, None)
+    ep.s = B.RtnEpilogue(*[getattr(ep.s, n) for n, _ in ep.s._fields_])
+    ep.s.relu = 1
+    assert ep.addr == ctypes.addressof(ep.s) == ep.ref().value
+
+
 STUB = r"""
 #include <unistd.h>
 static volatile int in_call;
