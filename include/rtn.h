@@ -274,9 +274,11 @@ int rtn_ternary_weight_gemm(const float *x, const void *w_codes, int64_t M, int6
  * rtn_ternary_conv2d_implicit_gemm:
  *   y[n][o][oh][ow] = alpha_w[o] * sum over in-bounds (c, kh, kw) of x * t_w,
  * then ReLU / BN affine as above; y_out fp32 [Nb][O][OH][OW].  Same exact split of
- * the activations and the same error bound with K = C*KH*KW.  workspace:
- * rtn_weight_conv2d_workspace_bytes(...) bytes, 16-byte aligned, overwritten by
- * every call.                                                                  */
+ * the activations and the same error bound with K = C*KH*KW.  workspace: at least
+ * rtn_weight_conv2d_prepared_bytes(C, O, KH, KW, pad) bytes, 16-byte aligned (the weights in
+ * the form rtn_weight_conv2d_prepare writes); overwritten by every call.
+ * rtn_weight_conv2d_workspace_bytes is an upper bound of that, three bf16 copies of the
+ * activations larger; nothing needs the difference.  Nb*H*W*rtn_padded_k(C) must be at most 2^36. */
 size_t rtn_weight_conv2d_workspace_bytes(int64_t Nb, int64_t C, int64_t H, int64_t W, int64_t O, int KH,
                                          int KW, int pad);
 int rtn_ternary_weight_conv2d(const float *x, const void *w_codes, int64_t Nb, int64_t C, int64_t H,
@@ -290,13 +292,17 @@ int rtn_ternary_weight_conv2d(const float *x, const void *w_codes, int64_t Nb, i
  * everything that depends only on the trained filters is stored ahead of time).
  *   rtn_weight_gemm_prepare: the codes [N][rtn_padded_k(K)] as bf16 values.
  *   rtn_weight_conv2d_prepare: the codes [O][KH][KW][rtn_padded_k(C)] as bf16 values in
- *   the order the matrix instruction takes them, then the per-filter epilogue table (alpha_w and the BN affine; nullable BN as above).
+ *   the order the matrix instruction takes them, then the per-filter epilogue table
+ *   (alpha_w and the BN affine; nullable BN as above).
+ * Their layout belongs to the build of the library: prepare again, do not store the buffer.
  * prepared: DEVICE, 16-byte aligned, at least rtn_weight_*_prepared_bytes(...) bytes;
  * it is only read by the *_prepared calls below, so one buffer serves any number of
  * calls, batch sizes and image sizes.  Those calls compute exactly what
  * rtn_ternary_weight_gemm / rtn_ternary_weight_conv2d compute (same kernels, same
- * bits); their workspace (same size functions as above) then holds only the GEMM's split
- * activations (the conv splits in registers).  The conv takes alpha_w and the BN affine from the prepared table. */
+ * bits).  The GEMM's workspace (same size function as above) then holds only the split
+ * activations; the conv splits in registers and needs none (NULL, 0; a buffer that is passed
+ * must have the size the one-call form needs, and is not touched).  The conv takes alpha_w and the
+ * BN affine from the prepared table. */
 size_t rtn_weight_gemm_prepared_bytes(int64_t N, int64_t K);
 int rtn_weight_gemm_prepare(const void *w_codes, int64_t N, int64_t K, void *prepared,
                             size_t prepared_bytes, void *stream);

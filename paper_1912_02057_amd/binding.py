@@ -384,13 +384,12 @@ def ternary_weight_conv2d(x, w_codes, O, KH, KW, stride, pad, alpha_w=None, relu
     if y_out is None:
         OH, OW = conv_out_hw(H, W, KH, KW, stride, pad)
         y_out = torch.empty((Nb, O, OH, OW), dtype=torch.float32, device=x.device)
-    if workspace is None:
-        workspace = torch.empty(lib().rtn_weight_conv2d_workspace_bytes(Nb, Cc, H, W, O, KH, KW, pad),
-                                dtype=torch.uint8, device=x.device)
     if prepared is not None:
         rc = _native().weight_conv2d_prepared(x, prepared, Nb, Cc, H, W, O, KH, KW, stride, pad, relu, y_out, workspace)
         _check(rc, "rtn_ternary_weight_conv2d_prepared")
         return y_out
+    if workspace is None:
+        workspace = torch.empty(lib().rtn_weight_conv2d_prepared_bytes(Cc, O, KH, KW, pad), dtype=torch.uint8, device=x.device)
     ga = _Gran(alpha_w)
     rc = lib().rtn_ternary_weight_conv2d(
         _dev(x, torch.float32), C.c_void_p(w_codes.data_ptr()), Nb, Cc, H, W, O, KH, KW, stride, pad, ga.ptr,

@@ -409,9 +409,8 @@ size_t rtn_weight_conv2d_workspace_bytes(int64_t Nb, int64_t C, int64_t H, int64
     rtn::ConvGeom g = {};
     if (make_geom(Nb, C, H > KH ? H : KH, W > KW ? W : KW, O, KH, KW, 1, pad, RTN_PAD_TRUE_ZERO, g) != RTN_OK) return 0;
     if (H <= 0 || W <= 0) return 0;
-    const size_t cp = (size_t)pad64(C);
-    return (size_t)3 * (size_t)Nb * (size_t)H * (size_t)W * cp * 2u + (size_t)O * KH * KW * cp * 2u + 16u +
-           rtn_conv2d_workspace_bytes(O, KH, KW, pad);
+    // (an upper bound that callers have stored: the calls need rtn_weight_conv2d_prepared_bytes of it)
+    return (size_t)3 * (size_t)Nb * (size_t)H * (size_t)W * (size_t)pad64(C) * 2u + rtn_weight_conv2d_prepared_bytes(C, O, KH, KW, pad);
 }
 
 static int weight_conv_impl(const float* x, const void* w_codes, const void* prepared, int64_t Nb, int64_t C, int64_t H, int64_t W,
@@ -424,15 +423,15 @@ static int weight_conv_impl(const float* x, const void* w_codes, const void* pre
     rtn::WConvArgs a = {};
     int rc = make_geom(Nb, C, H, W, O, KH, KW, stride, pad, RTN_PAD_TRUE_ZERO, a.g);
     if (rc != RTN_OK) return rc;
-    // three planes of K bytes each are walked by 32-bit offsets
-    if (3 * (int64_t)a.g.Cpad * 2 * KH * KW > kMaxK || Nb * H * W * (int64_t)a.g.Cpad > (int64_t)1 << 36)
-        return RTN_ERR_SHAPE;
+    if (Nb * H * W * (int64_t)a.g.Cpad > (int64_t)1 << 36) return RTN_ERR_SHAPE;
     if (!aligned(x, 4) || !aligned(w_codes, 16) || !aligned(prepared, 16) || !aligned(y_out, 4) || !aligned(bn_scale, 4) ||
         !aligned(bn_shift, 4))
         return RTN_ERR_ALIGN;
     if (gran_w != RTN_SCALAR && gran_w != RTN_VECTOR) return RTN_ERR_UNSUPPORTED;
     if (!prepared && (rc = make_param(alpha_w, gran_w, false, a.ep.alpha_w)) != RTN_OK) return rc;
-    if (!workspace || workspace_bytes < rtn_weight_conv2d_workspace_bytes(Nb, C, H, W, O, KH, KW, pad))
+    // the prepared form needs no workspace, and may be given none
+    if (!(prepared && !workspace && !workspace_bytes) &&
+        (!workspace || workspace_bytes < rtn_weight_conv2d_prepared_bytes(C, O, KH, KW, pad)))
         return RTN_ERR_WORKSPACE;
     if (!aligned(workspace, 16)) return RTN_ERR_ALIGN;
     a.ep.alpha_a.s = 1.0f;

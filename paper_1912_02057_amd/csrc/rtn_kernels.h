@@ -147,8 +147,7 @@ hipError_t launch_wgemm(const WGemmArgs& a, hipStream_t st);
 hipError_t launch_wgemm_prepare(const int8_t* w, int64_t N, int64_t Kpad, void* prepared, hipStream_t st);
 
 // conv form: x fp32 NCHW, w int8 [O][KH][KW][Cpad] (g.Cpad in elements), y fp32 NCHW;
-// workspace (one-call form): weights as bf16, then the epilogue table, behind room for 3
-// activation planes, which is not used
+// workspace (one-call form): weights as bf16, then the epilogue table
 struct WConvArgs {
     const float* x;
     const int8_t* w;

@@ -522,8 +522,8 @@ hipError_t launch_wconv(const WConvArgs& a, hipStream_t st)
 {
     const ConvGeom& g = a.g;
     const int64_t wn = (int64_t)g.O * g.KH * g.KW * g.Cpad;
-    // one-call form: the weight side goes behind what earlier forms of the workspace held
-    uint16_t* wb = a.prepared ? (uint16_t*)a.prepared : (uint16_t*)a.workspace + 3 * (int64_t)g.Nb * g.H * g.W * g.Cpad;
+    // one-call form: the weight side is prepared in the workspace
+    uint16_t* wb = (uint16_t*)(a.prepared ? a.prepared : a.workspace);
     if (!a.prepared) {
         const hipError_t e = launch_wconv_prepare(a.w, g, a.ep, wb, st);
         if (e != hipSuccess) return e;

@@ -254,6 +254,25 @@ def test_weight_conv_rejects(L):
     assert with_(_17=ODD) == B.RTN_ERR_ALIGN
 
 
+def test_weight_conv_workspace_is_the_weights_alone(L):
+    """The one-call form needs room for the prepared weights, whatever the batch; the length of a dot product is
+    limited as for the other convs.  (Unaligned workspaces: the check after those, so nothing is launched.)"""
+    a1 = _f(1.0)
+    need = L.rtn_weight_conv2d_prepared_bytes(64, 64, 3, 3, 1)
+    call = lambda nbytes, ws=ODD, Nb=256, C=64, k=3, pad=1: L.rtn_ternary_weight_conv2d(
+        FAKE, FAKE, Nb, C, 56, 56, 64, k, k, 1, pad, a1, B.RTN_SCALAR, 0, None, None, FAKE, ws, nbytes, None)
+    assert call(need) == B.RTN_ERR_ALIGN
+    assert call(need - 1) == B.RTN_ERR_WORKSPACE
+    assert L.rtn_weight_conv2d_workspace_bytes(256, 64, 56, 56, 64, 3, 3, 1) >= need       # an upper bound still
+    prepared = lambda ws, nbytes: L.rtn_ternary_weight_conv2d_prepared(FAKE, FAKE, 256, 64, 56, 56, 64, 3, 3, 1, 1, 0, FAKE, ws, nbytes, None)
+    assert prepared(ODD, need) == B.RTN_ERR_ALIGN and prepared(FAKE, need - 1) == B.RTN_ERR_WORKSPACE
+    assert prepared(None, need) == B.RTN_ERR_WORKSPACE
+    big = 699136                                              # 6 * big > 2^22 >= big
+    assert call(0, None, 1, big, 1, 0) == B.RTN_ERR_WORKSPACE
+    assert call(0, None, 1, (1 << 22) + 1, 1, 0) == B.RTN_ERR_SHAPE
+    assert call(0, None, 1 << 15, 700, 1, 0) == B.RTN_ERR_SHAPE  # Nb H W Cpad above 2^36
+
+
 def test_weight_prepare_rejects(L):
     a1 = _f(1.0)
     assert L.rtn_weight_gemm_prepared_bytes(8, 65) == 8 * 128 * 2

@@ -1424,6 +1424,34 @@ def test_weight_conv_wide_offsets(Nb, H, k, stride, pad):
     assert (err <= tol).all(), float((err / tol).max())
 
 
+def test_weight_conv_workspace_and_long_dot_products():
+    """699136 channels (six bytes each no longer fit the 2^22 that once limited this call): the one-call
+    form in a workspace of exactly the prepared weights' size, with a guard behind it, and the prepared
+    form with none and with a buffer that it must leave alone."""
+    Nb, C, O = 3, 699136, 33
+    _say("weight-only conv, %d channels" % C)
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(4)
+    x = torch.randn((Nb, C, 1, 1), generator=g, device=T.DEV)
+    cw, _ = B.ternarize_pack(torch.randn((O, C), generator=g, device=T.DEV), -0.6, 0.6, want_sum=False)
+    aw = torch.rand(O, generator=g, device=T.DEV) + 0.5
+    need = B.lib().rtn_weight_conv2d_prepared_bytes(C, O, 1, 1, 0)
+    buf = torch.full((need + 4096,), 0x5a, dtype=torch.uint8, device=T.DEV)
+    y = B.ternary_weight_conv2d(x, cw, O, 1, 1, 1, 0, aw, workspace=buf[:need])
+    assert bool((buf[need:] == 0x5a).all())
+    prep = B.weight_conv2d_prepare(cw, C, O, 1, 1, 0, aw)
+    buf.fill_(0x5a)
+    y2 = B.ternary_weight_conv2d(x, None, O, 1, 1, 1, 0, prepared=prep)
+    y3 = B.ternary_weight_conv2d(x, None, O, 1, 1, 1, 0, prepared=prep, workspace=buf)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2) and torch.equal(y, y3) and bool((buf == 0x5a).all())
+    xd, td, a = x.cpu().numpy().reshape(Nb, C).astype(np.float64), cw[:, :C].cpu().numpy().astype(np.float64), aw.cpu().numpy().astype(np.float64)
+    ref, scale = (xd @ td.T) * a, (np.abs(xd) @ np.abs(td).T) * a
+    tol = (4.0 * np.sqrt(3.0 * C) + 8.0) * 2.0 ** -24 * scale + 1.2e-7 * np.abs(ref)   # as _wconv_check
+    err = np.abs(y.cpu().numpy().reshape(Nb, O) - ref)
+    assert (err <= tol).all(), float((err / tol).max())
+
+
 def test_weight_conv_exact_on_ternary_activations():
     _say("weight-only conv on ternary activations")
     shape = wl.ConvShape("e", 64, 10, 96, 3, 1, 1)
