@@ -65,7 +65,7 @@ def oracle_gemm(case, relu=False, bn=None):
     return dict(ta=ta, tw=tw, D=D, Sa=Sa, Sw=Sw, y=y)
 
 
-def hip_gemm(case, fmt=B.RTN_CODE_I8, relu=False, bn=None, want_acc=True):
+def hip_gemm(case, fmt=B.RTN_CODE_I8, relu=False, bn=None, want_acc=True, path=B.RTN_PATH_AUTO):
     da, dw = case["delta_a"], case["delta_w"]
     xa, xw = dev(case["xa"]), dev(case["xw"])
     ca, sa = B.ternarize_pack(xa, thr_arg(-da), thr_arg(da), fmt)
@@ -74,10 +74,10 @@ def hip_gemm(case, fmt=B.RTN_CODE_I8, relu=False, bn=None, want_acc=True):
                     gran_arg(case["beta_w"]), sa, sw, relu=relu,
                     bn_scale=None if bn is None else dev(bn[0]), bn_shift=None if bn is None else dev(bn[1]))
     if want_acc == "separate":      # the two single-output launches (accumulators only, then y only)
-        acc, _ = B.ternary_gemm(ca, cw, case["M"], case["N"], case["K"], fmt=fmt, ep=None, want_acc=True)
-        _, y = B.ternary_gemm(ca, cw, case["M"], case["N"], case["K"], fmt=fmt, ep=ep, want_acc=False)
+        acc, _ = B.ternary_gemm(ca, cw, case["M"], case["N"], case["K"], fmt=fmt, path=path, ep=None, want_acc=True)
+        _, y = B.ternary_gemm(ca, cw, case["M"], case["N"], case["K"], fmt=fmt, path=path, ep=ep, want_acc=False)
     else:
-        acc, y = B.ternary_gemm(ca, cw, case["M"], case["N"], case["K"], fmt=fmt, ep=ep, want_acc=want_acc)
+        acc, y = B.ternary_gemm(ca, cw, case["M"], case["N"], case["K"], fmt=fmt, path=path, ep=ep, want_acc=want_acc)
     torch.cuda.synchronize()
     return dict(ca=ca, cw=cw, Sa=sa, Sw=sw, D=acc, y=y, ep=ep)
 

@@ -198,12 +198,32 @@ def test_gemm_acc_only_and_y_only_and_deterministic():
 
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (37, 19, 131), (130, 70, 1000), (256, 256, 4096)])
 def test_gemm_popc_vs_oracle(M, N, K):
+    """The popcount pattern on bit planes, and the same planes on the matrix cores (AUTO)."""
     _say("gemm_popc M=%d N=%d K=%d" % (M, N, K))
     case = wl.gemm_case(M, N, K, p_zero=0.5, seed=M + K)
     ref = T.oracle_gemm(case)
-    got = T.hip_gemm(case, fmt=B.RTN_CODE_BITPLANE)
-    assert (got["D"].cpu().numpy() == ref["D"]).all()
-    T.assert_y_close(got["y"].cpu().numpy(), ref["y"], "popc y")
+    for path in (B.RTN_PATH_POPC, B.RTN_PATH_AUTO):
+        got = T.hip_gemm(case, fmt=B.RTN_CODE_BITPLANE, path=path)
+        assert (got["D"].cpu().numpy() == ref["D"]).all()
+        T.assert_y_close(got["y"].cpu().numpy(), ref["y"], "popc y, path %d" % path)
+
+
+@pytest.mark.parametrize("K", [1 << 22, (1 << 22) - 64], ids=["even", "odd_words"])
+@pytest.mark.parametrize("path", [B.RTN_PATH_AUTO, B.RTN_PATH_POPC], ids=["auto", "popc"])
+def test_gemm_planes_longest_dot_product(K, path):
+    """K at its limit, where the matrix cores' sums of 4 per product reach 2^24, the last integer fp32 holds
+    exactly: rows of +1, of -1 and at random, with an even and an odd number of plane words."""
+    _say("gemm planes path=%d K=%d" % (path, K))
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(K & 255)
+    x = torch.randn((5, K), generator=g, device=T.DEV)
+    x[0], x[1] = 1.0, -1.0
+    ca, _ = B.ternarize_pack(x, -0.5, 0.5, B.RTN_CODE_BITPLANE)
+    acc, _ = B.ternary_gemm(ca, ca, 5, 5, K, fmt=B.RTN_CODE_BITPLANE, path=path, want_acc=True)
+    t = ((x > 0.5).double() - (x < -0.5).double()).cpu().numpy()
+    want = (t @ t.T).astype(np.int64)
+    assert want[0, 0] == K and want[0, 1] == -K
+    assert (acc.cpu().numpy() == want).all()
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 65, 64), (64, 64, 512), (65, 70, 513), (130, 129, 576), (200, 136, 1088),
@@ -886,9 +906,9 @@ def test_resnet18_layers_table4_parameters(idx):
 SWEEP = [(M, NK, p0) for M in (8192, 16384) for NK in (4096, 8192) for p0 in (0.2, 0.5, 0.8)]
 
 
-def _sweep_check(M, NK, p0, fmt, seed):
+def _sweep_check(M, NK, p0, fmt, seed, paths=(B.RTN_PATH_AUTO,)):
     case = wl.gemm_case(M, NK, NK, p_zero=p0, seed=seed)
-    got = T.hip_gemm(case, fmt=fmt, want_acc="separate")
+    got = T.hip_gemm(case, fmt=fmt, want_acc="separate", path=paths[0])
     rows = _sample_rows(M, 1024, seed)
     ta = orc.ternarize(case["xa"][rows], -0.5, 0.5)
     tw = orc.ternarize(case["xw"], -0.5, 0.5)
@@ -901,10 +921,13 @@ def _sweep_check(M, NK, p0, fmt, seed):
         assert (got["ca"][torch.as_tensor(rows)].cpu().numpy() == orc.encode_fp4(ta)).all()
         assert (got["cw"].cpu().numpy() == orc.encode_fp4(tw)).all()
     D = orc.gemm_acc_rows(ta, tw, np.arange(rows.size, dtype=np.int64))
-    assert (got["D"].cpu().numpy()[rows] == D).all()
     y = orc.gemm_epilogue(D, NK, Sa, Sw, case["alpha_a"][rows], case["beta_a"][rows],
                           case["alpha_w"], case["beta_w"])
-    T.assert_y_close(got["y"].cpu().numpy()[rows], y, "sweep %d %d %.1f" % (M, NK, p0))
+    for path in paths:
+        if path != paths[0]:
+            got = T.hip_gemm(case, fmt=fmt, want_acc="separate", path=path)
+        assert (got["D"].cpu().numpy()[rows] == D).all()
+        T.assert_y_close(got["y"].cpu().numpy()[rows], y, "sweep %d %d %.1f path %d" % (M, NK, p0, path))
     # the draw fixes E[D] = 0 and Var[D] = K (1 - p0)^2
     Dall = got["D"][:: max(1, M // 512)].double()
     assert abs(float(Dall.mean())) < 0.2
@@ -928,9 +951,10 @@ def test_config5_gemm_sweep_fp4(M, NK, p0):
 
 @pytest.mark.parametrize("M,NK,p0", SWEEP)
 def test_config5_gemm_sweep_popcount(M, NK, p0):
-    """The same sweep, all twelve points, on the bit-plane popcount path (Eq.8)."""
+    """The same sweep, all twelve points, on bit planes: the popcount path (Eq.8), and the same planes on
+    the matrix cores."""
     _say("sweep popc M=%d N=K=%d P(0)=%.1f" % (M, NK, p0))
-    _sweep_check(M, NK, p0, B.RTN_CODE_BITPLANE, seed=int(1000 * p0) + 7)
+    _sweep_check(M, NK, p0, B.RTN_CODE_BITPLANE, seed=int(1000 * p0) + 7, paths=(B.RTN_PATH_POPC, B.RTN_PATH_AUTO))
 
 
 # ------------------------------------ config 4: the chained ternary stack --------
