@@ -26,11 +26,11 @@
 //
 // What it replaced wrote the three terms to memory (6 bytes per activation) in a pass of its own
 // and re-read them once per tap and filter tile through LDS, with the weights fetched again for
-// each term.  ResNet-18's 19 layer shapes, GPU time (before -> now): batch 256 4.52 -> 2.51 ms, batch 64
-// 1.74 -> 0.87 ms, batch 1 1.02 -> 0.16 ms.  GATHER re-reads and re-splits its inputs once per tap, which
+// each term.  ResNet-18's 19 layer shapes, GPU time (before -> now): batch 256 4.48 -> 2.44 ms, batch 64
+// 1.73 -> 0.85 ms, batch 1 1.01 -> 0.16 ms.  GATHER re-reads and re-splits its inputs once per tap, which
 // the split pass did not: over 857 random geometries with windows of 1 to 7 and strides of 1 to 4 this
-// kernel takes 0.44 times the time at the median and more than 1.02 times on 6, all of them windows of
-// 4 and more that are strided or 5 and more wide, at some 10000 output pixels and more: 1.16 at worst.
+// kernel takes 0.43 times the time at the median and more than 1.02 times on 7, 1.14 times at worst: nearly
+// all windows of 4 and more that are strided or 5 and more wide, at some 10000 output pixels and more.
 #include "tmm_kernel.h"
 
 namespace rtn {
@@ -466,8 +466,9 @@ int64_t run_rows(const ConvGeom& g, int bq)
 // x = rows of the run / 64 (GATHER: stride - 1, at most 3).  A chunk's latency counts once for every
 // occ blocks that run side by side, its throughput for each.  The constants are fitted to the times of all
 // forms on 857 geometries (windows 1 to 7, strides 1 to 4, 3 to 512 channels, 7 to 500 pixels wide, batch 1
-// to 256): the cheapest form by this estimate takes 1.006 times the fastest one's time on average, more
-// than 1.15 times it on 12 of them, 1.45 times at worst.
+// to 256), each where no form of its tile with a smaller image fits; those stand first, and the roomier
+// ones are passed over there.  The cheapest form by this estimate takes 1.006 times the fastest one's
+// time on average, more than 1.15 times it on 12 of them, 1.45 times at worst.
 struct WcForm {
     int bp, bq, kg, window, rmax;  // window: side of a run's window, 0: GATHER
     hipError_t (*launch)(WcParams&, hipStream_t);
@@ -564,8 +565,11 @@ hipError_t launch_wconv(const WConvArgs& a, hipStream_t st)
     auto pick = [&](auto&& admits) {
         const WcForm* best = nullptr;
         double least = 0;
+        const WcForm* tighter = nullptr;  // the last form that fits
         for (const WcForm& f : kForms)
             if (admits(f) && fits(f)) {
+                if (tighter && f.window && f.window == tighter->window && f.bp == tighter->bp && f.bq == tighter->bq) continue;
+                tighter = &f;
                 const double c = cost(f);
                 if (!best || c < least) best = &f, least = c;
             }
