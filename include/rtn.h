@@ -132,7 +132,10 @@ int rtn_last_hip_error(void);
  * window, 64 or 128 padded channels: 64x256 twice, 64x128 twice, 128x128,
  * 128x256; any other problem runs the plain tile of that size); -1 (default)
  * lets the library choose from the problem shape.  Every configuration computes the same
- * result.  The setting is process-wide and not thread-safe.
+ * result, except that the weight-only conv adds its fp32 products in another order in some of
+ * them (there 8, 9, 10 and 12 are the 128x128, 64x256, 64x64 and a second 128x128 tile that gather
+ * their inputs tap by tap, 11 is 32x32), within the error bound stated there.  The setting is
+ * process-wide and not thread-safe.
  * Returns RTN_ERR_UNSUPPORTED for an index outside -1 .. rtn_num_tile_configs()-1. */
 int rtn_num_tile_configs(void);
 int rtn_set_tile_config(int index);
@@ -274,7 +277,9 @@ int rtn_ternary_weight_gemm(const float *x, const void *w_codes, int64_t M, int6
  * rtn_ternary_conv2d_implicit_gemm:
  *   y[n][o][oh][ow] = alpha_w[o] * sum over in-bounds (c, kh, kw) of x * t_w,
  * then ReLU / BN affine as above; y_out fp32 [Nb][O][OH][OW].  Same exact split of
- * the activations and the same error bound with K = C*KH*KW.  workspace: at least
+ * the activations and the same error bound with K = C*KH*KW.  The order of the sums is chosen
+ * with the tile, by the layer's shape and the batch: the same arguments give the same bits on
+ * every run, one image alone and in a batch may differ in the last ones.  workspace: at least
  * rtn_weight_conv2d_prepared_bytes(C, O, KH, KW, pad) bytes, 16-byte aligned (the weights in
  * the form rtn_weight_conv2d_prepare writes); overwritten by every call.
  * rtn_weight_conv2d_workspace_bytes is an upper bound of that, three bf16 copies of the
