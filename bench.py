@@ -373,7 +373,7 @@ def main():
         return
 
     if args.workload == "gemm_sweep":
-        # M x N x K sweep of the ternary GEMM over sparsity, on both contraction paths: codes resident,
+        # M x N x K sweep of the ternary GEMM over sparsity, on every contraction path: codes resident,
         # one timed call = contraction + fused epilogue (the pack of the activations is timed beside it)
         rows = []
         tot_macs, tot_s = 0.0, 0.0
@@ -383,7 +383,7 @@ def main():
                     case = wl.gemm_case(M, NK, NK, p_zero=p0, seed=int(1000 * p0) + 3)
                     xa, xw = to_dev(case["xa"]), to_dev(case["xw"])
                     for fmt, name in ((B.RTN_CODE_FP4, "mfma_fp4"), (B.RTN_CODE_I8, "mfma_i8"),
-                                      (B.RTN_CODE_BITPLANE, "popcount")):
+                                      (B.RTN_CODE_BITPLANE, "planes_mfma"), (B.RTN_CODE_BITPLANE, "popcount")):
                         ca, sa = B.ternarize_pack(xa, -0.5, 0.5, fmt)
                         cw, sw = B.ternarize_pack(xw, -0.5, 0.5, fmt)
                         ep = B.Epilogue(garg(case["alpha_a"]), garg(case["beta_a"]), garg(case["alpha_w"]),
@@ -862,7 +862,7 @@ def main():
                         bytes_per_launch=round(12.0 * macs_step / nlaunch, 0))
     elif args.workload == "resnet18_weight_only_convs":
         bf16_tflops = 3 * achieved_tops
-        roofline = dict(bound="mfma", kernel="activation split + k_tmm (bf16 MFMA implicit-GEMM conv, fp32 accumulate)",
+        roofline = dict(bound="mfma", kernel="k_wconv (activations split in registers, bf16 MFMA, fp32 accumulate)",
                         achieved=round(bf16_tflops, 1), peak=BF16_PEAK_TFLOPS, unit="TFLOP/s",
                         frac=round(bf16_tflops / BF16_PEAK_TFLOPS, 4), traffic=None,
                         launches_per_step=nlaunch, avg_launch_us=round(conv_total_s / nlaunch * 1e6, 1),
