@@ -308,8 +308,9 @@ __device__ __forceinline__ void gemm_epilogue(const TmmParams& prm, double* tab,
                         }
                     }
                 }
-                // keep the scheduler from hoisting every later load up here (every 4 rows let the
-                // 256 x 256 tile spill: 60 against 54 us at 4096^3 with ReLU and BN)
+                // keep the scheduler from hoisting every later load up here (every 4 rows let the FP4
+                // 256 x 256 tile spill: 60 against 54 us at 4096^3 with ReLU and BN; the bf16 one still
+                // spills 16 registers, the bit planes' 3)
                 if ((r & 1) == 1) __builtin_amdgcn_sched_barrier(0);
             }
     };

@@ -23,9 +23,11 @@
 // behind a row's end is read from the zero page.
 //
 // M = N = K = 4096: 56.6 us against 407 us for k_gemm_popc (and 38.5 us for the FP4 GEMM, which has
-// nothing to expand).  Bound by instruction issue beside the MFMAs: per k-slice a wave of the
-// 256 x 256 tile runs 80 expanding instructions for 16 MFMAs.  A wave tile of 128 x 128 halves that
-// share against 64 x 64, hence the largest tile as soon as it gives every CU a block.
+// nothing to expand).  Bound by vector-instruction issue: per k-slice a wave of the 256 x 256 tile runs
+// 80 expanding instructions for 16 MFMAs; counters over 8192 x 4096 x 4096 to 16384 x 8192 x 8192 give 10
+// to 12 vector instructions per MFMA in all (FP4 GEMM: 2.4 to 3.5) and the matrix cores 30 to 35 %
+// busy.  A wave tile of 128 x 128 halves that share against 64 x 64, hence the largest tile as soon as it
+// gives every CU a block (it spills 3 registers; the 4-byte form also 271 scalar ones).
 #include "tmm_kernel.h"
 
 namespace rtn {
