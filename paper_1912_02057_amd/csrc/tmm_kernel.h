@@ -87,6 +87,9 @@ struct TmmParams {
 // (CONV, TERN, DT) triple per translation unit.
 template <bool CONV, int TERN, int DT>
 hipError_t tmm_launch_index_raw(int cfg, TmmParams& prm, hipStream_t st);
+// The form for small grids (tmm_ksplit.hip): `form` of its table.  hipErrorInvalidValue: it does not fit this problem.
+template <bool CONV, int TERN, int DT>
+hipError_t launch_ksplit(int form, const TmmParams& prm, hipStream_t st);
 // The bf16-operand variants of the weight-only GEMM: 0 = 64x64, 1 = 128x128, 2 = 256x256.
 hipError_t tmm_launch_bf16(int variant, TmmParams& prm, hipStream_t st);
 

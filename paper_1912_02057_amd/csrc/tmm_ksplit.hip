@@ -1,0 +1,498 @@
+// The contraction on small grids: every wave of a block computes the block's whole output tile over a
+// share of K, and the shares meet in LDS.
+//
+// A layer of a few images, or a GEMM of a few rows, has fewer output tiles than the chip has CUs, and
+// k_tmm's time there is the serial chain of one block: 0.3 us per 64-byte K-step of its 64 x 64 tile (wait,
+// barrier, fragment reads, MFMAs one after the other), whatever the depth of its ring.  Here the K-steps are
+// dealt out in W contiguous shares to the W waves of a block.  Each wave loads its own operand stages (the
+// direct global -> LDS loads, swizzle and fragment addressing of k_tmm) into a ring of its own and waits for its
+// own loads only, so there is no barrier until the sums meet, and the W chains run side by side.  D is a sum of
+// integers (int32, or below 2^24 in fp32), so its order does not matter, and the epilogue repeats k_tmm's
+// operations: the outputs are the same bits whichever kernel runs.
+//
+// Operands straight into registers (no LDS): 1.1 to 2.1 times slower from 60 K-steps on.  An MFMA operand has
+// 32 rows in consecutive lanes, so every lane of such a load touches a cache line of its own, where a direct load
+// takes 64 bytes of each of 16 rows.
+//
+// Parameters, thresholds and residual values are fetched before the K loop.  What is left of a launch: 3.1 us
+// (GEMM) to 3.7 us (conv) with one K-step -- launch, first load, meeting, store -- and from 250 tiles on the
+// operand traffic L2 -> LDS.  us, k_tmm 64 x 64 -> here (times of back-to-back launches):
+//   conv, FP4, one image, 512 filters on 7 x 7, 36 K-steps     11.5 -> 5.4
+//   conv, FP4, one image, 256 filters on 14 x 14, 18 K-steps    8.0 -> 4.9
+//   conv, FP4, one image, 64 filters on 56 x 56, 9 K-steps      5.8 -> 4.6, block tail 7.5 -> 5.1
+//   GEMM, int8, 661 x 174 x 5600, 88 K-steps                   14.5 -> 6.8
+//   GEMM, FP4, 2 x 8144 x 300, 3 K-steps                        3.6 -> 3.1
+#include "tmm_kernel.h"
+
+namespace rtn {
+
+namespace {
+
+struct KsplitParams {
+    TmmParams t;
+    FastDiv div_spt, div_kw;  // by the K-steps per tap and the window's width
+};
+
+template <int TP, int TQ, int W, int NS, bool CONV, int TERN, int DT>
+__global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
+{
+    constexpr int BP = 32 * TP, BQ = 32 * TQ, T = TP * TQ;
+    constexpr int LP = BP / 16, LQ = BQ / 16, DPS = LP + LQ;  // loads per step
+    constexpr int STAGE = (BP + BQ) * 64, RING = NS * STAGE;
+    static_assert(RING >= T * 4096, "the accumulators lie over the ring");
+    static_assert(NS >= 2 && NS <= 4 && 3 * DPS < 64, "vmcnt range");
+    constexpr int V = 16 * T / W;              // outputs per thread
+    constexpr int QV = V < 4 ? V : 4;          // ... of which so many are consecutive rows
+    constexpr int NQ = V / QV;
+    static_assert(V >= 1 && V * W == 16 * T, "every thread has outputs");
+    static_assert(16 / QV % NQ == 0, "a thread's outputs lie in one 32 x 32 tile");
+    static_assert(DT == 0 || DT == 2, "codes");
+    const TmmParams& prm = kp.t;
+    const ConvGeom& g = prm.g;
+    using AccV = std::conditional_t<DT == 2, v16f, v16i>;
+    using AccS = std::conditional_t<DT == 2, float, int>;
+    typedef AccS AccQ __attribute__((ext_vector_type(QV == 1 ? 2 : QV)));
+
+    // [W][T][4][64 lanes][4] accumulators, [W][BQ] pixel sums, conv: the epilogue table; the code
+    // bytes of a ternarizing epilogue lie over the accumulators
+    extern __shared__ __attribute__((aligned(16))) int8_t smem[];
+    AccS* red = (AccS*)smem;
+    AccS* red_sa = (AccS*)(smem + W * RING);
+    const int toff = W * RING + (CONV ? W * BQ * 4 : 0);
+    const unsigned lds0 = (unsigned)(uintptr_t)smem;
+
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tileP, tileQ;
+    if (!block_tile(prm, tileP, tileQ)) return;
+    const int p0 = tileP * BP, q0 = tileQ * BQ;
+    const bool want_ep = TERN || prm.y != nullptr;
+    const int ohw = g.OH * g.OW;
+
+    const int nax = CONV ? conv_axis_classes(g) : 0;
+
+    // ---- operand loads: as in k_tmm, but by one wave for itself ------------------------------------------
+    // load j of a step covers 16 rows of an operand: lane l fetches row l >> 2, chunk (l & 3) ^ swz(row)
+    const int lrow = lane >> 2, lchunk = (lane & 3) ^ swz(lrow);
+    const int8_t* baseP = prm.P + (int64_t)p0 * prm.ldP;
+    const int8_t* baseQ = CONV ? prm.Q : prm.Q + (int64_t)q0 * prm.ldQ;
+    unsigned offP[LP], offQ[LQ];
+    const int8_t* gQ[LQ];
+    int vmask[LQ];  // conv: bit kh = row tap in the image, bit (8 + kw) = column tap in the image
+#pragma unroll
+    for (int i = 0; i < LP; ++i) {
+        int row = p0 + 16 * i + lrow;
+        row = row < prm.RP ? row : prm.RP - 1;  // tail rows: any valid data, never stored
+        offP[i] = (unsigned)(row - p0) * (unsigned)prm.ldP + lchunk * 16;
+    }
+#pragma unroll
+    for (int j = 0; j < LQ; ++j) {
+        int row = q0 + 16 * j + lrow;
+        row = row < prm.RQ ? row : prm.RQ - 1;
+        vmask[j] = 0;
+        offQ[j] = 0;
+        gQ[j] = nullptr;
+        if (CONV) {
+            const int nb = (int)fastdiv((uint32_t)row, g.div_ohw), pix = row - nb * ohw;
+            const int oh = (int)fastdiv((uint32_t)pix, g.div_ow), ow = pix - oh * g.OW;
+            const int ih0 = oh * g.stride - g.pad, iw0 = ow * g.stride - g.pad;
+            for (int k = 0; k < g.KH; ++k) vmask[j] |= ((unsigned)(ih0 + k) < (unsigned)g.H) << k;
+            for (int k = 0; k < g.KW; ++k) vmask[j] |= ((unsigned)(iw0 + k) < (unsigned)g.W) << (8 + k);
+            gQ[j] = prm.Q + (((int64_t)nb * g.H + ih0) * g.W + iw0) * g.Cpad + lchunk * 16;
+        } else {
+            offQ[j] = (unsigned)(row - q0) * (unsigned)prm.ldQ + lchunk * 16;
+        }
+    }
+    // this wave's share of the K-steps, and the position of the next step to load (wave-uniform)
+    const int first = (int)((unsigned)prm.nk * (unsigned)wave / W), end = (int)((unsigned)prm.nk * (unsigned)(wave + 1) / W);
+    const int n = end - first;
+    int kh = 0, kw = 0, cc = 0;
+    int64_t koffP = (int64_t)first * 64, koffQ = koffP;
+    const int spt = CONV ? g.Cpad >> 6 : prm.nk;  // steps per tap
+    if (CONV) {
+        const int tap = (int)fastdiv((uint32_t)first, kp.div_spt);
+        cc = first - tap * spt;
+        kh = (int)fastdiv((uint32_t)tap, kp.div_kw);
+        kw = tap - kh * g.KW;
+        koffQ = (int64_t)(kh * g.W + kw) * g.Cpad + cc * 64;
+    }
+    const int64_t rowskip = CONV ? (int64_t)(g.W - g.KW) * g.Cpad : 0;
+    const unsigned ring = lds0 + (unsigned)(wave * RING);
+    const int8_t* zero_page = (const int8_t*)g_zero16;
+    auto issue = [&](int slot) {
+        const unsigned dst = ring + (unsigned)(slot * STAGE);
+#pragma unroll
+        for (int i = 0; i < LP; ++i) dma16_base(uniform_ptr(baseP + koffP), offP[i], dst + i * 1024);
+#pragma unroll
+        for (int j = 0; j < LQ; ++j) {
+            if (CONV) {
+                const bool ok = ((vmask[j] >> kh) & (vmask[j] >> (8 + kw)) & 1) != 0;
+                dma16(ok ? gQ[j] + koffQ : zero_page, dst + BP * 64 + j * 1024);
+            } else {
+                dma16_base(uniform_ptr(baseQ + koffQ), offQ[j], dst + BP * 64 + j * 1024);
+            }
+        }
+        koffP += 64;
+        koffQ += 64;
+        if (CONV && ++cc == spt) {
+            cc = 0;
+            if (++kw == g.KW) {
+                kw = 0;
+                ++kh;
+                koffQ += rowskip;
+            }
+        }
+    };
+    int fragP[TP][2], fragQ[TQ][2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+        for (int i = 0; i < TP; ++i) {
+            const int row = i * 32 + (lane & 31);
+            fragP[i][ks] = row * 64 + (((ks * 2 + half) ^ swz(row)) << 4);
+        }
+#pragma unroll
+        for (int j = 0; j < TQ; ++j) {
+            const int row = j * 32 + (lane & 31);
+            fragQ[j][ks] = BP * 64 + row * 64 + (((ks * 2 + half) ^ swz(row)) << 4);
+        }
+    }
+    AccV acc[TP][TQ];
+    v4f sa4[TQ];
+    int sa1[TQ];
+#pragma unroll
+    for (int j = 0; j < TQ; ++j) {
+        sa4[j] = v4f{0.f, 0.f, 0.f, 0.f};
+        sa1[j] = 0;
+#pragma unroll
+        for (int i = 0; i < TP; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+    }
+    // pixel sums on the matrix cores, as in k_tmm: pixels 0 .. 15 in row 0, 16 .. 31 in row 1
+    const int sa_ones = ((lane & 15) < 2 && ((lane >> 4) & 1) == (lane & 15)) ? 0x22222222 : 0;
+    const v8i SA8 = {sa_ones, sa_ones, sa_ones, sa_ones, 0, 0, 0, 0};
+    (void)SA8;
+    auto multiply = [&](const v4i (&fa)[TP], const v4i (&fb)[TQ]) {
+#pragma unroll
+        for (int j = 0; j < TQ; ++j) {
+            const v4i q = fb[j];
+            if constexpr (DT == 2) {
+                const v8i B8 = {q[0], q[1], q[2], q[3], 0, 0, 0, 0};
+#pragma unroll
+                for (int i = 0; i < TP; ++i) {
+                    const v4i p = fa[i];
+                    const v8i A8 = {p[0], p[1], p[2], p[3], 0, 0, 0, 0};
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A8, B8, acc[i][j], 4, 4, 0, 0, 0, 0);
+                }
+                if (CONV) sa4[j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(SA8, B8, sa4[j], 4, 4, 0, 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int i = 0; i < TP; ++i) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], q, acc[i][j], 0, 0, 0);
+                if (CONV)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sa1[j] = __builtin_amdgcn_sdot4(q[e], 0x01010101, sa1[j], false);
+            }
+        }
+    };
+
+    for (int s = 0; s < NS && s < n; ++s) issue(s);
+    // ---- epilogue table (conv): rows g1, c2, bn scale, bn shift, then the classes that can occur -----
+    if (CONV && want_ep) {
+        const int nrows = 4 + conv_classes(g.pad), opitch = (g.O + 1) & ~1;
+        const bool compact = conv_compact(g);
+        const int lrows = 4 + nax * nax, pp = (g.pad + 1) * (g.pad + 1);
+        const int kib = (conv_table_bytes(BP, g) + 1023) >> 10;
+        for (int n = wave; n < kib; n += W) {
+            const int lin = n * 64 + lane;  // 16-byte unit = 2 doubles
+            int row = lin / (BP / 2);
+            const int u = lin - row * (BP / 2);
+            row = row < lrows ? row : lrows - 1;
+            if (row >= 4) {
+                const int c = row - 4, ra = c / nax, ca = c - ra * nax;
+                row = 4 + conv_axis_global(compact, g.pad, ra) * pp + conv_axis_global(compact, g.pad, ca);
+            }
+            int64_t idx = (int64_t)row * opitch + p0 + 2 * u;
+            const int64_t last = (int64_t)nrows * opitch - 2;
+            idx = idx < last ? idx : last;  // columns past O are never used
+            dma16(prm.cst_cls + idx, lds0 + (unsigned)(toff + n * 1024));
+        }
+    }
+
+    // ---- this thread's outputs: QV consecutive rows at t0[n] of column q ------------------------------
+    // thread = (lane, units): unit wave NQ + n holds rows 8 r4 + 4 half + QV sub ... of 32 x 32 tile ij
+    constexpr int SUBS = 4 / QV;
+    auto unit_sub = [&](int n) { return (wave * NQ + n) % SUBS; };
+    auto unit_r4 = [&](int n) { return (wave * NQ + n) / SUBS % 4; };
+    auto unit_ij = [&](int n) { return (wave * NQ + n) / (SUBS * 4); };
+    auto row_of = [&](int n) { return unit_ij(n) / TQ * 32 + 8 * unit_r4(n) + 4 * half + QV * unit_sub(n); };
+    const int jq = unit_ij(0) % TQ;  // the same for every n
+    const int q = q0 + jq * 32 + (lane & 31);
+    const bool qok = q < prm.RQ;
+    const int qq = qok ? q : prm.RQ - 1;
+    // parameters and residual values, fetched beside the operands
+    float f_aa[V], f_ba[V], f_lo[V], f_hi[V], f_res[V];
+    int f_sa[V];
+    float f_aw = 0.f, f_bw = 0.f, f_bs = 1.f, f_bh = 0.f;
+    int f_sw = 0, cls = 0;
+    int64_t obase = 0;
+    const EpiArgs& ep = prm.ep;
+    if (!CONV && want_ep) {
+        f_aw = ep.alpha_w.ptr ? ep.alpha_w.ptr[qq] : ep.alpha_w.s;
+        f_bw = ep.beta_w.ptr ? ep.beta_w.ptr[qq] : ep.beta_w.s;
+        f_sw = ep.sum_tw[qq];
+        if (ep.bn_scale) {
+            f_bs = ep.bn_scale[qq];
+            if (ep.bn_shift) f_bh = ep.bn_shift[qq];
+        }
+#pragma unroll
+        for (int n = 0; n < NQ; ++n)
+#pragma unroll
+            for (int e = 0; e < QV; ++e) {
+                int m = p0 + row_of(n) + e;
+                m = m < prm.RP ? m : prm.RP - 1;
+                f_aa[n * QV + e] = ep.alpha_a.ptr ? ep.alpha_a.ptr[m] : ep.alpha_a.s;
+                f_ba[n * QV + e] = ep.beta_a.ptr ? ep.beta_a.ptr[m] : ep.beta_a.s;
+                f_sa[n * QV + e] = ep.sum_ta[m];
+            }
+    }
+    if (CONV) {
+        const int nb = (int)fastdiv((uint32_t)qq, g.div_ohw), pix = qq - nb * ohw;
+        obase = (int64_t)nb * g.O * ohw + pix;
+        if (want_ep && !g.code_zero_pad) {
+            const int oh = (int)fastdiv((uint32_t)pix, g.div_ow), ow = pix - oh * g.OW;
+            int khl, khh, kwl, kwh;
+            tap_range(oh, g.stride, g.pad, g.KH, g.H, khl, khh);
+            tap_range(ow, g.stride, g.pad, g.KW, g.W, kwl, kwh);
+            const bool compact = conv_compact(g);
+            cls = conv_axis_class(compact, g.pad, khl, g.KH - 1 - khh) * nax +
+                  conv_axis_class(compact, g.pad, kwl, g.KW - 1 - kwh);
+        }
+        if (TERN)
+#pragma unroll
+            for (int n = 0; n < NQ; ++n)
+#pragma unroll
+                for (int e = 0; e < QV; ++e) {
+                    int o = p0 + row_of(n) + e;
+                    o = o < prm.RP ? o : prm.RP - 1;
+                    f_lo[n * QV + e] = prm.thr_lo.ptr ? prm.thr_lo.ptr[o] : prm.thr_lo.s;
+                    f_hi[n * QV + e] = prm.thr_hi.ptr ? prm.thr_hi.ptr[o] : prm.thr_hi.s;
+                    if (TERN == 2) f_res[n * QV + e] = prm.res ? prm.res[obase + (int64_t)o * ohw] : 0.0f;
+                }
+    }
+
+    // ---- this wave's share of K ----------------------------------------------------------------------
+    int slot = 0;
+    for (int s = 0; s < n; ++s) {
+        wait_groups<DPS>(n - 1 - s < NS - 1 ? n - 1 - s : NS - 1);
+        const int8_t* st = smem + wave * RING + slot * STAGE;
+        v4i fa[2][TP], fb[2][TQ];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+            for (int i = 0; i < TP; ++i) fa[ks][i] = *(const v4i*)(st + fragP[i][ks]);
+#pragma unroll
+            for (int j = 0; j < TQ; ++j) fb[ks][j] = *(const v4i*)(st + fragQ[j][ks]);
+        }
+        if (s + NS < n) {
+            wait_lgkm0();
+            issue(slot);
+        }
+        multiply(fa[0], fb[0]);
+        multiply(fa[1], fb[1]);
+        slot = slot + 1 == NS ? 0 : slot + 1;
+    }
+    wait_lgkm0();
+
+    // ---- the shares meet -------------------------------------------------------------------------------
+#pragma unroll
+    for (int i = 0; i < TP; ++i)
+#pragma unroll
+        for (int j = 0; j < TQ; ++j)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                typedef AccS V4 __attribute__((ext_vector_type(4)));
+                const V4 v = {acc[i][j][4 * r4], acc[i][j][4 * r4 + 1], acc[i][j][4 * r4 + 2], acc[i][j][4 * r4 + 3]};
+                *(V4*)(red + wave * (RING / 4) + (((i * TQ + j) * 4 + r4) * 64 + lane) * 4) = v;
+            }
+    if (CONV && want_ep) {
+#pragma unroll
+        for (int j = 0; j < TQ; ++j) {
+            if constexpr (DT == 2) {
+                if (lane < 16) {
+                    red_sa[wave * BQ + j * 32 + lane] = sa4[j][0];
+                    red_sa[wave * BQ + j * 32 + 16 + lane] = sa4[j][1];
+                }
+            } else {
+                const int s = sa1[j] + __shfl_xor(sa1[j], 32, 64);
+                if (lane < 32) red_sa[wave * BQ + j * 32 + lane] = s;
+            }
+        }
+        wait_vm<0>();  // the epilogue table's direct loads
+    }
+    __syncthreads();
+    AccS D[V], Sa = 0;
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+        const AccS* src = red + ((unit_ij(n) * 4 + unit_r4(n)) * 64 + lane) * 4 + unit_sub(n) * QV;
+#pragma unroll
+        for (int e = 0; e < QV; ++e) D[n * QV + e] = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            if constexpr (QV == 1) {
+                D[n] += src[w * (RING / 4)];
+            } else {
+                const AccQ v = *(const AccQ*)(src + w * (RING / 4));
+#pragma unroll
+                for (int e = 0; e < QV; ++e) D[n * QV + e] += v[e];
+            }
+        }
+    }
+    if (CONV && want_ep)
+#pragma unroll
+        for (int w = 0; w < W; ++w) Sa += red_sa[w * BQ + jq * 32 + (lane & 31)];
+
+    // ---- epilogue: the arithmetic of k_tmm's, operation by operation -----------------------------------
+    if constexpr (!CONV) {
+        const bool has_bn = ep.bn_scale != nullptr;
+        const double floor = __builtin_canonicalize(ep.relu ? 0.0 : (has_bn ? -__builtin_inf() : __builtin_nan("")));
+        const double aw = f_aw, bw = f_bw, sw = f_sw, bs = f_bs, bh = has_bn ? (double)f_bh : -0.0;
+#pragma unroll
+        for (int n = 0; n < NQ; ++n)
+#pragma unroll
+            for (int e = 0; e < QV; ++e) {
+                const int m = p0 + row_of(n) + e;
+                if (m >= prm.RP || !qok) continue;
+                const int64_t idx = (int64_t)m * prm.RQ + q;
+                const int x = n * QV + e;
+                if (prm.acc) prm.acc[idx] = (int)D[x];
+                if (prm.y) {
+                    const double aa = f_aa[x], ba = f_ba[x], r2 = aa * (double)f_sa[x] + (double)prm.Klogical * ba;
+                    const double v = aw * (aa * (double)D[x] + ba * sw) + bw * r2;
+                    prm.y[idx] = (float)(bs * __builtin_fmax(v, floor) + bh);
+                }
+            }
+        return;
+    } else {
+        const double* tab = (const double*)(smem + toff);
+        const double* ctab = tab + (4 + cls) * BP;
+        const double floor = __builtin_canonicalize(ep.relu ? 0.0 : -__builtin_inf());
+        const float out_floor = __builtin_canonicalizef(prm.relu_out ? 0.0f : -__builtin_inff());
+        uint8_t code[V];
+#pragma unroll
+        for (int n = 0; n < NQ; ++n)
+#pragma unroll
+            for (int e = 0; e < QV; ++e) {
+                const int t = row_of(n) + e, o = p0 + t, x = n * QV + e;
+                const bool ok = o < prm.RP && qok;
+                const int64_t idx = obase + (int64_t)o * ohw;
+                float z = 0.0f;
+                if (want_ep) {
+                    double v = tab[t] * (double)D[x] + (tab[BP + t] * (double)Sa + ctab[t]);
+                    v = __builtin_fmax(v, floor);
+                    z = (float)(tab[2 * BP + t] * v + tab[3 * BP + t]);
+                }
+                if (TERN == 2) z = __builtin_fmaxf(z + f_res[x], out_floor);
+                if (TERN != 1 && prm.y && ok) prm.y[idx] = z;
+                if (!TERN && prm.acc && ok) prm.acc[idx] = (int)D[x];
+                if (TERN) {
+                    const bool pos1 = z > f_hi[x], neg = z < f_lo[x];
+                    if (DT == 2)
+                        code[x] = o < prm.RP ? (uint8_t)(((unsigned)(pos1 | neg) << 1) | ((unsigned)neg << 3)) : 0;
+                    else
+                        code[x] = o < prm.RP ? (uint8_t)((int)pos1 - (int)neg) : 0;
+                }
+            }
+        if constexpr (TERN != 0) {
+            // codes as bytes [pixel][BP], then packed into the channel-innermost output rows
+            __syncthreads();  // the accumulators are read
+            uint8_t* cb = (uint8_t*)smem + (jq * 32 + (lane & 31)) * BP;
+#pragma unroll
+            for (int n = 0; n < NQ; ++n)
+#pragma unroll
+                for (int e = 0; e < QV; ++e) cb[row_of(n) + e] = code[n * QV + e];
+            __syncthreads();
+            constexpr int CPD = DT == 2 ? 8 : 4;        // codes per dword
+            constexpr int DPR = BP / CPD;               // dwords of a pixel of this tile
+            for (int d = tid; d < BQ * DPR; d += 64 * W) {
+                const int px = d / DPR, c = d % DPR, m = q0 + px;
+                const uint8_t* s = (const uint8_t*)smem + px * BP + c * CPD;
+                unsigned word;
+                if constexpr (DT == 2) {
+                    const uint2 v = *(const uint2*)s;  // a nibble per byte
+                    const unsigned a = v.x | (v.x >> 4), b2 = v.y | (v.y >> 4);
+                    word = (a & 0xff) | ((a >> 8) & 0xff00) | ((b2 & 0xff) << 16) | ((b2 << 8) & 0xff000000u);
+                } else {
+                    word = *(const unsigned*)s;
+                }
+                const int off = p0 / (DT == 2 ? 2 : 1) + c * 4;  // byte of the code row
+                if (m < prm.RQ && off < prm.ldc) *(unsigned*)(prm.codes + (int64_t)m * prm.ldc + off) = word;
+            }
+            // the zero codes of the row's padding, by the last tile along the channels
+            const int from = (p0 + BP) / (DT == 2 ? 2 : 1);
+            if (p0 + BP >= prm.RP && from < prm.ldc) {
+                const int units = (prm.ldc - from) / 16;
+                for (int d = tid; d < BQ * units; d += 64 * W) {
+                    const int px = d / units, m = q0 + px;
+                    if (m < prm.RQ)
+                        *(uint4*)(prm.codes + (int64_t)m * prm.ldc + from + (d - px * units) * 16) = make_uint4(0, 0, 0, 0);
+                }
+            }
+        }
+    }
+}
+
+template <int TP, int TQ, int W, int NS, bool CONV, int TERN, int DT>
+hipError_t launch(KsplitParams& kp, hipStream_t st)
+{
+    TmmParams& prm = kp.t;
+    const size_t smem = (size_t)W * NS * (TP + TQ) * 2048 +
+                        (CONV ? (size_t)W * TQ * 128 + (((size_t)conv_table_bytes(32 * TP, prm.g) + 1023) & ~(size_t)1023) : 0);
+    if (smem > (size_t)kMaxLds) return hipErrorInvalidValue;
+    auto kern = k_ksplit<TP, TQ, W, NS, CONV, TERN, DT>;
+    static bool attr_done = false;
+    if (!attr_done) {
+        const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
+        if (e != hipSuccess) return e;
+        attr_done = true;
+    }
+    const unsigned grid = tile_grid(prm, 32 * TP, 32 * TQ);
+    if (!grid) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * W), smem, st, kp);
+    return hipGetLastError();
+}
+
+template <bool CONV, int TERN, int DT>
+hipError_t launch_form(int form, KsplitParams& kp, hipStream_t st)
+{
+    switch (form) {
+        case 0: return launch<1, 1, 4, 4, CONV, TERN, DT>(kp, st);
+        case 1: return launch<1, 1, 8, 2, CONV, TERN, DT>(kp, st);
+        case 2: return launch<2, 1, 8, 3, CONV, TERN, DT>(kp, st);
+        case 3: return launch<2, 2, 8, 2, CONV, TERN, DT>(kp, st);
+        case 4: return launch<2, 2, 4, 2, CONV, TERN, DT>(kp, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace
+
+template <bool CONV, int TERN, int DT>
+hipError_t launch_ksplit(int form, const TmmParams& prm, hipStream_t st)
+{
+    KsplitParams kp = {};
+    kp.t = prm;
+    kp.div_spt = make_fastdiv((uint32_t)(CONV ? prm.g.Cpad >> 6 : 1));
+    kp.div_kw = make_fastdiv((uint32_t)(CONV ? prm.g.KW : 1));
+    return launch_form<CONV, TERN, DT>(form, kp, st);
+}
+template hipError_t launch_ksplit<false, 0, 0>(int, const TmmParams&, hipStream_t);
+template hipError_t launch_ksplit<false, 0, 2>(int, const TmmParams&, hipStream_t);
+template hipError_t launch_ksplit<true, 0, 0>(int, const TmmParams&, hipStream_t);
+template hipError_t launch_ksplit<true, 0, 2>(int, const TmmParams&, hipStream_t);
+template hipError_t launch_ksplit<true, 1, 0>(int, const TmmParams&, hipStream_t);
+template hipError_t launch_ksplit<true, 1, 2>(int, const TmmParams&, hipStream_t);
+template hipError_t launch_ksplit<true, 2, 0>(int, const TmmParams&, hipStream_t);
+template hipError_t launch_ksplit<true, 2, 2>(int, const TmmParams&, hipStream_t);
+
+}  // namespace rtn

@@ -81,12 +81,10 @@ hipError_t launch_index(int cfg, TmmParams& prm, hipStream_t st)
 // The conv rules come from timing the ResNet-18 layer shapes at batch 256: a
 // grid that fits the chip in one round beats a finer one that needs a second,
 // and the short-K layers prefer more resident blocks over a deeper ring.
-// Small grids: a K-step (64 bytes) of a block costs about 0.5 us with the 128 x 128 tile and
-// 0.3 us with the 64 x 64 one whatever the ring depth (12 stages: no faster than 4), so the finer
-// tile wins while its blocks run side by side, one or two per CU.  Beyond that the operand
+// Small grids that pick_ksplit() leaves here: a K-step (64 bytes) of a block costs about 0.5 us with the
+// 128 x 128 tile and 0.3 us with the 64 x 64 one whatever the ring depth (12 stages: no faster than 4), so the
+// finer tile wins while its blocks run side by side, one or two per CU.  Beyond that the operand
 // traffic of the small tile counts, the more the longer K is.  us, 128 x 128 -> 64 x 64 tile:
-//   conv, FP4, 256 filters on one 14 x 14 image (16 blocks, 18 steps)  13.3 -> 8.1
-//   GEMM, FP4, 128 x 1024 x 4096 (32 blocks, 32 steps)                 10.1 -> 7.0
 //   GEMM, int8, 512 x 4096 x 4096 (512 blocks, 64 steps)               20.1 -> 18.4
 //   weight-only GEMM, 512 x 4096 x 4096 (512 blocks, 384 steps)        98.4 -> 103.4, not taken
 //   GEMM, FP4, 1000 x 4000 x 1000 (1008 blocks, 8 steps)                9.5 -> 8.1
@@ -110,6 +108,29 @@ int pick_tile(int64_t rp, int64_t rq, int nk, bool conv)
     if (nblocks(rp, rq, 256, 256) >= 256) return 2;
     if (nblocks(rp, rq, 128, 128) >= 256 || rq > 64) return 1;
     return 0;
+}
+
+// The form of k_ksplit for a grid too small for k_tmm, or -1: the row of the table in tmm_ksplit.hip.
+// K's share of the time decides between the forms, the number of 32 x 32 tiles whether to cut K at all; past
+// these lines the small tiles' operand traffic (L2 to LDS) costs more than the cut saves.  Time against k_tmm's,
+// geometric mean (worst) over 336 random geometries (GEMM M 1 to 4096, N and K 64 to 8192; convs of 24 to 1024
+// channels and filters, 7 to 112 wide, windows 1, 3, 5, stride 1, 2, every epilogue; FP4 and int8):
+//   tiles <= 256:  GEMM 1.21 (1.11) at 1-3 K-steps, 1.37 at 4-8, 1.59 at 17-32, 1.90 at 33-64, 2.28 beyond
+//                  conv 1.19 (1.03) at 1-3 K-steps, 1.43 at 4-8, 1.95 at 17-32, 2.46 at 33-64, 2.98 beyond
+//   tiles <= 512:  GEMM 1.15 (1.04) at 1-3, 1.16 (1.11) at 17-32, 1.29 (1.20) beyond
+//                  conv 1.14 (1.06) at 1-3, 1.16 (1.07) at 9-16, 1.43 at 17-32, 1.7 to 2.1 beyond
+//   tiles <= 1024: GEMM 0.89 (0.85) at 17-32 K-steps, not taken; conv 1.03 (0.97) at 17-32, not taken, 1.41 (1.34)
+//                  at 33-64, 1.70 (1.45) beyond
+//   64 x 64 tiles in 257 .. 512: conv 1.00 at 33-64 K-steps, not taken, 1.3 (1.03) beyond
+int pick_ksplit(int64_t rp, int64_t rq, int nk, bool conv)
+{
+    if (nblocks(rp, rq, 32, 32) <= 512) {
+        if (nk <= 3) return 0;
+        return nk > 32 && nblocks(rp, rq, 32, 32) > 256 && nblocks(rp, rq, 64, 32) <= 256 ? 2 : 1;
+    }
+    if (!conv) return -1;
+    if (nk > 32 && nblocks(rp, rq, 64, 64) <= 256) return 3;
+    return nk > 64 && nblocks(rp, rq, 64, 64) <= 512 ? 4 : -1;
 }
 
 }  // namespace
@@ -140,6 +161,8 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t st)
     prm.acc = a.acc;
     prm.y = a.y;
     prm.ep = a.ep;
+    const int form = g_forced_tile >= 0 ? -1 : pick_ksplit(a.M, a.N, prm.nk, false);
+    if (form >= 0) return a.fp4 ? launch_ksplit<false, 0, 2>(form, prm, st) : launch_ksplit<false, 0, 0>(form, prm, st);
     const int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(a.M, a.N, prm.nk, false);
     return a.fp4 ? launch_index<false, 0, 2>(cfg, prm, st) : launch_index<false>(cfg, prm, st);
 }
@@ -270,6 +293,17 @@ hipError_t launch_conv_mfma(const ConvArgs& a, hipStream_t st)
     {
         const int64_t out_bytes = (int64_t)g.Nb * g.O * g.OH * g.OW * 4 * ((a.acc ? 1 : 0) + (a.y ? 1 : 0));
         prm.nt_out = out_bytes > (int64_t)128 << 20;
+    }
+    const int form = g_forced_tile >= 0 ? -1 : pick_ksplit(g.O, prm.RQ, prm.nk, true);
+    if (form >= 0) {
+        hipError_t e;
+        if (!a.codes)
+            e = a.fp4 ? launch_ksplit<true, 0, 2>(form, prm, st) : launch_ksplit<true, 0, 0>(form, prm, st);
+        else if (a.res != nullptr || a.y != nullptr || a.relu_out)
+            e = a.fp4 ? launch_ksplit<true, 2, 2>(form, prm, st) : launch_ksplit<true, 2, 0>(form, prm, st);
+        else
+            e = a.fp4 ? launch_ksplit<true, 1, 2>(form, prm, st) : launch_ksplit<true, 1, 0>(form, prm, st);
+        if (e != hipErrorInvalidValue) return e;  // (the table of a large pad can exceed the LDS)
     }
     int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(g.O, prm.RQ, prm.nk, true);
     // a 64-filter layer with a centred stride-1 window: the variant that keeps the

@@ -530,6 +530,59 @@ def test_small_grid_tile_choice(M, N, K, fmt):
     T.assert_y_close(got["y"].cpu().numpy(), ref["y"], "tile choice")
 
 
+# Small grids (K cut into shares, one per wave of a block): every form of the kernel at sizes that its rule
+# gives it -- ragged tiles, K-steps that do not divide by the waves, fewer K-steps than waves.
+KSPLIT_GEMMS = [(1, 64, 64), (33, 65, 150), (500, 480, 70),          # up to 3 K-steps, 480 tiles
+                (37, 100, 1100), (130, 500, 577),                    # eight waves
+                (70, 3200, 4300)]                                    # 300 tiles of 32 x 32, 34+ K-steps
+
+
+@pytest.mark.parametrize("fmt", [B.RTN_CODE_I8, FP4])
+@pytest.mark.parametrize("M,N,K", KSPLIT_GEMMS)
+def test_small_grid_gemm(M, N, K, fmt):
+    _say("small grid gemm %d x %d x %d fmt %d" % (M, N, K, fmt))
+    case = wl.gemm_case(M, N, K, seed=M + K)
+    ref = T.oracle_gemm(case)
+    for mode in (True, "separate"):
+        got = T.hip_gemm(case, fmt=fmt, want_acc=mode)
+        assert (got["D"].cpu().numpy() == ref["D"]).all()
+        T.assert_y_close(got["y"].cpu().numpy(), ref["y"], "small grid gemm")
+
+
+KSPLIT_CONVS = [  # C, H, W, O, k, stride, pad, batch
+    (64, 9, 11, 40, 1, 2, 0, 2),      # one K-step, 88 padding codes behind 40
+    (130, 7, 7, 70, 3, 1, 1, 1),      # ragged everywhere
+    (200, 6, 9, 100, 5, 1, 2, 1),     # 81 classes' table, 50+ K-steps on 8 waves
+    (300, 13, 13, 300, 3, 1, 1, 6),   # 320 tiles of 32 x 32, more than 256 blocks with three K-steps per tap (int8: 45)
+    (600, 28, 28, 70, 3, 1, 1, 7),    # 64 x 64 tiles, eight waves
+    (700, 28, 31, 70, 5, 1, 2, 10),   # ... and four: 272 blocks
+]
+
+
+@pytest.mark.parametrize("fmt", [B.RTN_CODE_I8, FP4])
+@pytest.mark.parametrize("geo", KSPLIT_CONVS, ids=lambda g: "x".join(map(str, g)))
+def test_small_grid_conv(geo, fmt):
+    """The plain, the ternarizing and the block-tail epilogue against the oracle."""
+    C, H, W, O, k, stride, pad, batch = geo
+    _say("small grid conv %s fmt %d" % (geo, fmt))
+    shape = wl.ConvShape("s", C, H, O, k, stride, pad)
+    case = wl.conv_case(shape, batch=batch, seed=C + H, bn=True, Wx=W)
+    lo, hi = np.float32(-0.5), np.float32(0.5)
+    ref = T.oracle_conv(case, True, relu=True)
+    for mode in (True, "separate"):
+        got = T.hip_conv(case, True, relu=True, want_acc=mode, fmt=fmt)
+        assert (got["D"].cpu().numpy() == ref["D"]).all()
+        T.assert_y_close(got["y"].cpu().numpy(), ref["y"], "small grid conv")
+    got = T.codes_as_i8(T.hip_conv_ternarize(case, lo, hi, True, relu=True, fmt=fmt), fmt, O)
+    T.assert_codes_match(got, T.oracle_next_codes(ref, lo, hi), ref["y"], lo, hi, "small grid codes")
+    res = np.random.default_rng(C).standard_normal(ref["y"].shape).astype(np.float32)
+    codes, y = T.hip_conv_ternarize(case, lo, hi, True, relu=True, residual=res, relu_out=True, want_y=True, fmt=fmt)
+    z = orc.add_relu(ref["y"], res, True)
+    want = orc.nchw_to_nhwc_i8(orc.ternarize_nchw(z, lo, hi), (O + 63) // 64 * 64)
+    T.assert_codes_match(T.codes_as_i8(codes, fmt, O), want, z, lo, hi, "small grid tail")
+    T.assert_y_close(y.cpu().numpy(), z, "small grid tail y")
+
+
 FP4_HALO_SHAPES = HALO_SHAPES + [
     ("h256", 256, 10, 136, 3, 1, 1, 3, None),      # 128 bytes per pixel: two K-steps per tap
     ("h200r", 200, 7, 130, 3, 1, 1, 9, 10),        # C padded to 256, ragged in O and pixels
