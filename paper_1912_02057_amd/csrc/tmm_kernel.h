@@ -227,7 +227,13 @@ __device__ __forceinline__ bool block_tile(const TmmParams& prm, int& tileP, int
 // only / both), and y without ReLU and BN on interior tiles, which needs 4 fp64 operations per
 // output instead of 6 and fewer registers -- picked once per block.  The GEMM keeps plain
 // stores: its tiles finish together, and the cache absorbs that burst faster than HBM takes it.
-template <int BP, int TP, int TQ, bool SUMS, class Acc, class Value>
+// ABREAST: interior tiles with y alone take one operation at a time over four outputs and more.  fp64 operations
+// of one wave that depend on each other issue every 10 cycles, independent ones every 5 (a conversion 8), and a tile
+// of 256 x 256 leaves a SIMD one wave: its 256 outputs per lane take 9.5 us so, 14.5 us one after the other; the
+// stores alone 7.1.  For the bit planes, whose kernel takes 20.8 instead of 23.6 us at 4096 x 4096 x 512 (69 instead
+// of 74 with the pack at K = 4096).  Not for the others: the FP4 GEMM's tiles end in a burst of stores either
+// way, and it lost 0.5 % at K = 4096 and at 16384 x 8192 x 8192.
+template <int BP, int TP, int TQ, bool SUMS, bool ABREAST = false, class Acc, class Value>
 __device__ __forceinline__ void gemm_epilogue(const TmmParams& prm, double* tab, int p0, int q0, int wrow, int wcol,
                                               bool full_tile, const Acc& acc, Value value)
 {
@@ -284,6 +290,43 @@ __device__ __forceinline__ void gemm_epilogue(const TmmParams& prm, double* tab,
             }
             accp[j] = ACC ? prm.acc + (nok[j] ? ncol : 0) : nullptr;
             yp[j] = Y ? prm.y + (nok[j] ? ncol : 0) : nullptr;
+        }
+        if constexpr (ABREAST && FULL && Y && !ACC) {
+            constexpr int RG = TQ >= 4 ? 1 : 4 / TQ;  // rows at a time
+#pragma unroll
+            for (int i = 0; i < TP; ++i)
+#pragma unroll
+                for (int r0 = 0; r0 < 16; r0 += RG) {
+                    double v[RG][TQ], aa[RG], ba[RG], r2[RG];
+                    int64_t rowoff[RG];
+#pragma unroll
+                    for (int r = 0; r < RG; ++r) {
+                        const int t = wrow + i * 32 + 8 * ((r0 + r) >> 2) + 4 * (lane >> 5) + ((r0 + r) & 3);
+                        rowoff[r] = (int64_t)(p0 + t) * N;
+                        aa[r] = tab[t];
+                        ba[r] = tab[BP + t];
+                        r2[r] = tab[2 * BP + t];
+                    }
+                    auto each = [&](auto&& f) {
+#pragma unroll
+                        for (int r = 0; r < RG; ++r)
+#pragma unroll
+                            for (int j = 0; j < TQ; ++j) f(r, j);
+                        __builtin_amdgcn_sched_barrier(0);
+                    };
+                    // (operation by operation what the compiler makes of the expression below)
+                    each([&](int r, int j) { v[r][j] = (double)value(acc[i][j][r0 + r]); });
+                    each([&](int r, int j) { v[r][j] = aa[r] * v[r][j]; });
+                    each([&](int r, int j) { v[r][j] = __builtin_fma(ba[r], sw[j], v[r][j]); });
+                    each([&](int r, int j) { v[r][j] = aw[j] * v[r][j]; });
+                    each([&](int r, int j) { v[r][j] = __builtin_fma(bw[j], r2[r], v[r][j]); });
+                    if (TAIL) {
+                        each([&](int r, int j) { v[r][j] = __builtin_fmax(v[r][j], relu_floor); });
+                        each([&](int r, int j) { v[r][j] = __builtin_fma(bs[j], v[r][j], bh[j]); });
+                    }
+                    each([&](int r, int j) { yp[j][rowoff[r]] = (float)v[r][j]; });
+                }
+            return;
         }
 #pragma unroll
         for (int i = 0; i < TP; ++i)

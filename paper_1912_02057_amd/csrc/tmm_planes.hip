@@ -22,12 +22,13 @@
 // when the rows' byte length is not a multiple of 16 (an odd number of plane words); what lies
 // behind a row's end is read from the zero page.
 //
-// M = N = K = 4096: 56.6 us against 407 us for k_gemm_popc (and 38.5 us for the FP4 GEMM, which has
-// nothing to expand).  Bound by vector-instruction issue: per k-slice a wave of the 256 x 256 tile runs
-// 80 expanding instructions for 16 MFMAs; counters over 8192 x 4096 x 4096 to 16384 x 8192 x 8192 give 10
-// to 12 vector instructions per MFMA in all (FP4 GEMM: 2.4 to 3.5) and the matrix cores 30 to 35 %
-// busy.  A wave tile of 128 x 128 halves that share against 64 x 64, hence the largest tile as soon as it
-// gives every CU a block (it spills 3 registers; the 4-byte form also 271 scalar ones).
+// M = N = K = 4096: 47 us against 407 us for k_gemm_popc (and 36.5 us for the FP4 GEMM, which has nothing to
+// expand); with an odd number of words, 4096 x 4096 x 4160, 61 us.  Bound by vector-instruction issue: per k-slice a
+// wave of the 256 x 256 tile runs 80 expanding instructions for 16 MFMAs, at one wave per SIMD.  A wave tile of
+// 128 x 128 halves that share against 64 x 64, hence the largest tile as soon as it gives every CU a block.
+// The expansion of a slice is dealt out behind the MFMAs of the slice before, and a load costs a 32-bit lane
+// offset on a scalar base (not a pointer per lane, and 271 scalar registers spilled in the 4-byte form): without the
+// two, 51.5 and 72.5 us.
 #include "tmm_kernel.h"
 
 namespace rtn {
@@ -65,28 +66,47 @@ __global__ __launch_bounds__(256, MINW) void k_gemm_planes(TmmParams prm, const 
     const unsigned rowb = (unsigned)prm.ldP;  // bytes of a plane row (both operands)
 
     // ---- loader: load j of a wave covers stage rows RPL * (wave + 4 j) .. + RPL - 1 ----------
-    const int lpos = (lane * EB) & 63;  // byte position within the 64-byte LDS row
+    // (4 RPL divides BP and BQ: which operand and plane a load belongs to is known when compiling, and so
+    // a load is a scalar base and a 32-bit lane offset, shared by the two planes)
+    static_assert(BP % (4 * RPL) == 0 && BQ % (4 * RPL) == 0, "a load lies in one plane");
+    const int lpos = (lane * EB) & 63;                     // byte position within the 64-byte LDS row
+    const int lrow = RPL * wave + lane * EB / 64;          // row of load 0
+    const int limP = prm.RP - 1 - p0, limQ = prm.RQ - 1 - q0;
+    const unsigned kb0 = (unsigned)((((lpos >> 4) ^ swz(lrow)) << 4) + (lpos & 15));  // swz: by row & 15, the same for every j
+    const int8_t* const bases[4] = {prm.P + (int64_t)p0 * rowb, Psign + (int64_t)p0 * rowb, prm.Q + (int64_t)q0 * rowb,
+                                    Qsign + (int64_t)q0 * rowb};
     auto issue = [&](int st) {
-        const unsigned dst0 = lds0 + (unsigned)((st & 1) * STAGE);
+        const unsigned dst0 = lds0 + (unsigned)((st & 1) * STAGE + RPL * wave * 64);
+        auto all = [&](auto whole) {
+            const unsigned kb = (unsigned)st * 64 + kb0;
 #pragma unroll
-        for (int j = 0; j < NL; ++j) {
-            const int rr = RPL * (wave + 4 * j);          // first row of this load (wave-uniform)
-            const int row = rr + lane * EB / 64;
-            const bool isP = rr < 2 * BP;
-            const int r0 = isP ? rr : rr - 2 * BP, half = isP ? BP : BQ;
-            const bool sgn = r0 >= half;
-            const int8_t* base = isP ? (sgn ? Psign : prm.P) : (sgn ? Qsign : prm.Q);
-            int gr = (isP ? p0 : q0) + (r0 - (sgn ? half : 0)) + lane * EB / 64;
-            const int lim = (isP ? prm.RP : prm.RQ) - 1;
-            gr = gr < lim ? gr : lim;  // rows past the end: any valid row, never stored
-            const unsigned kb = (unsigned)st * 64 + (unsigned)((((lpos >> 4) ^ swz(row)) << 4) + (lpos & 15));
-            const int8_t* src = kb < rowb ? base + (int64_t)gr * rowb + kb : (const int8_t*)g_zero16;
-            const unsigned dst = dst0 + (unsigned)rr * 64;
-            if constexpr (EB == 16)
-                dma16(src, dst);
-            else
-                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(dst), "v"(src) : "memory");
-        }
+            for (int j = 0; j < NL; ++j) {
+                const int rr = 4 * RPL * j;  // first row of this load, without the wave's share
+                const bool isP = rr < 2 * BP;
+                const int r0 = isP ? rr : rr - 2 * BP, half = isP ? BP : BQ, sgn = r0 >= half;
+                int row = r0 - (sgn ? half : 0) + lrow;
+                const int lim = isP ? limP : limQ;
+                row = row < lim ? row : lim;  // rows past the end: any valid row, never stored
+                const int8_t* base = uniform_ptr(bases[(isP ? 0 : 2) + sgn]);
+                const unsigned off = (unsigned)row * rowb + kb, dst = dst0 + (unsigned)rr * 64;
+                if constexpr (decltype(whole)::value) {
+                    if constexpr (EB == 16)
+                        dma16_base(base, off, dst);
+                    else
+                        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(dst), "v"(off), "s"(base) : "memory");
+                } else {  // the stage that reaches past the rows' end
+                    const int8_t* src = kb < rowb ? base + off : (const int8_t*)g_zero16;
+                    if constexpr (EB == 16)
+                        dma16(src, dst);
+                    else
+                        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(dst), "v"(src) : "memory");
+                }
+            }
+        };
+        if ((unsigned)(st + 1) * 64 <= rowb)
+            all(std::true_type{});
+        else
+            all(std::false_type{});
     };
 
     v16f acc[TP][TQ];
@@ -107,41 +127,45 @@ __global__ __launch_bounds__(256, MINW) void k_gemm_planes(TmmParams prm, const 
         block_barrier();
         if (st + 1 < nst) issue(st + 1);
         const int8_t* sb = smem + (st & 1) * STAGE;
+        constexpr int NM = TP * TQ, NF = TP + TQ;
+        v4i raw[2][NF][2];  // [half of the stage][fragment][mask, sign]
+        v8i frag[2][NF];
+        auto fetch = [&](int h, int f, int plane) {
+            const bool isP = f < TP;
+            const int row = (isP ? wp * WP + f * 32 : wq * WQ + (f - TP) * 32) + (lane & 31), ch = 2 * h + (lane >> 5);
+            raw[h][f][plane] = *(const v4i*)(sb + (isP ? plane * BP : (2 * BP + plane * BQ)) * 64 + row * 64 + ((ch ^ swz(row)) << 4));
+        };
+        auto expand = [&](int s, int f) {
+            frag[s & 1][f] = planes_to_fp4((unsigned)raw[s >> 2][f][0][s & 3], (unsigned)raw[s >> 2][f][1][s & 3]);
+        };
+        auto product = [&](int s, int n) {
+            const int i = n / TQ, j = n % TQ;
+            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(frag[s & 1][i], frag[s & 1][TP + j], acc[i][j], 4, 4, 0, 0, 0, 0);
+        };
+        // The 8 k-slices in a fixed issue order: behind every MFMA of a slice its share of the next slice's
+        // expansion, behind those of the first one also the second half's LDS reads.
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            v4i pm[TP], ps[TP], qm[TQ], qs[TQ];
-            const int ch = 2 * g + (lane >> 5);
+        for (int f = 0; f < NF; ++f) fetch(0, f, 0), fetch(0, f, 1);
 #pragma unroll
-            for (int t = 0; t < TP; ++t) {
-                const int row = wp * WP + t * 32 + (lane & 31);
-                const int o = row * 64 + ((ch ^ swz(row)) << 4);
-                pm[t] = *(const v4i*)(sb + o);
-                ps[t] = *(const v4i*)(sb + BP * 64 + o);
+        for (int f = 0; f < NF; ++f) expand(0, f);
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int n = 0; n < NM; ++n) {
+                product(s, n);
+                if (s == 0) {
+#pragma unroll
+                    for (int x = n * 2 * NF / NM; x < (n + 1) * 2 * NF / NM; ++x) fetch(1, x / 2, x % 2);
+                }
+                if (s < 7) {
+#pragma unroll
+                    for (int f = n * NF / NM; f < (n + 1) * NF / NM; ++f) expand(s + 1, f);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-#pragma unroll
-            for (int t = 0; t < TQ; ++t) {
-                const int row = wq * WQ + t * 32 + (lane & 31);
-                const int o = 2 * BP * 64 + row * 64 + ((ch ^ swz(row)) << 4);
-                qm[t] = *(const v4i*)(sb + o);
-                qs[t] = *(const v4i*)(sb + BQ * 64 + o);
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                v8i fp[TP], fq[TQ];
-#pragma unroll
-                for (int t = 0; t < TP; ++t) fp[t] = planes_to_fp4((unsigned)pm[t][e], (unsigned)ps[t][e]);
-#pragma unroll
-                for (int t = 0; t < TQ; ++t) fq[t] = planes_to_fp4((unsigned)qm[t][e], (unsigned)qs[t][e]);
-#pragma unroll
-                for (int i = 0; i < TP; ++i)
-#pragma unroll
-                    for (int j = 0; j < TQ; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp[i], fq[j], acc[i][j], 4, 4, 0, 0, 0, 0);
-            }
-        }
     }
     const bool full_tile = p0 + BP <= prm.RP && q0 + BQ <= prm.RQ;
-    gemm_epilogue<BP, TP, TQ, true>(prm, (double*)smem, p0, q0, wp * WP, wq * WQ, full_tile, acc,
+    gemm_epilogue<BP, TP, TQ, true, true>(prm, (double*)smem, p0, q0, wp * WP, wq * WQ, full_tile, acc,
                                     [](float s) { return 0.25f * s; });
 }
 
