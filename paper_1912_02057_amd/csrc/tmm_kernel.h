@@ -74,7 +74,7 @@ struct TmmParams {
     // ReLU; the fp32 value that is ternarized is also stored when y is given
     const float* res;
     int relu_out;
-    int nt_out;  // conv: store the fp32 / int32 outputs with the non-temporal hint
+    int nt_out;  // store the outputs with the non-temporal hint (conv: fp32 / int32, GEMM: y of the 256 x 256 tile)
     // bf16 operands (DT = 1): the weight rows (Q) are wwrap bytes long and are walked again
     // from the start each time the K offset passes their end
     unsigned wwrap;
@@ -225,15 +225,17 @@ __device__ __forceinline__ bool block_tile(const TmmParams& prm, int& tileP, int
 // exist (not for the weight-only form, whose beta_a and beta_w are 0).
 // The element loops exist in straight-line variants -- (interior / ragged tile) x (acc only / y
 // only / both), and y without ReLU and BN on interior tiles, which needs 4 fp64 operations per
-// output instead of 6 and fewer registers -- picked once per block.  The GEMM keeps plain
-// stores: its tiles finish together, and the cache absorbs that burst faster than HBM takes it.
+// output instead of 6 and fewer registers -- picked once per block.
+// NT: y is stored with the non-temporal hint.  The GEMM's tiles finish together, and a burst that the memory-side
+// cache holds is absorbed faster without it (and is there for the next kernel); a larger one is written back while
+// the next tiles are multiplied and takes 1244 -> 1480 cycles per K-step from them (launch_gemm_mfma decides).
 // ABREAST: interior tiles with y alone take one operation at a time over four outputs and more.  fp64 operations
 // of one wave that depend on each other issue every 10 cycles, independent ones every 5 (a conversion 8), and a tile
 // of 256 x 256 leaves a SIMD one wave: its 256 outputs per lane take 9.5 us so, 14.5 us one after the other; the
 // stores alone 7.1.  For the bit planes, whose kernel takes 20.8 instead of 23.6 us at 4096 x 4096 x 512 (69 instead
 // of 74 with the pack at K = 4096).  Not for the others: the FP4 GEMM's tiles end in a burst of stores either
 // way, and it lost 0.5 % at K = 4096 and at 16384 x 8192 x 8192.
-template <int BP, int TP, int TQ, bool SUMS, bool ABREAST = false, class Acc, class Value>
+template <int BP, int TP, int TQ, bool SUMS, bool ABREAST = false, bool NT = false, class Acc, class Value>
 __device__ __forceinline__ void gemm_epilogue(const TmmParams& prm, double* tab, int p0, int q0, int wrow, int wcol,
                                               bool full_tile, const Acc& acc, Value value)
 {
@@ -350,7 +352,10 @@ __device__ __forceinline__ void gemm_epilogue(const TmmParams& prm, double* tab,
                         if (Y) {
                             double v = aw[j] * (aa * (double)D + ba * sw[j]) + bw[j] * r2;
                             if (TAIL) v = bs[j] * __builtin_fmax(v, relu_floor) + bh[j];
-                            yp[j][rowoff] = (float)v;
+                            if constexpr (NT)
+                                __builtin_nontemporal_store((float)v, yp[j] + rowoff);
+                            else
+                                yp[j][rowoff] = (float)v;
                         }
                     }
                 }
@@ -396,7 +401,7 @@ __device__ __forceinline__ void gemm_epilogue(const TmmParams& prm, double* tab,
 // no scaling): a lane's 16 operand bytes are 32 codes of one row, everything else is
 // byte for byte the int8 form.  Which 32 of a K-step's 128 codes a lane holds, and in
 // which nibble order, is the same for both operands, so the sum over k is unaffected.
-template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0>
+template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0, bool NT = false>
 __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
 {
     static_assert(DT != 1 || !CONV, "bf16 operands: GEMM only");
@@ -865,7 +870,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
             dispatch3(run, std::false_type{});
     };
     if constexpr (!CONV) {
-        gemm_epilogue<BP, TP, TQ, DT != 1>(prm, (double*)smem, p0, q0, wp * WP, wq * WQ, full_tile, acc,
+        gemm_epilogue<BP, TP, TQ, DT != 1, false, NT>(prm, (double*)smem, p0, q0, wp * WP, wq * WQ, full_tile, acc,
                                             [](auto d) { return d; });
     } else {
         // y = g1[o]*D + c2[o]*Sa[m] + Cst[class(m)][o],  g1 = aa*aw, c2 = aa*bw;
@@ -1086,7 +1091,7 @@ inline unsigned tile_grid(TmmParams& prm, int bp, int bq)
     return (unsigned)((blocks + 7) / 8 * 8);
 }
 
-template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0>
+template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0, bool NT = false>
 hipError_t launch_cfg(TmmParams& prm, hipStream_t st)
 {
     constexpr int ring_bytes = NS * (BP + (HC ? 0 : BQ)) * 64;
@@ -1107,7 +1112,7 @@ hipError_t launch_cfg(TmmParams& prm, hipStream_t st)
     }
     if (smem > kMaxLds) return hipErrorInvalidValue;
     static bool attr_done = false;
-    auto kern = k_tmm<BP, BQ, WGP, WGQ, NS, MINW, CONV, TERN, HC, DT>;
+    auto kern = k_tmm<BP, BQ, WGP, WGQ, NS, MINW, CONV, TERN, HC, DT, NT>;
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)kMaxLds);

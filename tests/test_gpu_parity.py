@@ -549,6 +549,18 @@ def test_small_grid_gemm(M, N, K, fmt):
         T.assert_y_close(got["y"].cpu().numpy(), ref["y"], "small grid gemm")
 
 
+@pytest.mark.parametrize("fmt", [B.RTN_CODE_I8, FP4])
+def test_gemm_output_of_128_mib(fmt):
+    """The least output that is stored with the non-temporal hint, with ReLU and BN and without."""
+    _say("gemm 8192 x 4096 x 70 fmt %d" % fmt)
+    case = wl.gemm_case(8192, 4096, 70, seed=5)
+    rng = np.random.default_rng(6)
+    bn = (rng.uniform(0.5, 1.5, 4096).astype(np.float32), rng.standard_normal(4096).astype(np.float32))
+    for kw in ({}, dict(relu=True, bn=bn)):
+        ref, got = T.oracle_gemm(case, **kw), T.hip_gemm(case, fmt=fmt, want_acc=False, **kw)
+        T.assert_y_close(got["y"].cpu().numpy(), ref["y"], "gemm 128 MiB")
+
+
 KSPLIT_CONVS = [  # C, H, W, O, k, stride, pad, batch
     (64, 9, 11, 40, 1, 2, 0, 2),      # one K-step, 88 padding codes behind 40
     (130, 7, 7, 70, 3, 1, 1, 1),      # ragged everywhere
