@@ -36,107 +36,116 @@ __device__ __forceinline__ int wave_sum(int v)
     return v;
 }
 
-// ---- rows layout, int8 codes -------------------------------------------
-// One wavefront per row, four rows per 256-thread block.  Each lane handles 4
-// consecutive elements per step (one 16-byte load when VEC4), so a wave reads
-// 1 KiB and writes 256 B per step, both fully coalesced.
-template <bool VEC4>
-__global__ __launch_bounds__(256) void k_pack_rows_i8(PackArgs a)
+// ---- rows layout -----------------------------------------------------------
+// WPR waves per row: 1, or the 4 of a block where the rows alone would leave most of the chip without a wave.
+// A wave that waits for each step's loads before the next is bound by their latency, so it asks for up to 8 quads
+// (codes) or 8 words' worth (planes) of its row at a time, and the waves of a row take turns in runs of that size.  Quads are
+// loaded as 16 bytes at any K and row address: a global load of several dwords needs 4-byte alignment only.
+//   us, before (one wave per row, one step's loads in flight; K % 4 != 0: 4-byte loads) -> now:
+//     int8, 1000 x 2187  7.1 -> 4.2      FP4, 16 x 8192  10.6 -> 3.8     FP4, 4096 x 4096  14.3 -> 14.2
+//     int8, 4096 x 4095  25.4 -> 15.2    FP4, 16384 x 8191  182 -> 120 (5.0 TB/s), 16384 x 8192  127 -> 121
+//     planes, 16 x 8192  16.0 -> 4.8, 4096 x 4096  16.8 -> 14.2
+// elements k .. k + 3 of a row, k = k0 + 4 lane; NaN, whose code is 0, past its end
+__device__ __forceinline__ void load_quad(const float* xr, unsigned k0, unsigned lane, unsigned K, float (&v)[4])
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= a.rows) return;
-    const float lo = thr(a.lo, row), hi = thr(a.hi, row);
-    const float* xr = a.x + row * a.K;
-    int8_t* cr = (int8_t*)a.codes + row * a.Kpad;
-    int sum = 0;
-    for (int64_t k0 = 0; k0 < a.Kpad; k0 += 256) {
-        const int64_t k = k0 + 4 * lane;
-        if (k >= a.Kpad) break;
-        int t0 = 0, t1 = 0, t2 = 0, t3 = 0;
-        if (VEC4) {
-            if (k < a.K) {  // K % 4 == 0: the whole quad is in range
-                const float4 v = *(const float4*)(xr + k);
-                t0 = tern(v.x, lo, hi);
-                t1 = tern(v.y, lo, hi);
-                t2 = tern(v.z, lo, hi);
-                t3 = tern(v.w, lo, hi);
-            }
-        } else {
-            if (k + 0 < a.K) t0 = tern(xr[k + 0], lo, hi);
-            if (k + 1 < a.K) t1 = tern(xr[k + 1], lo, hi);
-            if (k + 2 < a.K) t2 = tern(xr[k + 2], lo, hi);
-            if (k + 3 < a.K) t3 = tern(xr[k + 3], lo, hi);
-        }
-        sum += t0 + t1 + t2 + t3;
-        const uint32_t packed = (uint32_t)(t0 & 0xff) | ((uint32_t)(t1 & 0xff) << 8) |
-                                ((uint32_t)(t2 & 0xff) << 16) | ((uint32_t)(t3 & 0xff) << 24);
-        *(uint32_t*)(cr + k) = packed;
-    }
-    if (a.sum_t) {
-        sum = wave_sum(sum);
-        if (lane == 0) a.sum_t[row] = sum;
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = __builtin_nanf("");
+    if (k0 >= K) return;  // the whole wave
+    const unsigned k = k0 + 4 * lane;
+    if (k + 4 <= K) {
+        const f4 q = *(const f4*)(xr + k);
+        v[0] = q[0], v[1] = q[1], v[2] = q[2], v[3] = q[3];
+    } else if (k < K) {  // one lane
+        v[0] = xr[k];
+        if (k + 1 < K) v[1] = xr[k + 1];
+        if (k + 2 < K) v[2] = xr[k + 2];
     }
 }
 
-// ---- rows layout, FP4 codes ------------------------------------------------
-// As above with two codes per byte.  A step covers 512 elements: every lane loads
-// elements 4l .. 4l+3 of the first and of the second 256 (two fully coalesced 1 KiB
-// reads per wave) and packs each quad into 16 bits.  A dword of output is 8 consecutive
-// elements, i.e. the quads of lanes 2j and 2j+1: the even lane assembles the dword of
-// the first half, the odd lane that of the second half, after one exchange with its
-// neighbour, so every lane stores one dword per step.  Kpad % 128 == 0.
-template <bool VEC4>
-__global__ __launch_bounds__(256) void k_pack_rows_fp4(PackArgs a)
+// The row sum from the waves' shares: every wave of a row (WPR > 1: the block) calls it.
+template <int WPR>
+__device__ __forceinline__ void store_row_sum(int32_t* sum_t, int64_t row, int sum, int sub, int lane)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if constexpr (WPR == 1) {
+        if (lane == 0) sum_t[row] = sum;
+    } else {
+        __shared__ int part[WPR];
+        if (lane == 0) part[sub] = sum;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            sum = 0;
+#pragma unroll
+            for (int w = 0; w < WPR; ++w) sum += part[w];
+            sum_t[row] = sum;
+        }
+    }
+}
+
+// Codes.  A step covers 512 elements: every lane loads elements 4l .. 4l+3 of the first and of the second 256
+// (NP = 2 coalesced 1 KiB reads per wave; rows of up to 256 take one).  int8: a dword per quad.  FP4: 16 bits per quad; a dword of output is 8
+// consecutive elements, i.e. the quads of lanes 2j and 2j+1: the even lane assembles the dword of the first
+// half, the odd lane that of the second half, after one exchange with its neighbour.
+template <bool FP4, int WPR, int UN, int NP = 2>
+__global__ __launch_bounds__(256) void k_pack_rows(PackArgs a)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = wave % WPR;
+    const int64_t row = (int64_t)blockIdx.x * (4 / WPR) + wave / WPR;
     if (row >= a.rows) return;
     const float lo = thr(a.lo, row), hi = thr(a.hi, row);
     const float* xr = a.x + row * a.K;
-    uint8_t* cr = (uint8_t*)a.codes + row * (a.Kpad >> 1);
+    uint8_t* cr = (uint8_t*)a.codes + row * (FP4 ? a.Kpad >> 1 : a.Kpad);
     const bool odd = lane & 1;
+    const unsigned K = (unsigned)a.K, Kpad = (unsigned)a.Kpad;
+    constexpr unsigned STEP = 256 * NP;
     int sum = 0;
-    for (int64_t k0 = 0; k0 < a.Kpad; k0 += 512) {
-        uint32_t h[2];
+    for (unsigned k1 = sub * STEP * UN; k1 < Kpad; k1 += STEP * UN * WPR) {
+        float v[UN][NP][4];
 #pragma unroll
-        for (int part = 0; part < 2; ++part) {
-            const int64_t k = k0 + 256 * part + 4 * lane;
-            int t[4] = {0, 0, 0, 0};
-            if (VEC4) {
-                if (k < a.K) {  // K % 4 == 0: the whole quad is in range
-                    const float4 v = *(const float4*)(xr + k);
-                    t[0] = tern(v.x, lo, hi), t[1] = tern(v.y, lo, hi), t[2] = tern(v.z, lo, hi), t[3] = tern(v.w, lo, hi);
+        for (int u = 0; u < UN; ++u)
+#pragma unroll
+            for (int part = 0; part < NP; ++part) load_quad(xr, k1 + STEP * u + 256 * part, lane, K, v[u][part]);
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const unsigned k0 = k1 + STEP * u;
+            if (k0 >= Kpad) break;
+            uint32_t h[NP];
+#pragma unroll
+            for (int part = 0; part < NP; ++part) {
+                int t[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t[e] = tern(v[u][part][e], lo, hi), sum += t[e];
+                if (FP4) {
+                    h[part] = nib(t[0]) | (nib(t[1]) << 4) | (nib(t[2]) << 8) | (nib(t[3]) << 12);
+                } else {
+                    const unsigned k = k0 + 256 * part + 4 * lane;
+                    if (k < Kpad)
+                        *(uint32_t*)(cr + k) = (uint32_t)(t[0] & 0xff) | ((uint32_t)(t[1] & 0xff) << 8) |
+                                               ((uint32_t)(t[2] & 0xff) << 16) | ((uint32_t)(t[3] & 0xff) << 24);
                 }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (k + e < a.K) t[e] = tern(xr[k + e], lo, hi);
             }
-            sum += t[0] + t[1] + t[2] + t[3];
-            h[part] = nib(t[0]) | (nib(t[1]) << 4) | (nib(t[2]) << 8) | (nib(t[3]) << 12);
+            if (FP4) {
+                // even lane: needs the neighbour's first-half quad; odd lane: the neighbour's second-half quad
+                const uint32_t h1 = NP == 2 ? h[NP - 1] : 0;  // (one half: the odd lanes have nothing to store)
+                const uint32_t recv = (uint32_t)__shfl_xor((int)(odd ? h[0] : h1), 1, 64);
+                const uint32_t word = odd ? (recv | (h1 << 16)) : (h[0] | (recv << 16));
+                if (NP == 1 && odd) continue;
+                const unsigned kw = k0 + (odd ? 256 + 4 * (lane - 1) : 4 * lane);  // first element of the dword
+                if (kw < Kpad) *(uint32_t*)(cr + (kw >> 1)) = word;
+            }
         }
-        // even lane: needs the neighbour's first-half quad; odd lane: the neighbour's second-half quad
-        const uint32_t recv = (uint32_t)__shfl_xor((int)(odd ? h[0] : h[1]), 1, 64);
-        const uint32_t word = odd ? (recv | (h[1] << 16)) : (h[0] | (recv << 16));
-        const int64_t kw = k0 + (odd ? 256 + 4 * (lane - 1) : 4 * lane);  // first element of the dword
-        if (kw < a.Kpad) *(uint32_t*)(cr + (kw >> 1)) = word;
     }
-    if (a.sum_t) {
-        sum = wave_sum(sum);
-        if (lane == 0) a.sum_t[row] = sum;
-    }
+    if (a.sum_t) store_row_sum<WPR>(a.sum_t, row, wave_sum(sum), sub, lane);
 }
 
-// ---- rows layout, bit planes --------------------------------------------
-// One wavefront per row.  Lane l reads element 64*w + l, so one 64-wide ballot
-// of (x > hi) / (x < lo) *is* plane word w; the row sum is popcount(pos) -
-// popcount(neg) on the scalar unit.  Four words are produced per step and
-// written by lanes 0..3 as one 32-byte store.
+// Bit planes.  Lane l reads element 64*w + l, so one 64-wide ballot of (x > hi) / (x < lo) *is* plane word w; the
+// row sum is popcount(pos) - popcount(neg) on the scalar unit.  Eight words are produced per step and written by
+// lanes 0..7 as one 64-byte store.
+template <int WPR, int UN>
 __global__ __launch_bounds__(256) void k_pack_rows_planes(PackArgs a)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = wave % WPR;
+    const int64_t row = (int64_t)blockIdx.x * (4 / WPR) + wave / WPR;
     if (row >= a.rows) return;
     const float lo = thr(a.lo, row), hi = thr(a.hi, row);
     const float* xr = a.x + row * a.K;
@@ -144,32 +153,30 @@ __global__ __launch_bounds__(256) void k_pack_rows_planes(PackArgs a)
     uint64_t* mrow = (uint64_t*)a.codes + row * words;
     uint64_t* srow = (uint64_t*)a.codes + a.rows * words + row * words;
     int sum = 0;
-    for (int64_t w0 = 0; w0 < words; w0 += 4) {
-        float v[4];
-        bool ok[4];
+    for (int64_t w0 = sub * UN; w0 < words; w0 += UN * WPR) {
+        float v[UN];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < UN; ++i) {
             const int64_t k = (w0 + i) * 64 + lane;
-            ok[i] = k < a.K;
-            v[i] = ok[i] ? xr[k] : 0.0f;
+            v[i] = k < a.K ? xr[k] : __builtin_nanf("");
         }
         uint64_t mword = 0, sword = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint64_t pos = __ballot(ok[i] && v[i] > hi);
-            const uint64_t neg = __ballot(ok[i] && v[i] < lo);
+        for (int i = 0; i < UN; ++i) {
+            const uint64_t pos = __ballot(v[i] > hi);
+            const uint64_t neg = __ballot(v[i] < lo);
             sum += __popcll(pos) - __popcll(neg);
             if (lane == i) {
                 mword = pos | neg;
                 sword = pos;
             }
         }
-        if (lane < 4 && w0 + lane < words) {
+        if (lane < UN && w0 + lane < words) {
             mrow[w0 + lane] = mword;
             srow[w0 + lane] = sword;
         }
     }
-    if (a.sum_t && lane == 0) a.sum_t[row] = sum;
+    if (a.sum_t) store_row_sum<WPR>(a.sum_t, row, sum, sub, lane);
 }
 
 // ---- NCHW layout, int8 codes, channel-innermost output -------------------
@@ -583,32 +590,34 @@ __global__ __launch_bounds__(256) void k_pack_nchw_planes(PackArgs a)
 
 }  // namespace
 
-hipError_t launch_pack_rows_i8(const PackArgs& a, hipStream_t st)
+// Four waves per row while the rows are fewer than 8 waves per CU and a row has work for more than one; a row of
+// one step takes the form without room for more (16384 x 100, int8: 6.5 against 4.7 us).
+template <bool FP4>
+static hipError_t launch_pack_rows_codes(const PackArgs& a, hipStream_t st)
 {
-    const dim3 grid((unsigned)((a.rows + 3) / 4)), block(256);
-    const bool vec4 = (a.K % 4 == 0) && (((uintptr_t)a.x) % 16 == 0);
-    if (vec4)
-        hipLaunchKernelGGL(k_pack_rows_i8<true>, grid, block, 0, st, a);
+    const dim3 four((unsigned)a.rows), one((unsigned)((a.rows + 3) / 4)), block(256);
+    if (a.Kpad <= 256)
+        hipLaunchKernelGGL((k_pack_rows<FP4, 1, 1, 1>), one, block, 0, st, a);
+    else if (a.Kpad <= 512)
+        hipLaunchKernelGGL((k_pack_rows<FP4, 1, 1>), one, block, 0, st, a);
+    else if (a.rows < 2048)
+        hipLaunchKernelGGL((k_pack_rows<FP4, 4, 4>), four, block, 0, st, a);
     else
-        hipLaunchKernelGGL(k_pack_rows_i8<false>, grid, block, 0, st, a);
+        hipLaunchKernelGGL((k_pack_rows<FP4, 1, 2>), one, block, 0, st, a);
     return hipGetLastError();
 }
-
-hipError_t launch_pack_rows_fp4(const PackArgs& a, hipStream_t st)
-{
-    const dim3 grid((unsigned)((a.rows + 3) / 4)), block(256);
-    const bool vec4 = (a.K % 4 == 0) && (((uintptr_t)a.x) % 16 == 0);
-    if (vec4)
-        hipLaunchKernelGGL(k_pack_rows_fp4<true>, grid, block, 0, st, a);
-    else
-        hipLaunchKernelGGL(k_pack_rows_fp4<false>, grid, block, 0, st, a);
-    return hipGetLastError();
-}
+hipError_t launch_pack_rows_i8(const PackArgs& a, hipStream_t st) { return launch_pack_rows_codes<false>(a, st); }
+hipError_t launch_pack_rows_fp4(const PackArgs& a, hipStream_t st) { return launch_pack_rows_codes<true>(a, st); }
 
 hipError_t launch_pack_rows_planes(const PackArgs& a, hipStream_t st)
 {
-    const dim3 grid((unsigned)((a.rows + 3) / 4)), block(256);
-    hipLaunchKernelGGL(k_pack_rows_planes, grid, block, 0, st, a);
+    const dim3 four((unsigned)a.rows), one((unsigned)((a.rows + 3) / 4)), block(256);
+    if (a.Kpad <= 256)
+        hipLaunchKernelGGL((k_pack_rows_planes<1, 4>), one, block, 0, st, a);
+    else if (a.rows < 2048)
+        hipLaunchKernelGGL((k_pack_rows_planes<4, 8>), four, block, 0, st, a);
+    else
+        hipLaunchKernelGGL((k_pack_rows_planes<1, 8>), one, block, 0, st, a);
     return hipGetLastError();
 }
 

@@ -549,6 +549,37 @@ def test_small_grid_gemm(M, N, K, fmt):
         T.assert_y_close(got["y"].cpu().numpy(), ref["y"], "small grid gemm")
 
 
+@pytest.mark.parametrize("rows,K", [
+    (1, 1), (5, 130), (4, 256), (3, 257), (7, 511),          # rows of one step
+    (3, 2047), (2, 8193), (2, 20003), (2047, 515),           # four waves per row: one run and several
+    (2048, 515), (2049, 1025)])                              # one wave per row, more than one step
+def test_pack_rows_forms(rows, K):
+    """All code formats, from a base that is 4-byte aligned only, under per-row thresholds on one side of zero (the
+    padding is code 0 all the same)."""
+    _say("pack rows %d x %d" % (rows, K))
+    rng = np.random.default_rng(rows + K)
+    x = rng.standard_normal((rows, K)).astype(np.float32)
+    x[0, K // 2] = np.nan
+    lo = rng.uniform(0.1, 0.3, rows).astype(np.float32)
+    hi = lo + rng.uniform(0.0, 0.5, rows).astype(np.float32)
+    t = orc.ternarize(x, lo, hi)
+    buf = torch.empty(rows * K + 1, dtype=torch.float32, device="cuda:0")
+    xd = buf[1:].view(rows, K)
+    xd.copy_(torch.from_numpy(x))
+    for fmt in (B.RTN_CODE_I8, FP4, B.RTN_CODE_BITPLANE):
+        codes, sums = B.ternarize_pack(xd, T.thr_arg(lo), T.thr_arg(hi), fmt)
+        assert (sums.cpu().numpy().reshape(-1) == t.sum(1)).all()
+        if fmt == B.RTN_CODE_BITPLANE:
+            m, sg = T.planes_from_dev(codes)
+            em, es = orc.encode_planes(t, (K + 63) // 64)
+            assert (m == em).all() and (sg == es).all()
+        elif fmt == FP4:
+            assert (codes.cpu().numpy() == orc.encode_fp4(t)).all()
+        else:
+            c = codes.cpu().numpy()
+            assert (c[:, :K] == t).all() and (c[:, K:] == 0).all()
+
+
 @pytest.mark.parametrize("fmt", [B.RTN_CODE_I8, FP4])
 def test_gemm_output_of_128_mib(fmt):
     """The least output that is stored with the non-temporal hint, with ReLU and BN and without."""
