@@ -770,19 +770,34 @@ __global__ __launch_bounds__(256) void k_act_backward(ActBwdArgs p)
     }
 }
 
-__global__ __launch_bounds__(256) void k_sum_partials(const double* partials, int64_t nblocks, double* out)
+// (1024 threads, eight blocks' sums of each in flight: 3136 blocks in one round of loads)
+constexpr int kSumThreads = 1024;
+__global__ __launch_bounds__(kSumThreads) void k_sum_partials(const double* partials, int64_t nblocks, double* out)
 {
-    __shared__ double red[2][4];
+    constexpr int UN = 8, NW = kSumThreads / 64;
+    __shared__ double red[2][NW];
     const int tid = threadIdx.x;
     double sg = 0.0, sb = 0.0;
-    for (int64_t b = tid; b < nblocks; b += 256) sg += partials[2 * b], sb += partials[2 * b + 1];
+    for (int64_t b0 = tid; b0 < nblocks; b0 += kSumThreads * UN) {
+        double g[UN], b[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int64_t i = b0 + kSumThreads * u;
+            g[u] = i < nblocks ? partials[2 * i] : 0.0;
+            b[u] = i < nblocks ? partials[2 * i + 1] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) sg += g[u], sb += b[u];
+    }
     sg = wave_sum(sg);
     sb = wave_sum(sb);
     if ((tid & 63) == 0) red[0][tid >> 6] = sg, red[1][tid >> 6] = sb;
     __syncthreads();
-    if (tid == 0) {
-        out[0] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-        out[1] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+    if (tid < 2) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) s += red[tid][w];
+        out[tid] = s;
     }
 }
 
@@ -815,16 +830,25 @@ __global__ __launch_bounds__(256) void k_weight_backward(WeightBwdArgs p)
         return __fmul_rn(kw, dwbar);
     };
     if (VEC) {  // K % 4 == 0 and 16-byte aligned tensors: every filter starts on a 16-byte boundary
+        // the loads of up to UN steps (4608 weights: 5) in flight together: a step at a time, the time of a
+        // launch was the sum of their latencies
+        constexpr int UN = 5;
         const int64_t k4n = p.K >> 2;
-#pragma unroll 2
-        for (int64_t k4 = threadIdx.x; k4 < k4n; k4 += 256) {
-            const float4 wv = ((const float4*)w)[k4], gv = ((const float4*)g)[k4];
-            float4 d;
-            d.x = element(wv.x, gv.x);
-            d.y = element(wv.y, gv.y);
-            d.z = element(wv.z, gv.z);
-            d.w = element(wv.w, gv.w);
-            if (dw) ((float4*)dw)[k4] = d;
+        for (int64_t k0 = threadIdx.x; k0 < k4n; k0 += 256 * UN) {
+            float4 wv[UN], gv[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u)
+                if (k0 + 256 * u < k4n) wv[u] = ((const float4*)w)[k0 + 256 * u], gv[u] = ((const float4*)g)[k0 + 256 * u];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                if (k0 + 256 * u >= k4n) break;
+                float4 d;
+                d.x = element(wv[u].x, gv[u].x);
+                d.y = element(wv[u].y, gv[u].y);
+                d.z = element(wv[u].z, gv[u].z);
+                d.w = element(wv[u].w, gv[u].w);
+                if (dw) ((float4*)dw)[k0 + 256 * u] = d;
+            }
         }
     } else {
         for (int64_t k = threadIdx.x; k < p.K; k += 256) {
@@ -861,7 +885,7 @@ hipError_t launch_act_backward(const ActBwdArgs& p, hipStream_t st)
         hipLaunchKernelGGL(k_act_backward<true>, dim3((unsigned)nb), dim3(256), 0, st, p);
     else
         hipLaunchKernelGGL(k_act_backward<false>, dim3((unsigned)nb), dim3(256), 0, st, p);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, st, p.partials, nb, p.sums);
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kSumThreads), 0, st, p.partials, nb, p.sums);
     return hipGetLastError();
 }
 
