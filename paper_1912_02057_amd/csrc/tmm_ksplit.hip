@@ -14,6 +14,11 @@
 // 32 rows in consecutive lanes, so every lane of such a load touches a cache line of its own, where a direct load
 // takes 64 bytes of each of 16 rows.
 //
+// RUN (conv, stride 1, centred window): the input pixels of the tile are loaded into LDS once, for all waves and
+// taps, and only the weights go through the rings: the operand traffic L2 -> LDS, which bounds a block of many
+// K-steps, falls to about half.  int8, 7 images of 27 x 27, 96 channels, 256 filters, 5 x 5 (320 tiles of 64 x 64, 50
+// K-steps): k_tmm 19.1, without RUN 18.1, with it 15.3 us; no gain below some 18 K-steps, where its barrier counts.
+//
 // Parameters, thresholds and residual values are fetched before the K loop.  What is left of a launch: 3.1 us
 // (GEMM) to 3.7 us (conv) with one K-step -- launch, first load, meeting, store -- and from 250 tiles on the
 // operand traffic L2 -> LDS.  us, k_tmm 64 x 64 -> here (times of back-to-back launches):
@@ -31,15 +36,26 @@ namespace {
 struct KsplitParams {
     TmmParams t;
     FastDiv div_spt, div_kw;  // by the K-steps per tap and the window's width
+    FastDiv div_upr;          // RUN: by the 16-byte units of a pixel's LDS row
+    int runb;                 // RUN: LDS bytes of the pixel run, whole KiB
 };
 
-template <int TP, int TQ, int W, int NS, bool CONV, int TERN, int DT>
+// LDS bytes in front of the pixel sums: rings, pixel run and its zero bytes, or the accumulators over them
+__host__ __device__ inline int ksplit_run_main(int waves, int tiles, int ring, int runb)
+{
+    const int a = waves * ring + runb + 16, b = waves * tiles * 4096;
+    return a > b ? a : b;
+}
+
+template <int TP, int TQ, int W, int NS, bool CONV, int TERN, int DT, bool RUN>
 __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
 {
     constexpr int BP = 32 * TP, BQ = 32 * TQ, T = TP * TQ;
-    constexpr int LP = BP / 16, LQ = BQ / 16, DPS = LP + LQ;  // loads per step
-    constexpr int STAGE = (BP + BQ) * 64, RING = NS * STAGE;
-    static_assert(RING >= T * 4096, "the accumulators lie over the ring");
+    constexpr int LP = BP / 16, LQ = RUN ? 0 : BQ / 16, LQA = LQ ? LQ : 1, DPS = LP + LQ;  // loads per step
+    constexpr int STAGE = (BP + (RUN ? 0 : BQ)) * 64, RING = NS * STAGE;
+    constexpr int REDB = RUN ? T * 4096 : RING;  // bytes between the waves' accumulators
+    static_assert(RUN || RING >= T * 4096, "a wave's accumulators lie over its ring");
+    static_assert(CONV || !RUN, "a conv's window");
     static_assert(NS >= 2 && NS <= 4 && 3 * DPS < 64, "vmcnt range");
     constexpr int V = 16 * T / W;              // outputs per thread
     constexpr int QV = V < 4 ? V : 4;          // ... of which so many are consecutive rows
@@ -57,8 +73,11 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
     // bytes of a ternarizing epilogue lie over the accumulators
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
     AccS* red = (AccS*)smem;
-    AccS* red_sa = (AccS*)(smem + W * RING);
-    const int toff = W * RING + (CONV ? W * BQ * 4 : 0);
+    // (RUN: [W rings][pixel run][16 zero bytes], all under the accumulators)
+    const int main_bytes = RUN ? ksplit_run_main(W, T, RING, kp.runb) : W * RING;
+    AccS* red_sa = (AccS*)(smem + main_bytes);
+    const int toff = main_bytes + (CONV ? W * BQ * 4 : 0);
+    const int pitch = g.Cpad + 16, zoff = W * RING + kp.runb;
     const unsigned lds0 = (unsigned)(uintptr_t)smem;
 
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
@@ -76,9 +95,9 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
     const int lrow = lane >> 2, lchunk = (lane & 3) ^ swz(lrow);
     const int8_t* baseP = prm.P + (int64_t)p0 * prm.ldP;
     const int8_t* baseQ = CONV ? prm.Q : prm.Q + (int64_t)q0 * prm.ldQ;
-    unsigned offP[LP], offQ[LQ];
-    const int8_t* gQ[LQ];
-    int vmask[LQ];  // conv: bit kh = row tap in the image, bit (8 + kw) = column tap in the image
+    unsigned offP[LP], offQ[LQA];
+    const int8_t* gQ[LQA];
+    int vmask[LQA];  // conv: bit kh = row tap in the image, bit (8 + kw) = column tap in the image
 #pragma unroll
     for (int i = 0; i < LP; ++i) {
         int row = p0 + 16 * i + lrow;
@@ -116,6 +135,7 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
         kw = tap - kh * g.KW;
         koffQ = (int64_t)(kh * g.W + kw) * g.Cpad + cc * 64;
     }
+    int f_kh = kh, f_kw = kw, f_cc = cc;  // RUN: the same of the step being multiplied
     const int64_t rowskip = CONV ? (int64_t)(g.W - g.KW) * g.Cpad : 0;
     const unsigned ring = lds0 + (unsigned)(wave * RING);
     const int8_t* zero_page = (const int8_t*)g_zero16;
@@ -156,6 +176,33 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
             const int row = j * 32 + (lane & 31);
             fragQ[j][ks] = BP * 64 + row * 64 + (((ks * 2 + half) ^ swz(row)) << 4);
         }
+    }
+    // RUN: stride 1 and a centred window, so output pixel m reads input pixel m + (kh - pad) W + (kw - pad) of the
+    // same flattened index space: the tile's inputs are one run of pixels, loaded once, and a tap is a row offset.
+    // An LDS row is the pixel's codes and 16 bytes more: an odd number of 16-byte units, so that 16 consecutive
+    // rows lie in different banks whatever the channels.
+    unsigned vrun[TQ];  // as vmask, for this lane's pixel of fragment j
+#pragma unroll
+    for (int j = 0; j < TQ; ++j) {
+        vrun[j] = 0;
+        if (RUN) {
+            int m = q0 + j * 32 + (lane & 31);
+            m = m < prm.RQ ? m : prm.RQ - 1;
+            const int nb = (int)fastdiv((uint32_t)m, g.div_ohw), pix = m - nb * ohw;
+            const int oh = (int)fastdiv((uint32_t)pix, g.div_ow), ow = pix - oh * g.OW;
+            for (int k = 0; k < g.KH; ++k) vrun[j] |= (unsigned)((unsigned)(oh + k - g.pad) < (unsigned)g.H) << k;
+            for (int k = 0; k < g.KW; ++k) vrun[j] |= (unsigned)((unsigned)(ow + k - g.pad) < (unsigned)g.W) << (8 + k);
+        }
+    }
+    if (RUN) {
+        const int total_px = g.Nb * g.H * g.W, first_px = q0 - g.pad * (g.W + 1), upr = pitch >> 4;
+        for (int u = wave; u < kp.runb >> 10; u += W) {
+            const int lin = u * 64 + lane, row = (int)fastdiv((uint32_t)lin, kp.div_upr), c = lin - row * upr;
+            int px = first_px + row;
+            px = px < 0 ? 0 : (px < total_px ? px : total_px - 1);  // past the tensor: only taps outside an image point there
+            dma16(c < upr - 1 ? prm.Q + (int64_t)px * g.Cpad + c * 16 : zero_page, lds0 + (unsigned)(W * RING + u * 1024));
+        }
+        if (tid == 0) *(uint4*)(smem + zoff) = make_uint4(0, 0, 0, 0);
     }
     AccV acc[TP][TQ];
     v4f sa4[TQ];
@@ -282,6 +329,10 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
     }
 
     // ---- this wave's share of K ----------------------------------------------------------------------
+    if (RUN) {  // everybody's share of the pixel run
+        wait_vm<0>();
+        __syncthreads();
+    }
     int slot = 0;
     for (int s = 0; s < n; ++s) {
         wait_groups<DPS>(n - 1 - s < NS - 1 ? n - 1 - s : NS - 1);
@@ -292,7 +343,19 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
 #pragma unroll
             for (int i = 0; i < TP; ++i) fa[ks][i] = *(const v4i*)(st + fragP[i][ks]);
 #pragma unroll
-            for (int j = 0; j < TQ; ++j) fb[ks][j] = *(const v4i*)(st + fragQ[j][ks]);
+            for (int j = 0; j < TQ; ++j) {
+                if constexpr (RUN) {
+                    const int row = j * 32 + (lane & 31) + f_kh * g.W + f_kw;
+                    const bool ok = ((vrun[j] >> f_kh) & (vrun[j] >> (8 + f_kw)) & 1) != 0;
+                    fb[ks][j] = *(const v4i*)(smem + (ok ? W * RING + row * pitch + f_cc * 64 + (ks * 2 + half) * 16 : zoff));
+                } else {
+                    fb[ks][j] = *(const v4i*)(st + fragQ[j][ks]);
+                }
+            }
+        }
+        if (RUN && ++f_cc == spt) {
+            f_cc = 0;
+            if (++f_kw == g.KW) f_kw = 0, ++f_kh;
         }
         if (s + NS < n) {
             wait_lgkm0();
@@ -303,6 +366,7 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
         slot = slot + 1 == NS ? 0 : slot + 1;
     }
     wait_lgkm0();
+    if (RUN) __syncthreads();  // the accumulators go over everybody's ring and the run
 
     // ---- the shares meet -------------------------------------------------------------------------------
 #pragma unroll
@@ -313,7 +377,7 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
             for (int r4 = 0; r4 < 4; ++r4) {
                 typedef AccS V4 __attribute__((ext_vector_type(4)));
                 const V4 v = {acc[i][j][4 * r4], acc[i][j][4 * r4 + 1], acc[i][j][4 * r4 + 2], acc[i][j][4 * r4 + 3]};
-                *(V4*)(red + wave * (RING / 4) + (((i * TQ + j) * 4 + r4) * 64 + lane) * 4) = v;
+                *(V4*)(red + wave * (REDB / 4) + (((i * TQ + j) * 4 + r4) * 64 + lane) * 4) = v;
             }
     if (CONV && want_ep) {
 #pragma unroll
@@ -340,9 +404,9 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             if constexpr (QV == 1) {
-                D[n] += src[w * (RING / 4)];
+                D[n] += src[w * (REDB / 4)];
             } else {
-                const AccQ v = *(const AccQ*)(src + w * (RING / 4));
+                const AccQ v = *(const AccQ*)(src + w * (REDB / 4));
 #pragma unroll
                 for (int e = 0; e < QV; ++e) D[n * QV + e] += v[e];
             }
@@ -442,14 +506,25 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
     }
 }
 
-template <int TP, int TQ, int W, int NS, bool CONV, int TERN, int DT>
+template <int TP, int TQ, int W, int NS, bool CONV, int TERN, int DT, bool RUN = false>
 hipError_t launch(KsplitParams& kp, hipStream_t st)
 {
     TmmParams& prm = kp.t;
-    const size_t smem = (size_t)W * NS * (TP + TQ) * 2048 +
-                        (CONV ? (size_t)W * TQ * 128 + (((size_t)conv_table_bytes(32 * TP, prm.g) + 1023) & ~(size_t)1023) : 0);
-    if (smem > (size_t)kMaxLds) return hipErrorInvalidValue;
-    auto kern = k_ksplit<TP, TQ, W, NS, CONV, TERN, DT>;
+    constexpr int ring = NS * (TP + (RUN ? 0 : TQ)) * 2048;
+    size_t smem = (size_t)W * ring;
+    if (RUN) {
+        const ConvGeom& g = prm.g;
+        const int upr = g.Cpad / 16 + 1;
+        const int64_t rows = 32 * TQ + 2 * (int64_t)g.pad * (g.W + 1), bytes = (rows * upr * 16 + 1023) & ~(int64_t)1023;
+        if (g.stride != 1 || g.KH != 2 * g.pad + 1 || g.KW != 2 * g.pad + 1 || bytes > kMaxLds) return hipErrorInvalidValue;
+        kp.runb = (int)bytes;
+        kp.div_upr = make_fastdiv((uint32_t)upr);
+        smem = (size_t)ksplit_run_main(W, TP * TQ, ring, kp.runb);
+    }
+    if (CONV) smem += (size_t)W * TQ * 128 + (((size_t)conv_table_bytes(32 * TP, prm.g) + 1023) & ~(size_t)1023);
+    // (the four-wave form with a pixel run is for grids of more than a block per CU: two have to fit)
+    if (smem > (size_t)(RUN && W == 4 ? kMaxLds / 2 : kMaxLds)) return hipErrorInvalidValue;
+    auto kern = k_ksplit<TP, TQ, W, NS, CONV, TERN, DT, RUN>;
     static bool attr_done = false;
     if (!attr_done) {
         const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
@@ -471,8 +546,17 @@ hipError_t launch_form(int form, KsplitParams& kp, hipStream_t st)
         case 2: return launch<2, 1, 8, 3, CONV, TERN, DT>(kp, st);
         case 3: return launch<2, 2, 8, 2, CONV, TERN, DT>(kp, st);
         case 4: return launch<2, 2, 4, 2, CONV, TERN, DT>(kp, st);
-        default: return hipErrorInvalidValue;
+        default: break;
     }
+    if constexpr (CONV) {
+        switch (form) {
+            case 5: return launch<2, 1, 8, 2, CONV, TERN, DT, true>(kp, st);
+            case 6: return launch<2, 2, 8, 2, CONV, TERN, DT, true>(kp, st);
+            case 7: return launch<2, 2, 4, 2, CONV, TERN, DT, true>(kp, st);
+            default: break;
+        }
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace

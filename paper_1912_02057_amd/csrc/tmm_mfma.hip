@@ -122,15 +122,31 @@ int pick_tile(int64_t rp, int64_t rq, int nk, bool conv)
 //   tiles <= 1024: GEMM 0.89 (0.85) at 17-32 K-steps, not taken; conv 1.03 (0.97) at 17-32, not taken, 1.41 (1.34)
 //                  at 33-64, 1.70 (1.45) beyond
 //   64 x 64 tiles in 257 .. 512: conv 1.00 at 33-64 K-steps, not taken, 1.3 (1.03) beyond
+// A conv of 257 to 512 tiles takes 64 x 32 ones, if they are no more than 256, from 9 K-steps on: 1.04 to 1.14 times
+// as fast at 9 to 36, 1.1 to 1.2 beyond.
 int pick_ksplit(int64_t rp, int64_t rq, int nk, bool conv)
 {
     if (nblocks(rp, rq, 32, 32) <= 512) {
         if (nk <= 3) return 0;
-        return nk > 32 && nblocks(rp, rq, 32, 32) > 256 && nblocks(rp, rq, 64, 32) <= 256 ? 2 : 1;
+        return nk > (conv ? 8 : 32) && nblocks(rp, rq, 32, 32) > 256 && nblocks(rp, rq, 64, 32) <= 256 ? 2 : 1;
     }
     if (!conv) return -1;
     if (nk > 32 && nblocks(rp, rq, 64, 64) <= 256) return 3;
     return nk > 64 && nblocks(rp, rq, 64, 64) <= 512 ? 4 : -1;
+}
+
+// The same for convs whose pixels are one run of the input; these forms are tried first (launch_ksplit refuses a run
+// that does not fit).  Against the best of the others, 121 random convs with windows 3 and 5: 64 x 32 tiles 1.05 to
+// 1.15 times as fast beyond 64 K-steps (0.95 to 1.04 below); 64 x 64 tiles, up to 256, 1.05 to 1.2 times from 18 to 25,
+// 1.05 to 1.15 beyond; up to 512 of them 1.1 to 1.25 at 36 to 50 (0.9 to 1.06 at 18 to 27) where two blocks fit a
+// CU, 0.7 to 0.85 where they do not.
+int pick_ksplit_run(const ConvGeom& g, int64_t rq, int nk)
+{
+    if (g.stride != 1 || g.KH < 3 || g.KH != 2 * g.pad + 1 || g.KW != 2 * g.pad + 1) return -1;
+    if (nblocks(g.O, rq, 32, 32) <= 512)
+        return nk > 64 && nblocks(g.O, rq, 32, 32) > 256 && nblocks(g.O, rq, 64, 32) <= 256 ? 5 : -1;
+    if (nblocks(g.O, rq, 64, 64) <= 256) return nk >= 18 ? 6 : -1;
+    return nk > 32 && nblocks(g.O, rq, 64, 64) <= 512 ? 7 : -1;
 }
 
 }  // namespace
@@ -299,16 +315,17 @@ hipError_t launch_conv_mfma(const ConvArgs& a, hipStream_t st)
         const int64_t out_bytes = (int64_t)g.Nb * g.O * g.OH * g.OW * 4 * ((a.acc ? 1 : 0) + (a.y ? 1 : 0));
         prm.nt_out = out_bytes > (int64_t)128 << 20;
     }
-    const int form = g_forced_tile >= 0 ? -1 : pick_ksplit(g.O, prm.RQ, prm.nk, true);
-    if (form >= 0) {
+    const int forms[2] = {pick_ksplit_run(g, prm.RQ, prm.nk), pick_ksplit(g.O, prm.RQ, prm.nk, true)};
+    for (int i = 0; i < 2 && g_forced_tile < 0; ++i) {
+        if (forms[i] < 0) continue;
         hipError_t e;
         if (!a.codes)
-            e = a.fp4 ? launch_ksplit<true, 0, 2>(form, prm, st) : launch_ksplit<true, 0, 0>(form, prm, st);
+            e = a.fp4 ? launch_ksplit<true, 0, 2>(forms[i], prm, st) : launch_ksplit<true, 0, 0>(forms[i], prm, st);
         else if (a.res != nullptr || a.y != nullptr || a.relu_out)
-            e = a.fp4 ? launch_ksplit<true, 2, 2>(form, prm, st) : launch_ksplit<true, 2, 0>(form, prm, st);
+            e = a.fp4 ? launch_ksplit<true, 2, 2>(forms[i], prm, st) : launch_ksplit<true, 2, 0>(forms[i], prm, st);
         else
-            e = a.fp4 ? launch_ksplit<true, 1, 2>(form, prm, st) : launch_ksplit<true, 1, 0>(form, prm, st);
-        if (e != hipErrorInvalidValue) return e;  // (the table of a large pad can exceed the LDS)
+            e = a.fp4 ? launch_ksplit<true, 1, 2>(forms[i], prm, st) : launch_ksplit<true, 1, 0>(forms[i], prm, st);
+        if (e != hipErrorInvalidValue) return e;  // (a long pixel run or the table of a large pad can exceed the LDS)
     }
     int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(g.O, prm.RQ, prm.nk, true);
     // a 64-filter layer with a centred stride-1 window: the variant that keeps the

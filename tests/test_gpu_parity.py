@@ -597,7 +597,11 @@ KSPLIT_CONVS = [  # C, H, W, O, k, stride, pad, batch
     (130, 7, 7, 70, 3, 1, 1, 1),      # ragged everywhere
     (200, 6, 9, 100, 5, 1, 2, 1),     # 81 classes' table, 50+ K-steps on 8 waves
     (300, 13, 13, 300, 3, 1, 1, 6),   # 320 tiles of 32 x 32, more than 256 blocks with three K-steps per tap (int8: 45)
-    (600, 28, 28, 70, 3, 1, 1, 7),    # 64 x 64 tiles, eight waves
+    (600, 28, 28, 70, 3, 1, 1, 7),    # 64 x 64 tiles, eight waves, with the tile's pixel run in LDS
+    (300, 55, 57, 70, 3, 2, 1, 7),    # ... and without
+    (1000, 9, 9, 300, 3, 1, 1, 12),   # 64 x 32 tiles with the pixel run
+    (96, 27, 26, 130, 5, 1, 2, 14),   # 64 x 64 tiles, four waves, with the pixel run (int8)
+    (130, 27, 26, 130, 5, 1, 2, 14),  # ... (FP4)
     (700, 28, 31, 70, 5, 1, 2, 10),   # ... and four: 272 blocks
 ]
 
