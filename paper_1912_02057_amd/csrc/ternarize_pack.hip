@@ -8,6 +8,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "choice.h"
 #include "rtn_kernels.h"
 
 namespace rtn {
@@ -38,13 +39,14 @@ __device__ __forceinline__ int wave_sum(int v)
 
 // ---- rows layout -----------------------------------------------------------
 // WPR waves per row: 1, or the 4 of a block where the rows alone would leave most of the chip without a wave.
-// A wave that waits for each step's loads before the next is bound by their latency, so it asks for up to 8 quads
-// (codes) or 8 words' worth (planes) of its row at a time, and the waves of a row take turns in runs of that size.  Quads are
-// loaded as 16 bytes at any K and row address: a global load of several dwords needs 4-byte alignment only.
+// A wave that waits for each step's loads before the next is bound by their latency, so it asks for up to 4 quads
+// (codes) or 8 words' worth (planes) of its row at a time, and the waves of a row take turns in runs of that size
+// (choice.h).  Quads are loaded as 16 bytes at any K and row address: a global load of several dwords needs 4-byte
+// alignment only.
 //   us, before (one wave per row, one step's loads in flight; K % 4 != 0: 4-byte loads) -> now:
-//     int8, 1000 x 2187  7.1 -> 4.2      FP4, 16 x 8192  10.6 -> 3.8     FP4, 4096 x 4096  14.3 -> 14.2
+//     int8, 1000 x 2187  10.4 -> 4.4     FP4, 16 x 8192  10.7 -> 3.9     FP4, 4096 x 4096  14.3 -> 14.2
 //     int8, 4096 x 4095  25.4 -> 15.2    FP4, 16384 x 8191  182 -> 120 (5.0 TB/s), 16384 x 8192  127 -> 121
-//     planes, 16 x 8192  16.0 -> 4.8, 4096 x 4096  16.8 -> 14.2
+//     planes, 16 x 8192  15.9 -> 4.9, 4096 x 4096  16.8 -> 14.2
 // elements k .. k + 3 of a row, k = k0 + 4 lane; NaN, whose code is 0, past its end
 __device__ __forceinline__ void load_quad(const float* xr, unsigned k0, unsigned lane, unsigned K, float (&v)[4])
 {
@@ -590,35 +592,42 @@ __global__ __launch_bounds__(256) void k_pack_nchw_planes(PackArgs a)
 
 }  // namespace
 
-// Four waves per row while the rows are fewer than 8 waves per CU and a row has work for more than one; a row of
-// one step takes the form without room for more (16384 x 100, int8: 6.5 against 4.7 us).
+// pack_rows_form() says which form
 template <bool FP4>
 static hipError_t launch_pack_rows_codes(const PackArgs& a, hipStream_t st)
 {
-    const dim3 four((unsigned)a.rows), one((unsigned)((a.rows + 3) / 4)), block(256);
-    if (a.Kpad <= 256)
-        hipLaunchKernelGGL((k_pack_rows<FP4, 1, 1, 1>), one, block, 0, st, a);
-    else if (a.Kpad <= 512)
-        hipLaunchKernelGGL((k_pack_rows<FP4, 1, 1>), one, block, 0, st, a);
-    else if (a.rows < 2048)
-        hipLaunchKernelGGL((k_pack_rows<FP4, 4, 4>), four, block, 0, st, a);
-    else
-        hipLaunchKernelGGL((k_pack_rows<FP4, 1, 2>), one, block, 0, st, a);
-    return hipGetLastError();
+    const PackRowsForm f = pack_rows_form(a.rows, a.Kpad);
+    auto go = [&](auto W, auto U, auto P) {
+        constexpr int WPR = decltype(W)::value, UN = decltype(U)::value, NP = decltype(P)::value;
+        if (f.waves != WPR || f.steps != UN || f.step != 256 * NP) return false;
+        hipLaunchKernelGGL((k_pack_rows<FP4, WPR, UN, NP>), dim3((unsigned)((a.rows * WPR + 3) / 4)), dim3(256), 0, st, a);
+        return true;
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I4 = std::integral_constant<int, 4>;
+    if (go(I1{}, I1{}, I1{}) || go(I1{}, I1{}, I2{}) || go(I1{}, I2{}, I1{}) || go(I1{}, I2{}, I2{}) || go(I4{}, I1{}, I2{}) ||
+        go(I4{}, I2{}, I2{}))
+        return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 hipError_t launch_pack_rows_i8(const PackArgs& a, hipStream_t st) { return launch_pack_rows_codes<false>(a, st); }
 hipError_t launch_pack_rows_fp4(const PackArgs& a, hipStream_t st) { return launch_pack_rows_codes<true>(a, st); }
 
 hipError_t launch_pack_rows_planes(const PackArgs& a, hipStream_t st)
 {
-    const dim3 four((unsigned)a.rows), one((unsigned)((a.rows + 3) / 4)), block(256);
-    if (a.Kpad <= 256)
-        hipLaunchKernelGGL((k_pack_rows_planes<1, 4>), one, block, 0, st, a);
-    else if (a.rows < 2048)
-        hipLaunchKernelGGL((k_pack_rows_planes<4, 8>), four, block, 0, st, a);
-    else
-        hipLaunchKernelGGL((k_pack_rows_planes<1, 8>), one, block, 0, st, a);
-    return hipGetLastError();
+    const PackRowsForm f = pack_rows_planes_form(a.rows, a.Kpad);
+    auto go = [&](auto W, auto U) {
+        constexpr int WPR = decltype(W)::value, UN = decltype(U)::value;
+        if (f.waves != WPR || f.steps != UN) return false;
+        hipLaunchKernelGGL((k_pack_rows_planes<WPR, UN>), dim3((unsigned)((a.rows * WPR + 3) / 4)), dim3(256), 0, st, a);
+        return true;
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I4 = std::integral_constant<int, 4>;
+    using I8 = std::integral_constant<int, 8>;
+    if (go(I1{}, I4{}) || go(I1{}, I8{}) || go(I4{}, I4{}) || go(I4{}, I8{})) return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 template <bool FP4>

@@ -552,7 +552,8 @@ def test_small_grid_gemm(M, N, K, fmt):
 @pytest.mark.parametrize("rows,K", [
     (1, 1), (5, 130), (4, 256), (3, 257), (7, 511),          # rows of one step
     (3, 2047), (2, 8193), (2, 20003), (2047, 515),           # four waves per row: one run and several
-    (2048, 515), (2049, 1025)])                              # one wave per row, more than one step
+    (2048, 515), (2049, 1025),                               # one wave per row, more than one step
+    (9, 513), (2047, 1024), (2047, 1025), (5, 2048), (3, 2049), (2048, 1280), (2049, 1281)])  # both sides of each line
 def test_pack_rows_forms(rows, K):
     """All code formats, from a base that is 4-byte aligned only, under per-row thresholds on one side of zero (the
     padding is code 0 all the same)."""
