@@ -35,4 +35,25 @@ inline PackRowsForm pack_rows_planes_form(int64_t rows, int64_t Kpad)
     return {4, Kpad <= 2048 ? 4 : 8, 64};
 }
 
+// Does a GEMM store y [M][N] with the non-temporal hint?  A burst of stores that the memory-side cache (256 MiB) absorbs
+// and writes back later slows the K loops of the tiles behind it, and hinted ones do not.  But a hinted store of a
+// part of a line goes to memory as it is, and the next kernel finds nothing in the cache.  us, plain -> hinted, two
+// inputs and outputs in turn; pack + GEMM, and the same with a pack of y behind it:
+//   FP4, 16384 x 8192 x 2048 (512 MiB)  271 -> 239    396 -> 365    16384 x 4096 x 2048 (256)  152 -> 117    197 -> 186
+//   int8, 16384 x 8192 x 4096           590 -> 557    712 -> 687    16384 x 2048 x 4096 (128)  199 -> 176    223 -> 216
+// Up to 256 MiB not for fewer than 8 K-steps, where no K loop is worth the reader's loss:
+//   FP4, 8192 x 4096 x 256 (128)         38 ->  42     64 ->  73    8192 x 8192 x 512 (256)     98 ->  99    140 -> 160
+//   int8, 8192 x 4096 x 256              40 ->  45     70 ->  77    8192 x 6144 x 256 (192)     58 ->  53     99 -> 103
+// and only for rows of whole 128-byte lines; beyond, of whole 64-byte halves:
+//   FP4, 12000 x 3000 x 2048 (137)      106 -> 112    132 -> 150    12000 x 2992 x 2048 (137)  102 -> 102    131 -> 137
+//   FP4, 16384 x 8191 x 2048 (512)      300 -> 326    429 -> 457    16384 x 8176 x 2048 (511)  298 -> 239    429 -> 396
+//   int8, 16384 x 8191 x 512            227 -> 273    375 -> 397    16384 x 8188 x 2048 (511)  299 -> 248    429 -> 441
+inline bool gemm_nt_hint(int64_t M, int64_t N, uintptr_t y, int nk)
+{
+    const int64_t bytes = M * N * 4, mib = (int64_t)1 << 20;
+    if (bytes < 128 * mib || (bytes <= 256 * mib && nk < 8)) return false;
+    const int64_t line = bytes <= 256 * mib ? 128 : 64;
+    return N * 4 % line == 0 && (int64_t)(y % (uintptr_t)line) == 0;
+}
+
 }  // namespace rtn

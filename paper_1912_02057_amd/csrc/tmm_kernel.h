@@ -228,7 +228,7 @@ __device__ __forceinline__ bool block_tile(const TmmParams& prm, int& tileP, int
 // output instead of 6 and fewer registers -- picked once per block.
 // NT: y is stored with the non-temporal hint.  The GEMM's tiles finish together, and a burst that the memory-side
 // cache holds is absorbed faster without it (and is there for the next kernel); a larger one is written back while
-// the next tiles are multiplied and takes 1244 -> 1480 cycles per K-step from them (launch_gemm_mfma decides).
+// the next tiles are multiplied and takes 1244 -> 1480 cycles per K-step from them (gemm_nt_hint() decides).
 // ABREAST: interior tiles with y alone take one operation at a time over four outputs and more.  fp64 operations
 // of one wave that depend on each other issue every 10 cycles, independent ones every 5 (a conversion 8), and a tile
 // of 256 x 256 leaves a SIMD one wave: its 256 outputs per lane take 9.5 us so, 14.5 us one after the other; the

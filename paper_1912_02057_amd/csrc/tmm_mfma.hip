@@ -4,6 +4,7 @@
 // weight copy.  The contraction kernel itself is in tmm_kernel.h.
 #include <cstdlib>
 
+#include "choice.h"
 #include "tmm_kernel.h"
 
 namespace rtn {
@@ -177,11 +178,7 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t st)
     prm.acc = a.acc;
     prm.y = a.y;
     prm.ep = a.ep;
-    // Outputs of 128 MiB and more take the non-temporal hint, us with the pack, without -> with it (two inputs and
-    // outputs in turn): FP4, 16384 x 8192 x 2048 (512 MiB) 270 -> 242, 8192 x 8192 x 4096 (256) 205 -> 189,
-    // 16384 x 2048 x 4096 (128) 146 -> 129; int8, 16384 x 4096 x 4096 (256) 332 -> 301, 8192 x 8192 x 1000 130 -> 130.
-    // 4096 x 4096 x 4096 (64) 54 -> 52 is left plain: the kernel that reads such an output next finds it in the cache.
-    prm.nt_out = a.y && a.M * a.N * 4 >= (int64_t)128 << 20;
+    prm.nt_out = a.y && gemm_nt_hint(a.M, a.N, (uintptr_t)a.y, prm.nk);
     const int form = g_forced_tile >= 0 ? -1 : pick_ksplit(a.M, a.N, prm.nk, false);
     if (form >= 0) return a.fp4 ? launch_ksplit<false, 0, 2>(form, prm, st) : launch_ksplit<false, 0, 0>(form, prm, st);
     const int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(a.M, a.N, prm.nk, false);

@@ -14,6 +14,7 @@ extern "C" void pack_form(int planes, int64_t rows, int64_t Kpad, int *out)
     const rtn::PackRowsForm f = planes ? rtn::pack_rows_planes_form(rows, Kpad) : rtn::pack_rows_form(rows, Kpad);
     out[0] = f.waves, out[1] = f.steps, out[2] = f.step;
 }
+extern "C" int nt_hint(int64_t M, int64_t N, uintptr_t y, int nk) { return rtn::gemm_nt_hint(M, N, y, nk); }
 """
 
 
@@ -25,6 +26,7 @@ def L(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + CSRC, str(d / "shim.cpp"), "-o", so], check=True)
     lib = C.CDLL(so)
     lib.pack_form.argtypes = [C.c_int, C.c_int64, C.c_int64, C.c_void_p]
+    lib.nt_hint.argtypes = [C.c_int64, C.c_int64, C.c_size_t, C.c_int]
     return lib
 
 
@@ -38,3 +40,18 @@ def test_row_pack_waves_have_work(L, planes):
             waves, turn = out[0], out[1] * out[2]
             assert waves in (1, 4) and turn > 0
             assert waves == 1 or (waves - 2) * turn < Kpad, (rows, Kpad, list(out))
+
+
+def test_gemm_store_hint(L):
+    """Only whole lines are hinted, and outputs that the memory-side cache holds only behind a K loop."""
+    base = 1 << 30
+    assert L.nt_hint(8192, 4096, base, 8) and L.nt_hint(16384, 8192, base, 1) and L.nt_hint(16384, 8176, base, 64)
+    assert not L.nt_hint(8192, 4096, base, 7) and not L.nt_hint(8191, 4096, base, 64)     # few K-steps; below 128 MiB
+    assert not L.nt_hint(16384, 4096, base, 7) and L.nt_hint(16385, 4096, base, 1)        # both sides of 256 MiB
+    for N in (3001, 3004, 3000, 2992):
+        assert not L.nt_hint(12000, N, base, 64)
+    for N in (8191, 8188, 8184):
+        assert not L.nt_hint(16384, N, base, 64)
+    for y in (4, 16, 32, 64):
+        assert not L.nt_hint(8192, 4096, base + y, 64)
+    assert L.nt_hint(16384, 8192, base + 64, 64) and not L.nt_hint(16384, 8192, base + 32, 64)

@@ -582,15 +582,32 @@ def test_pack_rows_forms(rows, K):
 
 
 @pytest.mark.parametrize("fmt", [B.RTN_CODE_I8, FP4])
-def test_gemm_output_of_128_mib(fmt):
-    """The least output that is stored with the non-temporal hint, with ReLU and BN and without."""
-    _say("gemm 8192 x 4096 x 70 fmt %d" % fmt)
-    case = wl.gemm_case(8192, 4096, 70, seed=5)
+@pytest.mark.parametrize("M,N,steps", [(8192, 4096, 8), (16401, 4112, 1)], ids=["128MiB", "257MiB_ragged"])
+def test_gemm_output_stored_with_hint(M, N, steps, fmt):
+    """The least outputs on both sides of 256 MiB that take the non-temporal hint, on whole tiles and on ragged ones in
+    both directions, alone and beside the accumulators, with ReLU and BN and without: sampled rows against the oracle,
+    all of it against the same call into an output 4 bytes past a line, which is stored plainly."""
+    K = steps * (128 if fmt == FP4 else 64) - 5
+    _say("gemm %d x %d x %d fmt %d" % (M, N, K, fmt))
+    case = wl.gemm_case(M, N, K, seed=5)
+    rows = _sample_rows(M, 24, 3)
+    sub = dict(case, M=len(rows), xa=case["xa"][rows], alpha_a=case["alpha_a"][rows], beta_a=case["beta_a"][rows])
     rng = np.random.default_rng(6)
-    bn = (rng.uniform(0.5, 1.5, 4096).astype(np.float32), rng.standard_normal(4096).astype(np.float32))
+    bn = (rng.uniform(0.5, 1.5, N).astype(np.float32), rng.standard_normal(N).astype(np.float32))
+    ca, sa = B.ternarize_pack(T.dev(case["xa"]), T.thr_arg(-case["delta_a"]), T.thr_arg(case["delta_a"]), fmt)
+    cw, sw = B.ternarize_pack(T.dev(case["xw"]), T.thr_arg(-case["delta_w"]), T.thr_arg(case["delta_w"]), fmt)
+    plain = torch.empty(M * N + 1, dtype=torch.float32, device=T.DEV)[1:].view(M, N)
     for kw in ({}, dict(relu=True, bn=bn)):
-        ref, got = T.oracle_gemm(case, **kw), T.hip_gemm(case, fmt=fmt, want_acc=False, **kw)
-        T.assert_y_close(got["y"].cpu().numpy(), ref["y"], "gemm 128 MiB")
+        ep = B.Epilogue(*[T.gran_arg(case[n]) for n in ("alpha_a", "beta_a", "alpha_w", "beta_w")], sa, sw, relu="bn" in kw,
+                        bn_scale=T.dev(bn[0]) if kw else None, bn_shift=T.dev(bn[1]) if kw else None)
+        ref = T.oracle_gemm(sub, **kw)
+        B.ternary_gemm(ca, cw, M, N, K, fmt=fmt, ep=ep, y_out=plain)
+        for want_acc in (False, True):
+            acc, y = B.ternary_gemm(ca, cw, M, N, K, fmt=fmt, ep=ep, want_acc=want_acc)
+            assert y.data_ptr() % 128 == 0 and torch.equal(y, plain)
+            T.assert_y_close(y[torch.from_numpy(rows).to(T.DEV)].cpu().numpy(), ref["y"], "hinted stores")
+            if want_acc:
+                assert (acc[torch.from_numpy(rows).to(T.DEV)].cpu().numpy() == ref["D"]).all()
 
 
 KSPLIT_CONVS = [  # C, H, W, O, k, stride, pad, batch
