@@ -56,4 +56,104 @@ inline bool gemm_nt_hint(int64_t M, int64_t N, uintptr_t y, int nk)
     return N * 4 % line == 0 && (int64_t)(y % (uintptr_t)line) == 0;
 }
 
+constexpr int64_t kMaxLds = 160 * 1024;
+
+inline int64_t nblocks(int64_t rp, int64_t rq, int bp, int bq)
+{
+    return ((rp + bp - 1) / bp) * ((rq + bq - 1) / bq);
+}
+
+// The forms of k_ksplit: tiles of 32 along P and Q, waves that share K, ring stages, pixel run in LDS (convs).
+struct KsplitForm {
+    int tp, tq, waves, stages;
+    bool run;
+};
+constexpr KsplitForm kKsplitForms[] = {{1, 1, 4, 4, false}, {1, 1, 8, 2, false}, {2, 1, 8, 3, false}, {2, 2, 8, 2, false},
+                                       {2, 2, 4, 2, false}, {2, 1, 8, 2, true},  {2, 2, 8, 2, true},  {2, 2, 4, 2, true}};
+constexpr int kKsplitGemmForms = 3, kNumKsplitForms = 8;
+
+// What the choice depends on.  GEMM: rows of P (M) and Q (N) and K-steps, the rest 0.  conv: P = filters, Q = output
+// pixels; a pixel's code bytes; rows of the epilogue table in LDS.
+struct KsplitShape {
+    int64_t rp, rq;
+    int nk, KH, KW, stride, pad, W, pixel_bytes, table_rows;
+};
+
+// LDS of the pixel run of a tile: rows of the pixel's codes and 16 bytes more, whole KiB
+inline int64_t ksplit_run_bytes(const KsplitForm& f, const KsplitShape& s)
+{
+    const int64_t rows = 32 * f.tq + 2 * (int64_t)s.pad * (s.W + 1);
+    return (rows * (s.pixel_bytes + 16) + 1023) & ~(int64_t)1023;
+}
+// rings, pixel run and its zero bytes, or the accumulators over them
+inline int64_t ksplit_main_bytes(const KsplitForm& f, const KsplitShape& s)
+{
+    const int64_t rings = f.waves * f.stages * (f.tp + (f.run ? 0 : f.tq)) * 2048;
+    if (!f.run) return rings;
+    const int64_t a = rings + ksplit_run_bytes(f, s) + 16, b = f.waves * f.tp * f.tq * 4096;
+    return a > b ? a : b;
+}
+// ... and a conv's pixel sums and epilogue table
+inline int64_t ksplit_lds_bytes(const KsplitForm& f, const KsplitShape& s)
+{
+    if (!s.KH) return ksplit_main_bytes(f, s);
+    return ksplit_main_bytes(f, s) + f.waves * f.tq * 128 + (((int64_t)s.table_rows * 32 * f.tp * 8 + 1023) & ~(int64_t)1023);
+}
+inline bool ksplit_fits(int form, const KsplitShape& s)
+{
+    const KsplitForm& f = kKsplitForms[form];
+    if (f.run && (s.stride != 1 || s.KH != 2 * s.pad + 1 || s.KW != 2 * s.pad + 1)) return false;
+    // (the four-wave form with a pixel run is for grids of more than a block per CU: two have to fit)
+    return ksplit_lds_bytes(f, s) <= (f.run && f.waves == 4 ? kMaxLds / 2 : kMaxLds);
+}
+
+// The form of k_ksplit for a grid too small for k_tmm, or -1.
+// K's share of the time decides between the forms, the number of 32 x 32 tiles whether to cut K at all; past
+// these lines the small tiles' operand traffic (L2 to LDS) costs more than the cut saves.
+// Time against k_tmm's, geometric mean (worst) over 336 random geometries (GEMM M 1 to 4096, N and K 64 to 8192; convs of 24 to 1024
+// channels and filters, 7 to 112 wide, windows 1, 3, 5, stride 1, 2, every epilogue; FP4 and int8):
+//   tiles <= 256:  GEMM 1.21 (1.11) at 1-3 K-steps, 1.37 at 4-8, 1.59 at 17-32, 1.90 at 33-64, 2.28 beyond
+//                  conv 1.19 (1.03) at 1-3 K-steps, 1.43 at 4-8, 1.95 at 17-32, 2.46 at 33-64, 2.98 beyond
+//   tiles <= 512:  GEMM 1.15 (1.04) at 1-3, 1.16 (1.11) at 17-32, 1.29 (1.20) beyond
+//                  conv 1.14 (1.06) at 1-3, 1.16 (1.07) at 9-16, 1.43 at 17-32, 1.7 to 2.1 beyond
+//   tiles <= 1024: GEMM 0.89 (0.85) at 17-32 K-steps, not taken; conv 1.03 (0.97) at 17-32, not taken, 1.41 (1.34)
+//                  at 33-64, 1.70 (1.45) beyond
+//   64 x 64 tiles in 257 .. 512: conv 1.00 at 33-64 K-steps, not taken, 1.3 (1.03) beyond
+// A conv of 257 to 512 tiles takes 64 x 32 ones, if they are no more than 256, from 9 K-steps on: 1.04 to 1.14 times
+// as fast at 9 to 36, 1.1 to 1.2 beyond.
+inline int pick_ksplit_plain(const KsplitShape& s)
+{
+    const bool conv = s.KH != 0;
+    const int64_t tiles = nblocks(s.rp, s.rq, 32, 32);
+    if (tiles <= 512) {
+        if (s.nk <= 3) return 0;
+        return s.nk > (conv ? 8 : 32) && tiles > 256 && nblocks(s.rp, s.rq, 64, 32) <= 256 ? 2 : 1;
+    }
+    if (!conv) return -1;
+    if (s.nk > 32 && nblocks(s.rp, s.rq, 64, 64) <= 256) return 3;
+    return s.nk > 64 && nblocks(s.rp, s.rq, 64, 64) <= 512 ? 4 : -1;
+}
+
+// The same for convs whose pixels are one run of the input; these forms come first.  Against the best of the others, 121 random convs with windows 3 and 5: 64 x 32 tiles 1.05 to
+// 1.15 times as fast beyond 64 K-steps (0.95 to 1.04 below); 64 x 64 tiles, up to 256, 1.05 to 1.2 times from 18 to 25,
+// 1.05 to 1.15 beyond; up to 512 of them 1.1 to 1.25 at 36 to 50 (0.9 to 1.06 at 18 to 27) where two blocks fit a
+// CU, 0.7 to 0.85 where they do not.
+inline int pick_ksplit_run(const KsplitShape& s)
+{
+    if (s.KH < 3) return -1;
+    if (nblocks(s.rp, s.rq, 32, 32) <= 512)
+        return s.nk > 64 && nblocks(s.rp, s.rq, 32, 32) > 256 && nblocks(s.rp, s.rq, 64, 32) <= 256 ? 5 : -1;
+    if (nblocks(s.rp, s.rq, 64, 64) <= 256) return s.nk >= 18 ? 6 : -1;
+    return s.nk > 32 && nblocks(s.rp, s.rq, 64, 64) <= 512 ? 7 : -1;
+}
+
+// The form that runs: with a pixel run where there is one and it fits (a long run or the table of a large pad can
+// exceed the LDS), else without; -1: k_tmm's tiles.
+inline int pick_ksplit(const KsplitShape& s)
+{
+    const int run = pick_ksplit_run(s), plain = pick_ksplit_plain(s);
+    if (run >= 0 && ksplit_fits(run, s)) return run;
+    return plain >= 0 && ksplit_fits(plain, s) ? plain : -1;
+}
+
 }  // namespace rtn

@@ -43,6 +43,7 @@
 #pragma once
 #include <type_traits>
 
+#include "choice.h"
 #include "epilogue_math.h"
 #include "rtn_kernels.h"
 
@@ -87,7 +88,8 @@ struct TmmParams {
 // (CONV, TERN, DT) triple per translation unit.
 template <bool CONV, int TERN, int DT>
 hipError_t tmm_launch_index_raw(int cfg, TmmParams& prm, hipStream_t st);
-// The form for small grids (tmm_ksplit.hip): `form` of its table.  hipErrorInvalidValue: it does not fit this problem.
+// The kernel for small grids (tmm_ksplit.hip) in form `form` of kKsplitForms, as pick_ksplit() chooses it.
+KsplitShape ksplit_shape(const TmmParams& prm, bool conv);
 template <bool CONV, int TERN, int DT>
 hipError_t launch_ksplit(int form, const TmmParams& prm, hipStream_t st);
 // The bf16-operand variants of the weight-only GEMM: 0 = 64x64, 1 = 128x128, 2 = 256x256.
@@ -1068,7 +1070,6 @@ inline int64_t table_bytes(int bp, bool conv, const ConvGeom& g)
 {
     return conv ? (int64_t)conv_table_bytes(bp, g) : (int64_t)3 * bp * 8;
 }
-constexpr int64_t kMaxLds = 160 * 1024;
 
 // Halo variant: stride 1, window centred on the output pixel, HC-byte pixel rows.
 inline bool halo_eligible(const TmmParams& prm, int hc)

@@ -38,14 +38,8 @@ struct KsplitParams {
     FastDiv div_spt, div_kw;  // by the K-steps per tap and the window's width
     FastDiv div_upr;          // RUN: by the 16-byte units of a pixel's LDS row
     int runb;                 // RUN: LDS bytes of the pixel run, whole KiB
+    int main;                 // LDS bytes in front of the pixel sums
 };
-
-// LDS bytes in front of the pixel sums: rings, pixel run and its zero bytes, or the accumulators over them
-__host__ __device__ inline int ksplit_run_main(int waves, int tiles, int ring, int runb)
-{
-    const int a = waves * ring + runb + 16, b = waves * tiles * 4096;
-    return a > b ? a : b;
-}
 
 template <int TP, int TQ, int W, int NS, bool CONV, int TERN, int DT, bool RUN>
 __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
@@ -74,7 +68,7 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
     AccS* red = (AccS*)smem;
     // (RUN: [W rings][pixel run][16 zero bytes], all under the accumulators)
-    const int main_bytes = RUN ? ksplit_run_main(W, T, RING, kp.runb) : W * RING;
+    const int main_bytes = RUN ? kp.main : W * RING;
     AccS* red_sa = (AccS*)(smem + main_bytes);
     const int toff = main_bytes + (CONV ? W * BQ * 4 : 0);
     const int pitch = g.Cpad + 16, zoff = W * RING + kp.runb;
@@ -506,53 +500,46 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
     }
 }
 
-template <int TP, int TQ, int W, int NS, bool CONV, int TERN, int DT, bool RUN = false>
-hipError_t launch(KsplitParams& kp, hipStream_t st)
+template <int FORM, bool CONV, int TERN, int DT>
+hipError_t launch(KsplitParams& kp, const KsplitShape& s, hipStream_t st)
 {
-    TmmParams& prm = kp.t;
-    constexpr int ring = NS * (TP + (RUN ? 0 : TQ)) * 2048;
-    size_t smem = (size_t)W * ring;
-    if (RUN) {
-        const ConvGeom& g = prm.g;
-        const int upr = g.Cpad / 16 + 1;
-        const int64_t rows = 32 * TQ + 2 * (int64_t)g.pad * (g.W + 1), bytes = (rows * upr * 16 + 1023) & ~(int64_t)1023;
-        if (g.stride != 1 || g.KH != 2 * g.pad + 1 || g.KW != 2 * g.pad + 1 || bytes > kMaxLds) return hipErrorInvalidValue;
-        kp.runb = (int)bytes;
-        kp.div_upr = make_fastdiv((uint32_t)upr);
-        smem = (size_t)ksplit_run_main(W, TP * TQ, ring, kp.runb);
+    constexpr KsplitForm f = kKsplitForms[FORM];
+    if (!ksplit_fits(FORM, s)) return hipErrorInvalidValue;
+    if (f.run) {
+        kp.runb = (int)ksplit_run_bytes(f, s);
+        kp.div_upr = make_fastdiv((uint32_t)(s.pixel_bytes / 16 + 1));
     }
-    if (CONV) smem += (size_t)W * TQ * 128 + (((size_t)conv_table_bytes(32 * TP, prm.g) + 1023) & ~(size_t)1023);
-    // (the four-wave form with a pixel run is for grids of more than a block per CU: two have to fit)
-    if (smem > (size_t)(RUN && W == 4 ? kMaxLds / 2 : kMaxLds)) return hipErrorInvalidValue;
-    auto kern = k_ksplit<TP, TQ, W, NS, CONV, TERN, DT, RUN>;
+    kp.main = (int)ksplit_main_bytes(f, s);
+    auto kern = k_ksplit<f.tp, f.tq, f.waves, f.stages, CONV, TERN, DT, f.run>;
     static bool attr_done = false;
     if (!attr_done) {
         const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
         if (e != hipSuccess) return e;
         attr_done = true;
     }
-    const unsigned grid = tile_grid(prm, 32 * TP, 32 * TQ);
+    const unsigned grid = tile_grid(kp.t, 32 * f.tp, 32 * f.tq);
     if (!grid) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * W), smem, st, kp);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * f.waves), (size_t)ksplit_lds_bytes(f, s), st, kp);
     return hipGetLastError();
 }
 
 template <bool CONV, int TERN, int DT>
-hipError_t launch_form(int form, KsplitParams& kp, hipStream_t st)
+hipError_t launch_form(int form, KsplitParams& kp, const KsplitShape& s, hipStream_t st)
 {
+    static_assert(kKsplitGemmForms == 3 && kNumKsplitForms == 8, "every form has a case");
     switch (form) {
-        case 0: return launch<1, 1, 4, 4, CONV, TERN, DT>(kp, st);
-        case 1: return launch<1, 1, 8, 2, CONV, TERN, DT>(kp, st);
-        case 2: return launch<2, 1, 8, 3, CONV, TERN, DT>(kp, st);
-        case 3: return launch<2, 2, 8, 2, CONV, TERN, DT>(kp, st);
-        case 4: return launch<2, 2, 4, 2, CONV, TERN, DT>(kp, st);
+        case 0: return launch<0, CONV, TERN, DT>(kp, s, st);
+        case 1: return launch<1, CONV, TERN, DT>(kp, s, st);
+        case 2: return launch<2, CONV, TERN, DT>(kp, s, st);
         default: break;
     }
     if constexpr (CONV) {
         switch (form) {
-            case 5: return launch<2, 1, 8, 2, CONV, TERN, DT, true>(kp, st);
-            case 6: return launch<2, 2, 8, 2, CONV, TERN, DT, true>(kp, st);
-            case 7: return launch<2, 2, 4, 2, CONV, TERN, DT, true>(kp, st);
+            case 3: return launch<3, CONV, TERN, DT>(kp, s, st);
+            case 4: return launch<4, CONV, TERN, DT>(kp, s, st);
+            case 5: return launch<5, CONV, TERN, DT>(kp, s, st);
+            case 6: return launch<6, CONV, TERN, DT>(kp, s, st);
+            case 7: return launch<7, CONV, TERN, DT>(kp, s, st);
             default: break;
         }
     }
@@ -561,6 +548,18 @@ hipError_t launch_form(int form, KsplitParams& kp, hipStream_t st)
 
 }  // namespace
 
+KsplitShape ksplit_shape(const TmmParams& prm, bool conv)
+{
+    KsplitShape s = {};
+    s.rp = prm.RP, s.rq = prm.RQ, s.nk = prm.nk;
+    if (conv) {
+        const ConvGeom& g = prm.g;
+        s.KH = g.KH, s.KW = g.KW, s.stride = g.stride, s.pad = g.pad, s.W = g.W, s.pixel_bytes = g.Cpad;
+        s.table_rows = 4 + conv_lds_classes(g);
+    }
+    return s;
+}
+
 template <bool CONV, int TERN, int DT>
 hipError_t launch_ksplit(int form, const TmmParams& prm, hipStream_t st)
 {
@@ -568,7 +567,7 @@ hipError_t launch_ksplit(int form, const TmmParams& prm, hipStream_t st)
     kp.t = prm;
     kp.div_spt = make_fastdiv((uint32_t)(CONV ? prm.g.Cpad >> 6 : 1));
     kp.div_kw = make_fastdiv((uint32_t)(CONV ? prm.g.KW : 1));
-    return launch_form<CONV, TERN, DT>(form, kp, st);
+    return launch_form<CONV, TERN, DT>(form, kp, ksplit_shape(prm, CONV), st);
 }
 template hipError_t launch_ksplit<false, 0, 0>(int, const TmmParams&, hipStream_t);
 template hipError_t launch_ksplit<false, 0, 2>(int, const TmmParams&, hipStream_t);

@@ -4,7 +4,6 @@
 // weight copy.  The contraction kernel itself is in tmm_kernel.h.
 #include <cstdlib>
 
-#include "choice.h"
 #include "tmm_kernel.h"
 
 namespace rtn {
@@ -59,11 +58,6 @@ __global__ __launch_bounds__(256) void k_conv_class_consts(const int32_t* tap, C
     cst[i] = v;
 }
 
-inline int64_t nblocks(int64_t rp, int64_t rq, int bp, int bq)
-{
-    return ((rp + bp - 1) / bp) * ((rq + bq - 1) / bq);
-}
-
 int g_forced_tile = -1;
 
 // A configuration whose LDS need (ring + the conv's table, which grows with the
@@ -111,45 +105,6 @@ int pick_tile(int64_t rp, int64_t rq, int nk, bool conv)
     return 0;
 }
 
-// The form of k_ksplit for a grid too small for k_tmm, or -1: the row of the table in tmm_ksplit.hip.
-// K's share of the time decides between the forms, the number of 32 x 32 tiles whether to cut K at all; past
-// these lines the small tiles' operand traffic (L2 to LDS) costs more than the cut saves.  Time against k_tmm's,
-// geometric mean (worst) over 336 random geometries (GEMM M 1 to 4096, N and K 64 to 8192; convs of 24 to 1024
-// channels and filters, 7 to 112 wide, windows 1, 3, 5, stride 1, 2, every epilogue; FP4 and int8):
-//   tiles <= 256:  GEMM 1.21 (1.11) at 1-3 K-steps, 1.37 at 4-8, 1.59 at 17-32, 1.90 at 33-64, 2.28 beyond
-//                  conv 1.19 (1.03) at 1-3 K-steps, 1.43 at 4-8, 1.95 at 17-32, 2.46 at 33-64, 2.98 beyond
-//   tiles <= 512:  GEMM 1.15 (1.04) at 1-3, 1.16 (1.11) at 17-32, 1.29 (1.20) beyond
-//                  conv 1.14 (1.06) at 1-3, 1.16 (1.07) at 9-16, 1.43 at 17-32, 1.7 to 2.1 beyond
-//   tiles <= 1024: GEMM 0.89 (0.85) at 17-32 K-steps, not taken; conv 1.03 (0.97) at 17-32, not taken, 1.41 (1.34)
-//                  at 33-64, 1.70 (1.45) beyond
-//   64 x 64 tiles in 257 .. 512: conv 1.00 at 33-64 K-steps, not taken, 1.3 (1.03) beyond
-// A conv of 257 to 512 tiles takes 64 x 32 ones, if they are no more than 256, from 9 K-steps on: 1.04 to 1.14 times
-// as fast at 9 to 36, 1.1 to 1.2 beyond.
-int pick_ksplit(int64_t rp, int64_t rq, int nk, bool conv)
-{
-    if (nblocks(rp, rq, 32, 32) <= 512) {
-        if (nk <= 3) return 0;
-        return nk > (conv ? 8 : 32) && nblocks(rp, rq, 32, 32) > 256 && nblocks(rp, rq, 64, 32) <= 256 ? 2 : 1;
-    }
-    if (!conv) return -1;
-    if (nk > 32 && nblocks(rp, rq, 64, 64) <= 256) return 3;
-    return nk > 64 && nblocks(rp, rq, 64, 64) <= 512 ? 4 : -1;
-}
-
-// The same for convs whose pixels are one run of the input; these forms are tried first (launch_ksplit refuses a run
-// that does not fit).  Against the best of the others, 121 random convs with windows 3 and 5: 64 x 32 tiles 1.05 to
-// 1.15 times as fast beyond 64 K-steps (0.95 to 1.04 below); 64 x 64 tiles, up to 256, 1.05 to 1.2 times from 18 to 25,
-// 1.05 to 1.15 beyond; up to 512 of them 1.1 to 1.25 at 36 to 50 (0.9 to 1.06 at 18 to 27) where two blocks fit a
-// CU, 0.7 to 0.85 where they do not.
-int pick_ksplit_run(const ConvGeom& g, int64_t rq, int nk)
-{
-    if (g.stride != 1 || g.KH < 3 || g.KH != 2 * g.pad + 1 || g.KW != 2 * g.pad + 1) return -1;
-    if (nblocks(g.O, rq, 32, 32) <= 512)
-        return nk > 64 && nblocks(g.O, rq, 32, 32) > 256 && nblocks(g.O, rq, 64, 32) <= 256 ? 5 : -1;
-    if (nblocks(g.O, rq, 64, 64) <= 256) return nk >= 18 ? 6 : -1;
-    return nk > 32 && nblocks(g.O, rq, 64, 64) <= 512 ? 7 : -1;
-}
-
 }  // namespace
 
 int tile_config_count() { return kNumTileConfigs; }
@@ -179,7 +134,7 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t st)
     prm.y = a.y;
     prm.ep = a.ep;
     prm.nt_out = a.y && gemm_nt_hint(a.M, a.N, (uintptr_t)a.y, prm.nk);
-    const int form = g_forced_tile >= 0 ? -1 : pick_ksplit(a.M, a.N, prm.nk, false);
+    const int form = g_forced_tile >= 0 ? -1 : pick_ksplit(ksplit_shape(prm, false));
     if (form >= 0) return a.fp4 ? launch_ksplit<false, 0, 2>(form, prm, st) : launch_ksplit<false, 0, 0>(form, prm, st);
     const int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(a.M, a.N, prm.nk, false);
     return a.fp4 ? launch_index<false, 0, 2>(cfg, prm, st) : launch_index<false>(cfg, prm, st);
@@ -312,17 +267,12 @@ hipError_t launch_conv_mfma(const ConvArgs& a, hipStream_t st)
         const int64_t out_bytes = (int64_t)g.Nb * g.O * g.OH * g.OW * 4 * ((a.acc ? 1 : 0) + (a.y ? 1 : 0));
         prm.nt_out = out_bytes > (int64_t)128 << 20;
     }
-    const int forms[2] = {pick_ksplit_run(g, prm.RQ, prm.nk), pick_ksplit(g.O, prm.RQ, prm.nk, true)};
-    for (int i = 0; i < 2 && g_forced_tile < 0; ++i) {
-        if (forms[i] < 0) continue;
-        hipError_t e;
-        if (!a.codes)
-            e = a.fp4 ? launch_ksplit<true, 0, 2>(forms[i], prm, st) : launch_ksplit<true, 0, 0>(forms[i], prm, st);
-        else if (a.res != nullptr || a.y != nullptr || a.relu_out)
-            e = a.fp4 ? launch_ksplit<true, 2, 2>(forms[i], prm, st) : launch_ksplit<true, 2, 0>(forms[i], prm, st);
-        else
-            e = a.fp4 ? launch_ksplit<true, 1, 2>(forms[i], prm, st) : launch_ksplit<true, 1, 0>(forms[i], prm, st);
-        if (e != hipErrorInvalidValue) return e;  // (a long pixel run or the table of a large pad can exceed the LDS)
+    const int form = g_forced_tile >= 0 ? -1 : pick_ksplit(ksplit_shape(prm, true));
+    if (form >= 0) {
+        if (!a.codes) return a.fp4 ? launch_ksplit<true, 0, 2>(form, prm, st) : launch_ksplit<true, 0, 0>(form, prm, st);
+        if (a.res != nullptr || a.y != nullptr || a.relu_out)
+            return a.fp4 ? launch_ksplit<true, 2, 2>(form, prm, st) : launch_ksplit<true, 2, 0>(form, prm, st);
+        return a.fp4 ? launch_ksplit<true, 1, 2>(form, prm, st) : launch_ksplit<true, 1, 0>(form, prm, st);
     }
     int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(g.O, prm.RQ, prm.nk, true);
     // a 64-filter layer with a centred stride-1 window: the variant that keeps the

@@ -5,6 +5,9 @@ import subprocess
 
 import pytest
 
+from paper_1912_02057_amd import binding as B
+from test_gpu_parity import KSPLIT_CONVS, KSPLIT_GEMMS
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1912_02057_amd", "csrc")
 
 SHIM = r"""
@@ -13,6 +16,11 @@ extern "C" void pack_form(int planes, int64_t rows, int64_t Kpad, int *out)
 {
     const rtn::PackRowsForm f = planes ? rtn::pack_rows_planes_form(rows, Kpad) : rtn::pack_rows_form(rows, Kpad);
     out[0] = f.waves, out[1] = f.steps, out[2] = f.step;
+}
+extern "C" int ksplit(const int64_t *v, int limit)
+{
+    const rtn::KsplitShape s = {v[0], v[1], (int)v[2], (int)v[3], (int)v[4], (int)v[5], (int)v[6], (int)v[7], (int)v[8], (int)v[9]};
+    return limit ? (int)rtn::ksplit_lds_bytes(rtn::kKsplitForms[limit - 1], s) : rtn::pick_ksplit(s);
 }
 extern "C" int nt_hint(int64_t M, int64_t N, uintptr_t y, int nk) { return rtn::gemm_nt_hint(M, N, y, nk); }
 """
@@ -26,6 +34,7 @@ def L(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + CSRC, str(d / "shim.cpp"), "-o", so], check=True)
     lib = C.CDLL(so)
     lib.pack_form.argtypes = [C.c_int, C.c_int64, C.c_int64, C.c_void_p]
+    lib.ksplit.argtypes = [C.c_void_p, C.c_int]
     lib.nt_hint.argtypes = [C.c_int64, C.c_int64, C.c_size_t, C.c_int]
     return lib
 
@@ -55,3 +64,27 @@ def test_gemm_store_hint(L):
     for y in (4, 16, 32, 64):
         assert not L.nt_hint(8192, 4096, base + y, 64)
     assert L.nt_hint(16384, 8192, base + 64, 64) and not L.nt_hint(16384, 8192, base + 32, 64)
+
+
+def _form(L, fmt, rp, rq, K=0, conv=None):
+    """The small-grid form of a GEMM (rp x rq x K) or of a conv (filters x pixels, conv = C, H, W, k, stride, pad)."""
+    codes = 128 if fmt == B.RTN_CODE_FP4 else 64        # of a K-step
+    v = [rp, rq, -(-K // codes)] + [0] * 7
+    if conv:
+        Cc, H, W, k, stride, pad = conv
+        axis = 2 * pad + 1 if min(H, W) >= k else (pad + 1) ** 2
+        v[2:] = [k * k * -(-Cc // codes), k, k, stride, pad, W, 64 * -(-Cc // codes), 4 + axis * axis]
+    return L.ksplit((C.c_int64 * 10)(*v), 0)
+
+
+def _conv_form(L, fmt, geo):
+    Cc, H, W, O, k, stride, pad, batch = geo
+    OH, OW = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+    return _form(L, fmt, O, batch * OH * OW, conv=(Cc, H, W, k, stride, pad))
+
+
+@pytest.mark.parametrize("fmt", [B.RTN_CODE_I8, B.RTN_CODE_FP4])
+def test_small_grid_tests_reach_every_form(L, fmt):
+    """The GPU tests of the small-grid kernel run all of its forms in both formats."""
+    assert {_form(L, fmt, *g) for g in KSPLIT_GEMMS} == {0, 1, 2}
+    assert {_conv_form(L, fmt, g) for g in KSPLIT_CONVS} >= set(range(8))

@@ -520,7 +520,8 @@ def test_all_tile_configs_fp4(cfg, tile_reset):
 @pytest.mark.parametrize("M,N,K,fmt", [
     (2047, 2043, 70, FP4), (2049, 2048, 70, FP4),    # 1024 and 1056 small tiles, few K-steps
     (1403, 1470, 833, B.RTN_CODE_I8), (1472, 1473, 833, B.RTN_CODE_I8),  # 506 and 552, 14 K-steps
-    (129, 130, 8200, FP4)])                          # 9 tiles, 65 K-steps
+    (1020, 1023, 8200, FP4), (1020, 1030, 8200, FP4),  # 256 and 272, 65 K-steps
+    (129, 130, 8200, FP4)])                          # 25 tiles of 32 x 32: K cut into shares
 def test_small_grid_tile_choice(M, N, K, fmt):
     """The library's own choice on both sides of each line of the small-tile rule."""
     _say("tile choice %d x %d x %d" % (M, N, K))
@@ -532,7 +533,7 @@ def test_small_grid_tile_choice(M, N, K, fmt):
 
 # Small grids (K cut into shares, one per wave of a block): every form of the kernel at sizes that its rule
 # gives it -- ragged tiles, K-steps that do not divide by the waves, fewer K-steps than waves.
-KSPLIT_GEMMS = [(1, 64, 64), (33, 65, 150), (500, 480, 70),          # up to 3 K-steps, 480 tiles
+KSPLIT_GEMMS = [(1, 64, 64), (33, 65, 150), (500, 960, 70),          # up to 3 K-steps, 480 tiles of 32 x 32
                 (37, 100, 1100), (130, 500, 577),                    # eight waves
                 (70, 3200, 4300)]                                    # 300 tiles of 32 x 32, 34+ K-steps
 
@@ -616,7 +617,8 @@ KSPLIT_CONVS = [  # C, H, W, O, k, stride, pad, batch
     (200, 6, 9, 100, 5, 1, 2, 1),     # 81 classes' table, 50+ K-steps on 8 waves
     (300, 13, 13, 300, 3, 1, 1, 6),   # 320 tiles of 32 x 32, more than 256 blocks with three K-steps per tap (int8: 45)
     (600, 28, 28, 70, 3, 1, 1, 7),    # 64 x 64 tiles, eight waves, with the tile's pixel run in LDS
-    (300, 55, 57, 70, 3, 2, 1, 7),    # ... and without
+    (300, 55, 57, 70, 3, 2, 1, 7),    # ... and without (int8)
+    (450, 55, 57, 70, 3, 2, 1, 7),    # ... (FP4)
     (1000, 9, 9, 300, 3, 1, 1, 12),   # 64 x 32 tiles with the pixel run
     (96, 27, 26, 130, 5, 1, 2, 14),   # 64 x 64 tiles, four waves, with the pixel run (int8)
     (130, 27, 26, 130, 5, 1, 2, 14),  # ... (FP4)
