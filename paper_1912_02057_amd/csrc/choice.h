@@ -110,23 +110,25 @@ inline bool ksplit_fits(int form, const KsplitShape& s)
 // The form of k_ksplit for a grid too small for k_tmm, or -1.
 // K's share of the time decides between the forms, the number of 32 x 32 tiles whether to cut K at all; past
 // these lines the small tiles' operand traffic (L2 to LDS) costs more than the cut saves.
-// Time against k_tmm's, geometric mean (worst) over 336 random geometries (GEMM M 1 to 4096, N and K 64 to 8192; convs of 24 to 1024
-// channels and filters, 7 to 112 wide, windows 1, 3, 5, stride 1, 2, every epilogue; FP4 and int8):
-//   tiles <= 256:  GEMM 1.21 (1.11) at 1-3 K-steps, 1.37 at 4-8, 1.59 at 17-32, 1.90 at 33-64, 2.28 beyond
-//                  conv 1.19 (1.03) at 1-3 K-steps, 1.43 at 4-8, 1.95 at 17-32, 2.46 at 33-64, 2.98 beyond
-//   tiles <= 512:  GEMM 1.15 (1.04) at 1-3, 1.16 (1.11) at 17-32, 1.29 (1.20) beyond
-//                  conv 1.14 (1.06) at 1-3, 1.16 (1.07) at 9-16, 1.43 at 17-32, 1.7 to 2.1 beyond
-//   tiles <= 1024: GEMM 0.89 (0.85) at 17-32 K-steps, not taken; conv 1.03 (0.97) at 17-32, not taken, 1.41 (1.34)
-//                  at 33-64, 1.70 (1.45) beyond
-//   64 x 64 tiles in 257 .. 512: conv 1.00 at 33-64 K-steps, not taken, 1.3 (1.03) beyond
-// A conv of 257 to 512 tiles takes 64 x 32 ones, if they are no more than 256, from 9 K-steps on: 1.04 to 1.14 times
-// as fast at 9 to 36, 1.1 to 1.2 beyond.
+// k_tmm's time over this kernel's, geometric mean (least) over 680 random geometries (GEMM M 1 to 4096, N and K 64 to
+// 8192; convs of 24 to 1024 channels and filters, 7 to 112 wide, windows 1, 3, 5, stride 1, 2, every epilogue; FP4, int8):
+//   K-steps           1-3          4-8          9-16         17-32        33-64        65-128
+//   GEMM, <= 256   1.23 (1.13)  1.38 (1.20)  1.45 (1.29)  1.67 (1.52)  1.91 (1.60)  2.26 (1.56)
+//   GEMM, <= 512   1.19 (1.11)  1.22 (1.15)  1.21 (1.11)  1.20 (1.12)  1.25 (1.10)  1.22 (1.03)
+//   GEMM, <= 1024, not taken, the best of the forms of 32 and 64:  0.86 (0.78), 0.94 (0.75), 0.95 (0.87)
+//   conv, <= 256   1.15 (1.02)  1.30 (1.12)  1.44 (1.35)  1.89 (1.74)  2.47 (2.10)  3.01 (2.69)
+//   conv, <= 512   1.09 (0.97)  1.22 (1.08)  1.26 (1.05)  1.48 (1.26)  1.72 (1.41)  2.00 (1.51)
+//   conv, <= 1024, with the pixel run's forms:             1.11 (1.00)  1.26 (1.01)  1.62 (1.48)
+//   conv, 64 x 64 tiles in 257 .. 512: 1.00 at 33-64 K-steps, not taken, 1.3 (1.03) beyond
+// A conv of 257 to 512 tiles takes four waves up to 8 K-steps (with eight 1.09, least 0.91: a ternarizing conv was slower
+// than with k_tmm), and 64 x 32 tiles, if they are no more than 256, from 9 on: 1.04 to 1.14 times as fast at 9 to 36,
+// 1.1 to 1.2 beyond.
 inline int pick_ksplit_plain(const KsplitShape& s)
 {
     const bool conv = s.KH != 0;
     const int64_t tiles = nblocks(s.rp, s.rq, 32, 32);
     if (tiles <= 512) {
-        if (s.nk <= 3) return 0;
+        if (s.nk <= (conv && tiles > 256 ? 8 : 3)) return 0;
         return s.nk > (conv ? 8 : 32) && tiles > 256 && nblocks(s.rp, s.rq, 64, 32) <= 256 ? 2 : 1;
     }
     if (!conv) return -1;

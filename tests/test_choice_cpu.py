@@ -88,3 +88,32 @@ def test_small_grid_tests_reach_every_form(L, fmt):
     """The GPU tests of the small-grid kernel run all of its forms in both formats."""
     assert {_form(L, fmt, *g) for g in KSPLIT_GEMMS} == {0, 1, 2}
     assert {_conv_form(L, fmt, g) for g in KSPLIT_CONVS} >= set(range(8))
+
+
+def test_small_grid_lines(L):
+    """Both sides of each line of the rule, in tiles and in K-steps."""
+    I8 = B.RTN_CODE_I8
+    for nk, form in ((1, 0), (3, 0), (4, 1), (33, 1)):                   # 256 tiles of 32 x 32
+        assert _form(L, I8, 512, 512, 64 * nk) == form
+    for nk, form in ((3, 0), (4, 1), (32, 1), (33, 2)):                  # 512, 256 of 64 x 32
+        assert _form(L, I8, 512, 1024, 64 * nk) == form
+    assert _form(L, I8, 32, 16384, 64 * 33) == 1                         # 512, 512 of 64 x 32
+    for nk in (1, 65):
+        assert _form(L, I8, 513, 1024, 64 * nk) == -1                    # 544
+    conv = lambda O, px, nk, k=1: _form(L, I8, O, px, conv=(64 * nk // (k * k), 16, 16, k, 1 if k > 1 else 2, k // 2))
+    for nk, form in ((3, 0), (4, 1), (9, 1)):
+        assert conv(512, 512, nk) == form
+    for nk, form in ((1, 0), (4, 0), (8, 0), (9, 2)):
+        assert conv(512, 1024, nk) == form
+    assert conv(32, 16384, 8) == 0 and conv(32, 16384, 9) == 1
+    for nk, form in ((32, -1), (33, 3)):
+        assert conv(1024, 1024, nk) == form                              # 256 of 64 x 64
+    for nk, form in ((64, -1), (65, 4)):
+        assert conv(1024, 2048, nk) == form                              # 512
+    assert conv(1024, 2049, 65) == -1
+    for nk, form in ((9, -1), (18, 6)):                                  # 3 x 3, stride 1: the pixel run
+        assert conv(1024, 1024, nk, 3) == form
+    for nk, form in ((27, -1), (36, 7)):
+        assert conv(1024, 2048, nk, 3) == form
+    for nk, form in ((63, 2), (72, 5)):
+        assert conv(512, 1024, nk, 3) == form

@@ -614,6 +614,7 @@ def test_gemm_output_stored_with_hint(M, N, steps, fmt):
 KSPLIT_CONVS = [  # C, H, W, O, k, stride, pad, batch
     (64, 9, 11, 40, 1, 2, 0, 2),      # one K-step, 88 padding codes behind 40
     (130, 7, 7, 70, 3, 1, 1, 1),      # ragged everywhere
+    (500, 14, 13, 300, 1, 1, 0, 7),   # 400 tiles of 32 x 32, 4 (FP4) or 8 K-steps on four waves
     (200, 6, 9, 100, 5, 1, 2, 1),     # 81 classes' table, 50+ K-steps on 8 waves
     (300, 13, 13, 300, 3, 1, 1, 6),   # 320 tiles of 32 x 32, more than 256 blocks with three K-steps per tap (int8: 45)
     (600, 28, 28, 70, 3, 1, 1, 7),    # 64 x 64 tiles, eight waves, with the tile's pixel run in LDS
