@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "choice.h"
+#include "lds_limit.h"
 #include "rtn_kernels.h"
 
 namespace rtn {
@@ -635,13 +636,6 @@ hipError_t launch_pack_nchw_codes(const PackArgs& a, hipStream_t st)
 {
     const size_t smem = (size_t)64 * (FP4 ? a.Kpad / 2 : a.Kpad);  // LDS image of the block's output run
     if (smem > 128 * 1024) return hipErrorInvalidValue;
-    static bool attr_done = false;
-    if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_pack_nchw_i8<FP4>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-        if (e != hipSuccess) return e;
-        attr_done = true;
-    }
     if (a.HW % 4 == 0 && ((uintptr_t)a.x) % 16 == 0 && a.K % 64 == 0 && a.N * a.K * a.HW < ((int64_t)1 << 30)) {
         // straight-line kernel; the widest pixel runs that still give every CU several blocks
         const int64_t px = a.N * a.HW;
@@ -689,6 +683,9 @@ hipError_t launch_pack_nchw_codes(const PackArgs& a, hipStream_t st)
                            make_fastdiv((uint32_t)a.HW));
         return hipGetLastError();
     }
+    static LdsLimit lds;
+    const hipError_t e = lds.raise((const void*)k_pack_nchw_i8<FP4>, 128 * 1024);
+    if (e != hipSuccess) return e;
     const dim3 grid((unsigned)((a.N * a.HW + 63) / 64)), block(256);
     hipLaunchKernelGGL(k_pack_nchw_i8<FP4>, grid, block, smem, st, a);
     return hipGetLastError();

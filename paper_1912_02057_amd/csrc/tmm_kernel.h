@@ -45,6 +45,7 @@
 
 #include "choice.h"
 #include "epilogue_math.h"
+#include "lds_limit.h"
 #include "rtn_kernels.h"
 
 namespace rtn {
@@ -1112,14 +1113,10 @@ hipError_t launch_cfg(TmmParams& prm, hipStream_t st)
         smem = stage_bytes > tb ? stage_bytes : tb;
     }
     if (smem > kMaxLds) return hipErrorInvalidValue;
-    static bool attr_done = false;
     auto kern = k_tmm<BP, BQ, WGP, WGQ, NS, MINW, CONV, TERN, HC, DT, NT>;
-    if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)kMaxLds);
-        if (e != hipSuccess) return e;
-        attr_done = true;
-    }
+    static LdsLimit lds;
+    const hipError_t e = lds.raise((const void*)kern, (int)kMaxLds);
+    if (e != hipSuccess) return e;
     const unsigned grid = tile_grid(prm, BP, BQ);
     if (!grid) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), (size_t)smem, st, prm);

@@ -511,12 +511,9 @@ hipError_t launch(KsplitParams& kp, const KsplitShape& s, hipStream_t st)
     }
     kp.main = (int)ksplit_main_bytes(f, s);
     auto kern = k_ksplit<f.tp, f.tq, f.waves, f.stages, CONV, TERN, DT, f.run>;
-    static bool attr_done = false;
-    if (!attr_done) {
-        const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
-        if (e != hipSuccess) return e;
-        attr_done = true;
-    }
+    static LdsLimit lds;
+    const hipError_t e = lds.raise((const void*)kern, (int)kMaxLds);
+    if (e != hipSuccess) return e;
     const unsigned grid = tile_grid(kp.t, 32 * f.tp, 32 * f.tq);
     if (!grid) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * f.waves), (size_t)ksplit_lds_bytes(f, s), st, kp);

@@ -175,12 +175,9 @@ hipError_t launch_planes(TmmParams& prm, const int8_t* ps, const int8_t* qs, hip
     constexpr int smem = 2 * 2 * (BP + BQ) * 64;  // two stages; the epilogue's [3][BP] doubles fit in one
     static_assert(3 * BP * 8 <= smem, "epilogue table over the stages");
     auto kern = k_gemm_planes<BP, BQ, WGP, WGQ, MINW, EB>;
-    static bool attr_done = false;
-    if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (e != hipSuccess) return e;
-        attr_done = true;
-    }
+    static LdsLimit lds;
+    const hipError_t e = lds.raise((const void*)kern, smem);
+    if (e != hipSuccess) return e;
     const unsigned grid = tile_grid(prm, BP, BQ);
     if (!grid) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), (size_t)smem, st, prm, ps, qs);

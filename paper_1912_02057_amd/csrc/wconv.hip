@@ -435,12 +435,9 @@ hipError_t launch_wc(WcParams& prm, hipStream_t st)
     prm.dc = KG / (g.KH * g.KW);
     prm.dtap = KG % (g.KH * g.KW);
     auto kern = k_wconv<BP, BQ, WGP, WGQ, KG, MINW, NTAP, CS, RMAX, BIG>;
-    static bool attr_done = false;
-    if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (e != hipSuccess) return e;
-        attr_done = true;
-    }
+    static LdsLimit lds;
+    const hipError_t e = lds.raise((const void*)kern, smem);
+    if (e != hipSuccess) return e;
     const unsigned grid = tile_grid(prm.t, BP, BQ);
     if (!grid) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WGP * WGQ * KG), (size_t)smem, st, prm);

@@ -117,3 +117,37 @@ def test_small_grid_lines(L):
         assert conv(1024, 2048, nk, 3) == form
     for nk, form in ((63, 2), (72, 5)):
         assert conv(512, 1024, nk, 3) == form
+
+
+LDS_SHIM = r"""
+#include "lds_limit.h"
+static int device, calls[70], fail;
+extern "C" hipError_t hipGetDevice(int *d) { *d = device; return hipSuccess; }
+extern "C" hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int)
+{
+    ++calls[device];
+    return fail ? hipErrorInvalidValue : hipSuccess;
+}
+extern "C" int launch_on(int dev, int failing)
+{
+    static rtn::LdsLimit lds;
+    device = dev, fail = failing;
+    return (int)lds.raise(nullptr, 1 << 17);
+}
+extern "C" int calls_on(int dev) { return calls[dev]; }
+"""
+
+
+def test_lds_limit_is_raised_on_every_device(tmp_path):
+    """Once per device, again after a failure, and at every launch beyond the 64 devices that have a bit."""
+    (tmp_path / "shim.cpp").write_text(LDS_SHIM)
+    so = str(tmp_path / "lds.so")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-shared", "-fPIC", "-I" + CSRC, "-isystem", rocm + "/include",
+                    str(tmp_path / "shim.cpp"), "-o", so, "-Wl,-Bsymbolic"], check=True)
+    S = C.CDLL(so)
+    for dev in (0, 1, 0, 1, 63, 63):
+        assert S.launch_on(dev, 0) == 0
+    assert [S.calls_on(d) for d in (0, 1, 63)] == [1, 1, 1]
+    assert S.launch_on(2, 1) != 0 and S.launch_on(2, 0) == 0 and S.launch_on(2, 0) == 0 and S.calls_on(2) == 2
+    assert S.launch_on(64, 0) == 0 and S.launch_on(64, 0) == 0 and S.calls_on(64) == 2
