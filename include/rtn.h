@@ -131,8 +131,9 @@ int rtn_last_hip_error(void);
  * conv variants that keep a tile's run of input pixels in LDS (stride 1, centred
  * window, 64 or 128 padded channels: 64x256 twice, 64x128 twice, 128x128,
  * 128x256; any other problem runs the plain tile of that size); -1 (default)
- * lets the library choose from the problem shape.  Every configuration computes the same
- * result, except that the weight-only conv adds its fp32 products in another order in some of
+ * lets the library choose from the problem shape, where the output tiles leave most of the chip idle
+ * also a kernel outside this list whose blocks share K among their waves.  Every configuration computes
+ * the same result, except that the weight-only conv adds its fp32 products in another order in some of
  * them (there 8, 9, 10 and 12 are the 128x128, 64x256, 64x64 and a second 128x128 tile that gather
  * their inputs tap by tap, 11 is 32x32), within the error bound stated there.  The setting is
  * process-wide and not thread-safe.

@@ -651,6 +651,57 @@ def test_small_grid_conv(geo, fmt):
     T.assert_y_close(y.cpu().numpy(), z, "small grid tail y")
 
 
+@pytest.mark.parametrize("fmt", [B.RTN_CODE_I8, FP4])
+@pytest.mark.parametrize("M,N,K", KSPLIT_GEMMS)
+def test_small_grid_gemm_is_the_same_bits(M, N, K, fmt, tile_reset):
+    """The small-grid kernel's epilogue repeats the 64 x 64 tile's operations: equal bits, with ReLU and BN and without."""
+    case = wl.gemm_case(M, N, K, seed=M + 2 * K)
+    rng = np.random.default_rng(K)
+    bn = (rng.uniform(0.5, 1.5, N).astype(np.float32), rng.standard_normal(N).astype(np.float32))
+    for kw in ({}, dict(relu=True), dict(bn=bn), dict(relu=True, bn=bn)):
+        outs = []
+        for cfg in (-1, 0):
+            B.set_tile_config(cfg)
+            outs.append(T.hip_gemm(case, fmt=fmt, want_acc=True, **kw))
+        assert torch.equal(outs[0]["D"], outs[1]["D"]) and torch.equal(outs[0]["y"], outs[1]["y"]), kw.keys()
+
+
+@pytest.mark.parametrize("true_zero", [True, False])
+@pytest.mark.parametrize("fmt", [B.RTN_CODE_I8, FP4])
+@pytest.mark.parametrize("geo", KSPLIT_CONVS, ids=lambda g: "x".join(map(str, g)))
+def test_small_grid_conv_is_the_same_bits(geo, fmt, true_zero, tile_reset):
+    """The same of the convs' three epilogues, in both padding modes."""
+    C, H, W, O, k, stride, pad, batch = geo
+    case = wl.conv_case(wl.ConvShape("s", C, H, O, k, stride, pad), batch=batch, seed=C + W, bn=True, Wx=W)
+    lo, hi = np.float32(-0.5), np.float32(0.5)
+    outs = []
+    for cfg in (-1, 0):
+        B.set_tile_config(cfg)
+        got = T.hip_conv(case, true_zero, relu=True, fmt=fmt)
+        res = torch.linspace(-1, 1, got["y"].numel()).view(got["y"].shape).numpy()
+        outs.append([got["D"], got["y"], T.hip_conv_ternarize(case, lo, hi, true_zero, relu=True, fmt=fmt),
+                     *T.hip_conv_ternarize(case, lo, hi, true_zero, residual=res, relu_out=True, want_y=True, fmt=fmt)])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("K", [70, 130], ids=["even_words", "odd_words"])
+@pytest.mark.parametrize("n", [200, 1801, 4101])
+def test_gemm_planes_y_only_with_relu_and_bn(n, K):
+    """y alone from bit planes, on interior and ragged tiles of 64, 128 and 256: its own form of the epilogue.  Sampled rows
+    against the oracle, all of it against the launch with accumulators, which takes the common form."""
+    _say("planes y only n=%d K=%d" % (n, K))
+    case = wl.gemm_case(n, n, K, seed=n + K)
+    rng = np.random.default_rng(n)
+    bn = (rng.uniform(-1.5, 1.5, n).astype(np.float32), rng.standard_normal(n).astype(np.float32))
+    rows = _sample_rows(n, 40, n)
+    sub = dict(case, M=len(rows), xa=case["xa"][rows], alpha_a=case["alpha_a"][rows], beta_a=case["beta_a"][rows])
+    for kw in ({}, dict(relu=True), dict(bn=bn), dict(relu=True, bn=bn)):
+        got = T.hip_gemm(case, fmt=B.RTN_CODE_BITPLANE, want_acc=False, **kw)["y"]
+        T.assert_y_close(got.cpu().numpy()[rows], T.oracle_gemm(sub, **kw)["y"], "planes, y only")
+        assert torch.equal(got, T.hip_gemm(case, fmt=B.RTN_CODE_BITPLANE, want_acc=True, **kw)["y"]), kw.keys()
+
+
 FP4_HALO_SHAPES = HALO_SHAPES + [
     ("h256", 256, 10, 136, 3, 1, 1, 3, None),      # 128 bytes per pixel: two K-steps per tap
     ("h200r", 200, 7, 130, 3, 1, 1, 9, 10),        # C padded to 256, ragged in O and pixels
@@ -1697,7 +1748,7 @@ def _weight_bwd_check(O, K, seed, want_dw=True):
 
 
 @pytest.mark.parametrize("O,K", [(1, 1), (3, 7), (2, 255), (5, 257), (64, 576), (130, 1153), (512, 4608),
-                                 (3, 70001)])
+                                 (3, 70001), (3, 5120), (3, 5124), (2, 10244), (3, 70000)])     # rounds of 5120 weights
 def test_weight_backward_vs_oracle(O, K):
     _say("weight backward O=%d K=%d" % (O, K))
     s1 = _weight_bwd_check(O, K, seed=O * 7 + K)
