@@ -229,15 +229,16 @@ __device__ __forceinline__ bool block_tile(const TmmParams& prm, int& tileP, int
 // The element loops exist in straight-line variants -- (interior / ragged tile) x (acc only / y
 // only / both), and y without ReLU and BN on interior tiles, which needs 4 fp64 operations per
 // output instead of 6 and fewer registers -- picked once per block.
+// Bound by the stores: a 256 x 256 tile of the FP4 GEMM takes 7.6 us (4096 x 4096 x 512; 9.1 at K = 4096), of which
+// the stores alone need 7.1 (8.5).  The fp64 operations of its one wave per SIMD pass beside them as long as nothing
+// spills (with 16 registers spilled: 14.3).
 // NT: y is stored with the non-temporal hint.  The GEMM's tiles finish together, and a burst that the memory-side
 // cache holds is absorbed faster without it (and is there for the next kernel); a larger one is written back while
-// the next tiles are multiplied and takes 1244 -> 1480 cycles per K-step from them (gemm_nt_hint() decides).
-// ABREAST: interior tiles with y alone take one operation at a time over four outputs and more.  fp64 operations
-// of one wave that depend on each other issue every 10 cycles, independent ones every 5 (a conversion 8), and a tile
-// of 256 x 256 leaves a SIMD one wave: its 256 outputs per lane take 9.5 us so, 14.5 us one after the other; the
-// stores alone 7.1.  For the bit planes, whose kernel takes 20.8 instead of 23.6 us at 4096 x 4096 x 512 (69 instead
-// of 74 with the pack at K = 4096).  Not for the others: the FP4 GEMM's tiles end in a burst of stores either
-// way, and it lost 0.5 % at K = 4096 and at 16384 x 8192 x 8192.
+// the next tiles are multiplied: 1610 cycles per K-step instead of 1316, against 12.8 us of epilogue instead of 9.8
+// (16384 x 8192 x 8192; gemm_nt_hint() decides).
+// ABREAST: interior tiles with y alone take one operation at a time over four outputs and more.  For the bit planes:
+// 4096 x 4096 x 4096 with the pack 64.2 us, 64.5 one output after the other.  Not for the FP4 GEMM: 4096 x 4096 x 512 20.3
+// against 18.8, 16384 x 8192 x 8192 509 against 505 and hinted 465 against 460.
 template <int BP, int TP, int TQ, bool SUMS, bool ABREAST = false, bool NT = false, class Acc, class Value>
 __device__ __forceinline__ void gemm_epilogue(const TmmParams& prm, double* tab, int p0, int q0, int wrow, int wcol,
                                               bool full_tile, const Acc& acc, Value value)

@@ -22,8 +22,8 @@
 // when the rows' byte length is not a multiple of 16 (an odd number of plane words); what lies
 // behind a row's end is read from the zero page.
 //
-// M = N = K = 4096: 47 us against 407 us for k_gemm_popc (and 36.5 us for the FP4 GEMM, which has nothing to
-// expand); with an odd number of words, 4096 x 4096 x 4160, 61 us.  Bound by vector-instruction issue: per k-slice a
+// M = N = K = 4096: 48 us against 407 us for k_gemm_popc (and 37.5 us for the FP4 GEMM, which has nothing to
+// expand); with an odd number of words, 4096 x 4096 x 4160, 57 us.  Bound by vector-instruction issue: per k-slice a
 // wave of the 256 x 256 tile runs 80 expanding instructions for 16 MFMAs, at one wave per SIMD.  A wave tile of
 // 128 x 128 halves that share against 64 x 64, hence the largest tile as soon as it gives every CU a block.
 // The expansion of a slice is dealt out behind the MFMAs of the slice before, and a load costs a 32-bit lane
