@@ -197,7 +197,7 @@ def main():
                            "pack_plus_conv_operands_evicted": round(ms_cold * 1e3, 2),
                            "note": "two dependent launches of a few microseconds each; bound by launch and memory "
                                    "latency, not by a roofline"},
-            "roofline": {"bound": "hbm", "kernel": "k_tmm conv (latency-bound at this size)",
+            "roofline": {"bound": "hbm", "kernel": "k_ksplit conv (latency-bound at this size)",
                          "achieved": round((sh.C * sh.H * sh.H * 5 + sh.O * sh.OH * sh.OH * 4) / (ms * 1e-3) / 1e9, 1),
                          "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": round((sh.C * sh.H * sh.H * 5 + sh.O * sh.OH * sh.OH * 4) / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 5),
