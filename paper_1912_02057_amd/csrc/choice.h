@@ -14,7 +14,7 @@ struct PackRowsForm {
 //   FP4, 16 x 1536  3.29 -> 2.84     int8, 2000 x 1536  5.28 -> 5.09     int8, 2100 x 1536  5.52 -> 5.60, not taken
 //   FP4, 16 x 8192  8.08 -> 3.91     int8, 2000 x 576   3.17 -> 3.65, not taken
 // Turns of one step up to 2048 elements, of two beyond: FP4, 16 x 2048 2.85 against 3.10, 16 x 8192 4.18 against 3.91
-// (four steps: 3.71 and 3.82, and 16 x 576 to 2000 x 2048 take 1.1 to 1.45 times as long: one wave has the row).  Of
+// (four steps: 3.71 and 3.82, and 16 x 576 to 2000 x 2048 take 1.1 to 1.5 times as long: one wave has the row).  Of
 // many rows, short ones take steps of 256: int8, 5000 x 1100 7.03 against 7.54, FP4 7.02 against 7.59; int8, 5000 x
 // 2048 9.90 against 9.64, not taken.
 inline PackRowsForm pack_rows_form(int64_t rows, int64_t Kpad)
@@ -47,7 +47,8 @@ inline PackRowsForm pack_rows_planes_form(int64_t rows, int64_t Kpad)
 // and only for rows of whole 128-byte lines; beyond, of whole 64-byte halves:
 //   FP4, 12000 x 3000 x 2048 (137)      106 -> 112    132 -> 150    12000 x 2992 x 2048 (137)  102 -> 102    131 -> 137
 //   FP4, 16384 x 8191 x 2048 (512)      300 -> 326    429 -> 457    16384 x 8176 x 2048 (511)  298 -> 239    429 -> 396
-//   int8, 16384 x 8191 x 512            227 -> 273    375 -> 397    16384 x 8188 x 2048 (511)  299 -> 248    429 -> 441
+//   FP4, 16384 x 8188 x 2048 (511)      299 -> 248    429 -> 441    16384 x 8188 x 512         198 -> 208    331 -> 338
+//   int8, 16384 x 8191 x 512            227 -> 273    375 -> 397
 inline bool gemm_nt_hint(int64_t M, int64_t N, uintptr_t y, int nk)
 {
     const int64_t bytes = M * N * 4, mib = (int64_t)1 << 20;
