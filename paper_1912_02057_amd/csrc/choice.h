@@ -137,10 +137,10 @@ inline int pick_ksplit_plain(const KsplitShape& s)
     return s.nk > 64 && nblocks(s.rp, s.rq, 64, 64) <= 512 ? 4 : -1;
 }
 
-// The same for convs whose pixels are one run of the input; these forms come first.  Against the best of the others, 121 random convs with windows 3 and 5: 64 x 32 tiles 1.05 to
-// 1.15 times as fast beyond 64 K-steps (0.95 to 1.04 below); 64 x 64 tiles, up to 256, 1.05 to 1.2 times from 18 to 25,
-// 1.05 to 1.15 beyond; up to 512 of them 1.1 to 1.25 at 36 to 50 (0.9 to 1.06 at 18 to 27) where two blocks fit a
-// CU, 0.7 to 0.85 where they do not.
+// The same for convs whose pixels are one run of the input; these forms come first.  Against the best of the others, 121
+// random convs with windows 3 and 5: 64 x 32 tiles 1.05 to 1.15 times as fast beyond 64 K-steps (0.95 to 1.04 below);
+// 64 x 64 tiles, up to 256, 1.05 to 1.2 times from 18 to 25, 1.05 to 1.15 beyond; up to 512 of them 1.1 to 1.25 at 36 to
+// 50 (0.9 to 1.06 at 18 to 27) where two blocks fit a CU, 0.7 to 0.85 where they do not.
 inline int pick_ksplit_run(const KsplitShape& s)
 {
     if (s.KH < 3) return -1;
