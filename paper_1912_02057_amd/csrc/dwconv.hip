@@ -1,14 +1,17 @@
 // Depthwise ternary convolution (one k x k ternary filter per channel; the 3x3 layers of
 // MobileNet, one of the networks the paper evaluates) with the per-channel four-term
-// reparameterization.  A dot product here has only k*k terms, so there is nothing for the
-// matrix cores to do: the kernel is a streaming one, 1 byte read and 4 bytes written per
-// output.  A block owns 64 consecutive output pixels x 64 channels.  In the compute phase
+// reparameterization.  A dot product here has only k*k terms: the kernels are streaming ones, 1 byte
+// read and 4 bytes written per output.  Three of them: 3 x 3 windows on the matrix cores, 3 x 3
+// windows on the vector ALU where the first does not apply, and any window.  In the last one a block
+// owns 64 consecutive output pixels x 64 channels.  In the compute phase
 // lanes run along channels -- the codes are channel-innermost, so a thread's dword is 4
 // channels of one input pixel and 16 threads read 64 contiguous bytes -- and a thread forms
 // its 4 pixels x 4 channels; the results cross an LDS tile so that in the store phase lanes
 // run along pixels, where the NCHW output of a channel is contiguous.
-#include "epilogue_math.h"
-#include "rtn_kernels.h"
+#include <cmath>
+#include <type_traits>
+
+#include "tmm_kernel.h"
 
 namespace rtn {
 
@@ -377,14 +380,273 @@ __global__ __launch_bounds__(256) void k_dwconv3(DwConvArgs a)
     }  // tiles
 }
 
+// ---- 3 x 3, pad <= 1, stride 1 and 2: on the int8 matrix cores ----------------------------
+// Streaming: 1 byte read and 4 written per output.  The kernel above is held by its vector instructions, some 80 issue
+// slots per output (MobileNet's 13 layers, batch 256: 1085 us; here 732, at 3.5 to 4.0 TB/s).  Here the dot products go to
+// the matrix cores, idle otherwise: v_mfma_i32_16x16x64_i8 multiplies 16 pixels by 16 channels over K = 4 taps x
+// 16 channels, with filter codes on the diagonal of each tap's 16 x 16 block.  15 of 16 products are with
+// zeros, and still the nine taps of 256 outputs are 3 instructions of 16 cycles.
+//  * The output pixels of a tile are consecutive, so their inputs are one run of consecutive pixels (tap (0, 0) of the first
+//    to tap (2, 2) of the last): loaded into LDS once, as it lies in memory.  An operand is 16 bytes per lane, 16
+//    channels of one tap of one pixel; a tap outside the image reads 16 zero bytes.  A lane looks after 3 taps of
+//    one pixel, not 9.  (Operands straight from memory: 1.9 times slower, a lane's 16 bytes are a line of their own.)
+//  * Pixels are the rows of the product, so a lane gets 4 consecutive pixels of one channel: a 16-byte
+//    store into NCHW without another turn through LDS, and the channel's factors are the lane's own registers.
+// BW: there is a weight offset, so that the pixel sums of the codes count (3 more matrix instructions, against ones).
+template <int NCG, bool BW, bool NT>
+__global__ __launch_bounds__(256, BW && NCG == 4 ? 3 : 4) void k_dwconv3_mm(DwConvArgs a)
+{
+    typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+    typedef int v4iu __attribute__((ext_vector_type(4), aligned(4)));
+    constexpr int CHB = 16 * NCG, RB = 16 * NCG;  // channels of a block = bytes of a pixel in LDS
+    // LDS: [run of pixels][16 zero bytes][classes][CHB] constants
+    extern __shared__ __attribute__((aligned(16))) int8_t dw_smem[];
+    const ConvGeom& g = a.g;
+    const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned lds0 = (unsigned)(uintptr_t)dw_smem;
+    const int zoff = a.run * RB;
+    double* cst = (double*)(dw_smem + zoff + 16);
+    const int ohw = g.OH * g.OW, total = g.Nb * ohw, total_in = g.Nb * g.H * g.W;  // (below 2^31)
+    const int cb = (int)blockIdx.y * CHB;
+    const EpiArgs& ep = a.ep;
+    const bool has_bn = ep.bn_scale != nullptr;
+    const double aa = (double)ep.alpha_a.s, ba = (double)ep.beta_a.s;
+    // input pixel of tap (0, 0) of output pixel m, and the window's first row and column
+    auto corner = [&](int m, int& ih0, int& iw0) {
+        const int nb = (int)fastdiv((uint32_t)m, g.div_ohw), pix = m - nb * ohw;
+        const int oh = (int)fastdiv((uint32_t)pix, g.div_ow), ow = pix - oh * g.OW;
+        ih0 = oh * g.stride - g.pad;
+        iw0 = ow * g.stride - g.pad;
+        return (nb * g.H + ih0) * g.W + iw0;
+    };
+    // chunk swizzle of a pixel's LDS row: the 16-byte reads of 16 consecutive rows hit all banks
+    auto swizzle = [](int row) { return NCG == 4 ? swz(row) : (row >> 3) & 1; };
+    // each XCD gets one contiguous run of pixels (grid.x is a multiple of 8), so that window rows meet in its L2;
+    // the groups of 16 pixels are dealt out evenly
+    const int chunk = (int)(gridDim.x >> 3);
+    const int bid = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
+    const int64_t ngroups = ((int64_t)total + 15) >> 4;
+    const int first = (int)(ngroups * bid / gridDim.x) * 16;
+    const int last = (int)(ngroups * (bid + 1) / gridDim.x) * 16;
+    // loads the run of tile t0 and returns its first pixel
+    auto load_run = [&](int t0) {
+        int t1 = t0 + a.tile < last ? t0 + a.tile : last, d0, d1;
+        t1 = t1 < total ? t1 : total;
+        const int run0 = corner(t0, d0, d1), rows = corner(t1 - 1, d0, d1) + 2 * g.W + 3 - run0;
+        for (int n = wave; n * (64 / NCG) < rows; n += 4) {
+            const int lin = n * 64 + lane, row = lin / NCG, q = lin % NCG;
+            int px = run0 + row;
+            px = px < 0 ? 0 : (px < total_in ? px : total_in - 1);  // past the tensor: only taps outside an image point there
+            dma16(a.a + (int64_t)px * g.Cpad + cb + ((q ^ swizzle(row)) << 4), lds0 + (unsigned)(n * 1024));
+        }
+        return run0;
+    };
+    if (first >= last) return;
+    // (pad <= 1 and an image at least as long as the window: a window is cut at one end of an
+    // axis at most, 3 x 3 classes; the others exist only for images shorter than 3)
+    const int nax = g.H < 3 || g.W < 3 ? 4 : 3;
+    if (tid < 4) ((int*)(dw_smem + zoff))[tid] = 0;
+    if (a.y) {
+        for (int idx = tid; idx < nax * nax * CHB; idx += 256) {
+            const int k = idx / CHB, cl = idx - k * CHB;
+            const int c = cb + cl < g.C ? cb + cl : g.C - 1;
+            const int* wr = (const int*)(a.w + (int64_t)c * a.Kp);
+            const int rc = k / nax, cc = k - rc * nax;
+            unsigned cnt[3] = {0, 0, 0};
+            int kv = 0;
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                const int kh = t / 3, kw = t % 3;
+                const bool out = (kh == 0 && (rc & 1)) || (kh == 2 && (rc & 2)) || (kw == 0 && (cc & 1)) || (kw == 2 && (cc & 2));
+                kv += !out;
+                cnt[t >> 2] |= (unsigned)!out << (8 * (t & 3));
+            }
+            int sw = __builtin_amdgcn_sdot4(wr[0], (int)cnt[0], 0, false);
+            sw = __builtin_amdgcn_sdot4(wr[1], (int)cnt[1], sw, false);
+            sw = __builtin_amdgcn_sdot4(wr[2] & 0xff, (int)cnt[2], sw, false);
+            const double aw = pval(ep.alpha_w, c), bw = pval(ep.beta_w, c);
+            cst[idx] = ba * aw * (double)sw + (double)kv * ba * bw;
+        }
+    }
+    // ---- once per wave: filter operands, channel factors, this lane's taps ----------------
+    // B operand: column = channel l15, k = 16 lk + byte: tap 4 h + lk, channel = byte, so a lane's only non-zero byte is l15
+    v4i wd[NCG][3], ones;
+    double g1[NCG], c2[NCG], bs[NCG], bh[NCG];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) ones[j] = l15 >> 2 == j ? 1 << (8 * (l15 & 3)) : 0;
+#pragma unroll
+    for (int i = 0; i < NCG; ++i) {
+        const bool cok = cb + 16 * i + l15 < g.C;
+        const int c = cok ? cb + 16 * i + l15 : g.C - 1;
+#pragma unroll
+        for (int h = 0; h < 3; ++h) {
+            const int t = 4 * h + lk;
+            const int v = cok && t < 9 ? (int)(uint8_t)a.w[(int64_t)c * a.Kp + (t < 9 ? t : 0)] : 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) wd[i][h][j] = l15 >> 2 == j ? v << (8 * (l15 & 3)) : 0;
+        }
+        g1[i] = c2[i] = bh[i] = 0.0;
+        bs[i] = 1.0;
+        if (a.y) {
+            g1[i] = aa * pval(ep.alpha_w, c);
+            if (BW) c2[i] = aa * pval(ep.beta_w, c);
+            bs[i] = has_bn ? (double)ep.bn_scale[c] : 1.0;
+            bh[i] = (has_bn && ep.bn_shift) ? (double)ep.bn_shift[c] : 0.0;
+        }
+    }
+    const double relu_floor = __builtin_canonicalize(ep.relu ? 0.0 : -__builtin_inf());
+    int tkh[3], tkw[3];
+#pragma unroll
+    for (int h = 0; h < 3; ++h) {
+        const int t = 4 * h + lk;
+        tkh[h] = t / 3;
+        tkw[h] = t - 3 * tkh[h];
+    }
+    for (int t0 = first; t0 < last; t0 += a.tile) {
+        const int t1 = t0 + a.tile < last ? t0 + a.tile : last;  // pixels t0 .. t1 - 1
+        if (t0 != first) __syncthreads();  // the run of the tile before has been read
+        const int run0 = load_run(t0);     // (issued before the set-up it only delays the set-up's own loads)
+        wait_vm<0>();
+        __syncthreads();
+        for (int m0 = t0 + wave * 16; m0 < t1; m0 += 64) {
+            // the pixel whose taps this lane multiplies (pixels past the end repeat the last one; never stored)
+            const int m = m0 + l15 < total ? m0 + l15 : total - 1;
+            int ih0, iw0;
+            const int row0 = corner(m, ih0, iw0) - run0;
+            int addr[3];
+#pragma unroll
+            for (int h = 0; h < 3; ++h) {
+                const bool inb = (unsigned)(ih0 + tkh[h]) < (unsigned)g.H && (unsigned)(iw0 + tkw[h]) < (unsigned)g.W && tkh[h] < 3;
+                const int row = row0 + tkh[h] * g.W + tkw[h];
+                addr[h] = inb ? row * RB + (swizzle(row) << 4) : -1;
+            }
+            // border class of that pixel; a lane stores pixels 4 lk .. + 3
+            const unsigned rc = (unsigned)(ih0 < 0) | (unsigned)(ih0 + 2 >= g.H) << 1, cc = (unsigned)(iw0 < 0) | (unsigned)(iw0 + 2 >= g.W) << 1;
+            const int cls = g.code_zero_pad ? 0 : (int)(rc * nax + cc) * CHB;
+            const double* crow[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) crow[r] = cst + __shfl(cls, 4 * lk + r, 64) + l15;
+            const int mq = m0 + 4 * lk;
+            auto base_of = [&](int p) {  // output offset of pixel p, channel 0
+                const int n = (int)fastdiv((uint32_t)p, g.div_ohw);
+                return (int64_t)n * g.C * ohw + (p - n * ohw);
+            };
+            // a quad of pixels that lies in one image is stored with one instruction (16 bytes on any multiple of 4)
+            const int nbq = (int)fastdiv((uint32_t)(mq < total ? mq : 0), g.div_ohw), pixq = mq - nbq * ohw;
+            const bool quad = pixq + 4 <= ohw && mq < total;
+            const int64_t obase = (int64_t)nbq * g.C * ohw + pixq;
+#pragma unroll
+            for (int i = 0; i < NCG; ++i) {
+                v4i d = {0, 0, 0, 0}, s = {0, 0, 0, 0};
+#pragma unroll
+                for (int h = 0; h < 3; ++h) {
+                    const v4i x = *(const v4i*)(dw_smem + (addr[h] < 0 ? zoff : addr[h] ^ (16 * i)));
+                    d = __builtin_amdgcn_mfma_i32_16x16x64_i8(x, wd[i][h], d, 0, 0, 0);
+                    if (BW) s = __builtin_amdgcn_mfma_i32_16x16x64_i8(x, ones, s, 0, 0, 0);
+                }
+                v4f y = {0.f, 0.f, 0.f, 0.f};
+                if (a.y)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        double v = BW ? g1[i] * (double)d[r] + c2[i] * (double)s[r] + crow[r][16 * i] : g1[i] * (double)d[r] + crow[r][16 * i];
+                        v = __builtin_fmax(v, relu_floor);
+                        y[r] = (float)(bs[i] * v + bh[i]);
+                    }
+                const int c = cb + 16 * i + l15;
+                if (c >= g.C || mq >= total) continue;
+                const int64_t coff = (int64_t)c * ohw;
+                if (quad) {
+                    if (a.y) {
+                        if (NT)
+                            __builtin_nontemporal_store(y, (v4fu*)(a.y + obase + coff));
+                        else
+                            *(v4fu*)(a.y + obase + coff) = y;
+                    }
+                    if (a.acc) *(v4iu*)(a.acc + obase + coff) = d;
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (mq + r >= total) break;
+                        const int64_t o = base_of(mq + r) + coff;
+                        if (a.y) {
+                            if (NT)
+                                __builtin_nontemporal_store(y[r], a.y + o);
+                            else
+                                a.y[o] = y[r];
+                        }
+                        if (a.acc) a.acc[o] = d[r];
+                    }
+                }
+            }
+        }
+    }
+}
+
+// Input pixels between tap (0, 0) of the first and tap (2, 2) of the last of `t` consecutive output pixels, at most:
+// each step is `stride` pixels, and some are the ends of a row or of an image.
+int64_t dw_run(const ConvGeom& g, int t)
+{
+    const int64_t s = g.stride, row = s * (g.W - g.OW), img = (int64_t)(g.H - (g.OH - 1) * s) * g.W - g.OW * s;
+    const int64_t nrow = (t - 2) / g.OW + 1, nimg = (t - 2) / ((int64_t)g.OH * g.OW) + 1;
+    return (t - 1) * s + nrow * (row > 0 ? row : 0) + nimg * (img > 0 ? img : 0) + 2 * (int64_t)g.W + 3;
+}
+
 }  // namespace
 
 hipError_t launch_dwconv(const DwConvArgs& a, hipStream_t st)
 {
     const int64_t total = (int64_t)a.g.Nb * a.g.OH * a.g.OW;
+    const bool big = total * a.g.C * 4 > ((int64_t)128 << 20);
+    const std::true_type yes{};
+    const std::false_type no{};
+    // The run of a tile's inputs decides: 64 pixels and more have to have it in 48 KB, so that three blocks fit a CU beside
+    // their constants (longer tiles where 32 KB hold them, for four), and it has to be no more than four times the
+    // inputs that belong to the tile.  MobileNet's 64 channels of 112 wide, stride 2, 44 KB and 2.7 times: 122 -> 89 us; but
+    // 4 x 64 x 60 x 340, stride 1, 11.7 times: 16.3 -> 19.8, and 2 x 32 x 300 x 330, stride 2, 5.7 times: 8.8 -> 9.4.
+    // Elsewhere (wide images, strides whose runs are mostly skipped) the kernel without it.
+    const int64_t rb = a.g.C <= 32 ? 32 : 64;
+    int tile = 0;
+    if (a.g.KH == 3 && a.g.KW == 3 && a.g.pad <= 1 && a.g.stride <= 2) {
+        for (tile = 256; tile > 64 && dw_run(a.g, tile) * rb > 32 * 1024; tile /= 2) {}
+        const int64_t run = dw_run(a.g, tile);
+        if (run * rb > 48 * 1024 || run > 4 * tile * a.g.stride * a.g.stride) tile = 0;
+    }
+    if (tile) {
+        // (an infinite alpha_a makes c2 = alpha_a * 0 a NaN: kept by the form with the sums)
+        const bool bw = a.ep.beta_w.ptr || a.ep.beta_w.s != 0.0f || !std::isfinite(a.ep.alpha_a.s);
+        // (the hint only for whole 64-byte halves of lines: 128 x 463 x 13 x 98 134 us without, 305 with it)
+        const bool nt = big && (a.g.OH * a.g.OW) % 16 == 0 && ((uintptr_t)a.y & 63) == 0;
+        DwConvArgs b = a;
+        b.tile = tile;
+        b.run = (int)((dw_run(a.g, tile) + 31) / 32 * 32);  // whole KiB of LDS
+        const size_t lds = (size_t)(b.run * rb + 16 + 16 * rb * 8);
+        const int64_t slabs = (a.g.C + rb - 1) / rb;
+        // four blocks per CU, all of them resident, each with an even share of the pixels: the set-up is paid once.  MobileNet's
+        // 13 layers at batch 256: 732 us, with two rounds of them 744, with three 767.  A wave takes 16 pixels at a time.
+        const int64_t most = (total + 63) / 64;
+        int64_t nb = 1024 / slabs < most ? 1024 / slabs : most;
+        nb = (nb + 7) / 8 * 8;
+        if (slabs > 0xffff) return hipErrorInvalidValue;
+        const dim3 grid((unsigned)nb, (unsigned)slabs);
+        auto launch = [&](auto ncg, auto w, auto n) {
+            hipLaunchKernelGGL((k_dwconv3_mm<decltype(ncg)::value, decltype(w)::value, decltype(n)::value>), grid, dim3(256), lds, st, b);
+        };
+        auto pick = [&](auto ncg) {
+            if (bw)
+                nt ? launch(ncg, yes, yes) : launch(ncg, yes, no);
+            else
+                nt ? launch(ncg, no, yes) : launch(ncg, no, no);
+        };
+        if (rb == 32)
+            pick(std::integral_constant<int, 2>{});
+        else
+            pick(std::integral_constant<int, 4>{});
+        return hipGetLastError();
+    }
     if (a.g.KH == 3 && a.g.KW == 3 && a.g.pad <= 1 &&
         (int64_t)a.g.Nb * a.g.H * a.g.W * a.g.Cpad < ((int64_t)1 << 31)) {
-        const bool nt = total * a.g.C * 4 > ((int64_t)128 << 20);
+        const bool nt = big;
         const size_t ntile = (a.y ? 1 : 0) + (a.acc ? 1 : 0);  // LDS tiles
         DwConvArgs b = a;
         // enough blocks for a dozen per CU, each walking up to 16 pixel tiles

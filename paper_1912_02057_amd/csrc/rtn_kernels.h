@@ -208,7 +208,9 @@ struct DwConvArgs {
     int32_t* acc;
     float* y;
     EpiArgs ep;
-    int tiles_per_block;  // set by launch_dwconv: consecutive pixel tiles a block of the 3 x 3 kernel walks
+    // set by launch_dwconv for the 3 x 3 kernels: consecutive pixel tiles a block walks; or (matrix cores) pixels of a
+    // tile and of its run of inputs, at most
+    int tiles_per_block, tile, run;
 };
 hipError_t launch_dwconv(const DwConvArgs& a, hipStream_t st);
 

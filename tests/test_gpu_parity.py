@@ -1906,6 +1906,36 @@ def test_depthwise_layers_at_bench_sizes(C, H, stride, batch):
     _dw_check(C, H, 3, stride, 1, batch, seed=C + batch)
 
 
+@pytest.mark.parametrize("C,H,W,stride,pad,batch", [
+    (33, 5, 7, 1, 1, 9), (64, 16, 16, 1, 1, 4), (100, 7, 7, 2, 1, 37), (32, 31, 29, 2, 0, 3), (20, 3, 65, 1, 0, 5),   # one and two slabs, images across tiles
+    (40, 4, 400, 1, 1, 2), (48, 6, 300, 2, 1, 2),       # runs of inputs beyond the LDS: the other 3x3 kernel
+    (17, 20, 21, 3, 1, 2), (70, 1, 40, 1, 1, 3)])       # stride 3, images shorter than the window
+def test_depthwise_3x3_forms(C, H, W, stride, pad, batch):
+    """Both 3x3 kernels at the edges of their ranges; without a weight offset (no pixel sums) the same bits
+    as with offsets of zero, and outputs at any multiple of 4 bytes."""
+    _say("depthwise 3x3 C=%d %dx%d s%d p%d batch %d" % (C, H, W, stride, pad, batch))
+    _dw_check(C, H, 3, stride, pad, batch, seed=C + W, W=W)
+    _dw_check(C, H, 3, stride, pad, batch, seed=C + W + 1, true_zero=False, W=W)
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(C)
+    ca, _ = B.ternarize_pack(torch.randn((batch, C, H, W), generator=g, device=T.DEV), -0.5, 0.5, want_sum=False)
+    cw, _ = B.ternarize_pack(torch.randn((C, 9), generator=g, device=T.DEV), -0.5, 0.5, want_sum=False)
+    aw = torch.rand(C, generator=g, device=T.DEV) + 0.5
+    shape = (batch, C, (H + 2 * pad - 3) // stride + 1, (W + 2 * pad - 3) // stride + 1)
+    n = int(np.prod(shape))
+    outs = []
+    for bw, off in ((None, 0), (torch.zeros(C, device=T.DEV), 0), (None, 1), (None, 3)):
+        raw = torch.full((n + 8,), -77.0, device=T.DEV)
+        y = raw[off:off + n].view(shape)
+        acc = torch.full((n + 8,), -77, dtype=torch.int32, device=T.DEV)
+        ep = B.Epilogue(1.1, 0.2, aw, bw, None, None)
+        B.ternary_depthwise_conv2d(ca, cw, batch, C, H, W, 3, 3, stride, pad, ep=ep, acc_out=acc[off:off + n].view(shape), y_out=y)
+        outs.append((y.clone(), acc[off:off + n].clone()))
+        assert (raw[:off] == -77).all() and (raw[off + n:] == -77).all() and (acc[:off] == -77).all() and (acc[off + n:] == -77).all()
+    for y, acc in outs[1:]:
+        assert torch.equal(y, outs[0][0]) and torch.equal(acc, outs[0][1])
+
+
 OTHER_NET_CONVS = [
     # MobileNet pointwise (1x1) layers, AlexNet's 5x5 and 3x3 layers (first layer stays fp32), NIN's 5x5 / 1x1
     wl.ConvShape("mobilenet.pw.64x128@56", 64, 56, 128, 1, 1, 0),
