@@ -12,6 +12,36 @@ struct Param {
     float s;
 };
 
+// Division of a 31-bit dividend by a fixed divisor as multiply-high + shift
+// (round-up magic number, exact for 0 <= n < 2^31); m == 0 encodes divisor 1.
+struct FastDiv {
+    uint32_t m, sh;
+};
+inline FastDiv make_fastdiv(uint32_t d)
+{
+    FastDiv f = {0, 0};
+    if (d <= 1) return f;
+    uint32_t L = 0;
+    while ((1ull << L) < d) ++L;
+    f.m = (uint32_t)(((1ull << (31 + L)) + d - 1) / d);
+    f.sh = L - 1;
+    return f;
+}
+__host__ __device__ inline uint32_t fastdiv(uint32_t n, FastDiv f)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return f.m ? (__umulhi(n, f.m) >> f.sh) : n;
+#else
+    return f.m ? (uint32_t)(((uint64_t)n * f.m) >> 32) >> f.sh : n;
+#endif
+}
+// The same without a branch on the divisor 1, for kernels whose time is their instructions.  (Not for k_tmm: without
+// those branches the compiler keeps the epilogue's coordinates in registers from the prologue on, 30 of which spill.)
+__device__ __forceinline__ uint32_t fastdiv_flat(uint32_t n, FastDiv f)
+{
+    return (__umulhi(n, f.m) + (n & (f.m ? 0u : ~0u))) >> f.sh;
+}
+
 struct PackArgs {
     const float* x;
     int64_t rows;     // ROWS: d0.  NCHW: unused
@@ -20,6 +50,7 @@ struct PackArgs {
     Param lo, hi;     // vector: per row (ROWS) / per d0 (NCHW)
     void* codes;
     int32_t* sum_t;   // nullable
+    FastDiv div_hw, div_groups;  // NCHW: by HW and by the groups of 64 channels (set by the launch code)
 };
 
 hipError_t launch_pack_rows_i8(const PackArgs& a, hipStream_t st);
@@ -71,30 +102,6 @@ struct EpiArgs {
     const float* bn_scale;  // nullable, per output column / channel
     const float* bn_shift;
 };
-
-// Division of a 31-bit dividend by a fixed divisor as multiply-high + shift
-// (round-up magic number, exact for 0 <= n < 2^31); m == 0 encodes divisor 1.
-struct FastDiv {
-    uint32_t m, sh;
-};
-inline FastDiv make_fastdiv(uint32_t d)
-{
-    FastDiv f = {0, 0};
-    if (d <= 1) return f;
-    uint32_t L = 0;
-    while ((1ull << L) < d) ++L;
-    f.m = (uint32_t)(((1ull << (31 + L)) + d - 1) / d);
-    f.sh = L - 1;
-    return f;
-}
-__host__ __device__ inline uint32_t fastdiv(uint32_t n, FastDiv f)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    return f.m ? (__umulhi(n, f.m) >> f.sh) : n;
-#else
-    return f.m ? (uint32_t)(((uint64_t)n * f.m) >> 32) >> f.sh : n;
-#endif
-}
 
 struct ConvGeom {
     int Nb, C, Cpad, H, W, O, KH, KW, stride, pad, OH, OW;

@@ -60,6 +60,8 @@ struct TmmParams {
     int ntiles;        // tilesP * tilesQ
     int band_tiles;    // 8 * tilesQ
     FastDiv div_band;
+    FastDiv div_lastband;  // by the P-tiles of the last band
+    FastDiv div_nax;       // conv: by the axis classes of the epilogue table in LDS
     int Klogical;      // K of the epilogue's constant term (GEMM)
     int hrows;         // halo variant: input pixels held in LDS (multiple of 16)
     ConvGeom g;        // conv only
@@ -139,6 +141,16 @@ __host__ __device__ inline int conv_axis_global(bool compact, int pad, int a)
 }
 __host__ __device__ inline int conv_table_bytes(int bp, const ConvGeom& g) { return (4 + conv_lds_classes(g)) * bp * 8; }
 
+// Taps of a window at i0 of an axis that lie in the image, one bit each.  (Closed form: a lane has this to do for
+// each of its pixels before it can load, and a launch on few blocks costs about 5 cycles per instruction of a wave.)
+__device__ __forceinline__ int tap_mask(int i0, int ksize, int extent)
+{
+    const int lo = i0 < 0 ? -i0 : 0;
+    int hi = extent - i0 < ksize ? extent - i0 : ksize;
+    hi = hi > lo ? hi : lo;
+    return (1 << hi) - (1 << lo);
+}
+
 // chunk swizzle of a 64-byte LDS row (depends on row & 15 only)
 __device__ __forceinline__ int swz(int row) { return ((row >> 1) & 3) ^ ((row >> 3) & 1); }
 
@@ -216,7 +228,7 @@ __device__ __forceinline__ bool block_tile(const TmmParams& prm, int& tileP, int
     const int band = (int)fastdiv((uint32_t)bid, prm.div_band);  // band = 8 * tilesQ tiles
     const int inband = bid - band * prm.band_tiles;
     const int bandw = prm.tilesP - band * 8 < 8 ? prm.tilesP - band * 8 : 8;
-    tileQ = bandw == 8 ? (inband >> 3) : inband / bandw;
+    tileQ = bandw == 8 ? (inband >> 3) : (int)fastdiv((uint32_t)inband, prm.div_lastband);
     tileP = band * 8 + inband - tileQ * bandw;
     return true;
 }
@@ -479,10 +491,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
             const int nb = (int)fastdiv((uint32_t)row, g.div_ohw), pix = row - nb * ohw;
             const int oh = (int)fastdiv((uint32_t)pix, g.div_ow), ow = pix - oh * g.OW;
             const int ih0 = oh * g.stride - g.pad, iw0 = ow * g.stride - g.pad;
-            int m = 0;
-            for (int k = 0; k < g.KH; ++k) m |= ((unsigned)(ih0 + k) < (unsigned)g.H) << k;
-            for (int k = 0; k < g.KW; ++k) m |= ((unsigned)(iw0 + k) < (unsigned)g.W) << (8 + k);
-            vmask[j] = m;
+            vmask[j] = tap_mask(ih0, g.KH, g.H) | tap_mask(iw0, g.KW, g.W) << 8;
             gQ[j] = prm.Q + (((int64_t)nb * g.H + ih0) * g.W + iw0) * g.Cpad + lchunk * 16;
         } else {
             offQ[j] = (unsigned)(row - q0) * (unsigned)prm.ldQ + lchunk * 16;
@@ -578,10 +587,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
             m = m < prm.RQ ? m : prm.RQ - 1;
             const int nb = (int)fastdiv((uint32_t)m, g.div_ohw), pix = m - nb * (g.OH * g.OW);
             const int oh = (int)fastdiv((uint32_t)pix, g.div_ow), ow = pix - oh * g.OW;
-            unsigned v = 0;
-            for (int k = 0; k < g.KH; ++k) v |= (unsigned)((unsigned)(oh + k - g.pad) < (unsigned)g.H) << k;
-            for (int k = 0; k < g.KW; ++k) v |= (unsigned)((unsigned)(ow + k - g.pad) < (unsigned)g.W) << (8 + k);
-            vmq[j] = v;
+            vmq[j] = (unsigned)(tap_mask(oh - g.pad, g.KH, g.H) | tap_mask(ow - g.pad, g.KW, g.W) << 8);
         }
     }
     int f_kh = 0, f_kw = 0, f_cc = 0, f_tapoff = 0;  // K position of the fragments being read
@@ -721,7 +727,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
             const int u = lin - row * (BP / 2);
             row = row < lrows ? row : lrows - 1;
             if (row >= 4) {
-                const int c = row - 4, ra = c / nax, ca = c - ra * nax;
+                const int c = row - 4, ra = (int)fastdiv((uint32_t)c, prm.div_nax), ca = c - ra * nax;
                 row = 4 + conv_axis_global(compact, g.pad, ra) * pp + conv_axis_global(compact, g.pad, ca);
             }
             int64_t idx = (int64_t)row * opitch + p0 + 2 * u;
@@ -1091,6 +1097,8 @@ inline unsigned tile_grid(TmmParams& prm, int bp, int bq)
     prm.ntiles = (int)blocks;
     prm.band_tiles = (int)(8 * tilesQ);
     prm.div_band = make_fastdiv((uint32_t)prm.band_tiles);
+    prm.div_lastband = make_fastdiv((uint32_t)(prm.tilesP & 7 ? prm.tilesP & 7 : 8));
+    prm.div_nax = make_fastdiv((uint32_t)conv_axis_classes(prm.g));
     return (unsigned)((blocks + 7) / 8 * 8);
 }
 

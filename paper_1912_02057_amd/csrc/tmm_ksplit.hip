@@ -36,6 +36,8 @@ namespace {
 struct KsplitParams {
     TmmParams t;
     FastDiv div_spt, div_kw;  // by the K-steps per tap and the window's width
+    FastDiv div_tp;           // by the tiles along P
+    int xcd_tiles;            // tiles of an XCD
     FastDiv div_upr;          // RUN: by the 16-byte units of a pixel's LDS row
     int runb;                 // RUN: LDS bytes of the pixel run, whole KiB
     int main;                 // LDS bytes in front of the pixel sums
@@ -76,8 +78,10 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
 
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int tileP, tileQ;
-    if (!block_tile(prm, tileP, tileQ)) return;
+    // one contiguous run of tiles per XCD, as block_tile(), in bands of any height
+    const int bid = (int)(blockIdx.x & 7) * kp.xcd_tiles + (int)(blockIdx.x >> 3);
+    if (bid >= prm.ntiles) return;
+    const int tileQ = (int)fastdiv_flat((uint32_t)bid, kp.div_tp), tileP = bid - tileQ * prm.tilesP;
     const int p0 = tileP * BP, q0 = tileQ * BQ;
     const bool want_ep = TERN || prm.y != nullptr;
     const int ohw = g.OH * g.OW;
@@ -98,21 +102,34 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
         row = row < prm.RP ? row : prm.RP - 1;  // tail rows: any valid data, never stored
         offP[i] = (unsigned)(row - p0) * (unsigned)prm.ldP + lchunk * 16;
     }
+    // conv: where output pixel q0 + 32 j + (lane & 31) is, its first tap's pixel and its taps in the image
+    int dnb[TQ], dpix[TQ], dih[TQ], diw[TQ], dcorner[TQ], dmask[TQ];
+#pragma unroll
+    for (int j = 0; j < TQ; ++j) {
+        dnb[j] = dpix[j] = dih[j] = diw[j] = dcorner[j] = dmask[j] = 0;
+        if (CONV) {
+            int m = q0 + j * 32 + (lane & 31);
+            m = m < prm.RQ ? m : prm.RQ - 1;
+            dnb[j] = (int)fastdiv_flat((uint32_t)m, g.div_ohw), dpix[j] = m - dnb[j] * ohw;
+            const int oh = (int)fastdiv_flat((uint32_t)dpix[j], g.div_ow), ow = dpix[j] - oh * g.OW;
+            dih[j] = oh * g.stride - g.pad, diw[j] = ow * g.stride - g.pad;
+            dcorner[j] = (dnb[j] * g.H + dih[j]) * g.W + diw[j];
+            dmask[j] = tap_mask(dih[j], g.KH, g.H) | tap_mask(diw[j], g.KW, g.W) << 8;
+        }
+    }
 #pragma unroll
     for (int j = 0; j < LQ; ++j) {
-        int row = q0 + 16 * j + lrow;
-        row = row < prm.RQ ? row : prm.RQ - 1;
         vmask[j] = 0;
         offQ[j] = 0;
         gQ[j] = nullptr;
         if (CONV) {
-            const int nb = (int)fastdiv((uint32_t)row, g.div_ohw), pix = row - nb * ohw;
-            const int oh = (int)fastdiv((uint32_t)pix, g.div_ow), ow = pix - oh * g.OW;
-            const int ih0 = oh * g.stride - g.pad, iw0 = ow * g.stride - g.pad;
-            for (int k = 0; k < g.KH; ++k) vmask[j] |= ((unsigned)(ih0 + k) < (unsigned)g.H) << k;
-            for (int k = 0; k < g.KW; ++k) vmask[j] |= ((unsigned)(iw0 + k) < (unsigned)g.W) << (8 + k);
-            gQ[j] = prm.Q + (((int64_t)nb * g.H + ih0) * g.W + iw0) * g.Cpad + lchunk * 16;
+            // (row 16 j + lrow of the tile: the lane that looked at it knows)
+            const int src = 16 * (j & 1) + lrow;
+            gQ[j] = prm.Q + (int64_t)__shfl(dcorner[j >> 1], src, 64) * g.Cpad + lchunk * 16;
+            vmask[j] = __shfl(dmask[j >> 1], src, 64);
         } else {
+            int row = q0 + 16 * j + lrow;
+            row = row < prm.RQ ? row : prm.RQ - 1;
             offQ[j] = (unsigned)(row - q0) * (unsigned)prm.ldQ + lchunk * 16;
         }
     }
@@ -123,9 +140,9 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
     int64_t koffP = (int64_t)first * 64, koffQ = koffP;
     const int spt = CONV ? g.Cpad >> 6 : prm.nk;  // steps per tap
     if (CONV) {
-        const int tap = (int)fastdiv((uint32_t)first, kp.div_spt);
+        const int tap = (int)fastdiv_flat((uint32_t)first, kp.div_spt);
         cc = first - tap * spt;
-        kh = (int)fastdiv((uint32_t)tap, kp.div_kw);
+        kh = (int)fastdiv_flat((uint32_t)tap, kp.div_kw);
         kw = tap - kh * g.KW;
         koffQ = (int64_t)(kh * g.W + kw) * g.Cpad + cc * 64;
     }
@@ -175,19 +192,6 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
     // same flattened index space: the tile's inputs are one run of pixels, loaded once, and a tap is a row offset.
     // An LDS row is the pixel's codes and 16 bytes more: an odd number of 16-byte units, so that 16 consecutive
     // rows lie in different banks whatever the channels.
-    unsigned vrun[TQ];  // as vmask, for this lane's pixel of fragment j
-#pragma unroll
-    for (int j = 0; j < TQ; ++j) {
-        vrun[j] = 0;
-        if (RUN) {
-            int m = q0 + j * 32 + (lane & 31);
-            m = m < prm.RQ ? m : prm.RQ - 1;
-            const int nb = (int)fastdiv((uint32_t)m, g.div_ohw), pix = m - nb * ohw;
-            const int oh = (int)fastdiv((uint32_t)pix, g.div_ow), ow = pix - oh * g.OW;
-            for (int k = 0; k < g.KH; ++k) vrun[j] |= (unsigned)((unsigned)(oh + k - g.pad) < (unsigned)g.H) << k;
-            for (int k = 0; k < g.KW; ++k) vrun[j] |= (unsigned)((unsigned)(ow + k - g.pad) < (unsigned)g.W) << (8 + k);
-        }
-    }
     if (RUN) {
         const int total_px = g.Nb * g.H * g.W, first_px = q0 - g.pad * (g.W + 1), upr = pitch >> 4;
         for (int u = wave; u < kp.runb >> 10; u += W) {
@@ -250,7 +254,7 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
             const int u = lin - row * (BP / 2);
             row = row < lrows ? row : lrows - 1;
             if (row >= 4) {
-                const int c = row - 4, ra = c / nax, ca = c - ra * nax;
+                const int c = row - 4, ra = (int)fastdiv_flat((uint32_t)c, prm.div_nax), ca = c - ra * nax;
                 row = 4 + conv_axis_global(compact, g.pad, ra) * pp + conv_axis_global(compact, g.pad, ca);
             }
             int64_t idx = (int64_t)row * opitch + p0 + 2 * u;
@@ -298,16 +302,14 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
             }
     }
     if (CONV) {
-        const int nb = (int)fastdiv((uint32_t)qq, g.div_ohw), pix = qq - nb * ohw;
+        const int nb = TQ == 2 && jq ? dnb[TQ - 1] : dnb[0], pix = TQ == 2 && jq ? dpix[TQ - 1] : dpix[0];
         obase = (int64_t)nb * g.O * ohw + pix;
         if (want_ep && !g.code_zero_pad) {
-            const int oh = (int)fastdiv((uint32_t)pix, g.div_ow), ow = pix - oh * g.OW;
-            int khl, khh, kwl, kwh;
-            tap_range(oh, g.stride, g.pad, g.KH, g.H, khl, khh);
-            tap_range(ow, g.stride, g.pad, g.KW, g.W, kwl, kwh);
+            const int ih0 = TQ == 2 && jq ? dih[TQ - 1] : dih[0], iw0 = TQ == 2 && jq ? diw[TQ - 1] : diw[0];
+            const int bh = ih0 + g.KH - g.H, bw = iw0 + g.KW - g.W;  // taps cut off at the far ends
             const bool compact = conv_compact(g);
-            cls = conv_axis_class(compact, g.pad, khl, g.KH - 1 - khh) * nax +
-                  conv_axis_class(compact, g.pad, kwl, g.KW - 1 - kwh);
+            cls = conv_axis_class(compact, g.pad, ih0 < 0 ? -ih0 : 0, bh > 0 ? bh : 0) * nax +
+                  conv_axis_class(compact, g.pad, iw0 < 0 ? -iw0 : 0, bw > 0 ? bw : 0);
         }
         if (TERN)
 #pragma unroll
@@ -340,7 +342,7 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
             for (int j = 0; j < TQ; ++j) {
                 if constexpr (RUN) {
                     const int row = j * 32 + (lane & 31) + f_kh * g.W + f_kw;
-                    const bool ok = ((vrun[j] >> f_kh) & (vrun[j] >> (8 + f_kw)) & 1) != 0;
+                    const bool ok = ((dmask[j] >> f_kh) & (dmask[j] >> (8 + f_kw)) & 1) != 0;
                     fb[ks][j] = *(const v4i*)(smem + (ok ? W * RING + row * pitch + f_cc * 64 + (ks * 2 + half) * 16 : zoff));
                 } else {
                     fb[ks][j] = *(const v4i*)(st + fragQ[j][ks]);
@@ -516,6 +518,8 @@ hipError_t launch(KsplitParams& kp, const KsplitShape& s, hipStream_t st)
     if (e != hipSuccess) return e;
     const unsigned grid = tile_grid(kp.t, 32 * f.tp, 32 * f.tq);
     if (!grid) return hipErrorInvalidValue;
+    kp.div_tp = make_fastdiv((uint32_t)kp.t.tilesP);
+    kp.xcd_tiles = (int)(grid / 8);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * f.waves), (size_t)ksplit_lds_bytes(f, s), st, kp);
     return hipGetLastError();
 }

@@ -128,11 +128,9 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
         const int r = ((wave + NW * i) % NSEG) * 64 + lane;
         if (GATHER) {
             const int m = q0 + r < prm.t.RQ ? q0 + r : prm.t.RQ - 1;
-            int ih0, iw0, nb, v = 0;
+            int ih0, iw0, nb;
             origin(m, ih0, iw0, nb);
-            for (int k = 0; k < g.KH; ++k) v |= ((unsigned)(ih0 + k) < (unsigned)g.H) << k;
-            for (int k = 0; k < g.KW; ++k) v |= ((unsigned)(iw0 + k) < (unsigned)g.W) << (8 + k);
-            tmask[i] = v;
+            tmask[i] = tap_mask(ih0, g.KH, g.H) | tap_mask(iw0, g.KW, g.W) << 8;
             if (BIG)  // (+ the tap's offset: in range when the tap is in the image)
                 voff[i] = (Off)(((int64_t)(nb - onb) * g.C * HW + (int64_t)ih0 * g.W + iw0) * 4);
             else
@@ -254,11 +252,7 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
             int ih0, iw0, nb;
             origin(m, ih0, iw0, nb);
             row0[j] = (nb * g.H + ih0) * g.W + iw0 - imin;
-            unsigned v = 0;
-#pragma unroll
-            for (int k = 0; k < KK; ++k)
-                v |= (unsigned)((unsigned)(ih0 + k) < (unsigned)g.H) << k | (unsigned)((unsigned)(iw0 + k) < (unsigned)g.W) << (8 + k);
-            vm[j] = v;
+            vm[j] = (unsigned)(tap_mask(ih0, KK, g.H) | tap_mask(iw0, KK, g.W) << 8);
         }
     }
     // the channels' epilogue factors: rows alpha, BN scale, BN shift of the prepared table
