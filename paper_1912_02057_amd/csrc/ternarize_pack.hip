@@ -237,119 +237,33 @@ __global__ __launch_bounds__(256) void k_pack_nchw_i8(PackArgs a)
     for (int e = threadIdx.x; e < chunks; e += 256) *(uint4*)(out + (size_t)e * 16) = *(const uint4*)(tile + (size_t)e * 16);
 }
 
-// ---- NCHW layout, int8 codes, 16-byte loads ---------------------------------
-// Variant for H*W % 4 == 0 and a 16-byte aligned input.  A block owns
+// ---- NCHW layout, 16-byte loads ---------------------------------------------------
+// For H*W % 4 == 0.  A block owns
 // PB = 4*LPR consecutive pixels; LPR lanes read one channel's run of them with
-// one 16-byte load each (lane l: pixels 4q..4q+3, q = l % LPR), and the
-// SUBS = 64/LPR lane groups of a wave read channels 16 apart.  Channels go in
-// groups of 64*SUBS: wave w, lane group s take channels 16*(w*SUBS+s) .. +15 of
-// the group, so a lane ends up with, for each of its 4 pixels, 16 code bytes
+// one 16-byte load each (lane l: pixels 4q..4q+3, q = l % LPR; a load of several dwords needs 4-byte alignment
+// only), and the SUBS = 64/LPR lane groups of a wave read channels 16 apart.  Channels go in
+// groups of CG = 64*SUBS: wave w, lane group s take channels 16*(w*SUBS+s) .. +15 of
+// the group, so a lane ends up with, for each of its 4 pixels, 16 codes
 // that are contiguous in the channel-innermost output.  They are parked in a
-// PB x (64*SUBS)-byte LDS image (always 16 KiB; 16-byte slots XOR-swizzled by
+// PB-pixel LDS image (always 16 KiB, FP4 8; slots of 16 codes, XOR-swizzled by
 // the pixel quad to spread banks) and streamed out with consecutive lanes
-// writing consecutive 16-byte pieces of a pixel's 64*SUBS contiguous bytes.
+// writing consecutive pieces of a pixel's contiguous bytes.
 // LPR = 64 gives the widest pixel runs; the smaller ones trade them for more
 // blocks (a tensor with few pixels and many channels) and fewer passes.
-// FP4: the same with 8-byte slots (16 channels = 8 bytes), i.e. an 8 KiB LDS image.
-template <int LPR, bool FP4>
-__global__ __launch_bounds__(256) void k_pack_nchw_i8_v4(PackArgs a)
-{
-    constexpr int SUBS = 64 / LPR, PB = 4 * LPR, SLOT = FP4 ? 8 : 16, NSLOT = 4 * SUBS, RB = SLOT * NSLOT;
-    constexpr int CG = 64 * SUBS;  // channels per group
-    __shared__ __attribute__((aligned(16))) uint8_t tile[PB * RB];
-    __shared__ int part[4 * SUBS][PB];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int quad = lane % LPR, cblk = wave * SUBS + lane / LPR;
-    const int64_t total = a.N * a.HW;
-    const int64_t q0 = (int64_t)blockIdx.x * PB, q = q0 + 4 * quad;
-    const bool pin = q < total;  // total % 4 == 0: all four pixels or none
-    const int64_t n = pin ? q / a.HW : 0;
-    const int64_t p = pin ? q - n * a.HW : 0;
-    const float lo = thr(a.lo, n), hi = thr(a.hi, n);
-    const float* xn = a.x + n * a.K * a.HW + p;
-    const int ngroup = (int)((a.Kpad + CG - 1) / CG);
-    const int64_t valid = total - q0 < PB ? total - q0 : PB;
-    const int64_t rowb = FP4 ? a.Kpad >> 1 : a.Kpad;
-    uint8_t* out = (uint8_t*)a.codes + q0 * rowb;
-    int sum[4] = {0, 0, 0, 0};
-    for (int cg = 0; cg < ngroup; ++cg) {
-        float4 v[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int64_t c = (int64_t)cg * CG + cblk * 16 + j;
-            v[j] = (pin && c < a.K) ? *(const float4*)(xn + c * a.HW) : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        uint32_t w4[4][4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) w4[i][k] = 0;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int64_t c = (int64_t)cg * CG + cblk * 16 + j;
-            const bool ok = pin && c < a.K;
-            const float e[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int t = ok ? tern(e[i], lo, hi) : 0;
-                sum[i] += t;
-                if (FP4)
-                    w4[i][j >> 3] |= nib(t) << (4 * (j & 7));
-                else
-                    w4[i][j >> 2] |= (uint32_t)(t & 0xff) << (8 * (j & 3));
-            }
-        }
-        if (cg > 0) __syncthreads();  // previous group fully streamed out
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            uint8_t* slot = tile + (4 * quad + i) * RB + (cblk ^ (quad & (NSLOT - 1))) * SLOT;
-            if (FP4)
-                *(uint2*)slot = make_uint2(w4[i][0], w4[i][1]);
-            else
-                *(uint4*)slot = make_uint4(w4[i][0], w4[i][1], w4[i][2], w4[i][3]);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < PB * NSLOT / 256; ++k) {
-            const int e = tid + 256 * k, px = e / NSLOT, pp = e % NSLOT;
-            const int logical = pp ^ ((px >> 2) & (NSLOT - 1));
-            const int64_t cbyte = (int64_t)cg * RB + logical * SLOT;  // the last group may overhang the row
-            if (px < valid && cbyte < rowb) {
-                if (FP4)
-                    *(uint2*)(out + (size_t)px * rowb + cbyte) = *(const uint2*)(tile + e * SLOT);
-                else
-                    *(uint4*)(out + (size_t)px * rowb + cbyte) = *(const uint4*)(tile + e * SLOT);
-            }
-        }
-    }
-    if (a.sum_t) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) part[cblk][4 * quad + i] = sum[i];
-        __syncthreads();
-        if (tid < valid && tid < PB) {
-            int s = 0;
-#pragma unroll
-            for (int b = 0; b < 4 * SUBS; ++b) s += part[b][tid];
-            a.sum_t[q0 + tid] = s;
-        }
-    }
-}
-
-// ---- NCHW layout, the common case in straight-line form ------------------------
-// The kernel above spends more time in the vector ALU than in memory (bounds
-// selects and 64-bit address arithmetic per element).  This one is for tensors
-// where none of that is needed: H*W % 4 == 0, C a multiple of the block's channel
-// group CG = 64*SUBS, the whole tensor below 4 GiB (a lane's byte offset fits 32
-// bits and is added to a wave-uniform base, so a load costs no vector instruction
-// besides itself).  Same tiling and LDS image as above.  Per element: two
+// HBM-bound, as long as little is done per element: a lane's byte offset fits 32
+// bits and is added to a wave-uniform base, so that a load costs no vector instruction
+// besides itself; two
 // compares, two selects and an OR into the code word when the thresholds are
 // ordered (ORDERED: scalar thresholds, lo <= hi checked by the entry point, so
 // x > hi and x < lo exclude each other), else the subtract form.  The side sum is
-// taken from the packed words (SUM).  An FP4 row whose padding exceeds the last
-// group (C % 128 == 64) gets its zero half written directly.
-template <int LPR, bool FP4, bool SUM, bool ORDERED>
-__global__ __launch_bounds__(256) void k_pack_nchw_fast(PackArgs a)
+// taken from the packed words (SUM).
+//  PART: the channels are not a multiple of CG; those past the last read the last and get code 0.  us, FP4, against the
+//  kernel with bounds selects and 64-bit addresses per element that it replaced: 64 x 32 x 112 x 112 38.0 -> 24.9,
+//  50 x 25 x 64 x 64 13.2 -> 8.2, 70 x 107 x 42 x 42 13.9 -> 12.0.
+template <int LPR, bool FP4, bool SUM, bool ORDERED, bool PART>
+__global__ __launch_bounds__(256) void k_pack_nchw(PackArgs a)
 {
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
     constexpr int SUBS = 64 / LPR, PB = 4 * LPR, SLOT = FP4 ? 8 : 16, NSLOT = 4 * SUBS, RB = SLOT * NSLOT;
     constexpr int CG = 64 * SUBS;
     constexpr int NW = FP4 ? 2 : 4;  // code words per pixel and lane
@@ -357,26 +271,33 @@ __global__ __launch_bounds__(256) void k_pack_nchw_fast(PackArgs a)
     __shared__ int part[SUM ? 4 * SUBS : 1][SUM ? PB : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int quad = lane % LPR, cblk = wave * SUBS + lane / LPR;
-    const int64_t total = a.N * a.HW;
-    const int64_t q0 = (int64_t)blockIdx.x * PB;
-    int64_t q = q0 + 4 * quad;
+    const int total = (int)(a.N * a.HW);
+    const int q0 = (int)blockIdx.x * PB;
+    int q = q0 + 4 * quad;
     q = q < total ? q : total - 4;  // total % 4 == 0; lanes past the end redo the last quad, never stored
     const int HW = (int)a.HW, K = (int)a.K;
-    const int n = (int)(q / HW), p = (int)(q - (int64_t)n * HW);
+    const int n = (int)fastdiv_flat((uint32_t)q, a.div_hw), p = q - n * HW;
+    const int n0 = (int)fastdiv_flat((uint32_t)q0, a.div_hw);  // the block's first image: offsets are from there
+    const float* const x0 = a.x + (int64_t)n0 * K * HW;
     const float lo = thr(a.lo, n), hi = thr(a.hi, n);
-    const uint32_t off = (uint32_t)((((int64_t)n * K + cblk * 16) * HW + p) * 4);
-    const int ngroup = K / CG;
-    const int64_t valid = total - q0 < PB ? total - q0 : PB;
+    const uint32_t off = ((uint32_t)((n - n0) * K + (PART ? 0 : cblk * 16)) * (uint32_t)HW + (uint32_t)p) * 4u;
+    const int ngroup = PART ? (K + CG - 1) / CG : K / CG;
+    const int valid = total - q0 < PB ? total - q0 : PB;
     const int rowb = (int)(FP4 ? a.Kpad >> 1 : a.Kpad);
-    uint8_t* out = (uint8_t*)a.codes + q0 * rowb;
+    uint8_t* out = (uint8_t*)a.codes + (int64_t)q0 * rowb;
     int sum[4] = {0, 0, 0, 0}, usum[4] = {0, 0, 0, 0};
     (void)usum;
     for (int cg = 0; cg < ngroup; ++cg) {
-        float4 v[16];
+        f4 v[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const float* base = a.x + (int64_t)(cg * CG + j) * HW;  // wave-uniform
-            v[j] = *(const float4*)((const char*)base + off);
+            if (PART) {
+                const int c = cg * CG + cblk * 16 + j;
+                v[j] = *(const f4*)((const char*)x0 + (off + (uint32_t)(c < K ? c : K - 1) * (uint32_t)HW * 4u));
+            } else {
+                const float* base = x0 + (int64_t)(cg * CG + j) * HW;  // wave-uniform
+                v[j] = *(const f4*)((const char*)base + off);
+            }
         }
         uint32_t w[4][NW];
 #pragma unroll
@@ -385,18 +306,18 @@ __global__ __launch_bounds__(256) void k_pack_nchw_fast(PackArgs a)
             for (int k = 0; k < NW; ++k) w[i][k] = 0;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const float e[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
             const int sh = FP4 ? 4 * (j & 7) : 8 * (j & 3);
-            const uint32_t cp = (FP4 ? 0x2u : 0x01u) << sh, cn = (FP4 ? 0xAu : 0xFFu) << sh;
+            const bool cok = !PART || cg * CG + cblk * 16 + j < K;
+            const uint32_t cp = cok ? (FP4 ? 0x2u : 0x01u) << sh : 0u, cn = cok ? (FP4 ? 0xAu : 0xFFu) << sh : 0u;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 uint32_t c;
                 if (ORDERED) {
-                    c = e[i] > hi ? cp : 0u;
-                    c = e[i] < lo ? cn : c;
+                    c = v[j][i] > hi ? cp : 0u;
+                    c = v[j][i] < lo ? cn : c;
                 } else {
                     // t in {-1, 0, 1}: the int8 code is t's low byte, the FP4 code (t << 1) & 0xA
-                    c = ((uint32_t)tern(e[i], lo, hi) << (FP4 ? sh + 1 : sh)) & cn;
+                    c = ((uint32_t)tern(v[j][i], lo, hi) << (FP4 ? sh + 1 : sh)) & cn;
                 }
                 w[i][FP4 ? j >> 3 : j >> 2] |= c;
             }
@@ -428,8 +349,8 @@ __global__ __launch_bounds__(256) void k_pack_nchw_fast(PackArgs a)
         for (int k = 0; k < PB * NSLOT / 256; ++k) {
             const int e = tid + 256 * k, px = e / NSLOT, pp = e % NSLOT;
             const int logical = pp ^ ((px >> 2) & (NSLOT - 1));
-            const int cbyte = cg * RB + logical * SLOT;
-            if (px < valid) {
+            const int cbyte = cg * RB + logical * SLOT;  // (PART: the last group may overhang the row)
+            if (px < valid && (!PART || cbyte < rowb)) {
                 if (FP4)
                     *(uint2*)(out + (size_t)px * rowb + cbyte) = *(const uint2*)(tile + e * SLOT);
                 else
@@ -461,6 +382,80 @@ __global__ __launch_bounds__(256) void k_pack_nchw_fast(PackArgs a)
             for (int b = 0; b < 4 * SUBS; ++b) s += part[b][tid];
             a.sum_t[q0 + tid] = s;
         }
+    }
+}
+
+// ---- NCHW layout, few pixels -----------------------------------------------------------
+// One image is a handful of blocks of the kernels around, each lane with dozens of elements one after the other.  Here a
+// block has 64 pixels x 64 channels and a lane 4 x 4 of them.  The blocks of the same pixels run on one XCD: their pieces of
+// a line meet in its L2.  Any H*W of at least 4 (a quad that begins in one image and ends in the next reads the last
+// 4 pixels of the one and the first 4 of the other and shifts them into place) and any number of channels; scalar
+// thresholds, tensors below 4 GiB, no sums.
+template <bool FP4>
+__global__ __launch_bounds__(256) void k_pack_nchw_small(PackArgs a)
+{
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+    constexpr int RB = FP4 ? 32 : 64;
+    __shared__ __attribute__((aligned(16))) uint8_t tile[64 * RB];
+    const int tid = threadIdx.x, quad = tid & 15, c4 = tid >> 4;
+    const int total = (int)(a.N * a.HW), HW = (int)a.HW, K = (int)a.K, ngroup = (K + 63) >> 6;
+    const int xi = (int)fastdiv_flat(blockIdx.x >> 3, a.div_groups), cg = (int)(blockIdx.x >> 3) - xi * ngroup;
+    const int q0 = (xi * 8 + (int)(blockIdx.x & 7)) * 64;
+    if (q0 >= total) return;
+    int q = q0 + 4 * quad;
+    q = q < total ? q : total - 1;  // lanes past the end read some pixel's quad, never stored
+    const int n = (int)fastdiv_flat((uint32_t)q, a.div_hw), p = q - n * HW;
+    const int pa = p < HW - 4 ? p : HW - 4, shift = p - pa;
+    const float lo = a.lo.s, hi = a.hi.s;
+    const int rowb = (int)(FP4 ? a.Kpad >> 1 : a.Kpad);
+    const int valid = total - q0 < 64 ? total - q0 : 64;
+    uint8_t* out = (uint8_t*)a.codes + (int64_t)q0 * rowb;
+    f4 v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int c = cg * 64 + c4 * 4 + j;
+        v[j] = *(const f4*)((const char*)a.x + (uint32_t)(((n * K + (c < K ? c : K - 1)) * HW + pa) * 4));
+    }
+    if (__any(shift)) {
+        f4 b[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int c = cg * 64 + c4 * 4 + j;
+            b[j] = v[j];
+            if (shift && n + 1 < (int)a.N)  // (behind the last image nothing is stored)
+                b[j] = *(const f4*)((const char*)a.x + (uint32_t)((((n + 1) * K + (c < K ? c : K - 1)) * HW) * 4));
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float c[8] = {v[j][0], v[j][1], v[j][2], v[j][3], b[j][0], b[j][1], b[j][2], b[j][3]};
+            float t[6];
+#pragma unroll
+            for (int e = 0; e < 6; ++e) t[e] = shift & 1 ? c[e + 1] : c[e];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[j][e] = shift & 2 ? t[e + 2] : t[e];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int t = cg * 64 + c4 * 4 + j < K ? tern(v[j][i], lo, hi) : 0;
+            w |= FP4 ? nib(t) << (4 * j) : (uint32_t)(t & 0xff) << (8 * j);
+        }
+        if (FP4)
+            *(uint16_t*)(tile + (4 * quad + i) * RB + c4 * 2) = (uint16_t)w;
+        else
+            *(uint32_t*)(tile + (4 * quad + i) * RB + c4 * 4) = w;
+    }
+    __syncthreads();
+    if (tid < 64 * RB / 16) {
+        const int px = tid / (RB / 16), cbyte = cg * RB + tid % (RB / 16) * 16;
+        if (px < valid) *(uint4*)(out + (size_t)px * rowb + cbyte) = *(const uint4*)(tile + tid * 16);
+    } else if (FP4 && cg == ngroup - 1 && ngroup * RB < rowb) {
+        // the zero codes behind the last group (FP4 rows are padded to 128 codes)
+        const int e = tid - 64 * RB / 16;
+        if (e / 2 < valid) *(uint4*)(out + (size_t)(e / 2) * rowb + ngroup * RB + e % 2 * 16) = make_uint4(0, 0, 0, 0);
     }
 }
 
@@ -636,43 +631,43 @@ hipError_t launch_pack_nchw_codes(const PackArgs& a, hipStream_t st)
 {
     const size_t smem = (size_t)64 * (FP4 ? a.Kpad / 2 : a.Kpad);  // LDS image of the block's output run
     if (smem > 128 * 1024) return hipErrorInvalidValue;
-    if (a.HW % 4 == 0 && ((uintptr_t)a.x) % 16 == 0 && a.K % 64 == 0 && a.N * a.K * a.HW < ((int64_t)1 << 30)) {
-        // straight-line kernel; the widest pixel runs that still give every CU several blocks
-        const int64_t px = a.N * a.HW;
-        const int lpr = (a.K % 256 == 0 && px < 2048 * 256) ? 16 : (a.K % 128 == 0 && px < 4096 * 256) ? 32 : 64;
-        const bool ordered = !a.lo.ptr && !a.hi.ptr, sum = a.sum_t != nullptr;
-        const dim3 grid((unsigned)((px + 4 * lpr - 1) / (4 * lpr)));
-        auto go = [&](auto L, auto S, auto O) {
-            hipLaunchKernelGGL((k_pack_nchw_fast<decltype(L)::value, FP4, decltype(S)::value, decltype(O)::value>), grid,
-                               dim3(256), 0, st, a);
-        };
-        auto go2 = [&](auto L) {
-            using T = std::true_type;
-            using F = std::false_type;
-            if (sum)
-                ordered ? go(L, T{}, T{}) : go(L, T{}, F{});
-            else
-                ordered ? go(L, F{}, T{}) : go(L, F{}, F{});
-        };
-        if (lpr == 16)
-            go2(std::integral_constant<int, 16>{});
-        else if (lpr == 32)
-            go2(std::integral_constant<int, 32>{});
-        else
-            go2(std::integral_constant<int, 64>{});
+    const bool ordered = !a.lo.ptr && !a.hi.ptr, sum = a.sum_t != nullptr;
+    const int64_t px = a.N * a.HW;
+    PackArgs b = a;
+    b.div_hw = make_fastdiv((uint32_t)a.HW);
+    // Few pixels and many channels, where the other kernels are a few blocks of many rounds.  us, FP4, those -> this one:
+    //   3 x 771 x 11 x 11  18.2 -> 7.1     8 x 866 x 5 x 5  18.4 -> 8.1     1 x 948 x 62 x 62  10.8 -> 7.9
+    //   1 x 512 x 7 x 7  4.8 -> 5.0, 2 x 163 x 85 x 85  7.5 -> 5.9 but 30 x 48 x 62 x 62  7.3 -> 9.7: not taken
+    if (ordered && !sum && a.HW >= 4 && a.N * a.K * a.HW < ((int64_t)1 << 30) && px <= 4096 && a.K > 512) {
+        const int64_t groups = (a.K + 63) / 64;
+        b.div_groups = make_fastdiv((uint32_t)groups);
+        hipLaunchKernelGGL(k_pack_nchw_small<FP4>, dim3((unsigned)((px + 511) / 512 * 8 * groups)), dim3(256), 0, st, b);
         return hipGetLastError();
     }
-    if (a.HW % 4 == 0 && ((uintptr_t)a.x) % 16 == 0) {
-        // widest pixel runs that still give every CU several blocks and one pass over
-        // the channels where the row is long enough
-        const int64_t px = a.N * a.HW;
-        if (a.Kpad >= 256 && px < 2048 * 256) {
-            hipLaunchKernelGGL((k_pack_nchw_i8_v4<16, FP4>), dim3((unsigned)((px + 63) / 64)), dim3(256), 0, st, a);
-        } else if (a.Kpad >= 128 && px < 4096 * 256) {
-            hipLaunchKernelGGL((k_pack_nchw_i8_v4<32, FP4>), dim3((unsigned)((px + 127) / 128)), dim3(256), 0, st, a);
-        } else {
-            hipLaunchKernelGGL((k_pack_nchw_i8_v4<64, FP4>), dim3((unsigned)((px + 255) / 256)), dim3(256), 0, st, a);
-        }
+    if (a.HW % 4 == 0 && a.K * (2 * a.HW + 256) < ((int64_t)1 << 30)) {  // (32-bit offsets from a block's first image)
+        // the widest pixel runs that still give every CU several blocks
+        const int lpr = (a.Kpad >= 256 && px < 2048 * 256) ? 16 : (a.Kpad >= 128 && a.K > 64 && px < 4096 * 256) ? 32 : 64;
+        const bool part = a.K % (64 * 64 / lpr) != 0;
+        const dim3 grid((unsigned)((px + 4 * lpr - 1) / (4 * lpr)));
+        const std::true_type yes{};
+        const std::false_type no{};
+        auto go = [&](auto L, auto S, auto O, auto P) {
+            hipLaunchKernelGGL((k_pack_nchw<decltype(L)::value, FP4, decltype(S)::value, decltype(O)::value, decltype(P)::value>),
+                               grid, dim3(256), 0, st, b);
+        };
+        auto go2 = [&](auto L, auto S) {
+            if (part)
+                ordered ? go(L, S, yes, yes) : go(L, S, no, yes);
+            else
+                ordered ? go(L, S, yes, no) : go(L, S, no, no);
+        };
+        auto go1 = [&](auto L) { sum ? go2(L, yes) : go2(L, no); };
+        if (lpr == 16)
+            go1(std::integral_constant<int, 16>{});
+        else if (lpr == 32)
+            go1(std::integral_constant<int, 32>{});
+        else
+            go1(std::integral_constant<int, 64>{});
         return hipGetLastError();
     }
     // small images with H*W % 4 != 0: one block per image over the flat C*H*W run

@@ -145,6 +145,30 @@ def test_pack_nchw_straight_line_kernel(shape):
             assert s2 is None and (codes2.cpu().numpy() == want).all()
 
 
+@pytest.mark.parametrize("shape", [(3, 771, 11, 11), (8, 513, 5, 5), (1, 640, 8, 8), (5, 520, 3, 9), (2, 600, 2, 2),   # few pixels, many channels
+                                   (2, 65, 10, 10), (3, 33, 30, 34), (1, 250, 20, 20), (40, 129, 2, 2)])              # channels beyond a group
+def test_pack_nchw_forms(shape):
+    """The pack for few pixels (quads that span two images, a group of channels cut off) and the one for channels that are no
+    multiple of its groups; inputs at any multiple of 4 bytes."""
+    _say("pack_nchw forms %s" % (shape,))
+    rng = np.random.default_rng(5 + sum(shape))
+    x = rng.standard_normal(shape).astype(np.float32)
+    x.flat[1], x.flat[2], x.flat[-1] = np.nan, np.inf, -np.inf
+    lo, hi = np.float32(-0.7), np.float32(0.5)
+    t = orc.ternarize(x, lo, hi)
+    nhwc = orc.nchw_to_nhwc_i8(t, shape[1])
+    for off in (0, 1):
+        raw = torch.zeros(x.size + 4, dtype=torch.float32, device=T.DEV)
+        xd = raw[off:off + x.size].view(shape)
+        xd.copy_(T.dev(x))
+        for fmt in (B.RTN_CODE_FP4, B.RTN_CODE_I8):
+            want = T.fp4_rows(nhwc) if fmt == B.RTN_CODE_FP4 else orc.nchw_to_nhwc_i8(t, (shape[1] + 63) // 64 * 64)
+            codes, s = B.ternarize_pack(xd, lo, hi, fmt, want_sum=False)
+            assert s is None and (codes.cpu().numpy() == want).all()
+            codes, s = B.ternarize_pack(xd, lo, hi, fmt)
+            assert (codes.cpu().numpy() == want).all() and (s.cpu().numpy() == orc.pixel_sums(t)).all()
+
+
 # ------------------------------------------------------ S2 + S4: GEMM -------
 GEMM_SHAPES = [(1, 1, 1), (37, 19, 131), (64, 64, 64), (65, 33, 64), (300, 200, 576), (129, 257, 1000),
                (512, 384, 2048), (1024, 1024, 512)]
