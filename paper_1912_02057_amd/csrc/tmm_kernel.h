@@ -42,6 +42,7 @@
 // over several translation units (tmm_inst_*.hip) so that they compile in parallel.
 #pragma once
 #include <type_traits>
+#include <utility>
 
 #include "choice.h"
 #include "epilogue_math.h"
@@ -189,6 +190,30 @@ __device__ __forceinline__ const int8_t* uniform_ptr(const int8_t* p)
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
     return (const int8_t*)(uintptr_t)(((uint64_t)hi << 32) | lo);
+}
+
+// Direct global -> LDS load through a buffer resource: lane byte offset `voff` (32 bits) plus the wave-uniform `soff` on a
+// scalar base.  Nothing is added per lane and load, the LDS address is one scalar addition, and a lane with an offset from
+// kOutside on reads nothing: zeros land in its 16 bytes.
+constexpr unsigned kOutside = 0x80000000u;
+__device__ __forceinline__ v4i buffer_base(const int8_t* p)
+{
+    const uint64_t v = (uint64_t)(uintptr_t)p;
+    return v4i{(int)__builtin_amdgcn_readfirstlane((uint32_t)v), (int)(__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) & 0xffff),
+               (int)kOutside, 0x00020000};
+}
+template <int OFF>
+__device__ __forceinline__ void dma_buf(v4i rsrc, unsigned voff, unsigned soff, unsigned lds_off)
+{
+    asm volatile("s_add_u32 m0, %0, %1\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds" ::"s"(__builtin_amdgcn_readfirstlane(lds_off)),
+                 "n"(OFF), "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff))
+                 : "memory", "scc");
+}
+
+template <class F, int... N>
+__device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int, N...>)
+{
+    (f(std::integral_constant<int, N>{}), ...);
 }
 
 template <int N>
@@ -417,7 +442,7 @@ __device__ __forceinline__ void gemm_epilogue(const TmmParams& prm, double* tab,
 // no scaling): a lane's 16 operand bytes are 32 codes of one row, everything else is
 // byte for byte the int8 form.  Which 32 of a K-step's 128 codes a lane holds, and in
 // which nibble order, is the same for both operands, so the sum over k is unaffected.
-template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0, bool NT = false>
+template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0, bool NT = false, bool BIG = false>
 __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
 {
     static_assert(DT != 1 || !CONV, "bf16 operands: GEMM only");
@@ -464,11 +489,12 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     // chunk (l & 3) of that row.
     const int lrow = lane >> 2;
     const int lchunk = (lane & 3) ^ swz(lrow);
-    // Dense operands: block-uniform base + per-lane offset (at most 256 rows of
-    // at most 2^22 bytes).  The conv's Q operand needs a pointer per lane, since
-    // an out-of-image tap is redirected to the zero page.
-    const int8_t* baseP = prm.P + (int64_t)p0 * prm.ldP;
-    const int8_t* baseQ = CONV ? prm.Q : prm.Q + (int64_t)q0 * prm.ldQ;
+    // A block-uniform base and a 32-bit offset per lane (at most 256 rows of at most 2^22 bytes).  The conv's Q operand
+    // is counted from its tile's first image and from `bias` bytes before it, where the first tap of a corner pixel lies,
+    // so that no offset is negative; a tap outside the image gets one that reads nothing.  BIG: images for which
+    // 32 bits do not suffice (and the 64 x 64 tile, which is always there) take a pointer per lane, the zero page for
+    // such a tap, and five more instructions per load.
+    const v4i rsrcP = buffer_base(prm.P + (int64_t)p0 * prm.ldP);
     unsigned offP[LP];
 #pragma unroll
     for (int j = 0; j < LP; ++j) {
@@ -478,80 +504,91 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     }
     const int8_t* gQ[LQA];
     unsigned offQ[LQA];
-    int vmask[LQA];  // conv: bit kh = row tap valid, bit (8 + kw) = column tap valid
+    int vout[LQA];  // conv: bit kh = row tap outside the image, bit (8 + kw) = column tap outside
+    const int bias = CONV ? g.pad * (g.W + 1) * g.Cpad : 0;
+    const int nb0 = CONV && !HALO ? (int)fastdiv((uint32_t)q0, g.div_ohw) : 0;
+    const v4i rsrcQ = buffer_base(CONV ? prm.Q + (int64_t)nb0 * (g.H * g.W) * g.Cpad - bias : prm.Q + (int64_t)q0 * prm.ldQ);
 #pragma unroll
     for (int j = 0; j < LQ; ++j) {
         int row = q0 + 16 * (wave + 4 * j) + lrow;
         row = row < prm.RQ ? row : prm.RQ - 1;
         gQ[j] = nullptr;
         offQ[j] = 0;
-        vmask[j] = 0;
+        vout[j] = 0;
         if (CONV) {
             const int ohw = g.OH * g.OW;
             const int nb = (int)fastdiv((uint32_t)row, g.div_ohw), pix = row - nb * ohw;
             const int oh = (int)fastdiv((uint32_t)pix, g.div_ow), ow = pix - oh * g.OW;
             const int ih0 = oh * g.stride - g.pad, iw0 = ow * g.stride - g.pad;
-            vmask[j] = tap_mask(ih0, g.KH, g.H) | tap_mask(iw0, g.KW, g.W) << 8;
-            gQ[j] = prm.Q + (((int64_t)nb * g.H + ih0) * g.W + iw0) * g.Cpad + lchunk * 16;
+            vout[j] = ~(tap_mask(ih0, g.KH, g.H) | tap_mask(iw0, g.KW, g.W) << 8);
+            if (BIG)
+                gQ[j] = prm.Q + (((int64_t)nb * g.H + ih0) * g.W + iw0) * g.Cpad + lchunk * 16;
+            else
+                offQ[j] = (unsigned)(((nb - nb0) * g.H + ih0) * g.W + iw0) * (unsigned)g.Cpad + (unsigned)(bias + lchunk * 16);
         } else {
             offQ[j] = (unsigned)(row - q0) * (unsigned)prm.ldQ + lchunk * 16;
         }
     }
-    // K position of the step being issued: byte offset into a dense row, or for
-    // the conv's Q operand the tap (kh, kw) and the offset of its 64 channels.
-    int l_kh = 0, l_kw = 0, l_cc = 0;
-    int64_t is_koffP = 0, is_koffQ = 0;
-    unsigned is_sbase = 0;
-    int is_kh = 0, is_kw = 0;
+    // K position of the next step to issue: byte offset into a P row and, for Q, into a dense row or of the tap
+    // (kh, kw) and its 64 channels from a pixel's first tap -- (kh W + kw) Cpad + cc as a running sum: + 64 per step,
+    // which also carries over from the last chunk of a tap to the next tap of the row, and + (W - KW) Cpad at the
+    // end of a window row.  Scalar instructions in this loop cost matrix-core time: no multiplications, no branches.
+    unsigned n_kP = 0, n_kQ = 0, n_slot = 0, is_kP = 0, is_kQ = 0, is_base = 0;
+    int n_cc = 0, n_kw = 0, n_shr = 31, is_shr = 31, is_shc = 23;  // shifts that bring bits kh, 8 + kw to the sign
+    const unsigned ring0 = lds0 + (unsigned)(roff + wave * 1024);
+    const unsigned rowskip = CONV ? (unsigned)(g.W - g.KW) * (unsigned)g.Cpad : 0;
     const int8_t* zero_page = (const int8_t*)g_zero16;
-
-    int64_t l_koff = 0;   // conv: running byte offset of the step being issued within the window
-    const int64_t l_rowskip = CONV ? (int64_t)(g.W - g.KW) * g.Cpad : 0;
-    auto issue_begin = [&](int kt) {
-        is_sbase = lds0 + (unsigned)(roff + (kt % NS) * STAGE);
-        is_koffP = (int64_t)kt * 64;
+    auto issue_begin = [&]() {
+        is_base = ring0 + n_slot;
+        is_kP = n_kP;
+        is_kQ = n_kQ;
+        n_slot = n_slot + STAGE == NS * STAGE ? 0u : n_slot + STAGE;
+        n_kP += 64;
+        n_kQ += 64;
         if (CONV && !HALO) {
-            // byte offset of tap (kh, kw), channel chunk cc from a pixel's tap (0, 0):
-            // (kh W + kw) Cpad + cc, kept as a running sum (scalar multiplies in this loop cost
-            // matrix-core time): + 64 per step, which also carries over from the last chunk of a
-            // tap to the next tap of the row, and + (W - KW) Cpad at the end of a window row
-            is_kh = l_kh;
-            is_kw = l_kw;
-            is_koffQ = l_koff;
-            l_koff += 64;
-            l_cc += 64;
-            if (l_cc == g.Cpad) {
-                l_cc = 0;
-                if (++l_kw == g.KW) {
-                    l_kw = 0;
-                    ++l_kh;
-                    l_koff += l_rowskip;
-                }
-            }
-        } else {
-            is_koffQ = is_koffP;
-            if (DT == 1) is_koffQ = (int64_t)((unsigned)is_koffP % prm.wwrap);
+            is_shr = n_shr;
+            is_shc = 23 - n_kw;
+            n_cc += 64;
+            const bool tap = n_cc == g.Cpad;
+            n_cc = tap ? 0 : n_cc;
+            n_kw += tap ? 1 : 0;
+            const bool end = n_kw == g.KW;
+            n_kw = end ? 0 : n_kw;
+            n_shr -= end ? 1 : 0;
+            n_kQ += end ? rowskip : 0u;
         }
+        if (DT == 1) n_kQ = n_kQ == prm.wwrap ? 0u : n_kQ;
     };
     // the idx-th of the DPS direct loads of the step set up by issue_begin()
-    auto issue_one = [&](int idx) {
-        if (idx < LP) {
-            dma16_base(uniform_ptr(baseP + is_koffP), offP[idx], is_sbase + (wave + 4 * idx) * 1024);
-        } else {
-            const int j = idx - LP;
-            const unsigned dst = is_sbase + BP * 64 + (wave + 4 * j) * 1024;
-            if (CONV) {
-                const bool ok = ((vmask[j] >> is_kh) & (vmask[j] >> (8 + is_kw)) & 1) != 0;
-                dma16(ok ? gQ[j] + is_koffQ : zero_page, dst);
+    auto issue_one = [&](auto index) {
+        constexpr int idx = decltype(index)::value;
+        if constexpr (idx < LP) {
+            dma_buf<4096 * idx>(rsrcP, offP[idx], is_kP, is_base);
+        } else if constexpr (LQ != 0) {
+            constexpr int j = idx - LP;
+            if constexpr (CONV) {
+                const int out = vout[j] << is_shr | vout[j] << is_shc;
+                if constexpr (BIG)
+                    dma16(out < 0 ? zero_page : gQ[j] + is_kQ, is_base + BP * 64 + 4096 * j);
+                else
+                    dma_buf<BP * 64 + 4096 * j>(rsrcQ, offQ[j] | ((unsigned)out & kOutside), is_kQ, is_base);
             } else {
-                dma16_base(uniform_ptr(baseQ + is_koffQ), offQ[j], dst);
+                dma_buf<BP * 64 + 4096 * j>(rsrcQ, offQ[j], is_kQ, is_base);
             }
         }
     };
-    auto issue = [&](int kt) {
-        issue_begin(kt);
-#pragma unroll
-        for (int i = 0; i < DPS; ++i) issue_one(i);
+    auto issue_some = [&](auto from, auto to) {  // loads from .. to - 1
+        constexpr int f = decltype(from)::value, n = decltype(to)::value - f;
+        if constexpr (n > 0) issue_one(std::integral_constant<int, f>{});
+        if constexpr (n > 1) issue_one(std::integral_constant<int, f + 1>{});
+        if constexpr (n > 2) issue_one(std::integral_constant<int, f + 2>{});
+        if constexpr (n > 3) issue_one(std::integral_constant<int, f + 3>{});
+        static_assert(n <= 4, "loads behind one matrix instruction");
+    };
+    auto issue = [&]() {
+        issue_begin();
+        issue_some(std::integral_constant<int, 0>{}, std::integral_constant<int, (DPS < 4 ? DPS : 4)>{});
+        issue_some(std::integral_constant<int, (DPS < 4 ? DPS : 4)>{}, std::integral_constant<int, DPS>{});
     };
 
     // ---- fragment addressing ------------------------------------------------
@@ -604,9 +641,9 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     };
     v4i fa[2][TP], fb[2][TQ];
     constexpr int NF = TP + TQ;  // fragments per k-slice
-    // idx-th fragment of slice ks of step kt: P fragments first, then Q
-    auto load_frag = [&](int kt, int ks, int idx) {
-        const int8_t* st = smem + roff + (kt % NS) * STAGE;
+    // idx-th fragment of slice ks of the step in stage `slot` (its offset in the ring): P fragments first, then Q
+    auto load_frag = [&](unsigned slot, int ks, int idx) {
+        const int8_t* st = smem + roff + slot;
         if (idx < TP) {
             fa[ks][idx] = *(const v4i*)(st + fragP[idx][ks]);
         } else if (!HALO) {
@@ -620,9 +657,9 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
             fb[ks][j] = *(const v4i*)(smem + addr);
         }
     };
-    auto load_frags = [&](int kt, int ks) {
+    auto load_frags = [&](unsigned slot, int ks) {
 #pragma unroll
-        for (int i = 0; i < NF; ++i) load_frag(kt, ks, i);
+        for (int i = 0; i < NF; ++i) load_frag(slot, ks, i);
     };
 
     // conv: Sa of an output pixel -- the sum of t_a over its in-bounds taps -- is the
@@ -655,16 +692,16 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
     // One k-slice of MFMAs in a fixed issue order: after the n-th MFMA come its
-    // share of the next slice's fragment reads (slice fks of step fkt) and, if
-    // ISSUE, of the direct loads of step ikt; a scheduling fence after each
+    // share of the next slice's fragment reads (slice fks of the step in stage fslot) and, if
+    // ISSUE, of the next step's direct loads; a scheduling fence after each
     // group keeps the compiler from sinking the reads back to their first use,
     // so LDS and load-issue latency hide behind matrix-core time.
-    auto slice = [&](auto with_frags, auto with_issue, int ks, int fkt, int fks, int ikt) {
+    auto slice = [&](auto with_frags, auto with_issue, int ks, unsigned fslot, int fks) {
         constexpr bool FRAGS = decltype(with_frags)::value, ISSUE = decltype(with_issue)::value;
-        if (ISSUE) issue_begin(ikt);
+        if (ISSUE) issue_begin();
         if (HALO && FRAGS && fks == 0) frag_step_advance();
-#pragma unroll
-        for (int n = 0; n < NM; ++n) {
+        auto group = [&](auto index) {
+            constexpr int n = decltype(index)::value;
             if constexpr (DT == 1)
                 acc[n / TQ][n % TQ] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                     __builtin_bit_cast(v8bf, fa[ks][n / TQ]), __builtin_bit_cast(v8bf, fb[ks][n % TQ]),
@@ -675,7 +712,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
                 const v8i A8 = {pa[0], pa[1], pa[2], pa[3], 0, 0, 0, 0}, B8 = {pb[0], pb[1], pb[2], pb[3], 0, 0, 0, 0};
                 acc[n / TQ][n % TQ] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A8, B8, acc[n / TQ][n % TQ], 4, 4, 0,
                                                                                       0, 0, 0);
-                if (CONV && n < TQ)
+                if constexpr (CONV && n < TQ)
                     sa_acc[n] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(SA8, B8, sa_acc[n], 4, 4, 0, 0, 0, 0);
             } else
                 acc[n / TQ][n % TQ] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ks][n / TQ], fb[ks][n % TQ],
@@ -685,14 +722,13 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
                 // so the last read is long done at the end of the slice
                 constexpr int PER = (NF + NM - 1) / NM;
 #pragma unroll
-                for (int f = n * PER; f < (n + 1) * PER && f < NF; ++f) load_frag(fkt, fks, f);
+                for (int f = n * PER; f < (n + 1) * PER && f < NF; ++f) load_frag(fslot, fks, f);
             }
-            if (ISSUE) {
-#pragma unroll
-                for (int d = n * DPS / NM; d < (n + 1) * DPS / NM; ++d) issue_one(d);
-            }
+            if constexpr (ISSUE)
+                issue_some(std::integral_constant<int, n * DPS / NM>{}, std::integral_constant<int, (n + 1) * DPS / NM>{});
             __builtin_amdgcn_sched_barrier(0);
-        }
+        };
+        for_each_index(group, std::make_integer_sequence<int, NM>{});
         if (CONV && DT == 0) {
 #pragma unroll
             for (int j = 0; j < TQ; ++j)
@@ -752,7 +788,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
         }
         if (tid < 8) *(uint4*)(smem + zoff + tid * 16) = make_uint4(0, 0, 0, 0);
     }
-    for (int s = 0; s < npro; ++s) issue(s);
+    for (int s = 0; s < npro; ++s) issue();
 
     // Block-tail form: the residual values this lane will add, fetched now so that their
     // HBM latency passes behind the K loop (tiles whose accumulators leave the registers
@@ -809,27 +845,34 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     block_barrier();
     load_frags(0, 0);
     int kt = 0;
+    unsigned cur = 0, nxt = STAGE;  // stages of steps kt and kt + 1
+    auto advance = [&]() {
+        cur = nxt;
+        nxt = nxt + STAGE == NS * STAGE ? 0u : nxt + STAGE;
+    };
     // Steady state: between the two k-slices, stage kt is fully in registers
     // (slice-1 fragments waited for), step kt+1 has landed for this wave
     // (all but the NS-2 younger load groups done) and, after the barrier, for
     // every wave; the freed stage is refilled with step kt+NS.
     for (; kt + NS < nk; ++kt) {
-        slice(yes, no, 0, kt, 1, 0);
+        slice(yes, no, 0, cur, 1);
         wait_lgkm0();
         wait_vm<(NS - 2) * DPS>();
         block_barrier();
-        slice(yes, yes, 1, kt + 1, 0, kt + NS);
+        slice(yes, yes, 1, nxt, 0);
+        advance();
     }
     // Drain: nothing left to issue.
     for (; kt + 1 < nk; ++kt) {
-        slice(yes, no, 0, kt, 1, 0);
+        slice(yes, no, 0, cur, 1);
         wait_lgkm0();
         wait_vm<0>();
         block_barrier();
-        slice(yes, no, 1, kt + 1, 0, 0);
+        slice(yes, no, 1, nxt, 0);
+        advance();
     }
-    slice(yes, no, 0, kt, 1, 0);
-    slice(no, no, 1, 0, 0, 0);
+    slice(yes, no, 0, cur, 1);
+    slice(no, no, 1, 0, 0);
 
     __builtin_amdgcn_s_setprio(0);
     // ---- epilogue ---------------------------------------------------------------
@@ -1102,11 +1145,19 @@ inline unsigned tile_grid(TmmParams& prm, int bp, int bq)
     return (unsigned)((blocks + 7) / 8 * 8);
 }
 
-template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0, bool NT = false>
+// Does a conv's tile of bq pixels lie within 32-bit offsets from its first image?
+inline bool conv_offsets_fit(const ConvGeom& g, int bq)
+{
+    const int64_t images = (bq - 1) / ((int64_t)g.OH * g.OW) + 2, row = (int64_t)g.W * g.Cpad;
+    return (images * g.H + 16) * row < (int64_t)kOutside;
+}
+
+template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0, bool NT = false, bool BIG = false>
 hipError_t launch_cfg(TmmParams& prm, hipStream_t st)
 {
     constexpr int ring_bytes = NS * (BP + (HC ? 0 : BQ)) * 64;
     int64_t stage_bytes = ring_bytes;
+    if (CONV && !HC && !BIG && !conv_offsets_fit(prm.g, BQ)) return hipErrorInvalidValue;
     if (HC) {
         if (!halo_eligible(prm, HC)) return hipErrorInvalidValue;
         prm.hrows = (BQ + 2 * prm.g.pad * (prm.g.W + 1) + 15) & ~15;
@@ -1122,7 +1173,7 @@ hipError_t launch_cfg(TmmParams& prm, hipStream_t st)
         smem = stage_bytes > tb ? stage_bytes : tb;
     }
     if (smem > kMaxLds) return hipErrorInvalidValue;
-    auto kern = k_tmm<BP, BQ, WGP, WGQ, NS, MINW, CONV, TERN, HC, DT, NT>;
+    auto kern = k_tmm<BP, BQ, WGP, WGQ, NS, MINW, CONV, TERN, HC, DT, NT, BIG>;
     static LdsLimit lds;
     const hipError_t e = lds.raise((const void*)kern, (int)kMaxLds);
     if (e != hipSuccess) return e;
