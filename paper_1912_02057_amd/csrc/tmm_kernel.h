@@ -155,11 +155,12 @@ __device__ __forceinline__ int tap_mask(int i0, int ksize, int extent)
 // chunk swizzle of a 64-byte LDS row (depends on row & 15 only)
 __device__ __forceinline__ int swz(int row) { return ((row >> 1) & 3) ^ ((row >> 3) & 1); }
 
-// chunk swizzle of a pixel row of the halo image: HC-byte rows, HC/16 chunks
+// Byte of 16-byte chunk q of pixel row `row` of the halo image (rows of HC bytes, HC/16 chunks): the chunk is XOR-ed with
+// the row so that 16 consecutive rows hit 16 different bank groups.
 template <int HC>
-__device__ __forceinline__ int halo_swz(int row)
+__device__ __forceinline__ int halo_byte(int row, int q)
 {
-    return HC == 64 ? swz(row) : ((row >> 1) & 7);
+    return row * HC | (((row << (HC == 64 ? 2 : 3)) ^ (q << 4)) & (HC - 16));
 }
 
 // Direct global -> LDS load: every lane fetches 16 bytes at gptr; the wave's
@@ -208,6 +209,15 @@ __device__ __forceinline__ void dma_buf(v4i rsrc, unsigned voff, unsigned soff, 
     asm volatile("s_add_u32 m0, %0, %1\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds" ::"s"(__builtin_amdgcn_readfirstlane(lds_off)),
                  "n"(OFF), "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff))
                  : "memory", "scc");
+}
+
+// Keeps the computation of v here: the compiler would put off selects until their result is used, and hold all
+// their operands until then.
+__device__ __forceinline__ void pin(unsigned& v)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(v));
+#endif
 }
 
 template <class F, int... N>
@@ -610,34 +620,35 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     }
     // Halo variant: the Q fragment of tap (kh, kw), channel offset cc is row
     // ml + kh W + kw of the pixel run (ml = the lane's output pixel within the
-    // tile), 16 bytes at chunk q = cc/16 + 2 ks + (l >> 5), swizzled by the row
-    // (halo_swz) so that 16 consecutive rows hit 16 different 16-byte bank
-    // groups; a tap outside the image reads the zero bytes behind the run.
+    // tile), 16 bytes at chunk q = cc/16 + 2 ks + (l >> 5); a tap outside the image reads the zero bytes
+    // behind the run.  The two slices of a step differ in one bit of the address, so it is formed once per step.
     int mlb[TQ];
-    unsigned vmq[TQ];  // bit kh = row tap in the image, bit (8 + kw) = column tap in the image
+    int vmq[TQ];  // bit kh = row tap outside the image, bit (8 + kw) = column tap outside
+    int fq[TQ];
 #pragma unroll
     for (int j = 0; j < TQ; ++j) {
         mlb[j] = wq * WQ + j * 32 + (lane & 31);
-        vmq[j] = 0;
+        vmq[j] = fq[j] = 0;
         if (HALO) {
             int m = q0 + mlb[j];
             m = m < prm.RQ ? m : prm.RQ - 1;
             const int nb = (int)fastdiv((uint32_t)m, g.div_ohw), pix = m - nb * (g.OH * g.OW);
             const int oh = (int)fastdiv((uint32_t)pix, g.div_ow), ow = pix - oh * g.OW;
-            vmq[j] = (unsigned)(tap_mask(oh - g.pad, g.KH, g.H) | tap_mask(ow - g.pad, g.KW, g.W) << 8);
+            vmq[j] = ~(tap_mask(oh - g.pad, g.KH, g.H) | tap_mask(ow - g.pad, g.KW, g.W) << 8);
         }
     }
-    int f_kh = 0, f_kw = 0, f_cc = 0, f_tapoff = 0;  // K position of the fragments being read
+    // K position of the fragments being read: chunk, tap as a row offset and as shifts of the masks above
+    int f_q = 0, f_kw = 0, f_shr = 31, f_tapoff = 0;
     auto frag_step_advance = [&]() {
-        f_cc += 64;
-        if (f_cc == HC) {
-            f_cc = 0;
-            if (++f_kw == g.KW) {
-                f_kw = 0;
-                ++f_kh;
-            }
-            f_tapoff = f_kh * g.W + f_kw;
-        }
+        f_q += 4;
+        const bool tap = f_q == HC / 16;
+        f_q = tap ? 0 : f_q;
+        f_kw += tap ? 1 : 0;
+        f_tapoff += tap ? 1 : 0;
+        const bool end = f_kw == g.KW;
+        f_kw = end ? 0 : f_kw;
+        f_shr -= end ? 1 : 0;
+        f_tapoff += end ? g.W - g.KW : 0;
     };
     v4i fa[2][TP], fb[2][TQ];
     constexpr int NF = TP + TQ;  // fragments per k-slice
@@ -650,11 +661,11 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
             fb[ks][idx - TP] = *(const v4i*)(st + fragQ[idx - TP][ks]);
         } else {
             const int j = idx - TP;
-            const int hr = mlb[j] + f_tapoff;
-            const int q = (f_cc >> 4) + ks * 2 + (lane >> 5);
-            const bool ok = ((vmq[j] >> f_kh) & (vmq[j] >> (8 + f_kw)) & 1) != 0;
-            const int addr = ok ? hr * HC + ((q ^ halo_swz<HC>(hr)) << 4) : zoff + ((lane >> 5) << 4);
-            fb[ks][j] = *(const v4i*)(smem + addr);
+            if (ks == 0) {
+                const int out = vmq[j] << f_shr | vmq[j] << (23 - f_kw);
+                fq[j] = out < 0 ? zoff : halo_byte<HC>(mlb[j] + f_tapoff, f_q + (lane >> 5));
+            }
+            fb[ks][j] = *(const v4i*)(smem + (fq[j] ^ (32 * ks)));
         }
     };
     auto load_frags = [&](unsigned slot, int ks) {
@@ -774,7 +785,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     }
     if (HALO) {
         // the pixel run: 1 KiB per load, lane l lands at 16-byte unit n*64 + l; which chunk
-        // of its row a lane fetches is permuted by the row swizzle.  Runs past either
+        // of its row a lane fetches is permuted as halo_byte() has it.  Runs past either
         // end of the tensor re-read the end pixel (only out-of-image taps point there).
         const int total_px = g.Nb * g.H * g.W;
         const int first_px = q0 - g.pad * (g.W + 1);
@@ -784,7 +795,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
             const int row = lin / (HC / 16), qp = lin % (HC / 16);
             int px = first_px + row;
             px = px < 0 ? 0 : (px < total_px ? px : total_px - 1);
-            dma16(prm.Q + (int64_t)px * HC + ((qp ^ halo_swz<HC>(row)) << 4), lds0 + (unsigned)(n * 1024));
+            dma16(prm.Q + (int64_t)px * HC + (halo_byte<HC>(row, qp) & (HC - 1)), lds0 + (unsigned)(n * 1024));
         }
         if (tid < 8) *(uint4*)(smem + zoff + tid * 16) = make_uint4(0, 0, 0, 0);
     }
@@ -953,97 +964,124 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
             // STREAM: the block-tail form -- z + residual (fp32 add, as a separate add
             // kernel would do it), a second ReLU, and the fp32 result stored as well.
             const float relu_out_floor = __builtin_canonicalizef(prm.relu_out ? 0.0f : -__builtin_inff());
+            // A channel's factors are read from LDS once for the lane's TQ pixels: pixel by pixel (48 bytes per output
+            // and lane, at 128 bytes a cycle for the CU) those reads were more than the arithmetic: 64 filters on 56 x 56,
+            // 256 images, ternarizing, 67.1 -> 60.1 us (with the halo addresses above).
             auto run_codes = [&](auto full, auto stream, auto nt) {
                 constexpr bool FULL = decltype(full)::value, STREAM = decltype(stream)::value;
+                bool mok[TQ];
+                int8_t* cp[TQ];
+                double Sa[TQ];
+                const double* ctab[TQ];
+                int64_t obase[TQ];
 #pragma unroll
                 for (int j = 0; j < TQ; ++j) {
                     const int m = q0 + wq * WQ + j * 32 + (lane & 31);
-                    const bool mok = FULL || m < prm.RQ;
-                    int8_t* cp = prm.codes + (int64_t)(mok ? m : 0) * prm.ldc;
-                    const double Sa = (double)sa_full[j];
-                    const double* ctab = tab + (4 + pixcls[j]) * BP;
-                    int64_t obase = 0;
+                    mok[j] = FULL || m < prm.RQ;
+                    cp[j] = prm.codes + (int64_t)(mok[j] ? m : 0) * prm.ldc;
+                    Sa[j] = (double)sa_full[j];
+                    ctab[j] = tab + (4 + pixcls[j]) * BP;
+                    obase[j] = 0;
                     if (STREAM) {
-                        const int mm = mok ? m : 0;
+                        const int mm = mok[j] ? m : 0;
                         const int nb = (int)fastdiv((uint32_t)mm, g.div_ohw), pix = mm - nb * ohw;
-                        obase = (int64_t)nb * g.O * ohw + pix;
+                        obase[j] = (int64_t)nb * g.O * ohw + pix;
                     }
+                }
 #pragma unroll
-                    for (int i = 0; i < TP; ++i) {
-                        // residual values of this lane's 16 channels, fetched ahead of their use
-                        float rv[16];
-                        if constexpr (RES_EARLY) {
+                for (int i = 0; i < TP; ++i) {
+                    // residual values of this lane's 16 channels, fetched ahead of their use
+                    float rv[STREAM ? TQ : 1][16];
+                    if constexpr (RES_EARLY) {
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) rv[r] = rv_all[j][i][r];
-                        } else if (STREAM) {
+                        for (int j = 0; j < TQ; ++j)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) rv[j][r] = rv_all[j][i][r];
+                    } else if constexpr (STREAM) {
+#pragma unroll
+                        for (int j = 0; j < TQ; ++j)
 #pragma unroll
                             for (int r = 0; r < 16; ++r) {
                                 const int o = p0 + wp * WP + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                                rv[r] = 0.0f;
-                                if (prm.res && (FULL || (mok && o < prm.RP)))
-                                    rv[r] = __builtin_nontemporal_load(prm.res + obase + (int64_t)o * ohw);
+                                rv[j][r] = 0.0f;
+                                if (prm.res && (FULL || (mok[j] && o < prm.RP)))
+                                    rv[j][r] = __builtin_nontemporal_load(prm.res + obase[j] + (int64_t)o * ohw);
                             }
-                        }
-                        unsigned half4[4];  // FP4 output: this lane's 4 nibbles of each channel group
+                    }
+                    unsigned half4[TQ][4];  // FP4 output: this lane's 4 nibbles of each channel group
 #pragma unroll
-                        for (int r4 = 0; r4 < 4; ++r4) {
-                            const int t0 = wp * WP + i * 32 + 8 * r4 + 4 * (lane >> 5);
-                            const int o0 = p0 + t0;
-                            unsigned word = 0;
+                    for (int r4 = 0; r4 < 4; ++r4) {
+                        const int t0 = wp * WP + i * 32 + 8 * r4 + 4 * (lane >> 5);
+                        const int o0 = p0 + t0;
+                        unsigned word[TQ];
 #pragma unroll
-                            for (int b = 0; b < 4; ++b) {
-                                const int t = t0 + b;
-                                const bool ook = FULL || o0 + b < prm.RP;
-                                const double g1 = tab[t], c2 = tab[BP + t], bs = tab[2 * BP + t], bh = tab[3 * BP + t];
-                                const float2 th = thr[t];
-                                const int D = acc[i][j][4 * r4 + b];
-                                double v = g1 * (double)D + (c2 * Sa + ctab[t]);
+                        for (int j = 0; j < TQ; ++j) word[j] = 0;
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) {
+                            const int t = t0 + b;
+                            const bool ook = FULL || o0 + b < prm.RP;
+                            const double g1 = tab[t], c2 = tab[BP + t], bs = tab[2 * BP + t], bh = tab[3 * BP + t];
+                            const float2 th = thr[t];
+#pragma unroll
+                            for (int j = 0; j < TQ; ++j) {
+                                const auto D = acc[i][j][4 * r4 + b];
+                                double v = g1 * (double)D + (c2 * Sa[j] + ctab[j][t]);
                                 v = __builtin_fmax(v, relu_floor);
                                 float z = (float)(bs * v + bh);
-                                if (STREAM) {
-                                    z = __builtin_fmaxf(z + rv[4 * r4 + b], relu_out_floor);
-                                    if (prm.y && (FULL || (mok && ook))) put(nt, z, prm.y + obase + (int64_t)(o0 + b) * ohw);
+                                if constexpr (STREAM) {
+                                    z = __builtin_fmaxf(z + rv[j][4 * r4 + b], relu_out_floor);
+                                    if (prm.y && (FULL || (mok[j] && ook))) put(nt, z, prm.y + obase[j] + (int64_t)(o0 + b) * ohw);
                                 }
                                 if constexpr (DT == 2) {
                                     // E2M1 nibble: +1 -> 0x2, -1 -> 0xA
-                                    const bool pos = z > th.y, neg = z < th.x;
-                                    unsigned nb4 = ((unsigned)(pos | neg) << 1) | ((unsigned)neg << 3);
-                                    if (!FULL && !ook) nb4 = 0;
-                                    word |= nb4 << (4 * b);
+                                    unsigned c = z > th.y ? 0x2u << (4 * b) : 0u;
+                                    c = z < th.x ? 0xAu << (4 * b) : c;
+                                    if (!FULL && !ook) c = 0;
+                                    word[j] |= c;
                                 } else {
                                     int code = (int)(z > th.y) - (int)(z < th.x);
                                     if (!FULL && !ook) code = 0;
-                                    word |= (unsigned)(code & 0xff) << (8 * b);
+                                    word[j] |= (unsigned)(code & 0xff) << (8 * b);
                                 }
                             }
+                        }
+#pragma unroll
+                        for (int j = 0; j < TQ; ++j) {
                             if constexpr (DT == 2) {
-                                half4[r4] = word;
+                                pin(word[j]);
+                                half4[j][r4] = word[j];
                             } else {
-                                if (FULL || (mok && o0 < prm.ldc)) *(unsigned*)(cp + o0) = word;
+                                if (FULL || (mok[j] && o0 < prm.ldc)) *(unsigned*)(cp[j] + o0) = word[j];
                             }
-                            __builtin_amdgcn_sched_barrier(0);
                         }
-                        if constexpr (DT == 2) {
-                            // A dword of the FP4 code tensor is 8 consecutive channels: the 4 of this
-                            // lane and the 4 of lane ^ 32 (same pixel).  The lower lane half assembles
-                            // channel groups 0 and 2, the upper half groups 1 and 3; each sends the
-                            // other the two 16-bit halves it needs in one cross-lane move.
-                            const bool upper = (lane >> 5) != 0;
-                            const unsigned send = upper ? (half4[0] | (half4[2] << 16)) : (half4[1] | (half4[3] << 16));
-                            const unsigned recv = (unsigned)__shfl_xor((int)send, 32, 64);
-                            const unsigned wa = upper ? ((recv & 0xffffu) | (half4[1] << 16)) : (half4[0] | (recv << 16));
-                            const unsigned wb = upper ? ((recv >> 16) | (half4[3] << 16)) : (half4[2] | (recv & 0xffff0000u));
-                            const int c0 = p0 + wp * WP + i * 32 + (upper ? 8 : 0);  // first channel of word wa
-                            if (FULL || (mok && (c0 >> 1) < prm.ldc)) *(unsigned*)(cp + (c0 >> 1)) = wa;
-                            if (FULL || (mok && ((c0 + 16) >> 1) < prm.ldc)) *(unsigned*)(cp + ((c0 + 16) >> 1)) = wb;
-                        }
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                     if constexpr (DT == 2) {
-                        // a 64-row tile covers half of a 128-code row: the last tile along the
-                        // channels also writes the zero codes of the other half
-                        if (BP == 64 && wp == 0 && (p0 + BP) / 2 < prm.ldc && p0 + BP >= prm.RP && mok)
-                            *(uint4*)(cp + (p0 + BP) / 2 + 16 * (lane >> 5)) = make_uint4(0, 0, 0, 0);
+                        // A dword of the FP4 code tensor is 8 consecutive channels: the 4 of this
+                        // lane and the 4 of lane ^ 32 (same pixel).  The lower lane half assembles
+                        // channel groups 0 and 2, the upper half groups 1 and 3; each sends the
+                        // other the two 16-bit halves it needs in one cross-lane move.
+                        const bool upper = (lane >> 5) != 0;
+                        const int c0 = p0 + wp * WP + i * 32 + (upper ? 8 : 0);  // first channel of word wa
+#pragma unroll
+                        for (int j = 0; j < TQ; ++j) {
+                            const unsigned(&h)[4] = half4[j];
+                            const unsigned send = upper ? (h[0] | (h[2] << 16)) : (h[1] | (h[3] << 16));
+                            const unsigned recv = (unsigned)__shfl_xor((int)send, 32, 64);
+                            const unsigned wa = upper ? ((recv & 0xffffu) | (h[1] << 16)) : (h[0] | (recv << 16));
+                            const unsigned wb = upper ? ((recv >> 16) | (h[3] << 16)) : (h[2] | (recv & 0xffff0000u));
+                            if (FULL || (mok[j] && (c0 >> 1) < prm.ldc)) *(unsigned*)(cp[j] + (c0 >> 1)) = wa;
+                            if (FULL || (mok[j] && ((c0 + 16) >> 1) < prm.ldc)) *(unsigned*)(cp[j] + ((c0 + 16) >> 1)) = wb;
+                        }
                     }
+                }
+                if constexpr (DT == 2) {
+                    // a 64-row tile covers half of a 128-code row: the last tile along the
+                    // channels also writes the zero codes of the other half
+                    if (BP == 64 && wp == 0 && (p0 + BP) / 2 < prm.ldc && p0 + BP >= prm.RP)
+#pragma unroll
+                        for (int j = 0; j < TQ; ++j)
+                            if (mok[j]) *(uint4*)(cp[j] + (p0 + BP) / 2 + 16 * (lane >> 5)) = make_uint4(0, 0, 0, 0);
                 }
             };
             constexpr std::integral_constant<bool, TERN == 2> tail{};
