@@ -801,28 +801,63 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     }
     for (int s = 0; s < npro; ++s) issue();
 
-    // Block-tail form: the residual values this lane will add, fetched now so that their
+    // Block-tail form: where this lane's output pixels lie in the residual and in y, in bytes from channel p0 + wp WP of the
+    // image of pixel q0 (the rows of a tile that lie 4 apart are lane halves): an access is then a scalar pointer per
+    // row and a 32-bit lane offset (with a 64-bit lane address each, and bounds tests on whole tiles, the 64
+    // loads of a lane were 900 instructions).
+    using Off = std::conditional_t<BIG, int64_t, uint32_t>;
+    const bool full_tile = p0 + BP <= prm.RP && q0 + BQ <= prm.RQ;
+    Off yoff[TERN == 2 ? TQ : 1];
+    int64_t ybase = 0;
+    if constexpr (TERN == 2) {
+        const int ohw = g.OH * g.OW, nbq = (int)fastdiv((uint32_t)q0, g.div_ohw);
+        ybase = ((int64_t)nbq * g.O + p0 + wp * WP) * ohw;
+#pragma unroll
+        for (int j = 0; j < TQ; ++j) {
+            int m = q0 + wq * WQ + j * 32 + (lane & 31);
+            m = m < prm.RQ ? m : prm.RQ - 1;
+            const int nb = (int)fastdiv((uint32_t)m, g.div_ohw), pix = m - nb * ohw;
+            yoff[j] = ((Off)(nb - nbq) * (Off)g.O * (Off)ohw + (Off)pix + (Off)(lane >> 5) * 4 * (Off)ohw) * 4;
+        }
+    }
+    // row 8 (r >> 2) + 4 half + (r & 3) of 32-row tile i, of a tensor at `t`
+    auto row_of = [&](auto* t, int i, int r) {
+        return t + ybase + (int64_t)(i * 32 + 8 * (r >> 2) + (r & 3)) * (g.OH * g.OW);
+    };
+    auto at = [](auto* row, Off off) { return (decltype(row))((char*)row + off); };
+    (void)row_of, (void)at, (void)ybase;
+    // The residual values this lane will add, fetched now so that their
     // HBM latency passes behind the K loop (tiles whose accumulators leave the registers
     // for it; the larger tiles fetch them in the epilogue, 16 at a time).
     constexpr bool RES_EARLY = TERN == 2 && TP * TQ <= 4;
     float rv_all[RES_EARLY ? TQ : 1][RES_EARLY ? TP : 1][16];
     if constexpr (RES_EARLY) {
-        const int ohw = g.OH * g.OW;
-#pragma unroll
-        for (int j = 0; j < TQ; ++j) {
-            const int m = q0 + wq * WQ + j * 32 + (lane & 31);
-            const bool mok = m < prm.RQ;
-            const int mm = mok ? m : 0;
-            const int nb = (int)fastdiv((uint32_t)mm, g.div_ohw), pix = mm - nb * ohw;
-            const float* rp = prm.res + ((int64_t)nb * g.O * ohw + pix);
+        auto load_res = [&](auto full) {
 #pragma unroll
             for (int i = 0; i < TP; ++i)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
+                    float* row = row_of((float*)prm.res, i, r);
                     const int o = p0 + wp * WP + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    rv_all[j][i][r] = 0.0f;
-                    if (prm.res && mok && o < prm.RP) rv_all[j][i][r] = __builtin_nontemporal_load(rp + (int64_t)o * ohw);
+#pragma unroll
+                    for (int j = 0; j < TQ; ++j) {
+                        rv_all[j][i][r] = 0.0f;
+                        if (decltype(full)::value || (q0 + wq * WQ + j * 32 + (lane & 31) < prm.RQ && o < prm.RP))
+                            rv_all[j][i][r] = __builtin_nontemporal_load(at(row, yoff[j]));
+                    }
                 }
+        };
+        if (!prm.res) {
+#pragma unroll
+            for (int j = 0; j < TQ; ++j)
+#pragma unroll
+                for (int i = 0; i < TP; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) rv_all[j][i][r] = 0.0f;
+        } else if (full_tile) {
+            load_res(std::true_type{});
+        } else {
+            load_res(std::false_type{});
         }
     }
 
@@ -907,7 +942,6 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     // ReLU and BN with neutral parameters when off, as in gemm_epilogue
     const double relu_floor = __builtin_canonicalize(ep.relu ? 0.0 : -__builtin_inf());
     double* tab = (double*)(smem + (CONV ? toff : 0));
-    const bool full_tile = p0 + BP <= prm.RP && q0 + BQ <= prm.RQ;
     // The element loops exist in 6 straight-line variants (interior / ragged
     // tile) x (acc only / y only / both), picked once per block.
     auto dispatch3 = [&](auto&& run, auto nt) {
@@ -973,7 +1007,6 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
                 int8_t* cp[TQ];
                 double Sa[TQ];
                 const double* ctab[TQ];
-                int64_t obase[TQ];
 #pragma unroll
                 for (int j = 0; j < TQ; ++j) {
                     const int m = q0 + wq * WQ + j * 32 + (lane & 31);
@@ -981,12 +1014,6 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
                     cp[j] = prm.codes + (int64_t)(mok[j] ? m : 0) * prm.ldc;
                     Sa[j] = (double)sa_full[j];
                     ctab[j] = tab + (4 + pixcls[j]) * BP;
-                    obase[j] = 0;
-                    if (STREAM) {
-                        const int mm = mok[j] ? m : 0;
-                        const int nb = (int)fastdiv((uint32_t)mm, g.div_ohw), pix = mm - nb * ohw;
-                        obase[j] = (int64_t)nb * g.O * ohw + pix;
-                    }
                 }
 #pragma unroll
                 for (int i = 0; i < TP; ++i) {
@@ -1005,7 +1032,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
                                 const int o = p0 + wp * WP + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                                 rv[j][r] = 0.0f;
                                 if (prm.res && (FULL || (mok[j] && o < prm.RP)))
-                                    rv[j][r] = __builtin_nontemporal_load(prm.res + obase[j] + (int64_t)o * ohw);
+                                    rv[j][r] = __builtin_nontemporal_load(at(row_of((float*)prm.res, i, r), yoff[j]));
                             }
                     }
                     unsigned half4[TQ][4];  // FP4 output: this lane's 4 nibbles of each channel group
@@ -1022,6 +1049,8 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
                             const bool ook = FULL || o0 + b < prm.RP;
                             const double g1 = tab[t], c2 = tab[BP + t], bs = tab[2 * BP + t], bh = tab[3 * BP + t];
                             const float2 th = thr[t];
+                            float* yrow = STREAM ? row_of(prm.y, i, 4 * r4 + b) : nullptr;
+                            (void)yrow;
 #pragma unroll
                             for (int j = 0; j < TQ; ++j) {
                                 const auto D = acc[i][j][4 * r4 + b];
@@ -1030,7 +1059,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
                                 float z = (float)(bs * v + bh);
                                 if constexpr (STREAM) {
                                     z = __builtin_fmaxf(z + rv[j][4 * r4 + b], relu_out_floor);
-                                    if (prm.y && (FULL || (mok[j] && ook))) put(nt, z, prm.y + obase[j] + (int64_t)(o0 + b) * ohw);
+                                    if (prm.y && (FULL || (mok[j] && ook))) put(nt, z, at(yrow, yoff[j]));
                                 }
                                 if constexpr (DT == 2) {
                                     // E2M1 nibble: +1 -> 0x2, -1 -> 0xA
@@ -1183,11 +1212,12 @@ inline unsigned tile_grid(TmmParams& prm, int bp, int bq)
     return (unsigned)((blocks + 7) / 8 * 8);
 }
 
-// Does a conv's tile of bq pixels lie within 32-bit offsets from its first image?
-inline bool conv_offsets_fit(const ConvGeom& g, int bq)
+// Does a conv's tile of bq pixels lie within 32-bit offsets from its first image, of codes and (block tail) of outputs?
+inline bool conv_offsets_fit(const ConvGeom& g, int bq, bool halo, bool tail)
 {
-    const int64_t images = (bq - 1) / ((int64_t)g.OH * g.OW) + 2, row = (int64_t)g.W * g.Cpad;
-    return (images * g.H + 16) * row < (int64_t)kOutside;
+    const int64_t ohw = (int64_t)g.OH * g.OW, images = (bq - 1) / ohw + 2, row = (int64_t)g.W * g.Cpad;
+    if (tail && ((images - 1) * g.O + 8) * ohw * 4 > (int64_t)0xffffffffu) return false;
+    return halo || (images * g.H + 16) * row < (int64_t)kOutside;
 }
 
 template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0, bool NT = false, bool BIG = false>
@@ -1195,7 +1225,7 @@ hipError_t launch_cfg(TmmParams& prm, hipStream_t st)
 {
     constexpr int ring_bytes = NS * (BP + (HC ? 0 : BQ)) * 64;
     int64_t stage_bytes = ring_bytes;
-    if (CONV && !HC && !BIG && !conv_offsets_fit(prm.g, BQ)) return hipErrorInvalidValue;
+    if (CONV && !BIG && !conv_offsets_fit(prm.g, BQ, HC != 0, TERN == 2)) return hipErrorInvalidValue;
     if (HC) {
         if (!halo_eligible(prm, HC)) return hipErrorInvalidValue;
         prm.hrows = (BQ + 2 * prm.g.pad * (prm.g.W + 1) + 15) & ~15;
