@@ -105,6 +105,24 @@ int pick_tile(int64_t rp, int64_t rq, int nk, bool conv)
     return 0;
 }
 
+// Tiles with the pixel run in LDS, for windows of 3 and more and 64-byte pixels (FP4: up to 128 channels), or -1.  The
+// 64 x 128 one, four blocks per CU, as long as its run leaves room for them (images up to some 130 wide): a block's prologue,
+// K loop and stores pass behind three others'.  The 64 x 256 one where there are rounds enough of it, but not for
+// block tails, whose residual values it has registers for in two blocks per CU only.  us, 64 x 256 against 64 x 128,
+// and what ran before where it was neither; FP4, stride 1:
+//   256 x 64 x 56 x 56, 64 filters    plain 51.4, 54.4    codes 53.1, 53.5    tail 112.0, 103.7 (9-stage 64 x 256: 105.6)
+//   64 x 64 x 56 x 56, 64 filters     plain 18.5, 18.3    codes 21.7, 18.3    tail 37.1, 32.1
+//   256 x 128 x 28 x 28, 128          plain 28.9, 30.0    codes 30.9, 30.0    tail 66.1, 58.6 (128 x 128: 67.4)
+//   256 x 128 x 14 x 14, 512          plain 30.7, 31.7    codes 31.5, 31.6    tail 68.5, 65.9 (128 x 128: 34.9, 33.3, 70.9)
+//   30 x 128 x 56 x 56, 64            plain 12.8, 10.7    codes 12.3, 10.1    tail 19.4, 16.5
+//   int8, 200 x 64 x 14 x 14, 256     plain 16.7, 16.1    codes 16.3, 15.3    tail 33.0, 30.2 (128 x 128: 19.3, 19.9, 34.2)
+int pick_halo(const TmmParams& prm, bool codes, bool tail)
+{
+    const ConvGeom& g = prm.g;
+    if (g.KH < 3 || !halo_eligible(prm, 64) || (128 + 2 * g.pad * (g.W + 1)) * 64 > 24 * 1024) return -1;
+    return !tail && nblocks(g.O, prm.RQ, 64, 256) >= (codes ? 3072 : 1536) ? 15 : 17;
+}
+
 }  // namespace
 
 int tile_config_count() { return kNumTileConfigs; }
@@ -275,26 +293,28 @@ hipError_t launch_conv_mfma(const ConvArgs& a, hipStream_t st)
         return a.fp4 ? launch_ksplit<true, 1, 2>(form, prm, st) : launch_ksplit<true, 1, 0>(form, prm, st);
     }
     int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(g.O, prm.RQ, prm.nk, true);
-    // a 64-filter layer with a centred stride-1 window: the variant that keeps the
-    // tile's input pixel run in LDS (measured faster there; on par or slower elsewhere)
-    if (g_forced_tile < 0 && cfg == 7 && halo_eligible(prm, 64)) cfg = 15;
-    // ... and up to 128 filters (FP4 codes: 128 channels are 64 bytes per pixel) the 64 x 128 form of it
-    // Two more choices measured on the 128- and 512-filter layers (not for the block-tail
-    // epilogue, which prefers the deeper ring): the two-stage ring with four blocks per CU
-    // instead of the three-stage one, and, up to 128 filters with 64-byte pixels (FP4
-    // codes: 128 channels), the 64 x 128 form of the pixel-run variant.
-    const bool tail_form = a.codes && (a.res != nullptr || a.y != nullptr || a.relu_out);
-    if (g_forced_tile < 0 && !tail_form) {
-        if (cfg == 1 && nblocks(g.O, prm.RQ, 128, 128) >= 256) cfg = 12;
-        if (cfg == 12 && g.O <= 128 && halo_eligible(prm, 64)) cfg = 17;
+    const bool tail = a.codes && (a.res != nullptr || a.y != nullptr || a.relu_out);
+    if (g_forced_tile < 0) {
+        const int halo = pick_halo(prm, a.codes && !tail, tail);
+        if (halo >= 0 && nblocks(g.O, prm.RQ, 64, 64) > 1024)
+            cfg = halo;
+        else if (cfg == 7 && halo_eligible(prm, 64))
+            cfg = 15;
+        // Two more choices measured on the 128- and 512-filter layers (not for the block-tail
+        // epilogue, which prefers the deeper ring): the two-stage ring with four blocks per CU
+        // instead of the three-stage one, and, up to 128 filters with 64-byte pixels (FP4
+        // codes: 128 channels), the 64 x 128 form of the pixel-run variant.
+        if (!tail) {
+            if (cfg == 1 && nblocks(g.O, prm.RQ, 128, 128) >= 256) cfg = 12;
+            if (cfg == 12 && g.O <= 128 && halo_eligible(prm, 64)) cfg = 17;
+        }
     }
     if (!a.codes) return a.fp4 ? launch_index<true, 0, 2>(cfg, prm, st) : launch_index<true>(cfg, prm, st);
-    const bool tail = a.res != nullptr || a.y != nullptr || a.relu_out;
     // the block-tail epilogue prefetches its residual values only for the tiles with
     // 64 accumulators per lane: prefer 128x128 over 128x256 there
     if (tail && g_forced_tile < 0 && cfg == 13) cfg = 12;
-    // FP4 block tails, from a sweep over all configurations on the ResNet-18 shapes: the pixel-run
-    // tile with the whole 9-step weight slab resident (123.5 against 126.9 us on the 64-filter
+    // FP4 block tails, from a sweep over all configurations on the ResNet-18 shapes: where the run of the tile above is too
+    // long, the one with the whole 9-step weight slab resident (123.5 against 126.9 us on the 64-filter
     // layers), and the two-stage 128 x 128 ring on the 512-filter layers (40.6 against 42.4 us)
     if (tail && a.fp4 && g_forced_tile < 0) {
         if (cfg == 15 && prm.nk <= 9) cfg = 14;
