@@ -215,7 +215,8 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
 
     // ---- weights: fragment (32-filter tile, 16-channel slice, tap) is rows x 2 halves x 16 bytes ---
     const int nslice = g.Cpad >> 4;  // 16-channel slices the weights hold per tap
-    int64_t wbase[TP];
+    // (through buffer resources: a scalar base per 32-filter tile, of at most 2^28 bytes, a lane offset and a scalar offset)
+    __amdgpu_buffer_rsrc_t wrsrc[TP];
     unsigned wlane[TP], wstep[TP];
     const int lastpt = (prm.t.RP - 1) >> 5;
 #pragma unroll
@@ -224,19 +225,27 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
         pt = pt < lastpt ? pt : lastpt;
         const int rows = prm.t.RP - pt * 32 < 32 ? prm.t.RP - pt * 32 : 32;
         const int row = (lane & 31) < rows ? (lane & 31) : rows - 1;
-        wbase[t] = (int64_t)pt * 32 * ntap * g.Cpad * 2;
+        wrsrc[t] = __builtin_amdgcn_make_buffer_rsrc((void*)(prm.w + (int64_t)pt * 32 * ntap * g.Cpad * 2), 0, 0x7fffffff, 0x00020000);
         wlane[t] = (unsigned)(half * rows + row) * 16;
         wstep[t] = (unsigned)rows * 32;
     }
     v4i pw[PD][TP];
     // step s of a chunk
     auto load_w = [&](const Chunk& ck, int s, v4i* dst) {
+        if constexpr (!GATHER && CS == 1) {  // a chunk's steps follow each other
+            const unsigned idx = (unsigned)(ck.c * NTAP);
+#pragma unroll
+            for (int t = 0; t < TP; ++t)
+                dst[t] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(wrsrc[t], (int)wlane[t], (int)(idx * wstep[t] + s * wstep[t]), 0));
+            return;
+        }
         int slice = ck.c * CS + (GATHER ? s : s / (NTAP ? NTAP : 1));
         const int tap = GATHER ? ck.tap : s % (NTAP ? NTAP : 1);
         slice = slice < nslice ? slice : nslice - 1;  // past the end: multiplied with zero activations
-        const int64_t idx = (int64_t)slice * ntap + tap;
+        const unsigned idx = (unsigned)(slice * ntap + tap);
 #pragma unroll
-        for (int t = 0; t < TP; ++t) dst[t] = *(const v4i*)(prm.w + (wbase[t] + idx * wstep[t]) + wlane[t]);
+        for (int t = 0; t < TP; ++t)
+            dst[t] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(wrsrc[t], (int)wlane[t], (int)(idx * wstep[t]), 0));
     };
 
     // ---- fragment rows of this lane's output pixels ------------------------------------------
@@ -367,7 +376,8 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
         const int nb = (int)fastdiv((uint32_t)mm, g.div_ohw);
         yp[j] = prm.t.y + ((int64_t)nb * g.O * ohw + (mm - nb * ohw));
     }
-    auto run = [&](auto nt) {
+    auto run = [&](auto full, auto nt) {
+        constexpr bool FULL = decltype(full)::value;
 #pragma unroll
         for (int i = 0; i < TP; ++i)
 #pragma unroll
@@ -379,7 +389,7 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
                 for (int j = 0; j < TQ; ++j) {
                     const double v = __builtin_fmax(g1 * (double)acc[i][j][r], relu_floor);
                     const float z = (float)(bs * v + bh);
-                    if (ook && mok[j]) {
+                    if (FULL || (ook && mok[j])) {
                         if constexpr (decltype(nt)::value)
                             __builtin_nontemporal_store(z, yp[j] + (int64_t)o * ohw);
                         else
@@ -389,10 +399,12 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
                 if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
             }
     };
-    if (prm.t.nt_out)
-        run(std::true_type{});
+    const std::true_type yes{};
+    const std::false_type no{};
+    if (p0 + BP <= prm.t.RP && q0 + BQ <= prm.t.RQ)
+        prm.t.nt_out ? run(yes, yes) : run(yes, no);
     else
-        run(std::false_type{});
+        prm.t.nt_out ? run(no, yes) : run(no, no);
 }
 
 // int8 codes [O][taps][Cpad] -> bf16 weights in fragment order: for every 32-filter tile (the last
