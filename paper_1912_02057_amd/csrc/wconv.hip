@@ -177,12 +177,15 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
                 for (int e = 0; e < 8; ++e) xr[i][e] = *(const float*)(xc + (Off)(e < last ? e : last) * (Off)HW * 4 + o);
             } else {
                 if (((wave + NW * i) % NSEG) * 64 >= prm.span) continue;  // (wave-uniform, like the channel tail)
+                // (a scalar base, the lane's offset and a scalar one: nothing to add per load)
+                const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)xc, 0, -1, 0x00020000);
+                auto load = [&](int e) { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)voff[i], e * HW * 4, 0)); };
                 if (c + 8 <= g.C) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) xr[i][e] = *(const float*)(xc + (int64_t)e * HW * 4 + voff[i]);
+                    for (int e = 0; e < 8; ++e) xr[i][e] = load(e);
                 } else {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) xr[i][e] = c + e < g.C ? *(const float*)(xc + (int64_t)e * HW * 4 + voff[i]) : 0.0f;
+                    for (int e = 0; e < 8; ++e) xr[i][e] = c + e < g.C ? load(e) : 0.0f;
                 }
             }
         }
