@@ -1960,6 +1960,38 @@ def test_depthwise_3x3_forms(C, H, W, stride, pad, batch):
         assert torch.equal(y, outs[0][0]) and torch.equal(acc, outs[0][1])
 
 
+@pytest.mark.parametrize("side", [3200, 4096])
+def test_conv_on_images_beyond_32_bit_offsets(side):
+    """Windows far apart on one image of 0.65 and 1.07 GB of codes (a tile's offsets fit 32 bits in the one and not
+    in the other): the same bits as on the small image of just those windows."""
+    _say("conv stride 64 on %d x %d" % (side, side))
+    C, O, k, s = 64, 256, 3, 64
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(side)
+    lut = torch.tensor([a | b << 4 for a in (0, 2, 10) for b in (0, 2, 10)], dtype=torch.uint8, device=T.DEV)
+    OH = (side - k) // s + 1
+    pick = (torch.arange(OH, device=T.DEV)[:, None] * s + torch.arange(k, device=T.DEV)).reshape(-1)
+    small = torch.zeros((1, OH * k, OH * k, 64), dtype=torch.uint8, device=T.DEV)      # 64 channels are padded to 128 codes
+    small[..., :32] = lut[torch.randint(0, 9, (1, OH * k, OH * k, 32), generator=g, device=T.DEV)]
+    big = torch.full((1, side, side, 64), 0x22, dtype=torch.uint8, device=T.DEV)       # what lies between is never read
+    big[0][pick[:, None], pick[None, :]] = small[0]
+    w = torch.randn((O, C, k, k), generator=g, device=T.DEV)
+    cw, sw = B.ternarize_pack(w, -0.4, 0.4, B.RTN_CODE_FP4)
+    ep = B.Epilogue(1.1, 0.2, torch.rand(O, generator=g, device=T.DEV) + 0.5, torch.rand(O, generator=g, device=T.DEV) - 0.5, None, sw, relu=True)
+    res = torch.randn((1, O, OH, OH), generator=g, device=T.DEV)
+    out = []
+    for codes, n, stride in ((big, side, s), (small, OH * k, k)):
+        y = B.ternary_conv2d(codes, cw, 1, C, n, n, O, k, k, stride, 0, ep=ep, fmt=B.RTN_CODE_FP4)[1]
+        y2 = torch.empty_like(y)
+        c1 = B.ternary_conv2d_ternarize(codes, cw, 1, C, n, n, O, k, k, stride, 0, ep, -0.4, 0.6, fmt=B.RTN_CODE_FP4)
+        c2 = B.ternary_conv2d_ternarize(codes, cw, 1, C, n, n, O, k, k, stride, 0, ep, -0.4, 0.6, residual=res, relu_out=True, y_out=y2,
+                                        fmt=B.RTN_CODE_FP4)
+        out.append([t[0] if isinstance(t, (tuple, list)) else t for t in (y, c1, c2, y2)])
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+
+
 OTHER_NET_CONVS = [
     # MobileNet pointwise (1x1) layers, AlexNet's 5x5 and 3x3 layers (first layer stays fp32), NIN's 5x5 / 1x1
     wl.ConvShape("mobilenet.pw.64x128@56", 64, 56, 128, 1, 1, 0),
