@@ -17,7 +17,7 @@
 // output tile, its 4 waves a WGP x WGQ grid of (BP/WGP) x (BQ/WGQ) sub-tiles
 // made of 32x32 MFMA tiles.  K advances 64 bytes per step (two MFMA k-slices).
 //
-// Data movement: operand tiles go global -> LDS directly (global_load_lds,
+// Data movement: operand tiles go global -> LDS directly (buffer_load ... lds,
 // 16 bytes per lane, no register staging) into NS ring stages, NS steps ahead
 // of the MFMAs; completion is tracked by hand with s_waitcnt vmcnt and ONE
 // workgroup barrier per K-step placed between the two k-slices, so that the

@@ -22,9 +22,9 @@
 // Parameters, thresholds and residual values are fetched before the K loop.  What is left of a launch: 3.1 us
 // (GEMM) to 3.7 us (conv) with one K-step -- launch, first load, meeting, store -- and from 250 tiles on the
 // operand traffic L2 -> LDS.  us, k_tmm 64 x 64 -> here (times of back-to-back launches):
-//   conv, FP4, one image, 512 filters on 7 x 7, 36 K-steps     11.5 -> 5.4
-//   conv, FP4, one image, 256 filters on 14 x 14, 18 K-steps    8.0 -> 4.9
-//   conv, FP4, one image, 64 filters on 56 x 56, 9 K-steps      5.8 -> 4.6, block tail 7.5 -> 5.1
+//   conv, FP4, one image, 512 filters on 7 x 7, 36 K-steps     11.5 -> 5.0
+//   conv, FP4, one image, 256 filters on 14 x 14, 18 K-steps    8.0 -> 4.8, block tail 4.7
+//   conv, FP4, one image, 64 filters on 56 x 56, 9 K-steps      5.8 -> 4.5, block tail 7.5 -> 4.6
 //   GEMM, int8, 661 x 174 x 5600, 88 K-steps                   14.5 -> 6.8
 //   GEMM, FP4, 2 x 8144 x 300, 3 K-steps                        3.6 -> 3.1
 #include "tmm_kernel.h"

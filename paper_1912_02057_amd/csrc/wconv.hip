@@ -26,8 +26,10 @@
 //
 // What it replaced wrote the three terms to memory (6 bytes per activation) in a pass of its own
 // and re-read them once per tap and filter tile through LDS, with the weights fetched again for
-// each term.  ResNet-18's 19 layer shapes, GPU time (before -> now): batch 256 4.48 -> 2.44 ms, batch 64
-// 1.73 -> 0.85 ms, batch 1 1.01 -> 0.16 ms.  GATHER re-reads and re-splits its inputs once per tap, which
+// each term.  ResNet-18's 19 layer shapes, GPU time (before -> this kernel with 64-bit addresses): batch 256
+// 4.48 -> 2.44 ms, batch 64 1.73 -> 0.85 ms, batch 1 1.01 -> 0.16 ms; with buffer resources (a scalar base, the lane's
+// offset, a scalar one: no address arithmetic per load) and whole tiles stored without tests batch 256 takes 0.935 times
+// that (2599 -> 2429 us on one machine; machines differ by 5 %).  GATHER re-reads and re-splits its inputs once per tap, which
 // the split pass did not: over 857 random geometries with windows of 1 to 7 and strides of 1 to 4 this
 // kernel takes 0.43 times the time at the median and more than 1.02 times on 7, 1.14 times at worst: nearly
 // all windows of 4 and more that are strided or 5 and more wide, at some 10000 output pixels and more.
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(64 * WGP * WGQ * KG, MINW) void k_wconv(WcParams pr
                 if (((wave + NW * i) % NSEG) * 64 >= prm.span) continue;  // (wave-uniform, like the channel tail)
                 // (a scalar base, the lane's offset and a scalar one: nothing to add per load)
                 const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)xc, 0, -1, 0x00020000);
-                auto load = [&](int e) { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)voff[i], e * HW * 4, 0)); };
+                auto load = [&](int e) { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)voff[i], (int)(4u * e * (unsigned)HW), 0)); };
                 if (c + 8 <= g.C) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) xr[i][e] = load(e);
