@@ -45,6 +45,7 @@
 #include <utility>
 
 #include "choice.h"
+#include "conv_offsets.h"
 #include "epilogue_math.h"
 #include "lds_limit.h"
 #include "rtn_kernels.h"
@@ -515,7 +516,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     const int8_t* gQ[LQA];
     unsigned offQ[LQA];
     int vout[LQA];  // conv: bit kh = row tap outside the image, bit (8 + kw) = column tap outside
-    const int bias = CONV ? g.pad * (g.W + 1) * g.Cpad : 0;
+    const int bias = CONV && !HALO && !BIG ? g.pad * (g.W + 1) * g.Cpad : 0;
     const int nb0 = CONV && !HALO ? (int)fastdiv((uint32_t)q0, g.div_ohw) : 0;
     const v4i rsrcQ = buffer_base(CONV ? prm.Q + (int64_t)nb0 * (g.H * g.W) * g.Cpad - bias : prm.Q + (int64_t)q0 * prm.ldQ);
 #pragma unroll
@@ -540,34 +541,29 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
         }
     }
     // K position of the next step to issue: byte offset into a P row and, for Q, into a dense row or of the tap
-    // (kh, kw) and its 64 channels from a pixel's first tap -- (kh W + kw) Cpad + cc as a running sum: + 64 per step,
-    // which also carries over from the last chunk of a tap to the next tap of the row, and + (W - KW) Cpad at the
-    // end of a window row.  Scalar instructions in this loop cost matrix-core time: no multiplications, no branches.
-    unsigned n_kP = 0, n_kQ = 0, n_slot = 0, is_kP = 0, is_kQ = 0, is_base = 0;
-    int n_cc = 0, n_kw = 0, n_shr = 31, is_shr = 31, is_shc = 23;  // shifts that bring bits kh, 8 + kw to the sign
+    // (kh, kw) and its 64 channels from a pixel's first tap.
+    using KOff = ConvOff<BIG>;
+    unsigned n_kP = 0, n_slot = 0, is_kP = 0, is_base = 0;
+    KOff is_kQ = 0;
+    TapWalk<KOff> n_q;
+    int is_shr = 31, is_shc = 23;  // shifts that bring bits kh, 8 + kw to the sign
     const unsigned ring0 = lds0 + (unsigned)(roff + wave * 1024);
-    const unsigned rowskip = CONV ? (unsigned)(g.W - g.KW) * (unsigned)g.Cpad : 0;
+    const KOff rowskip = CONV ? TapWalk<KOff>::row_skip(g.W, g.KW, g.Cpad) : 0;
     const int8_t* zero_page = (const int8_t*)g_zero16;
     auto issue_begin = [&]() {
         is_base = ring0 + n_slot;
         is_kP = n_kP;
-        is_kQ = n_kQ;
+        is_kQ = n_q.off;
         n_slot = n_slot + STAGE == NS * STAGE ? 0u : n_slot + STAGE;
         n_kP += 64;
-        n_kQ += 64;
         if (CONV && !HALO) {
-            is_shr = n_shr;
-            is_shc = 23 - n_kw;
-            n_cc += 64;
-            const bool tap = n_cc == g.Cpad;
-            n_cc = tap ? 0 : n_cc;
-            n_kw += tap ? 1 : 0;
-            const bool end = n_kw == g.KW;
-            n_kw = end ? 0 : n_kw;
-            n_shr -= end ? 1 : 0;
-            n_kQ += end ? rowskip : 0u;
+            is_shr = n_q.shr;
+            is_shc = 23 - n_q.kw;
+            n_q.step(g.Cpad, g.KW, rowskip);
+        } else {
+            n_q.off += 64;
         }
-        if (DT == 1) n_kQ = n_kQ == prm.wwrap ? 0u : n_kQ;
+        if (DT == 1) n_q.off = n_q.off == prm.wwrap ? 0u : n_q.off;
     };
     // the idx-th of the DPS direct loads of the step set up by issue_begin()
     auto issue_one = [&](auto index) {

@@ -1,4 +1,4 @@
-"""The size rules of csrc/choice.h, compiled for the host."""
+"""The size rules of csrc/choice.h and the offsets of csrc/conv_offsets.h, compiled for the host."""
 import ctypes as C
 import os
 import subprocess
@@ -12,6 +12,19 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 SHIM = r"""
 #include "choice.h"
+#include "conv_offsets.h"
+template <bool BIG>
+static void walk(int W, int Cpad, int KW, int steps, int64_t *out)
+{
+    using Walk = rtn::TapWalk<rtn::ConvOff<BIG>>;
+    Walk w;
+    for (int i = 0; i < steps; ++i, w.step(Cpad, KW, Walk::row_skip(W, KW, Cpad)))
+        out[3 * i] = (int64_t)w.off, out[3 * i + 1] = 31 - w.shr, out[3 * i + 2] = w.kw;
+}
+extern "C" void tap_walk(int big, int W, int Cpad, int KW, int steps, int64_t *out)
+{
+    big ? walk<true>(W, Cpad, KW, steps, out) : walk<false>(W, Cpad, KW, steps, out);
+}
 extern "C" void pack_form(int planes, int64_t rows, int64_t Kpad, int *out)
 {
     const rtn::PackRowsForm f = planes ? rtn::pack_rows_planes_form(rows, Kpad) : rtn::pack_rows_form(rows, Kpad);
@@ -35,6 +48,7 @@ def L(tmp_path_factory):
     lib = C.CDLL(so)
     lib.pack_form.argtypes = [C.c_int, C.c_int64, C.c_int64, C.c_void_p]
     lib.ksplit.argtypes = [C.c_void_p, C.c_int]
+    lib.tap_walk.argtypes = [C.c_int] * 5 + [C.c_void_p]
     lib.nt_hint.argtypes = [C.c_int64, C.c_int64, C.c_size_t, C.c_int]
     return lib
 
@@ -117,6 +131,18 @@ def test_small_grid_lines(L):
         assert conv(1024, 2048, nk, 3) == form
     for nk, form in ((63, 2), (72, 5)):
         assert conv(512, 1024, nk, 3) == form
+
+
+@pytest.mark.parametrize("big,W,Cpad,KH,KW", [
+    (0, 56, 64, 3, 3), (0, 1, 128, 3, 3), (0, 1, 64, 5, 2), (0, 1009, 2048, 7, 7), (1, 56, 64, 3, 3), (1, 1, 128, 3, 3),
+    (1, 1 << 25, 64, 3, 3), (1, (1 << 24) + 3, 64, 5, 5), (1, 1 << 30, 64, 2, 2), (1, 700001, 1024, 7, 7), (1, 1 << 24, 8192, 3, 3)])
+def test_tap_offsets_of_a_window(L, big, W, Cpad, KH, KW):
+    """The running offset of a window's K-steps is (kh W + kw) Cpad + cc, also where that passes 32 bits."""
+    steps = [((kh * W + kw) * Cpad + cc, kh, kw) for kh in range(KH) for kw in range(KW) for cc in range(0, Cpad, 64)]
+    assert big or max(steps)[0] < 1 << 32
+    out = (C.c_int64 * (3 * len(steps)))()
+    L.tap_walk(big, W, Cpad, KW, len(steps), out)
+    assert [tuple(out[3 * i:3 * i + 3]) for i in range(len(steps))] == steps
 
 
 LDS_SHIM = r"""

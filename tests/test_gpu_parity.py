@@ -1992,6 +1992,27 @@ def test_conv_on_images_beyond_32_bit_offsets(side):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("fmt,C", [(B.RTN_CODE_I8, 64), (B.RTN_CODE_FP4, 128)])
+def test_conv_window_rows_2_gib_apart(fmt, C):
+    """An image of two rows of 2^25 pixels, 64 bytes each: the third row of a window is 2^32 bytes from the first.  The
+    same sums as on cuts of the image, at both ends and in the middle."""
+    W, O = 1 << 25, 8
+    _say("conv on 2 x %d, fmt %s" % (W, fmt))
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(C)
+    dt = torch.int8 if fmt == B.RTN_CODE_I8 else torch.uint8
+    values = torch.tensor([-1, 0, 1] if fmt == B.RTN_CODE_I8 else [a | b << 4 for a in (0, 2, 10) for b in (0, 2, 10)], dtype=dt, device=T.DEV)
+    part = values[torch.randint(0, len(values), (1, 2, 40961, 64), generator=g, device=T.DEV)]
+    codes = part.repeat(1, 1, W // 40961 + 1, 1)[:, :, :W].contiguous()
+    cw, sw = B.ternarize_pack(torch.randn((O, C, 3, 3), generator=g, device=T.DEV), -0.4, 0.4, fmt)
+    ep = B.Epilogue(1.1, 0.2, torch.rand(O, generator=g, device=T.DEV) + 0.5, torch.rand(O, generator=g, device=T.DEV) - 0.5, None, sw)
+    y = B.ternary_conv2d(codes, cw, 1, C, 2, W, O, 3, 3, 1, 1, ep=ep, fmt=fmt)[1].view(O, 2, W)
+    for c0, c1 in ((0, 300), (W // 2 - 150, W // 2 + 150), (W - 300, W)):
+        cut = B.ternary_conv2d(codes[:, :, c0:c1].contiguous(), cw, 1, C, 2, c1 - c0, O, 3, 3, 1, 1, ep=ep, fmt=fmt)[1].view(O, 2, c1 - c0)
+        first, last = int(c0 > 0), c1 - c0 - int(c1 < W)      # (the cut's own borders)
+        assert torch.equal(y[:, :, c0 + first:c0 + last], cut[:, :, first:last])
+
+
 OTHER_NET_CONVS = [
     # MobileNet pointwise (1x1) layers, AlexNet's 5x5 and 3x3 layers (first layer stays fp32), NIN's 5x5 / 1x1
     wl.ConvShape("mobilenet.pw.64x128@56", 64, 56, 128, 1, 1, 0),
