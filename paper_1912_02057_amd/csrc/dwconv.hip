@@ -624,10 +624,10 @@ hipError_t launch_dwconv(const DwConvArgs& a, hipStream_t st)
         const int64_t slabs = (a.g.C + rb - 1) / rb;
         // four blocks per CU, all of them resident, each with an even share of the pixels: the set-up is paid once.  MobileNet's
         // 13 layers at batch 256: 732 us, with two rounds of them 744, with three 767.  A wave takes 16 pixels at a time.
+        // (8 blocks a slab at least, one per XCD, however many channels there are: at most 2^22 / 9)
         const int64_t most = (total + 63) / 64;
         int64_t nb = 1024 / slabs < most ? 1024 / slabs : most;
-        nb = (nb + 7) / 8 * 8;
-        if (slabs > 0xffff) return hipErrorInvalidValue;
+        nb = nb < 1 ? 8 : (nb + 7) / 8 * 8;
         const dim3 grid((unsigned)nb, (unsigned)slabs);
         auto launch = [&](auto ncg, auto w, auto n) {
             hipLaunchKernelGGL((k_dwconv3_mm<decltype(ncg)::value, decltype(w)::value, decltype(n)::value>), grid, dim3(256), lds, st, b);

@@ -508,7 +508,7 @@ const WcForm kForms[] = {
     wc_form<64, 256, 1, 4, 1, 2, 0, 2, 256>(1.76, 0.982, 5.76, 1.74, 0.251, 3),
     wc_form<128, 128, 2, 2, 1, 2, 0, 2, 128>(1.17, 0.701, 5.29, 2.14, 0.12, 3),
     wc_form<128, 128, 2, 2, 2, 4, 0, 2, 128>(1.78, 1.43, 5.36, 2.76, 0.17, 3),
-    wc_form<64, 64, 2, 2, 4, 4, 0, 2, 64>(1.34, 1.04, 4.56, 1.25, 0.218, 3),
+    wc_form<64, 64, 2, 2, 4, 8, 0, 2, 64>(1.34, 1.04, 4.56, 1.25, 0.218, 3),
 };
 
 }  // namespace
@@ -595,7 +595,7 @@ hipError_t launch_wconv(const WConvArgs& a, hipStream_t st)
     } else {
         f = pick([](const WcForm&) { return true; });
     }
-    if (!f) return launch_wc<64, 64, 2, 2, 4, 4, 0, 2, 64, true>(prm, st);
+    if (!f) return launch_wc<64, 64, 2, 2, 4, 8, 0, 2, 64, true>(prm, st);
     prm.span = (int)rows(*f);
     return f->launch(prm, st);
 }

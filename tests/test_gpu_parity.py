@@ -1960,6 +1960,24 @@ def test_depthwise_3x3_forms(C, H, W, stride, pad, batch):
         assert torch.equal(y, outs[0][0]) and torch.equal(acc, outs[0][1])
 
 
+@pytest.mark.parametrize("C,H,stride,batch", [(8200, 5, 1, 2), (65536, 3, 1, 1), (65600, 3, 1, 1), (70001, 6, 2, 1)])
+def test_depthwise_3x3_thousands_of_channels(C, H, stride, batch):
+    """More slabs of 64 channels than a share of the blocks each."""
+    _say("depthwise 3x3 C=%d" % C)
+    rng = np.random.default_rng(C)
+    ta = rng.integers(-1, 2, (batch, C, H, H)).astype(np.int8)
+    tw = rng.integers(-1, 2, (C, 9)).astype(np.int8)
+    aw = rng.uniform(0.5, 1.5, C).astype(np.float32)
+    D, y = orc.dwconv(ta, tw.reshape(C, 3, 3), stride, 1, np.float32(1.2), np.float32(0.15), aw, None, True)
+    cw = np.zeros((C, 64), np.int8)
+    cw[:, :9] = tw
+    ep = B.Epilogue(1.2, 0.15, T.dev(aw), None, None, None)
+    acc, yy = B.ternary_depthwise_conv2d(T.dev(orc.nchw_to_nhwc_i8(ta, (C + 63) // 64 * 64)), T.dev(cw), batch, C, H, H, 3, 3, stride, 1, ep=ep,
+                                         want_acc=True)
+    assert (acc.cpu().numpy() == D).all()
+    T.assert_y_close(yy.cpu().numpy(), y, "depthwise y")
+
+
 @pytest.mark.parametrize("side", [3200, 4096])
 def test_conv_on_images_beyond_32_bit_offsets(side):
     """Windows far apart on one image of 0.65 and 1.07 GB of codes (a tile's offsets fit 32 bits in the one and not
