@@ -166,20 +166,40 @@ __device__ __forceinline__ int halo_byte(int row, int q)
 
 // Direct global -> LDS load: every lane fetches 16 bytes at gptr; the wave's
 // 1 KiB lands at LDS byte offset lds_off (wave-uniform) + 16 * lane.
-// Both statements overwrite M0.  It cannot be named as a clobber (the compiler keeps M0
+// The statements overwrite M0.  It cannot be named as a clobber (the compiler keeps M0
 // reserved and warns that a clobber of it is not honoured); it is safe because on this
 // target the compiler itself writes M0 only immediately before an instruction that
 // reads it, never across other code, so no value of its own lives in M0 here.
+// The wait states are these statements' own, too: gfx9 wants one between a scalar write of M0 and a load to LDS, and
+// five between a vector instruction's write of a scalar register (v_readfirstlane) and a load that reads it, and the
+// compiler does not look for either in here.  So there is one instruction between, and where the load has a scalar
+// operand it is a scalar copy of that, which reads any write and needs no wait itself.
 __device__ __forceinline__ void dma16(const void* gptr, unsigned lds_off)
 {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_off), "v"(gptr) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_off), "v"(gptr) : "memory");
+}
+// 4 bytes per lane
+__device__ __forceinline__ void dma4(const void* gptr, unsigned lds_off)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_off), "v"(gptr) : "memory");
 }
 
 // Same, with the address split into a wave-uniform 64-bit base (SGPR pair) and
 // a per-lane unsigned 32-bit byte offset: nothing to add per lane per K-step.
 __device__ __forceinline__ void dma16_base(const void* sbase, unsigned voff, unsigned lds_off)
 {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(voff), "s"(sbase)
+    const void* base;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+                 : "=&s"(base)
+                 : "s"(lds_off), "v"(voff), "s"(sbase)
+                 : "memory");
+}
+__device__ __forceinline__ void dma4_base(const void* sbase, unsigned voff, unsigned lds_off)
+{
+    const void* base;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dword %2, %0"
+                 : "=&s"(base)
+                 : "s"(lds_off), "v"(voff), "s"(sbase)
                  : "memory");
 }
 
@@ -207,8 +227,10 @@ __device__ __forceinline__ v4i buffer_base(const int8_t* p)
 template <int OFF>
 __device__ __forceinline__ void dma_buf(v4i rsrc, unsigned voff, unsigned soff, unsigned lds_off)
 {
-    asm volatile("s_add_u32 m0, %0, %1\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds" ::"s"(__builtin_amdgcn_readfirstlane(lds_off)),
-                 "n"(OFF), "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff))
+    unsigned off;
+    asm volatile("s_add_u32 m0, %1, %2\n\ts_mov_b32 %0, %5\n\tbuffer_load_dwordx4 %3, %4, %0 offen lds"
+                 : "=&s"(off)
+                 : "s"(__builtin_amdgcn_readfirstlane(lds_off)), "n"(OFF), "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff))
                  : "memory", "scc");
 }
 

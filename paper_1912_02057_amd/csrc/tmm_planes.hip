@@ -93,13 +93,13 @@ __global__ __launch_bounds__(256, MINW) void k_gemm_planes(TmmParams prm, const 
                     if constexpr (EB == 16)
                         dma16_base(base, off, dst);
                     else
-                        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(dst), "v"(off), "s"(base) : "memory");
+                        dma4_base(base, off, dst);
                 } else {  // the stage that reaches past the rows' end
                     const int8_t* src = kb < rowb ? base + off : (const int8_t*)g_zero16;
                     if constexpr (EB == 16)
                         dma16(src, dst);
                     else
-                        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(dst), "v"(src) : "memory");
+                        dma4(src, dst);
                 }
             }
         };
