@@ -35,6 +35,26 @@ inline PackRowsForm pack_rows_planes_form(int64_t rows, int64_t Kpad)
     return {4, Kpad <= 2048 ? 4 : 8, 64};
 }
 
+// NCHW packs of few pixels and many channels, with scalar thresholds and no sums: does k_pack_nchw_small run?  `flat`: the
+// kernel with one block per image could (its LDS holds the image).  us, FP4, what runs otherwise -> this one:
+//   quads of pixels that lie in one image: everywhere
+//     64 x 1024 x 8 x 8  8.1 -> 4.2     1 x 948 x 62 x 62  10.8 -> 7.9     20 x 1024 x 14 x 14  9.8 -> 8.5
+//   else its time grows with the images: up to 17 of them or 800 pixels, and always beyond 1000 channels, where the
+//   general kernel takes twice the LDS
+//     9 x 513 x 9 x 9  13.6 -> 8.9      19 x 513 x 9 x 9  13.8 -> 13.1     49 x 513 x 9 x 9  15.0 -> 19.1
+//     88 x 513 x 3 x 3  15.3 -> 11.8    16 x 513 x 7 x 7  13.6 -> 11.7     177 x 513 x 3 x 3  15.3 -> 17.4
+//     33 x 768 x 11 x 11  18.7 -> 20.2  81 x 1021 x 7 x 7  24.4 -> 24.7    83 x 2048 x 7 x 7  46.0 -> 30.5
+//   against a block per image, whose time grows with the image: (int8) 1 x 516 x 9 x 9  6.9 -> 4.8
+//     1 x 1024 x 7 x 7  7.1 -> 5.4      2 x 1024 x 7 x 7  7.2 -> 6.4       2 x 768 x 7 x 7  5.7 -> 6.0
+//     83 x 576 x 7 x 7  5.3 -> 21.8     8 x 1280 x 7 x 7  8.6 -> 12.7      9 x 768 x 9 x 9  8.5 -> 9.6
+inline bool pack_nchw_few_pixels(int64_t N, int64_t K, int64_t HW, bool flat)
+{
+    if (N * HW > 4096 || K <= 512 || HW < 4) return false;
+    if (HW % 4 == 0) return true;
+    if (flat) return K * HW >= 26000 + 11000 * N;
+    return K > 1000 || N <= 17 || N * HW <= 800;
+}
+
 // Does a GEMM store y [M][N] with the non-temporal hint?  A burst of stores that the memory-side cache (256 MiB) absorbs
 // and writes back later slows the K loops of the tiles behind it, and hinted ones do not.  But a hinted store of a
 // part of a line goes to memory as it is, and the next kernel finds nothing in the cache.  us, plain -> hinted, two

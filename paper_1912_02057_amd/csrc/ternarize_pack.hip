@@ -635,10 +635,11 @@ hipError_t launch_pack_nchw_codes(const PackArgs& a, hipStream_t st)
     const int64_t px = a.N * a.HW;
     PackArgs b = a;
     b.div_hw = make_fastdiv((uint32_t)a.HW);
-    // Few pixels and many channels, where the other kernels are a few blocks of many rounds.  us, FP4, those -> this one:
-    //   3 x 771 x 11 x 11  18.2 -> 7.1     8 x 866 x 5 x 5  18.4 -> 8.1     1 x 948 x 62 x 62  10.8 -> 7.9
-    //   1 x 512 x 7 x 7  4.8 -> 5.0, 2 x 163 x 85 x 85  7.5 -> 5.9 but 30 x 48 x 62 x 62  7.3 -> 9.7: not taken
-    if (ordered && !sum && a.HW >= 4 && a.N * a.K * a.HW < ((int64_t)1 << 30) && px <= 4096 && a.K > 512) {
+    // small images with H*W % 4 != 0: one block per image over the flat C*H*W run
+    const size_t flat_smem = (size_t)a.HW * (a.Kpad + 4) + (size_t)a.HW * 4;
+    const bool flat = a.HW % 4 != 0 && (a.K * a.HW) % 4 == 0 && ((uintptr_t)a.x) % 16 == 0 && flat_smem <= 64 * 1024 && a.HW >= 4 &&
+                      a.K * a.HW < ((int64_t)1 << 30) && a.N <= 0x7fffffff;
+    if (ordered && !sum && a.N * a.K * a.HW < ((int64_t)1 << 30) && pack_nchw_few_pixels(a.N, a.K, a.HW, flat)) {
         const int64_t groups = (a.K + 63) / 64;
         b.div_groups = make_fastdiv((uint32_t)groups);
         hipLaunchKernelGGL(k_pack_nchw_small<FP4>, dim3((unsigned)((px + 511) / 512 * 8 * groups)), dim3(256), 0, st, b);
@@ -670,10 +671,7 @@ hipError_t launch_pack_nchw_codes(const PackArgs& a, hipStream_t st)
             go1(std::integral_constant<int, 64>{});
         return hipGetLastError();
     }
-    // small images with H*W % 4 != 0: one block per image over the flat C*H*W run
-    const size_t flat_smem = (size_t)a.HW * (a.Kpad + 4) + (size_t)a.HW * 4;
-    if ((a.K * a.HW) % 4 == 0 && ((uintptr_t)a.x) % 16 == 0 && flat_smem <= 64 * 1024 && a.HW >= 4 &&
-        a.K * a.HW < ((int64_t)1 << 30) && a.N <= 0x7fffffff) {
+    if (flat) {
         hipLaunchKernelGGL(k_pack_nchw_i8_flat<FP4>, dim3((unsigned)a.N), dim3(1024), flat_smem, st, a,
                            make_fastdiv((uint32_t)a.HW));
         return hipGetLastError();

@@ -35,6 +35,7 @@ extern "C" int ksplit(const int64_t *v, int limit)
     const rtn::KsplitShape s = {v[0], v[1], (int)v[2], (int)v[3], (int)v[4], (int)v[5], (int)v[6], (int)v[7], (int)v[8], (int)v[9]};
     return limit ? (int)rtn::ksplit_lds_bytes(rtn::kKsplitForms[limit - 1], s) : rtn::pick_ksplit(s);
 }
+extern "C" int few_pixels(int64_t N, int64_t K, int64_t HW, int flat) { return rtn::pack_nchw_few_pixels(N, K, HW, flat); }
 extern "C" int nt_hint(int64_t M, int64_t N, uintptr_t y, int nk) { return rtn::gemm_nt_hint(M, N, y, nk); }
 """
 
@@ -49,6 +50,7 @@ def L(tmp_path_factory):
     lib.pack_form.argtypes = [C.c_int, C.c_int64, C.c_int64, C.c_void_p]
     lib.ksplit.argtypes = [C.c_void_p, C.c_int]
     lib.tap_walk.argtypes = [C.c_int] * 5 + [C.c_void_p]
+    lib.few_pixels.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_int]
     lib.nt_hint.argtypes = [C.c_int64, C.c_int64, C.c_size_t, C.c_int]
     return lib
 
@@ -63,6 +65,19 @@ def test_row_pack_waves_have_work(L, planes):
             waves, turn = out[0], out[1] * out[2]
             assert waves in (1, 4) and turn > 0
             assert waves == 1 or (waves - 2) * turn < Kpad, (rows, Kpad, list(out))
+
+
+def test_pack_of_few_pixels(L):
+    """Both sides of each line of the rule."""
+    few = lambda N, K, H, W, flat: bool(L.few_pixels(N, K, H * W, flat))
+    assert few(64, 1024, 8, 8, 0) and few(1, 948, 62, 62, 0)
+    assert not few(65, 1024, 8, 8, 0) and not few(1, 512, 8, 8, 0) and not few(100, 600, 1, 3, 0)
+    assert few(17, 513, 9, 9, 0) and few(88, 513, 3, 3, 0) and few(83, 2048, 7, 7, 0)
+    assert not few(18, 513, 9, 9, 0) and not few(89, 513, 3, 3, 0) and not few(33, 768, 11, 11, 0)
+    # many small images with a block each: five times as long without it
+    assert few(1, 516, 9, 9, 1) and few(2, 1024, 7, 7, 1)
+    for shape in ((2, 768, 7, 7), (83, 576, 7, 7), (8, 1280, 7, 7), (9, 768, 9, 9), (444, 516, 3, 3), (64, 2048, 5, 5)):
+        assert not few(*shape, 1)
 
 
 def test_gemm_store_hint(L):
