@@ -55,6 +55,29 @@ inline bool pack_nchw_few_pixels(int64_t N, int64_t K, int64_t HW, bool flat)
     return K > 1000 || N <= 17 || N * HW <= 800;
 }
 
+// Lanes of k_pack_nchw that share a channel's run of pixels (4 each, 16 / 32 / 64 lanes): a block takes 64 to 256 pixels
+// and its groups are 256 to 64 channels.  The widest run that still gives every CU several blocks:
+// fewer lanes mean more blocks and fewer rounds over the channels, but masked channels and a vector address per
+// load where the channels are no multiple of the group.  So multiples of 64 take the run whose group divides them, if
+// that is blocks enough.  us, int8, a masked group of 256 -> a group that divides:
+//   multiples of 128, from 11264 pixels on
+//     256 x 384 x 14 x 14  23.2 -> 18.4   64 x 640 x 28 x 28  34.8 -> 29.6   46 x 1152 x 14 x 14  14.0 -> 12.9, not taken
+//   of 64, images up to 1024 pixels, where the last round of blocks, of four at most, has one for more than half of the CUs,
+//   or, with more than a third of the channels masked, in any number of rounds
+//     256 x 320 x 14 x 14  20.3 -> 16.6   256 x 576 x 14 x 14  34.1 -> 27.3  64 x 576 x 28 x 28  29.6 -> 26.2
+//     408 x 320 x 14 x 14  28.1 -> 25.0   1327 x 192 x 14 x 14  46.2 -> 42.3
+//     16 x 448 x 28 x 28   8.3 -> 13.2,   16 x 320 x 56 x 56   20.0 -> 20.6 and 256 x 448 x 28 x 28  80 -> 105: not taken
+inline int pack_nchw_lanes(int64_t K, int64_t Kpad, int64_t px, int64_t HW)
+{
+    if (K % 256 && K % 128 == 0 && px >= 11264) return px < 4096 * 256 ? 32 : 64;
+    if (K % 128 && K % 64 == 0) {
+        const int64_t blocks = (px + 255) / 256, masked = (K + 255) / 256 * 256 - K;
+        if (HW <= 1024 && ((blocks <= 1024 && (blocks - 1) % 256 >= 128) || (blocks > 256 && 2 * masked > K))) return 64;
+    }
+    if (Kpad >= 256 && px < 2048 * 256) return 16;
+    return Kpad >= 128 && K > 64 && px < 4096 * 256 ? 32 : 64;
+}
+
 // Does a GEMM store y [M][N] with the non-temporal hint?  A burst of stores that the memory-side cache (256 MiB) absorbs
 // and writes back later slows the K loops of the tiles behind it, and hinted ones do not.  But a hinted store of a
 // part of a line goes to memory as it is, and the next kernel finds nothing in the cache.  us, plain -> hinted, two

@@ -646,8 +646,7 @@ hipError_t launch_pack_nchw_codes(const PackArgs& a, hipStream_t st)
         return hipGetLastError();
     }
     if (a.HW % 4 == 0 && a.K * (2 * a.HW + 256) < ((int64_t)1 << 30)) {  // (32-bit offsets from a block's first image)
-        // the widest pixel runs that still give every CU several blocks
-        const int lpr = (a.Kpad >= 256 && px < 2048 * 256) ? 16 : (a.Kpad >= 128 && a.K > 64 && px < 4096 * 256) ? 32 : 64;
+        const int lpr = pack_nchw_lanes(a.K, a.Kpad, px, a.HW);
         const bool part = a.K % (64 * 64 / lpr) != 0;
         const dim3 grid((unsigned)((px + 4 * lpr - 1) / (4 * lpr)));
         const std::true_type yes{};

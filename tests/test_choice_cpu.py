@@ -36,6 +36,7 @@ extern "C" int ksplit(const int64_t *v, int limit)
     return limit ? (int)rtn::ksplit_lds_bytes(rtn::kKsplitForms[limit - 1], s) : rtn::pick_ksplit(s);
 }
 extern "C" int few_pixels(int64_t N, int64_t K, int64_t HW, int flat) { return rtn::pack_nchw_few_pixels(N, K, HW, flat); }
+extern "C" int pack_lanes(int64_t K, int64_t Kpad, int64_t px, int64_t HW) { return rtn::pack_nchw_lanes(K, Kpad, px, HW); }
 extern "C" int nt_hint(int64_t M, int64_t N, uintptr_t y, int nk) { return rtn::gemm_nt_hint(M, N, y, nk); }
 """
 
@@ -51,6 +52,7 @@ def L(tmp_path_factory):
     lib.ksplit.argtypes = [C.c_void_p, C.c_int]
     lib.tap_walk.argtypes = [C.c_int] * 5 + [C.c_void_p]
     lib.few_pixels.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_int]
+    lib.pack_lanes.argtypes = [C.c_int64] * 4
     lib.nt_hint.argtypes = [C.c_int64, C.c_int64, C.c_size_t, C.c_int]
     return lib
 
@@ -78,6 +80,21 @@ def test_pack_of_few_pixels(L):
     assert few(1, 516, 9, 9, 1) and few(2, 1024, 7, 7, 1)
     for shape in ((2, 768, 7, 7), (83, 576, 7, 7), (8, 1280, 7, 7), (9, 768, 9, 9), (444, 516, 3, 3), (64, 2048, 5, 5)):
         assert not few(*shape, 1)
+
+
+def test_pack_groups_divide_the_channels(L):
+    """Channels that a group divides are not masked where that is blocks enough; a row of any length has its run."""
+    lanes = lambda N, K, H: L.pack_lanes(K, -(-K // 64) * 64, N * H * H, H * H)
+    for K in (64, 128, 256, 512, 768, 1024, 2048):
+        for N, H in ((1, 8), (16, 28), (256, 28), (32, 56)):
+            assert K % (4096 // lanes(N, K, H)) == 0
+    for K in (384, 640, 896, 1152, 1920):
+        assert lanes(256, K, 14) == lanes(64, K, 28) == lanes(32, K, 56) == 32 and lanes(14, K, 28) == 16
+    for K in (192, 320, 448, 576, 960):
+        assert lanes(256, K, 14) == lanes(64, K, 28) == 64 and lanes(408, K, 14) == (64 if K == 320 else 32 if K == 192 else 16)
+        for N, H in ((16, 28), (16, 56), (32, 56), (160, 14)):
+            assert lanes(N, K, H) == (32 if K == 192 else 16)
+    assert lanes(256, 100, 14) == 32 and lanes(256, 300, 14) == 16 and lanes(256, 50, 14) == 64
 
 
 def test_gemm_store_hint(L):
