@@ -78,6 +78,13 @@ inline int pack_nchw_lanes(int64_t K, int64_t Kpad, int64_t px, int64_t HW)
     return Kpad >= 128 && K > 64 && px < 4096 * 256 ? 32 : 64;
 }
 
+// Do 32-bit offsets from a block's first image reach all elements of its at most 256 pixels?
+inline bool pack_nchw_offsets_fit(int64_t N, int64_t K, int64_t HW)
+{
+    const int64_t spanned = 255 / HW + 2, images = N < spanned ? N : spanned;
+    return images * K * HW < (int64_t)1 << 30;
+}
+
 // Does a GEMM store y [M][N] with the non-temporal hint?  A burst of stores that the memory-side cache (256 MiB) absorbs
 // and writes back later slows the K loops of the tiles behind it, and hinted ones do not.  But a hinted store of a
 // part of a line goes to memory as it is, and the next kernel finds nothing in the cache.  us, plain -> hinted, two

@@ -260,9 +260,11 @@ __global__ __launch_bounds__(256) void k_pack_nchw_i8(PackArgs a)
 //  PART: the channels are not a multiple of CG; those past the last read the last and get code 0.  us, FP4, against the
 //  kernel with bounds selects and 64-bit addresses per element that it replaced: 64 x 32 x 112 x 112 38.0 -> 24.9,
 //  50 x 25 x 64 x 64 13.2 -> 8.2, 70 x 107 x 42 x 42 13.9 -> 12.0.
-template <int LPR, bool FP4, bool SUM, bool ORDERED, bool PART>
+//  Off: of a lane's elements from the block's first image; 64 bits where 32 do not reach (pack_nchw_offsets_fit()).
+template <int LPR, bool FP4, bool SUM, bool ORDERED, bool PART, class Off = uint32_t>
 __global__ __launch_bounds__(256) void k_pack_nchw(PackArgs a)
 {
+    static_assert(PART || sizeof(Off) == 4, "64-bit offsets: the form with a vector address per load");
     typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
     constexpr int SUBS = 64 / LPR, PB = 4 * LPR, SLOT = FP4 ? 8 : 16, NSLOT = 4 * SUBS, RB = SLOT * NSLOT;
     constexpr int CG = 64 * SUBS;
@@ -280,7 +282,7 @@ __global__ __launch_bounds__(256) void k_pack_nchw(PackArgs a)
     const int n0 = (int)fastdiv_flat((uint32_t)q0, a.div_hw);  // the block's first image: offsets are from there
     const float* const x0 = a.x + (int64_t)n0 * K * HW;
     const float lo = thr(a.lo, n), hi = thr(a.hi, n);
-    const uint32_t off = ((uint32_t)((n - n0) * K + (PART ? 0 : cblk * 16)) * (uint32_t)HW + (uint32_t)p) * 4u;
+    const Off off = ((Off)((n - n0) * K + (PART ? 0 : cblk * 16)) * (Off)HW + (Off)p) * 4u;
     const int ngroup = PART ? (K + CG - 1) / CG : K / CG;
     const int valid = total - q0 < PB ? total - q0 : PB;
     const int rowb = (int)(FP4 ? a.Kpad >> 1 : a.Kpad);
@@ -293,7 +295,7 @@ __global__ __launch_bounds__(256) void k_pack_nchw(PackArgs a)
         for (int j = 0; j < 16; ++j) {
             if (PART) {
                 const int c = cg * CG + cblk * 16 + j;
-                v[j] = *(const f4*)((const char*)x0 + (off + (uint32_t)(c < K ? c : K - 1) * (uint32_t)HW * 4u));
+                v[j] = *(const f4*)((const char*)x0 + (off + (Off)(c < K ? c : K - 1) * (Off)HW * 4u));
             } else {
                 const float* base = x0 + (int64_t)(cg * CG + j) * HW;  // wave-uniform
                 v[j] = *(const f4*)((const char*)base + off);
@@ -364,7 +366,7 @@ __global__ __launch_bounds__(256) void k_pack_nchw(PackArgs a)
         const int px = e / padu, u = e - px * padu;
         if (px < valid) *(uint4*)(out + (size_t)px * rowb + donebytes + 16 * u) = make_uint4(0, 0, 0, 0);
     }
-    if (SUM) {
+    if (SUM && (sizeof(Off) == 4 || a.sum_t)) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             int t = sum[i];
@@ -645,7 +647,14 @@ hipError_t launch_pack_nchw_codes(const PackArgs& a, hipStream_t st)
         hipLaunchKernelGGL(k_pack_nchw_small<FP4>, dim3((unsigned)((px + 511) / 512 * 8 * groups)), dim3(256), 0, st, b);
         return hipGetLastError();
     }
-    if (a.HW % 4 == 0 && a.K * (2 * a.HW + 256) < ((int64_t)1 << 30)) {  // (32-bit offsets from a block's first image)
+    // (At least half a million pixels.  Always with the sums, which memory hides, stored where they are wanted: FP4, 1 x 64 x
+    // 4100 x 4100 1014 us, without them 1183; 1 x 37 x 5000 x 5000 965 and 948, the general kernel 1420.)
+    if (a.HW % 4 == 0 && !pack_nchw_offsets_fit(a.N, a.K, a.HW)) {
+        const dim3 grid((unsigned)((px + 255) / 256));
+        hipLaunchKernelGGL((k_pack_nchw<64, FP4, true, false, true, uint64_t>), grid, dim3(256), 0, st, b);
+        return hipGetLastError();
+    }
+    if (a.HW % 4 == 0) {
         const int lpr = pack_nchw_lanes(a.K, a.Kpad, px, a.HW);
         const bool part = a.K % (64 * 64 / lpr) != 0;
         const dim3 grid((unsigned)((px + 4 * lpr - 1) / (4 * lpr)));

@@ -37,6 +37,7 @@ extern "C" int ksplit(const int64_t *v, int limit)
 }
 extern "C" int few_pixels(int64_t N, int64_t K, int64_t HW, int flat) { return rtn::pack_nchw_few_pixels(N, K, HW, flat); }
 extern "C" int pack_lanes(int64_t K, int64_t Kpad, int64_t px, int64_t HW) { return rtn::pack_nchw_lanes(K, Kpad, px, HW); }
+extern "C" int pack_offsets_fit(int64_t N, int64_t K, int64_t HW) { return rtn::pack_nchw_offsets_fit(N, K, HW); }
 extern "C" int nt_hint(int64_t M, int64_t N, uintptr_t y, int nk) { return rtn::gemm_nt_hint(M, N, y, nk); }
 """
 
@@ -53,6 +54,7 @@ def L(tmp_path_factory):
     lib.tap_walk.argtypes = [C.c_int] * 5 + [C.c_void_p]
     lib.few_pixels.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_int]
     lib.pack_lanes.argtypes = [C.c_int64] * 4
+    lib.pack_offsets_fit.argtypes = [C.c_int64] * 3
     lib.nt_hint.argtypes = [C.c_int64, C.c_int64, C.c_size_t, C.c_int]
     return lib
 
@@ -95,6 +97,16 @@ def test_pack_groups_divide_the_channels(L):
         for N, H in ((16, 28), (16, 56), (32, 56), (160, 14)):
             assert lanes(N, K, H) == (32 if K == 192 else 16)
     assert lanes(256, 100, 14) == 32 and lanes(256, 300, 14) == 16 and lanes(256, 50, 14) == 64
+
+
+def test_pack_offsets(L):
+    """32-bit offsets for every block whose images they reach: the last element of 256 consecutive pixels, in bytes."""
+    for N, K, HW in ((1, 64, 9000000), (1, 64, 1 << 24), (2, 64, 9000000), (2, 64, 1 << 23), (1, 2048, 1 << 19), (3, 2048, 1 << 18),
+                     (1 << 20, 2048, 4), (4096, 2048, 256), (1000, 2048, 4096), (1, 1, (1 << 30) - 4), (1, 1, 1 << 30)):
+        last = max(((N * HW - 1 if q + 255 >= N * HW else q + 255) // HW - q // HW) for q in (0, HW - 1, 4 * (HW // 8))) + 1
+        fits = bool(L.pack_offsets_fit(N, K, HW))
+        assert not fits or 4 * last * K * HW <= 1 << 32, (N, K, HW)
+        assert fits or 4 * min(N, last + 1) * K * HW >= 1 << 32, (N, K, HW)
 
 
 def test_gemm_store_hint(L):

@@ -169,6 +169,29 @@ def test_pack_nchw_forms(shape):
             assert (codes.cpu().numpy() == want).all() and (s.cpu().numpy() == orc.pixel_sums(t)).all()
 
 
+@pytest.mark.parametrize("shape", [(1, 64, 3000, 3000), (2, 64, 2900, 2900),      # offsets of 31 bits and more; two images, 32
+                                   (2, 37, 3840, 3844), (1, 130, 2900, 2900)])      # more
+def test_pack_nchw_large_images(shape):
+    """Images of 2 to 4.4 GB, where a block's offsets no longer fit 32 bits, against torch's comparisons."""
+    _say("pack_nchw large %s" % (shape,))
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(sum(shape))
+    x = torch.randn(shape, generator=g, device=T.DEV)
+    t = ((x > 0.5).to(torch.int8) - (x < -0.7).to(torch.int8)).permute(0, 2, 3, 1)
+    codes, s = B.ternarize_pack(x, -0.7, 0.5, B.RTN_CODE_I8)
+    assert torch.equal(codes[..., :shape[1]], t) and not codes[..., shape[1]:].any()
+    sums = t.sum(-1, dtype=torch.int32)
+    assert torch.equal(s.reshape(sums.shape), sums)
+    del codes, s, sums
+    codes, _ = B.ternarize_pack(x, -0.7, 0.5, B.RTN_CODE_FP4, want_sum=False)
+    del x
+    nib = torch.tensor([0, 2, 10], dtype=torch.uint8, device=T.DEV)      # of codes 0, 1, -1
+    for half in (0, 1):
+        want = nib[t[..., half::2].long() % 3]
+        got = (codes >> (4 * half)) & 15
+        assert torch.equal(got[..., :want.shape[-1]], want) and not got[..., want.shape[-1]:].any()
+
+
 # ------------------------------------------------------ S2 + S4: GEMM -------
 GEMM_SHAPES = [(1, 1, 1), (37, 19, 131), (64, 64, 64), (65, 33, 64), (300, 200, 576), (129, 257, 1000),
                (512, 384, 2048), (1024, 1024, 512)]
