@@ -31,4 +31,17 @@ struct TapWalk {
     }
 };
 
+// Does a conv's tile of bq pixels lie within 32-bit offsets from its first image, of codes (with the window's reach before
+// and behind an image) and, for a block tail, of outputs?  `ohw` output pixels of an image, `pixel` bytes of its codes.
+// The pixel-run tiles (halo) take 64-bit pointers to their codes.
+inline bool conv_offsets_fit(int64_t Nb, int64_t H, int64_t W, int64_t pixel, int64_t O, int64_t ohw, int bq, bool halo, bool tail)
+{
+    const int64_t spanned = (bq - 1) / ohw + 2, images = Nb < spanned ? Nb : spanned;
+    if (tail && ((images - 1) * O + 8) * ohw * 4 > (int64_t)0xffffffffu) return false;
+    return halo || (images * H + 16) * W * pixel < (int64_t)0x80000000u;
+}
+
+// Input pixels that a pixel-run tile of bq pixels holds, a multiple of 16
+inline int64_t halo_rows(int bq, int pad, int W) { return (bq + 2 * (int64_t)pad * ((int64_t)W + 1) + 15) & ~(int64_t)15; }
+
 }  // namespace rtn

@@ -1230,12 +1230,9 @@ inline unsigned tile_grid(TmmParams& prm, int bp, int bq)
     return (unsigned)((blocks + 7) / 8 * 8);
 }
 
-// Does a conv's tile of bq pixels lie within 32-bit offsets from its first image, of codes and (block tail) of outputs?
 inline bool conv_offsets_fit(const ConvGeom& g, int bq, bool halo, bool tail)
 {
-    const int64_t ohw = (int64_t)g.OH * g.OW, images = (bq - 1) / ohw + 2, row = (int64_t)g.W * g.Cpad;
-    if (tail && ((images - 1) * g.O + 8) * ohw * 4 > (int64_t)0xffffffffu) return false;
-    return halo || (images * g.H + 16) * row < (int64_t)kOutside;
+    return rtn::conv_offsets_fit(g.Nb, g.H, g.W, g.Cpad, g.O, (int64_t)g.OH * g.OW, bq, halo, tail);
 }
 
 template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0, bool NT = false, bool BIG = false>
@@ -1246,8 +1243,9 @@ hipError_t launch_cfg(TmmParams& prm, hipStream_t st)
     if (CONV && !BIG && !conv_offsets_fit(prm.g, BQ, HC != 0, TERN == 2)) return hipErrorInvalidValue;
     if (HC) {
         if (!halo_eligible(prm, HC)) return hipErrorInvalidValue;
-        prm.hrows = (BQ + 2 * prm.g.pad * (prm.g.W + 1) + 15) & ~15;
-        stage_bytes += (int64_t)prm.hrows * HC + 128;
+        const int64_t rows = halo_rows(BQ, prm.g.pad, prm.g.W);
+        prm.hrows = (int)rows;
+        stage_bytes += rows * HC + 128;
     }
     int64_t smem;
     if (CONV) {

@@ -119,7 +119,7 @@ int pick_tile(int64_t rp, int64_t rq, int nk, bool conv)
 int pick_halo(const TmmParams& prm, bool codes, bool tail)
 {
     const ConvGeom& g = prm.g;
-    if (g.KH < 3 || !halo_eligible(prm, 64) || (128 + 2 * g.pad * (g.W + 1)) * 64 > 24 * 1024) return -1;
+    if (g.KH < 3 || !halo_eligible(prm, 64) || halo_rows(128, g.pad, g.W) * 64 > 24 * 1024) return -1;
     return !tail && nblocks(g.O, prm.RQ, 64, 256) >= (codes ? 3072 : 1536) ? 15 : 17;
 }
 

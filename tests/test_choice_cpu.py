@@ -25,6 +25,11 @@ extern "C" void tap_walk(int big, int W, int Cpad, int KW, int steps, int64_t *o
 {
     big ? walk<true>(W, Cpad, KW, steps, out) : walk<false>(W, Cpad, KW, steps, out);
 }
+extern "C" int conv_fit(int64_t Nb, int64_t H, int64_t W, int64_t pixel, int64_t O, int64_t ohw, int bq, int halo, int tail)
+{
+    return rtn::conv_offsets_fit(Nb, H, W, pixel, O, ohw, bq, halo, tail);
+}
+extern "C" int64_t halo_rows(int bq, int pad, int W) { return rtn::halo_rows(bq, pad, W); }
 extern "C" void pack_form(int planes, int64_t rows, int64_t Kpad, int *out)
 {
     const rtn::PackRowsForm f = planes ? rtn::pack_rows_planes_form(rows, Kpad) : rtn::pack_rows_form(rows, Kpad);
@@ -55,6 +60,8 @@ def L(tmp_path_factory):
     lib.few_pixels.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_int]
     lib.pack_lanes.argtypes = [C.c_int64] * 4
     lib.pack_offsets_fit.argtypes = [C.c_int64] * 3
+    lib.conv_fit.argtypes = [C.c_int64] * 6 + [C.c_int] * 3
+    lib.halo_rows.argtypes, lib.halo_rows.restype = [C.c_int] * 3, C.c_int64
     lib.nt_hint.argtypes = [C.c_int64, C.c_int64, C.c_size_t, C.c_int]
     return lib
 
@@ -187,6 +194,38 @@ def test_tap_offsets_of_a_window(L, big, W, Cpad, KH, KW):
     out = (C.c_int64 * (3 * len(steps)))()
     L.tap_walk(big, W, Cpad, KW, len(steps), out)
     assert [tuple(out[3 * i:3 * i + 3]) for i in range(len(steps))] == steps
+
+
+@pytest.mark.parametrize("Nb,H,W,pixel,k,stride", [
+    (1, 4096, 4096, 64, 3, 1), (2, 4096, 4096, 64, 3, 64), (1, 5780, 5780, 64, 3, 64), (1, 5800, 5800, 64, 3, 64), (300, 3, 2, 64, 3, 1),
+    (9, 8, 1000, 8192, 7, 1), (33, 5, 2000, 8192, 5, 2), (5, 300, 300, 8192, 1, 1), (1, 2, 1 << 25, 64, 3, 1), (1, 1, 1 << 24, 64, 1, 1)])
+def test_conv_offsets_fit(L, Nb, H, W, pixel, k, stride):
+    """Where a tile's offsets are said to fit, the last byte that it reads lies below 2^31 from its base (the first tap of a
+    corner pixel of its first image), and so does a tap outside; an image that no tile shares is not counted twice."""
+    pad = min(k // 2, 2)
+    OH, OW = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+    ohw, bias = OH * OW, pad * (W + 1) * pixel
+    for bq in (64, 128, 256):
+        most = 0
+        for q0 in {0, bq, ohw // bq * bq, (Nb * ohw - 1) // bq * bq, (ohw * Nb // 2) // bq * bq}:
+            m = min(q0 + bq, Nb * ohw) - 1
+            if m < q0:
+                continue
+            nb, pix = m // ohw - q0 // ohw, m % ohw
+            oh, ow = (pix // OW, pix % OW) if nb == 0 else (OH - 1, OW - 1)
+            most = max(most, ((nb * H + oh * stride - pad + k - 1) * W + ow * stride - pad + k) * pixel + bias)
+        fits = bool(L.conv_fit(Nb, H, W, pixel, 8, ohw, bq, 0, 0))
+        assert not fits or most < 1 << 31, (bq, most)
+        assert fits or (min(Nb, (bq - 1) // ohw + 2) * H + 16) * W * pixel >= 1 << 31
+        assert L.conv_fit(Nb, H, W, pixel, 8, ohw, bq, 1, 0)
+    assert bool(L.conv_fit(1, 4096, 4096, 64, 8, 4096 ** 2, 64, 0, 0)) and not L.conv_fit(2, 4096, 4096, 64, 8, 4096 ** 2, 64, 0, 0)
+    assert L.conv_fit(1, 4096, 4096, 64, 128, 4096 ** 2, 64, 1, 1) and not L.conv_fit(2, 4096, 4096, 64, 128, 4096 ** 2, 64, 1, 1)
+
+
+def test_halo_rows(L):
+    """The pixel run of a tile is counted in 64 bits, whole multiples of 16."""
+    assert L.halo_rows(128, 1, 56) == 256 and L.halo_rows(256, 2, 13) == 320
+    assert L.halo_rows(128, 2, (1 << 31) - 1025) == (128 + 4 * ((1 << 31) - 1024) + 15) // 16 * 16
 
 
 LDS_SHIM = r"""

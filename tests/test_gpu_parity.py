@@ -2001,32 +2001,41 @@ def test_depthwise_3x3_thousands_of_channels(C, H, stride, batch):
     T.assert_y_close(yy.cpu().numpy(), y, "depthwise y")
 
 
-@pytest.mark.parametrize("side", [3200, 4096])
-def test_conv_on_images_beyond_32_bit_offsets(side):
-    """Windows far apart on one image of 0.65 and 1.07 GB of codes (a tile's offsets fit 32 bits in the one and not
-    in the other): the same bits as on the small image of just those windows."""
-    _say("conv stride 64 on %d x %d" % (side, side))
+@pytest.mark.parametrize("fmt", [B.RTN_CODE_FP4, B.RTN_CODE_I8])
+@pytest.mark.parametrize("side,pad,batch,cfg", [
+    (3200, 0, 1, -1), (4096, 0, 1, -1), (4097, 1, 1, 0), (4097, 1, 1, 1), (3201, 1, 2, 13),   # 0.65 to 1.3 GB of codes: 32-bit offsets
+    (4097, 1, 2, -1),                                                                         # a tile on two images of 1.07 GB
+    (5825, 0, 1, -1), (5825, 1, 1, 1), (5825, 1, 1, -1)])                                     # 2.17 GB: windows beyond 2^31
+def test_conv_on_images_beyond_32_bit_offsets(side, pad, batch, cfg, fmt, tile_reset):
+    """Windows far apart on large images, with 32-bit offsets up to their limit and with the 64-bit ones beyond it; padded,
+    the first and the last window reach out of the image: the same bits as on the small image of just those windows."""
+    _say("conv stride 64 on %d x %d x %d pad %d fmt %d cfg %d" % (batch, side, side, pad, fmt, cfg))
     C, O, k, s = 64, 256, 3, 64
     g = torch.Generator(device=T.DEV)
     g.manual_seed(side)
-    lut = torch.tensor([a | b << 4 for a in (0, 2, 10) for b in (0, 2, 10)], dtype=torch.uint8, device=T.DEV)
-    OH = (side - k) // s + 1
-    pick = (torch.arange(OH, device=T.DEV)[:, None] * s + torch.arange(k, device=T.DEV)).reshape(-1)
-    small = torch.zeros((1, OH * k, OH * k, 64), dtype=torch.uint8, device=T.DEV)      # 64 channels are padded to 128 codes
-    small[..., :32] = lut[torch.randint(0, 9, (1, OH * k, OH * k, 32), generator=g, device=T.DEV)]
-    big = torch.full((1, side, side, 64), 0x22, dtype=torch.uint8, device=T.DEV)       # what lies between is never read
-    big[0][pick[:, None], pick[None, :]] = small[0]
+    i8 = fmt == B.RTN_CODE_I8
+    dt, n = (torch.int8, 64) if i8 else (torch.uint8, 32)                 # (64 channels are padded to 128 FP4 codes)
+    values = torch.tensor([-1, 0, 1] if i8 else [a | b << 4 for a in (0, 2, 10) for b in (0, 2, 10)], dtype=dt, device=T.DEV)
+    OH = (side + 2 * pad - k) // s + 1
+    pick = [r for i in range(OH) for r in range(s * i - pad, s * i - pad + k) if 0 <= r < side]
+    assert len(pick) == OH * k - 2 * pad
+    small = torch.zeros((batch, len(pick), len(pick), 64), dtype=dt, device=T.DEV)
+    small[..., :n] = values[torch.randint(0, len(values), small.shape[:3] + (n,), generator=g, device=T.DEV)]
+    big = torch.full((batch, side, side, 64), 1 if i8 else 0x22, dtype=dt, device=T.DEV)       # what lies between is never read
+    at = torch.tensor(pick, device=T.DEV)
+    big[:, at[:, None], at[None, :]] = small
     w = torch.randn((O, C, k, k), generator=g, device=T.DEV)
-    cw, sw = B.ternarize_pack(w, -0.4, 0.4, B.RTN_CODE_FP4)
+    cw, sw = B.ternarize_pack(w, -0.4, 0.4, fmt)
     ep = B.Epilogue(1.1, 0.2, torch.rand(O, generator=g, device=T.DEV) + 0.5, torch.rand(O, generator=g, device=T.DEV) - 0.5, None, sw, relu=True)
-    res = torch.randn((1, O, OH, OH), generator=g, device=T.DEV)
+    res = torch.randn((batch, O, OH, OH), generator=g, device=T.DEV)
     out = []
-    for codes, n, stride in ((big, side, s), (small, OH * k, k)):
-        y = B.ternary_conv2d(codes, cw, 1, C, n, n, O, k, k, stride, 0, ep=ep, fmt=B.RTN_CODE_FP4)[1]
+    for codes, n, stride in ((big, side, s), (small, len(pick), k)):
+        B.set_tile_config(cfg if codes is big else -1)
+        y = B.ternary_conv2d(codes, cw, batch, C, n, n, O, k, k, stride, pad, ep=ep, fmt=fmt)[1]
         y2 = torch.empty_like(y)
-        c1 = B.ternary_conv2d_ternarize(codes, cw, 1, C, n, n, O, k, k, stride, 0, ep, -0.4, 0.6, fmt=B.RTN_CODE_FP4)
-        c2 = B.ternary_conv2d_ternarize(codes, cw, 1, C, n, n, O, k, k, stride, 0, ep, -0.4, 0.6, residual=res, relu_out=True, y_out=y2,
-                                        fmt=B.RTN_CODE_FP4)
+        c1 = B.ternary_conv2d_ternarize(codes, cw, batch, C, n, n, O, k, k, stride, pad, ep, -0.4, 0.6, fmt=fmt)
+        c2 = B.ternary_conv2d_ternarize(codes, cw, batch, C, n, n, O, k, k, stride, pad, ep, -0.4, 0.6, residual=res, relu_out=True, y_out=y2,
+                                        fmt=fmt)
         out.append([t[0] if isinstance(t, (tuple, list)) else t for t in (y, c1, c2, y2)])
     torch.cuda.synchronize()
     for a, b in zip(*out):
