@@ -31,14 +31,30 @@ struct TapWalk {
     }
 };
 
-// Does a conv's tile of bq pixels lie within 32-bit offsets from its first image, of codes (with the window's reach before
-// and behind an image) and, for a block tail, of outputs?  `ohw` output pixels of an image, `pixel` bytes of its codes.
-// The pixel-run tiles (halo) take 64-bit pointers to their codes.
-inline bool conv_offsets_fit(int64_t Nb, int64_t H, int64_t W, int64_t pixel, int64_t O, int64_t ohw, int bq, bool halo, bool tail)
+// Input pixels between tap (0, 0) of the first and the last tap of the last of t consecutive output pixels, at most: each
+// step is `stride` pixels, and some are the ends of a row or of an image.
+inline int64_t conv_span(int64_t H, int64_t W, int64_t OH, int64_t OW, int64_t KH, int64_t KW, int64_t stride, int64_t t)
+{
+    const int64_t row = stride * (W - OW), img = (H - (OH - 1) * stride) * W - OW * stride;
+    const int64_t nrow = (t - 2) / OW + 1, nimg = (t - 2) / (OH * OW) + 1;
+    return (t - 1) * stride + nrow * (row > 0 ? row : 0) + nimg * (img > 0 ? img : 0) + (KH - 1) * W + KW;
+}
+
+// A padded window's corner lies at most this many pixels before that of an earlier output pixel (of the image before,
+// where the padding at its end and at the start of the next are more than the window).
+constexpr int64_t conv_reach_back(int64_t pad, int64_t W) { return pad * (W + 1); }
+
+// Does a conv's tile of bq pixels lie within 32-bit offsets from that far before its first window?  `pixel` bytes of codes.
+inline bool conv_codes_fit(int64_t H, int64_t W, int64_t OH, int64_t OW, int64_t KH, int64_t KW, int64_t stride, int64_t pad, int64_t pixel, int bq)
+{
+    return (conv_span(H, W, OH, OW, KH, KW, stride, bq) + conv_reach_back(pad, W)) * pixel + 128 < (int64_t)0x80000000u;
+}
+
+// Do a block tail's outputs of a tile of bq pixels, 8 channels of all its images, lie within 32-bit offsets?
+inline bool conv_outputs_fit(int64_t Nb, int64_t O, int64_t ohw, int bq)
 {
     const int64_t spanned = (bq - 1) / ohw + 2, images = Nb < spanned ? Nb : spanned;
-    if (tail && ((images - 1) * O + 8) * ohw * 4 > (int64_t)0xffffffffu) return false;
-    return halo || (images * H + 16) * W * pixel < (int64_t)0x80000000u;
+    return ((images - 1) * O + 8) * ohw * 4 <= (int64_t)0xffffffffu;
 }
 
 // Input pixels that a pixel-run tile of bq pixels holds, a multiple of 16

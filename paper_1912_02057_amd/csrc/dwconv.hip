@@ -583,14 +583,8 @@ __global__ __launch_bounds__(256, BW && NCG == 4 ? 3 : 4) void k_dwconv3_mm(DwCo
     }
 }
 
-// Input pixels between tap (0, 0) of the first and tap (2, 2) of the last of `t` consecutive output pixels, at most:
-// each step is `stride` pixels, and some are the ends of a row or of an image.
-int64_t dw_run(const ConvGeom& g, int t)
-{
-    const int64_t s = g.stride, row = s * (g.W - g.OW), img = (int64_t)(g.H - (g.OH - 1) * s) * g.W - g.OW * s;
-    const int64_t nrow = (t - 2) / g.OW + 1, nimg = (t - 2) / ((int64_t)g.OH * g.OW) + 1;
-    return (t - 1) * s + nrow * (row > 0 ? row : 0) + nimg * (img > 0 ? img : 0) + 2 * (int64_t)g.W + 3;
-}
+// Input pixels of the run of `t` consecutive output pixels, at most
+int64_t dw_run(const ConvGeom& g, int t) { return conv_span(g.H, g.W, g.OH, g.OW, 3, 3, g.stride, t); }
 
 }  // namespace
 

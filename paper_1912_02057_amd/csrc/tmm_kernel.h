@@ -523,10 +523,10 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     const int lrow = lane >> 2;
     const int lchunk = (lane & 3) ^ swz(lrow);
     // A block-uniform base and a 32-bit offset per lane (at most 256 rows of at most 2^22 bytes).  The conv's Q operand
-    // is counted from its tile's first image and from `bias` bytes before it, where the first tap of a corner pixel lies,
-    // so that no offset is negative; a tap outside the image gets one that reads nothing.  BIG: images for which
-    // 32 bits do not suffice (and the 64 x 64 tile, which is always there) take a pointer per lane, the zero page for
-    // such a tap, and five more instructions per load.
+    // is counted from `bias` bytes before the first tap of the tile's first pixel, so that no offset is negative (counted
+    // from its image, images of 2 GiB would not fit 32 bits); a tap outside the image gets one that reads nothing.
+    // BIG: image rows for which 32 bits do not suffice (and the 64 x 64 tile, which is always there) take a pointer per
+    // lane, the zero page for such a tap, and five more instructions per load.
     const v4i rsrcP = buffer_base(prm.P + (int64_t)p0 * prm.ldP);
     unsigned offP[LP];
 #pragma unroll
@@ -538,9 +538,14 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     const int8_t* gQ[LQA];
     unsigned offQ[LQA];
     int vout[LQA];  // conv: bit kh = row tap outside the image, bit (8 + kw) = column tap outside
-    const int bias = CONV && !HALO && !BIG ? g.pad * (g.W + 1) * g.Cpad : 0;
-    const int nb0 = CONV && !HALO ? (int)fastdiv((uint32_t)q0, g.div_ohw) : 0;
-    const v4i rsrcQ = buffer_base(CONV ? prm.Q + (int64_t)nb0 * (g.H * g.W) * g.Cpad - bias : prm.Q + (int64_t)q0 * prm.ldQ);
+    int bias = 0, first_px = 0;  // (the pixel may lie before the tensor)
+    if (CONV && !HALO && !BIG) {
+        const int nb = (int)fastdiv((uint32_t)q0, g.div_ohw), pix = q0 - nb * (g.OH * g.OW);
+        const int oh = (int)fastdiv((uint32_t)pix, g.div_ow), ow = pix - oh * g.OW;
+        first_px = (nb * g.H + oh * g.stride - g.pad) * g.W + ow * g.stride - g.pad;
+        bias = (int)conv_reach_back(g.pad, g.W) * g.Cpad;
+    }
+    const v4i rsrcQ = buffer_base(CONV ? prm.Q + (int64_t)first_px * g.Cpad - bias : prm.Q + (int64_t)q0 * prm.ldQ);
 #pragma unroll
     for (int j = 0; j < LQ; ++j) {
         int row = q0 + 16 * (wave + 4 * j) + lrow;
@@ -557,7 +562,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
             if (BIG)
                 gQ[j] = prm.Q + (((int64_t)nb * g.H + ih0) * g.W + iw0) * g.Cpad + lchunk * 16;
             else
-                offQ[j] = (unsigned)(((nb - nb0) * g.H + ih0) * g.W + iw0) * (unsigned)g.Cpad + (unsigned)(bias + lchunk * 16);
+                offQ[j] = (unsigned)((nb * g.H + ih0) * g.W + iw0 - first_px) * (unsigned)g.Cpad + (unsigned)(bias + lchunk * 16);
         } else {
             offQ[j] = (unsigned)(row - q0) * (unsigned)prm.ldQ + lchunk * 16;
         }
@@ -1230,9 +1235,11 @@ inline unsigned tile_grid(TmmParams& prm, int bp, int bq)
     return (unsigned)((blocks + 7) / 8 * 8);
 }
 
+// (the pixel-run tiles, halo, take 64-bit pointers to their codes)
 inline bool conv_offsets_fit(const ConvGeom& g, int bq, bool halo, bool tail)
 {
-    return rtn::conv_offsets_fit(g.Nb, g.H, g.W, g.Cpad, g.O, (int64_t)g.OH * g.OW, bq, halo, tail);
+    return (halo || conv_codes_fit(g.H, g.W, g.OH, g.OW, g.KH, g.KW, g.stride, g.pad, g.Cpad, bq)) &&
+           (!tail || conv_outputs_fit(g.Nb, g.O, (int64_t)g.OH * g.OW, bq));
 }
 
 template <int BP, int BQ, int WGP, int WGQ, int NS, int MINW, bool CONV, int TERN = 0, int HC = 0, int DT = 0, bool NT = false, bool BIG = false>

@@ -259,6 +259,24 @@ hipError_t launch_wgemm(const WGemmArgs& a, hipStream_t st)
 hipError_t launch_conv_mfma(const ConvArgs& a, hipStream_t st)
 {
     const ConvGeom& g = a.g;
+    const bool tail = a.codes && (a.res != nullptr || a.y != nullptr || a.relu_out);
+    const int64_t ohw = (int64_t)g.OH * g.OW, outputs = (int64_t)g.O * ohw;
+    if (tail && g.Nb > 1 && ohw >= 4096 && !conv_outputs_fit(g.Nb, g.O, ohw, 64)) {
+        // images of some 4 GiB of outputs each, one by one: a tile on two of them would need 64-bit offsets
+        const int64_t inputs = (int64_t)g.H * g.W * (a.fp4 ? g.Cpad / 2 : g.Cpad);
+        for (int n = 0; n < g.Nb; ++n) {
+            ConvArgs one = a;
+            one.g.Nb = 1;
+            one.a = a.a + n * inputs;
+            one.codes = a.codes + n * ohw * a.ldc;
+            if (a.acc) one.acc = a.acc + n * outputs;
+            if (a.y) one.y = a.y + n * outputs;
+            if (a.res) one.res = a.res + n * outputs;
+            const hipError_t e = launch_conv_mfma(one, st);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     TmmParams prm = {};
     prm.P = a.w;
     prm.Q = a.a;
@@ -288,12 +306,11 @@ hipError_t launch_conv_mfma(const ConvArgs& a, hipStream_t st)
     const int form = g_forced_tile >= 0 ? -1 : pick_ksplit(ksplit_shape(prm, true));
     if (form >= 0) {
         if (!a.codes) return a.fp4 ? launch_ksplit<true, 0, 2>(form, prm, st) : launch_ksplit<true, 0, 0>(form, prm, st);
-        if (a.res != nullptr || a.y != nullptr || a.relu_out)
+        if (tail)
             return a.fp4 ? launch_ksplit<true, 2, 2>(form, prm, st) : launch_ksplit<true, 2, 0>(form, prm, st);
         return a.fp4 ? launch_ksplit<true, 1, 2>(form, prm, st) : launch_ksplit<true, 1, 0>(form, prm, st);
     }
     int cfg = g_forced_tile >= 0 ? g_forced_tile : pick_tile(g.O, prm.RQ, prm.nk, true);
-    const bool tail = a.codes && (a.res != nullptr || a.y != nullptr || a.relu_out);
     if (g_forced_tile < 0) {
         const int halo = pick_halo(prm, a.codes && !tail, tail);
         if (halo >= 0 && nblocks(g.O, prm.RQ, 64, 64) > 1024)

@@ -1,6 +1,7 @@
 """The size rules of csrc/choice.h and the offsets of csrc/conv_offsets.h, compiled for the host."""
 import ctypes as C
 import os
+import random
 import subprocess
 
 import pytest
@@ -25,10 +26,13 @@ extern "C" void tap_walk(int big, int W, int Cpad, int KW, int steps, int64_t *o
 {
     big ? walk<true>(W, Cpad, KW, steps, out) : walk<false>(W, Cpad, KW, steps, out);
 }
-extern "C" int conv_fit(int64_t Nb, int64_t H, int64_t W, int64_t pixel, int64_t O, int64_t ohw, int bq, int halo, int tail)
+extern "C" int64_t conv_span(const int64_t *v, int t) { return rtn::conv_span(v[0], v[1], v[2], v[3], v[4], v[5], v[6], t); }
+extern "C" int64_t reach_back(int64_t pad, int64_t W) { return rtn::conv_reach_back(pad, W); }
+extern "C" int codes_fit(const int64_t *v, int64_t pad, int64_t pixel, int bq)
 {
-    return rtn::conv_offsets_fit(Nb, H, W, pixel, O, ohw, bq, halo, tail);
+    return rtn::conv_codes_fit(v[0], v[1], v[2], v[3], v[4], v[5], v[6], pad, pixel, bq);
 }
+extern "C" int outputs_fit(int64_t Nb, int64_t O, int64_t ohw, int bq) { return rtn::conv_outputs_fit(Nb, O, ohw, bq); }
 extern "C" int64_t halo_rows(int bq, int pad, int W) { return rtn::halo_rows(bq, pad, W); }
 extern "C" void pack_form(int planes, int64_t rows, int64_t Kpad, int *out)
 {
@@ -60,7 +64,9 @@ def L(tmp_path_factory):
     lib.few_pixels.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_int]
     lib.pack_lanes.argtypes = [C.c_int64] * 4
     lib.pack_offsets_fit.argtypes = [C.c_int64] * 3
-    lib.conv_fit.argtypes = [C.c_int64] * 6 + [C.c_int] * 3
+    lib.conv_span.argtypes, lib.conv_span.restype = [C.c_void_p, C.c_int], C.c_int64
+    lib.reach_back.argtypes, lib.reach_back.restype = [C.c_int64] * 2, C.c_int64
+    lib.codes_fit.argtypes, lib.outputs_fit.argtypes = [C.c_void_p, C.c_int64, C.c_int64, C.c_int], [C.c_int64] * 3 + [C.c_int]
     lib.halo_rows.argtypes, lib.halo_rows.restype = [C.c_int] * 3, C.c_int64
     lib.nt_hint.argtypes = [C.c_int64, C.c_int64, C.c_size_t, C.c_int]
     return lib
@@ -196,30 +202,42 @@ def test_tap_offsets_of_a_window(L, big, W, Cpad, KH, KW):
     assert [tuple(out[3 * i:3 * i + 3]) for i in range(len(steps))] == steps
 
 
-@pytest.mark.parametrize("Nb,H,W,pixel,k,stride", [
-    (1, 4096, 4096, 64, 3, 1), (2, 4096, 4096, 64, 3, 64), (1, 5780, 5780, 64, 3, 64), (1, 5800, 5800, 64, 3, 64), (300, 3, 2, 64, 3, 1),
-    (9, 8, 1000, 8192, 7, 1), (33, 5, 2000, 8192, 5, 2), (5, 300, 300, 8192, 1, 1), (1, 2, 1 << 25, 64, 3, 1), (1, 1, 1 << 24, 64, 1, 1)])
-def test_conv_offsets_fit(L, Nb, H, W, pixel, k, stride):
-    """Where a tile's offsets are said to fit, the last byte that it reads lies below 2^31 from its base (the first tap of a
-    corner pixel of its first image), and so does a tap outside; an image that no tile shares is not counted twice."""
-    pad = min(k // 2, 2)
-    OH, OW = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
-    ohw, bias = OH * OW, pad * (W + 1) * pixel
-    for bq in (64, 128, 256):
-        most = 0
-        for q0 in {0, bq, ohw // bq * bq, (Nb * ohw - 1) // bq * bq, (ohw * Nb // 2) // bq * bq}:
-            m = min(q0 + bq, Nb * ohw) - 1
-            if m < q0:
-                continue
-            nb, pix = m // ohw - q0 // ohw, m % ohw
-            oh, ow = (pix // OW, pix % OW) if nb == 0 else (OH - 1, OW - 1)
-            most = max(most, ((nb * H + oh * stride - pad + k - 1) * W + ow * stride - pad + k) * pixel + bias)
-        fits = bool(L.conv_fit(Nb, H, W, pixel, 8, ohw, bq, 0, 0))
-        assert not fits or most < 1 << 31, (bq, most)
-        assert fits or (min(Nb, (bq - 1) // ohw + 2) * H + 16) * W * pixel >= 1 << 31
-        assert L.conv_fit(Nb, H, W, pixel, 8, ohw, bq, 1, 0)
-    assert bool(L.conv_fit(1, 4096, 4096, 64, 8, 4096 ** 2, 64, 0, 0)) and not L.conv_fit(2, 4096, 4096, 64, 8, 4096 ** 2, 64, 0, 0)
-    assert L.conv_fit(1, 4096, 4096, 64, 128, 4096 ** 2, 64, 1, 1) and not L.conv_fit(2, 4096, 4096, 64, 128, 4096 ** 2, 64, 1, 1)
+def _conv_dims(H, W, KH, KW, stride, pad):
+    OH, OW = (H + 2 * pad - KH) // stride + 1, (W + 2 * pad - KW) // stride + 1
+    return OH, OW, (C.c_int64 * 7)(H, W, OH, OW, KH, KW, stride)
+
+
+def test_conv_span(L):
+    """Over random geometries: every window of a tile lies between the reach before its first one and the span behind it."""
+    rng = random.Random(7)
+    for _ in range(3000):
+        KH, KW, stride = rng.randint(1, 7), rng.randint(1, 7), rng.choice([1, 1, 2, 3, 5, 64])
+        pad = rng.randint(0, min(KH, KW, 3) - 1)
+        H, W, Nb = rng.randint(max(1, KH - 2 * pad), 40), rng.randint(max(1, KW - 2 * pad), 40), rng.randint(1, 5)
+        OH, OW, v = _conv_dims(H, W, KH, KW, stride, pad)
+
+        def corner(m):
+            nb, pix = divmod(m, OH * OW)
+            return (nb * H + pix // OW * stride - pad) * W + pix % OW * stride - pad
+
+        for bq in (32, 64, 256):
+            q0 = rng.randrange(0, Nb * OH * OW)
+            ends = [corner(m) - corner(q0) for m in range(q0, min(q0 + bq, Nb * OH * OW))]
+            assert -L.reach_back(pad, W) <= min(ends)
+            assert max(ends) + (KH - 1) * W + KW <= L.conv_span(v, bq)
+
+
+def test_conv_offsets_fit(L):
+    """Images of any size fit 32-bit offsets, rows of hundreds of millions of bytes do not; outputs fit that are not
+    2^32 bytes apart."""
+    for H, W, pixel, k, stride, fits in ((4096, 4096, 64, 3, 1, True), (5825, 5825, 64, 3, 64, True), (30000, 30000, 64, 3, 1, True),
+                                         (2, 1 << 25, 64, 3, 1, False), (2, 1 << 23, 64, 3, 1, True), (2, 1 << 24, 64, 3, 1, False),
+                                         (1, 1 << 25, 64, 1, 1, True), (5, 1 << 20, 1024, 5, 1, False), (1, 1 << 18, 64, 1, 64, True)):
+        _, _, v = _conv_dims(H, W, k, min(k, W), stride, k // 2)
+        for bq in (64, 128, 256):
+            assert bool(L.codes_fit(v, k // 2, pixel, bq)) == fits, (H, W, bq)
+    assert L.outputs_fit(1, 128, 4096 ** 2, 64) and not L.outputs_fit(2, 128, 4096 ** 2, 64) and not L.outputs_fit(1, 8, 1 << 27, 64)
+    assert L.outputs_fit(256, 512, 49, 64) and L.outputs_fit(2, 128, 2800 ** 2, 256) and L.outputs_fit(1 << 20, 4096, 49, 256)
 
 
 def test_halo_rows(L):

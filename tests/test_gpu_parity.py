@@ -2003,12 +2003,11 @@ def test_depthwise_3x3_thousands_of_channels(C, H, stride, batch):
 
 @pytest.mark.parametrize("fmt", [B.RTN_CODE_FP4, B.RTN_CODE_I8])
 @pytest.mark.parametrize("side,pad,batch,cfg", [
-    (3200, 0, 1, -1), (4096, 0, 1, -1), (4097, 1, 1, 0), (4097, 1, 1, 1), (3201, 1, 2, 13),   # 0.65 to 1.3 GB of codes: 32-bit offsets
-    (4097, 1, 2, -1),                                                                         # a tile on two images of 1.07 GB
-    (5825, 0, 1, -1), (5825, 1, 1, 1), (5825, 1, 1, -1)])                                     # 2.17 GB: windows beyond 2^31
+    (3200, 0, 1, -1), (4097, 1, 1, 0), (4097, 1, 2, 1), (4097, 1, 3, -1),       # 0.65 and 1.07 GB of codes an image, tiles on two of them
+    (5825, 0, 1, -1), (5825, 1, 1, 13), (5825, 1, 1, -1), (8257, 1, 1, 1)])     # 2.2 and 4.4 GB
 def test_conv_on_images_beyond_32_bit_offsets(side, pad, batch, cfg, fmt, tile_reset):
-    """Windows far apart on large images, with 32-bit offsets up to their limit and with the 64-bit ones beyond it; padded,
-    the first and the last window reach out of the image: the same bits as on the small image of just those windows."""
+    """Windows far apart on images that 32-bit offsets do not span (a tile's own windows they do): padded, the first and the
+    last window reach out of the image.  The same bits as on the small image of just those windows."""
     _say("conv stride 64 on %d x %d x %d pad %d fmt %d cfg %d" % (batch, side, side, pad, fmt, cfg))
     C, O, k, s = 64, 256, 3, 64
     g = torch.Generator(device=T.DEV)
@@ -2056,11 +2055,45 @@ def test_conv_window_rows_2_gib_apart(fmt, C):
     codes = part.repeat(1, 1, W // 40961 + 1, 1)[:, :, :W].contiguous()
     cw, sw = B.ternarize_pack(torch.randn((O, C, 3, 3), generator=g, device=T.DEV), -0.4, 0.4, fmt)
     ep = B.Epilogue(1.1, 0.2, torch.rand(O, generator=g, device=T.DEV) + 0.5, torch.rand(O, generator=g, device=T.DEV) - 0.5, None, sw)
-    y = B.ternary_conv2d(codes, cw, 1, C, 2, W, O, 3, 3, 1, 1, ep=ep, fmt=fmt)[1].view(O, 2, W)
+    res = torch.randn((1, O, 2, W), generator=g, device=T.DEV)
+
+    def forms(codes, res):
+        w = res.shape[-1]
+        y, y2 = B.ternary_conv2d(codes, cw, 1, C, 2, w, O, 3, 3, 1, 1, ep=ep, fmt=fmt)[1], torch.empty_like(res)
+        c1 = B.ternary_conv2d_ternarize(codes, cw, 1, C, 2, w, O, 3, 3, 1, 1, ep, -0.4, 0.6, fmt=fmt)
+        c2 = B.ternary_conv2d_ternarize(codes, cw, 1, C, 2, w, O, 3, 3, 1, 1, ep, -0.4, 0.6, residual=res, relu_out=True, y_out=y2, fmt=fmt)
+        c1, c2 = [(c[0] if isinstance(c, (tuple, list)) else c).view(2, w, -1).permute(2, 0, 1) for c in (c1, c2)]
+        return [y.view(O, 2, w), y2.view(O, 2, w), c1, c2]
+
+    whole = forms(codes, res)
     for c0, c1 in ((0, 300), (W // 2 - 150, W // 2 + 150), (W - 300, W)):
-        cut = B.ternary_conv2d(codes[:, :, c0:c1].contiguous(), cw, 1, C, 2, c1 - c0, O, 3, 3, 1, 1, ep=ep, fmt=fmt)[1].view(O, 2, c1 - c0)
+        cut = forms(codes[:, :, c0:c1].contiguous(), res[..., c0:c1].contiguous())
         first, last = int(c0 > 0), c1 - c0 - int(c1 < W)      # (the cut's own borders)
-        assert torch.equal(y[:, :, c0 + first:c0 + last], cut[:, :, first:last])
+        for a, b in zip(whole, cut):
+            assert torch.equal(a[:, :, c0 + first:c0 + last], b[:, :, first:last])
+
+
+@pytest.mark.parametrize("fmt", [B.RTN_CODE_FP4, B.RTN_CODE_I8])
+def test_block_tail_with_4_gib_of_outputs_an_image(fmt):
+    """Two images of 4.4 GB of outputs each (1 x 1 windows): the same bits as on cuts of the images."""
+    C, O, H, W = 16, 80, 3700, 3701
+    _say("block tail 2 x %d x %d x %d, fmt %d" % (O, H, W, fmt))
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(O)
+    ca, _ = B.ternarize_pack(torch.randn((2, C, H, W), generator=g, device=T.DEV), -0.5, 0.5, fmt, want_sum=False)
+    cw, sw = B.ternarize_pack(torch.randn((O, C, 1, 1), generator=g, device=T.DEV), -0.4, 0.4, fmt)
+    ep = B.Epilogue(1.1, 0.2, torch.rand(O, generator=g, device=T.DEV) + 0.5, torch.rand(O, generator=g, device=T.DEV) - 0.5, None, sw, relu=True)
+    res = torch.randn((2, O, H, W), generator=g, device=T.DEV)
+    y = torch.full_like(res, float("nan"))
+    codes = B.ternary_conv2d_ternarize(ca, cw, 2, C, H, W, O, 1, 1, 1, 0, ep, -0.4, 0.6, residual=res, relu_out=True, y_out=y, fmt=fmt)
+    codes = (codes[0] if isinstance(codes, (tuple, list)) else codes).view(2, H, W, -1)
+    for n in (0, 1):
+        for h in (0, H // 2, H - 2):
+            yc = torch.empty((1, O, 2, W), device=T.DEV)
+            cc = B.ternary_conv2d_ternarize(ca[n:n + 1, h:h + 2].contiguous(), cw, 1, C, 2, W, O, 1, 1, 1, 0, ep, -0.4, 0.6,
+                                            residual=res[n:n + 1, :, h:h + 2].contiguous(), relu_out=True, y_out=yc, fmt=fmt)
+            cc = (cc[0] if isinstance(cc, (tuple, list)) else cc).view(1, 2, W, -1)
+            assert torch.equal(yc, y[n:n + 1, :, h:h + 2]) and torch.equal(cc, codes[n:n + 1, h:h + 2])
 
 
 OTHER_NET_CONVS = [
