@@ -85,6 +85,23 @@ inline bool pack_nchw_offsets_fit(int64_t N, int64_t K, int64_t HW)
     return images * K * HW < (int64_t)1 << 30;
 }
 
+// Depthwise 3 x 3, outputs that the memory-side cache does not hold, in planes that are no whole 64-byte halves of lines: where
+// the stores themselves are what a launch takes, the vector kernel's runs of 64 pixels with the non-temporal hint are faster
+// than the matrix-core kernel's parts of lines, which cannot take it.  us, matrix cores -> vector (odd planes of 27 to
+// 137 wide, 32 to 256 channels, 150 to 400 MiB of y: 165 launches)
+//   y and acc, stride 1  256 x 1024 x 13 x 13 (169 MiB) 181 -> 121   256 x 512 x 24 x 21 (252) 204 -> 189, 400 MiB 0.9 times, not taken
+//   y and acc, stride 2  256 x 128 x 48 x 66 (99) 100 -> 91          at 230 MiB 1.0, not taken
+//   y, stride 2          256 x 64 x 113 x 113 (203) 136 -> 113       600 x 128 x 60 x 72 (316) 248 -> 239, 400 MiB 0.9 times, not taken
+//   up to 48 channels    200 x 32 x 93 x 136 (308) 143 -> 123        100 x 48 x 93 x 136 (231) 119 -> 106
+//   y, stride 1          256 x 512 x 24 x 21 (252) 88 -> 118, not taken
+inline bool dw_vector_stores(int64_t C, int stride, int64_t y_bytes, bool acc)
+{
+    const int64_t mib = y_bytes >> 20;
+    if (C <= 48) return acc ? mib > 128 && (C <= 32 || mib <= 280) : mib > (stride == 2 ? 128 : 220);
+    if (acc) return stride == 2 ? mib > 96 && mib <= 200 : mib > 128 && mib <= 280;
+    return stride == 2 && mib > 128 && mib <= 320;
+}
+
 // Does a GEMM store y [M][N] with the non-temporal hint?  A burst of stores that the memory-side cache (256 MiB) absorbs
 // and writes back later slows the K loops of the tiles behind it, and hinted ones do not.  But a hinted store of a
 // part of a line goes to memory as it is, and the next kernel finds nothing in the cache.  us, plain -> hinted, two

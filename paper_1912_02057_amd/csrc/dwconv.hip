@@ -606,11 +606,14 @@ hipError_t launch_dwconv(const DwConvArgs& a, hipStream_t st)
         const int64_t run = dw_run(a.g, tile);
         if (run * rb > 48 * 1024 || run > 4 * tile * a.g.stride * a.g.stride) tile = 0;
     }
+    // (the hint only for whole 64-byte halves of lines: 128 x 463 x 13 x 98 134 us without, 305 with it)
+    const bool halves = (a.g.OH * a.g.OW) % 16 == 0 && ((uintptr_t)a.y & 63) == 0;
+    const bool vector = a.g.KH == 3 && a.g.KW == 3 && a.g.pad <= 1 && (int64_t)a.g.Nb * a.g.H * a.g.W * a.g.Cpad < ((int64_t)1 << 31);
+    if (tile && a.y && vector && !halves && dw_vector_stores(a.g.C, a.g.stride, total * a.g.C * 4, a.acc != nullptr)) tile = 0;
     if (tile) {
         // (an infinite alpha_a makes c2 = alpha_a * 0 a NaN: kept by the form with the sums)
         const bool bw = a.ep.beta_w.ptr || a.ep.beta_w.s != 0.0f || !std::isfinite(a.ep.alpha_a.s);
-        // (the hint only for whole 64-byte halves of lines: 128 x 463 x 13 x 98 134 us without, 305 with it)
-        const bool nt = big && (a.g.OH * a.g.OW) % 16 == 0 && ((uintptr_t)a.y & 63) == 0;
+        const bool nt = big && halves;
         DwConvArgs b = a;
         b.tile = tile;
         b.run = (int)((dw_run(a.g, tile) + 31) / 32 * 32);  // whole KiB of LDS
@@ -638,8 +641,7 @@ hipError_t launch_dwconv(const DwConvArgs& a, hipStream_t st)
             pick(std::integral_constant<int, 4>{});
         return hipGetLastError();
     }
-    if (a.g.KH == 3 && a.g.KW == 3 && a.g.pad <= 1 &&
-        (int64_t)a.g.Nb * a.g.H * a.g.W * a.g.Cpad < ((int64_t)1 << 31)) {
+    if (vector) {
         const bool nt = big;
         const size_t ntile = (a.y ? 1 : 0) + (a.acc ? 1 : 0);  // LDS tiles
         DwConvArgs b = a;

@@ -47,6 +47,7 @@ extern "C" int ksplit(const int64_t *v, int limit)
 extern "C" int few_pixels(int64_t N, int64_t K, int64_t HW, int flat) { return rtn::pack_nchw_few_pixels(N, K, HW, flat); }
 extern "C" int pack_lanes(int64_t K, int64_t Kpad, int64_t px, int64_t HW) { return rtn::pack_nchw_lanes(K, Kpad, px, HW); }
 extern "C" int pack_offsets_fit(int64_t N, int64_t K, int64_t HW) { return rtn::pack_nchw_offsets_fit(N, K, HW); }
+extern "C" int dw_vector(int64_t C, int stride, int64_t y_bytes, int acc) { return rtn::dw_vector_stores(C, stride, y_bytes, acc); }
 extern "C" int nt_hint(int64_t M, int64_t N, uintptr_t y, int nk) { return rtn::gemm_nt_hint(M, N, y, nk); }
 """
 
@@ -68,6 +69,7 @@ def L(tmp_path_factory):
     lib.reach_back.argtypes, lib.reach_back.restype = [C.c_int64] * 2, C.c_int64
     lib.codes_fit.argtypes, lib.outputs_fit.argtypes = [C.c_void_p, C.c_int64, C.c_int64, C.c_int], [C.c_int64] * 3 + [C.c_int]
     lib.halo_rows.argtypes, lib.halo_rows.restype = [C.c_int] * 3, C.c_int64
+    lib.dw_vector.argtypes = [C.c_int64, C.c_int, C.c_int64, C.c_int]
     lib.nt_hint.argtypes = [C.c_int64, C.c_int64, C.c_size_t, C.c_int]
     return lib
 
@@ -120,6 +122,15 @@ def test_pack_offsets(L):
         fits = bool(L.pack_offsets_fit(N, K, HW))
         assert not fits or 4 * last * K * HW <= 1 << 32, (N, K, HW)
         assert fits or 4 * min(N, last + 1) * K * HW >= 1 << 32, (N, K, HW)
+
+
+def test_depthwise_stores_in_parts_of_lines(L):
+    """Both sides of each line of the rule, in MiB of y."""
+    for Ch, stride, acc, yes, no in ((1024, 1, 1, (129, 169, 280), (128, 281, 400)), (128, 2, 1, (97, 200), (96, 201, 400)),
+                                     (64, 2, 0, (129, 203, 320), (128, 321)), (512, 1, 0, (), (130, 252, 600)), (32, 1, 0, (221, 308, 600), (220, 130)),
+                                     (48, 1, 1, (129, 280), (128, 281)), (32, 1, 1, (129, 400), (128,)), (40, 2, 0, (129, 600), (128,))):
+        for mib, want in [(m, True) for m in yes] + [(m, False) for m in no]:
+            assert bool(L.dw_vector(Ch, stride, mib << 20, acc)) == want, (Ch, stride, acc, mib)
 
 
 def test_gemm_store_hint(L):
