@@ -90,7 +90,7 @@ inline bool pack_nchw_offsets_fit(int64_t N, int64_t K, int64_t HW)
 // than the matrix-core kernel's parts of lines, which cannot take it.  us, matrix cores -> vector (odd planes of 27 to
 // 137 wide, 32 to 256 channels, 150 to 400 MiB of y: 165 launches)
 //   y and acc, stride 1  256 x 1024 x 13 x 13 (169 MiB) 181 -> 121   256 x 512 x 24 x 21 (252) 204 -> 189, 400 MiB 0.9 times, not taken
-//   y and acc, stride 2  256 x 128 x 48 x 66 (99) 100 -> 91          at 230 MiB 1.0, not taken
+//   y and acc, stride 2  256 x 64 x 113 x 113 (203) 238 -> 232       188 x 372 x 42 x 42 (117) 131 -> 143, at 230 MiB 1.0, not taken
 //   y, stride 2          256 x 64 x 113 x 113 (203) 136 -> 113       600 x 128 x 60 x 72 (316) 248 -> 239, 400 MiB 0.9 times, not taken
 //   up to 48 channels    200 x 32 x 93 x 136 (308) 143 -> 123        100 x 48 x 93 x 136 (231) 119 -> 106
 //   y, stride 1          256 x 512 x 24 x 21 (252) 88 -> 118, not taken
@@ -98,7 +98,7 @@ inline bool dw_vector_stores(int64_t C, int stride, int64_t y_bytes, bool acc)
 {
     const int64_t mib = y_bytes >> 20;
     if (C <= 48) return acc ? mib > 128 && (C <= 32 || mib <= 280) : mib > (stride == 2 ? 128 : 220);
-    if (acc) return stride == 2 ? mib > 96 && mib <= 200 : mib > 128 && mib <= 280;
+    if (acc) return mib > 128 && mib <= (stride == 2 ? 200 : 280);
     return stride == 2 && mib > 128 && mib <= 320;
 }
 

@@ -126,7 +126,7 @@ def test_pack_offsets(L):
 
 def test_depthwise_stores_in_parts_of_lines(L):
     """Both sides of each line of the rule, in MiB of y."""
-    for Ch, stride, acc, yes, no in ((1024, 1, 1, (129, 169, 280), (128, 281, 400)), (128, 2, 1, (97, 200), (96, 201, 400)),
+    for Ch, stride, acc, yes, no in ((1024, 1, 1, (129, 169, 280), (128, 281, 400)), (128, 2, 1, (129, 200), (128, 201, 400)),
                                      (64, 2, 0, (129, 203, 320), (128, 321)), (512, 1, 0, (), (130, 252, 600)), (32, 1, 0, (221, 308, 600), (220, 130)),
                                      (48, 1, 1, (129, 280), (128, 281)), (32, 1, 1, (129, 400), (128,)), (40, 2, 0, (129, 600), (128,))):
         for mib, want in [(m, True) for m in yes] + [(m, False) for m in no]:
