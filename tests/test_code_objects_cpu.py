@@ -76,3 +76,18 @@ def test_direct_loads_have_their_wait_states(objects):
     assert len(loads) > 1000
     assert not [l for l in loads if l[1] is None or l[1] < 1][:5]
     assert not [l for l in loads if l[2] is not None and l[2] < 5][:5]
+
+
+def _kernels(obj):
+    """name -> (vector registers, bytes of scratch) from the object's metadata"""
+    notes = subprocess.run([LLVM + "/llvm-readelf", "--notes", obj], check=True, stdout=subprocess.PIPE, text=True).stdout
+    field = lambda text, key: int(re.search(r"\.%s:\s+(\d+)" % key, text)[1])
+    return {re.search(r"\.name:\s+(_Z\S+)", k)[1]: (field(k, "vgpr_count"), field(k, "private_segment_fixed_size"))
+            for k in re.split(r"\n  - \.agpr_count|\n  - \.args", notes)[1:] if re.search(r"\.name:\s+_Z", k)}
+
+
+def test_gathering_weight_only_conv_has_two_blocks_per_cu(objects):
+    """Its 64 x 64 form has blocks of 16 waves and LDS for two of them: 64 registers a lane, without scratch."""
+    found = {n: v for obj in objects for n, v in _kernels(obj).items() if re.search(r"k_wconvILi64ELi64ELi2ELi2ELi4ELi\d+ELi0ELi2ELi64E", n)}
+    assert len(found) == 2
+    assert all(vgprs <= 64 and scratch == 0 for vgprs, scratch in found.values()), found
