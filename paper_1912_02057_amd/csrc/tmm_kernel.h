@@ -732,7 +732,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     // so LDS and load-issue latency hide behind matrix-core time.
     auto slice = [&](auto with_frags, auto with_issue, int ks, unsigned fslot, int fks) {
         constexpr bool FRAGS = decltype(with_frags)::value, ISSUE = decltype(with_issue)::value;
-        if (ISSUE) issue_begin();
+        if (ISSUE && NM > 1) issue_begin();
         if (HALO && FRAGS && fks == 0) frag_step_advance();
         auto group = [&](auto index) {
             constexpr int n = decltype(index)::value;
@@ -915,9 +915,10 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     load_frags(0, 0);
     int kt = 0;
     unsigned cur = 0, nxt = STAGE;  // stages of steps kt and kt + 1
+    auto after = [&](unsigned slot) { return slot + STAGE == NS * STAGE ? 0u : slot + STAGE; };
     auto advance = [&]() {
         cur = nxt;
-        nxt = nxt + STAGE == NS * STAGE ? 0u : nxt + STAGE;
+        nxt = after(nxt);
     };
     // Steady state: between the two k-slices, stage kt is fully in registers
     // (slice-1 fragments waited for), step kt+1 has landed for this wave
@@ -925,11 +926,18 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
     // every wave; the freed stage is refilled with step kt+NS.
     for (; kt + NS < nk; ++kt) {
         slice(yes, no, 0, cur, 1);
+        unsigned third = after(nxt);
+        if (NM == 1) {
+            // (one matrix instruction per slice: a step is a chain of LDS reads, and this bookkeeping passes behind the
+            // first of them; behind the second one the loads do)
+            issue_begin();
+            __builtin_amdgcn_sched_barrier(0);
+        }
         wait_lgkm0();
         wait_vm<(NS - 2) * DPS>();
         block_barrier();
         slice(yes, yes, 1, nxt, 0);
-        advance();
+        cur = nxt, nxt = third;
     }
     // Drain: nothing left to issue.
     for (; kt + 1 < nk; ++kt) {
