@@ -174,33 +174,42 @@ __device__ __forceinline__ int halo_byte(int row, int q)
 // five between a vector instruction's write of a scalar register (v_readfirstlane) and a load that reads it, and the
 // compiler does not look for either in here.  So there is one instruction between, and where the load has a scalar
 // operand it is a scalar copy of that, which reads any write and needs no wait itself.
+// OFF is added on the way to M0: loads that follow each other in LDS share one address.
+template <int OFF = 0>
 __device__ __forceinline__ void dma16(const void* gptr, unsigned lds_off)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_off), "v"(gptr) : "memory");
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_off)), "n"(OFF),
+                 "v"(gptr)
+                 : "memory", "scc");
 }
 // 4 bytes per lane
+template <int OFF = 0>
 __device__ __forceinline__ void dma4(const void* gptr, unsigned lds_off)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_off), "v"(gptr) : "memory");
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_off)), "n"(OFF),
+                 "v"(gptr)
+                 : "memory", "scc");
 }
 
-// Same, with the address split into a wave-uniform 64-bit base (SGPR pair) and
+// The same, with the address split into a wave-uniform 64-bit base (SGPR pair) and
 // a per-lane unsigned 32-bit byte offset: nothing to add per lane per K-step.
+template <int OFF = 0>
 __device__ __forceinline__ void dma16_base(const void* sbase, unsigned voff, unsigned lds_off)
 {
     const void* base;
-    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+    asm volatile("s_add_u32 m0, %1, %2\n\ts_mov_b64 %0, %4\n\tglobal_load_lds_dwordx4 %3, %0"
                  : "=&s"(base)
-                 : "s"(lds_off), "v"(voff), "s"(sbase)
-                 : "memory");
+                 : "s"(__builtin_amdgcn_readfirstlane(lds_off)), "n"(OFF), "v"(voff), "s"(sbase)
+                 : "memory", "scc");
 }
+template <int OFF = 0>
 __device__ __forceinline__ void dma4_base(const void* sbase, unsigned voff, unsigned lds_off)
 {
     const void* base;
-    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dword %2, %0"
+    asm volatile("s_add_u32 m0, %1, %2\n\ts_mov_b64 %0, %4\n\tglobal_load_lds_dword %3, %0"
                  : "=&s"(base)
-                 : "s"(lds_off), "v"(voff), "s"(sbase)
-                 : "memory");
+                 : "s"(__builtin_amdgcn_readfirstlane(lds_off)), "n"(OFF), "v"(voff), "s"(sbase)
+                 : "memory", "scc");
 }
 
 // Pin a wave-uniform pointer into scalar registers (the "s" operands above must
@@ -602,7 +611,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
             if constexpr (CONV) {
                 const int out = vout[j] << is_shr | vout[j] << is_shc;
                 if constexpr (BIG)
-                    dma16(out < 0 ? zero_page : gQ[j] + is_kQ, is_base + BP * 64 + 4096 * j);
+                    dma16<BP * 64 + 4096 * j>(out < 0 ? zero_page : gQ[j] + is_kQ, is_base);
                 else
                     dma_buf<BP * 64 + 4096 * j>(rsrcQ, offQ[j] | ((unsigned)out & kOutside), is_kQ, is_base);
             } else {

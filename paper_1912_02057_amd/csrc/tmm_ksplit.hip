@@ -152,17 +152,17 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
     const int8_t* zero_page = (const int8_t*)g_zero16;
     auto issue = [&](int slot) {
         const unsigned dst = ring + (unsigned)(slot * STAGE);
-#pragma unroll
-        for (int i = 0; i < LP; ++i) dma16_base(uniform_ptr(baseP + koffP), offP[i], dst + i * 1024);
-#pragma unroll
-        for (int j = 0; j < LQ; ++j) {
+        auto load_p = [&](auto i) { dma16_base<i * 1024>(uniform_ptr(baseP + koffP), offP[i], dst); };
+        auto load_q = [&](auto j) {
             if (CONV) {
                 const bool ok = ((vmask[j] >> kh) & (vmask[j] >> (8 + kw)) & 1) != 0;
-                dma16(ok ? gQ[j] + koffQ : zero_page, dst + BP * 64 + j * 1024);
+                dma16<BP * 64 + j * 1024>(ok ? gQ[j] + koffQ : zero_page, dst);
             } else {
-                dma16_base(uniform_ptr(baseQ + koffQ), offQ[j], dst + BP * 64 + j * 1024);
+                dma16_base<BP * 64 + j * 1024>(uniform_ptr(baseQ + koffQ), offQ[j], dst);
             }
-        }
+        };
+        for_each_index(load_p, std::make_integer_sequence<int, LP>{});
+        for_each_index(load_q, std::make_integer_sequence<int, LQ>{});
         koffP += 64;
         koffQ += 64;
         if (CONV && ++cc == spt) {

@@ -79,29 +79,29 @@ __global__ __launch_bounds__(256, MINW) void k_gemm_planes(TmmParams prm, const 
         const unsigned dst0 = lds0 + (unsigned)((st & 1) * STAGE + RPL * wave * 64);
         auto all = [&](auto whole) {
             const unsigned kb = (unsigned)st * 64 + kb0;
-#pragma unroll
-            for (int j = 0; j < NL; ++j) {
-                const int rr = 4 * RPL * j;  // first row of this load, without the wave's share
-                const bool isP = rr < 2 * BP;
-                const int r0 = isP ? rr : rr - 2 * BP, half = isP ? BP : BQ, sgn = r0 >= half;
+            auto load = [&](auto j) {
+                constexpr int rr = 4 * RPL * decltype(j)::value;  // first row of this load, without the wave's share
+                constexpr bool isP = rr < 2 * BP;
+                constexpr int r0 = isP ? rr : rr - 2 * BP, half = isP ? BP : BQ, sgn = r0 >= half;
                 int row = r0 - (sgn ? half : 0) + lrow;
                 const int lim = isP ? limP : limQ;
                 row = row < lim ? row : lim;  // rows past the end: any valid row, never stored
                 const int8_t* base = uniform_ptr(bases[(isP ? 0 : 2) + sgn]);
-                const unsigned off = (unsigned)row * rowb + kb, dst = dst0 + (unsigned)rr * 64;
+                const unsigned off = (unsigned)row * rowb + kb;
                 if constexpr (decltype(whole)::value) {
                     if constexpr (EB == 16)
-                        dma16_base(base, off, dst);
+                        dma16_base<rr * 64>(base, off, dst0);
                     else
-                        dma4_base(base, off, dst);
+                        dma4_base<rr * 64>(base, off, dst0);
                 } else {  // the stage that reaches past the rows' end
                     const int8_t* src = kb < rowb ? base + off : (const int8_t*)g_zero16;
                     if constexpr (EB == 16)
-                        dma16(src, dst);
+                        dma16<rr * 64>(src, dst0);
                     else
-                        dma4(src, dst);
+                        dma4<rr * 64>(src, dst0);
                 }
-            }
+            };
+            for_each_index(load, std::make_integer_sequence<int, NL>{});
         };
         if ((unsigned)(st + 1) * 64 <= rowb)
             all(std::true_type{});
