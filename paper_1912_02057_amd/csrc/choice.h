@@ -131,6 +131,17 @@ inline int64_t nblocks(int64_t rp, int64_t rq, int bp, int bq)
     return ((rp + bp - 1) / bp) * ((rq + bq - 1) / bq);
 }
 
+// Tile `bid` of a grid in bands of 8 tiles along P, all columns of a band and along P first: a run of tiles, as an XCD has
+// it, is a block of rows and columns.  `band_tiles` 8 x columns; the divisions by that and by the height of the last band are
+// the caller's (multiplications on the device).
+template <class DivBand, class DivLast>
+constexpr void band_tile(int bid, int tilesP, int band_tiles, DivBand div_band, DivLast div_last, int& tileP, int& tileQ)
+{
+    const int band = div_band(bid), inband = bid - band * band_tiles, left = tilesP - band * 8;
+    tileQ = left >= 8 ? inband >> 3 : div_last(inband);
+    tileP = band * 8 + inband - tileQ * (left < 8 ? left : 8);
+}
+
 // The forms of k_ksplit: tiles of 32 along P and Q, waves that share K, ring stages, pixel run in LDS (convs).
 struct KsplitForm {
     int tp, tq, waves, stages;

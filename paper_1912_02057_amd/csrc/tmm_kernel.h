@@ -292,11 +292,8 @@ __device__ __forceinline__ bool block_tile(const TmmParams& prm, int& tileP, int
     const int chunk = (int)(gridDim.x >> 3);  // grid is padded to a multiple of 8
     const int bid = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
     if (bid >= prm.ntiles) return false;
-    const int band = (int)fastdiv((uint32_t)bid, prm.div_band);  // band = 8 * tilesQ tiles
-    const int inband = bid - band * prm.band_tiles;
-    const int bandw = prm.tilesP - band * 8 < 8 ? prm.tilesP - band * 8 : 8;
-    tileQ = bandw == 8 ? (inband >> 3) : (int)fastdiv((uint32_t)inband, prm.div_lastband);
-    tileP = band * 8 + inband - tileQ * bandw;
+    band_tile(bid, prm.tilesP, prm.band_tiles, [&](int n) { return (int)fastdiv((uint32_t)n, prm.div_band); },
+              [&](int n) { return (int)fastdiv((uint32_t)n, prm.div_lastband); }, tileP, tileQ);
     return true;
 }
 

@@ -78,10 +78,18 @@ __global__ __launch_bounds__(64 * W) void k_ksplit(KsplitParams kp)
 
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // one contiguous run of tiles per XCD, as block_tile(), in bands of any height
+    // One contiguous run of tiles per XCD.  conv: all filters of a pixel tile follow each other, the inputs are read by one
+    // XCD.  GEMM: in bands, as k_tmm, so that rows that the kernel before wrote are fetched by one or two XCDs, not by
+    // half of them (pack and GEMM, FP4, 2048 x 124 x 2460: 11.9 us without the bands, 10.0).
     const int bid = (int)(blockIdx.x & 7) * kp.xcd_tiles + (int)(blockIdx.x >> 3);
     if (bid >= prm.ntiles) return;
-    const int tileQ = (int)fastdiv_flat((uint32_t)bid, kp.div_tp), tileP = bid - tileQ * prm.tilesP;
+    int tileP, tileQ;
+    if (CONV) {
+        tileQ = (int)fastdiv_flat((uint32_t)bid, kp.div_tp), tileP = bid - tileQ * prm.tilesP;
+    } else {
+        band_tile(bid, prm.tilesP, prm.band_tiles, [&](int n) { return (int)fastdiv_flat((uint32_t)n, prm.div_band); },
+                  [&](int n) { return (int)fastdiv_flat((uint32_t)n, prm.div_lastband); }, tileP, tileQ);
+    }
     const int p0 = tileP * BP, q0 = tileQ * BQ;
     const bool want_ep = TERN || prm.y != nullptr;
     const int ohw = g.OH * g.OW;

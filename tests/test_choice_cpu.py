@@ -48,6 +48,11 @@ extern "C" int few_pixels(int64_t N, int64_t K, int64_t HW, int flat) { return r
 extern "C" int pack_lanes(int64_t K, int64_t Kpad, int64_t px, int64_t HW) { return rtn::pack_nchw_lanes(K, Kpad, px, HW); }
 extern "C" int pack_offsets_fit(int64_t N, int64_t K, int64_t HW) { return rtn::pack_nchw_offsets_fit(N, K, HW); }
 extern "C" int dw_vector(int64_t C, int stride, int64_t y_bytes, int acc) { return rtn::dw_vector_stores(C, stride, y_bytes, acc); }
+extern "C" void band_tile(int bid, int tilesP, int tilesQ, int *out)
+{
+    const int last = tilesP & 7 ? tilesP & 7 : 8;
+    rtn::band_tile(bid, tilesP, 8 * tilesQ, [&](int n) { return n / (8 * tilesQ); }, [&](int n) { return n / last; }, out[0], out[1]);
+}
 extern "C" int nt_hint(int64_t M, int64_t N, uintptr_t y, int nk) { return rtn::gemm_nt_hint(M, N, y, nk); }
 """
 
@@ -131,6 +136,21 @@ def test_depthwise_stores_in_parts_of_lines(L):
                                      (48, 1, 1, (129, 280), (128, 281)), (32, 1, 1, (129, 400), (128,)), (40, 2, 0, (129, 600), (128,))):
         for mib, want in [(m, True) for m in yes] + [(m, False) for m in no]:
             assert bool(L.dw_vector(Ch, stride, mib << 20, acc)) == want, (Ch, stride, acc, mib)
+
+
+def test_tiles_of_an_xcd_are_a_block(L):
+    """Each tile once; the run of tiles that an XCD has lies in as few bands of 8 rows as it can."""
+    out = (C.c_int * 2)()
+    for tilesP, tilesQ in ((1, 1), (64, 4), (72, 4), (3, 100), (8, 9), (9, 8), (13, 17), (100, 3)):
+        tiles = []
+        for bid in range(tilesP * tilesQ):
+            L.band_tile(bid, tilesP, tilesQ, out)
+            tiles.append((out[0], out[1]))
+        assert sorted(tiles) == [(p, q) for p in range(tilesP) for q in range(tilesQ)]
+        share = -(-len(tiles) // 8)
+        for x in range(0, len(tiles), share):
+            rows = {p for p, _ in tiles[x:x + share]}
+            assert len(rows) <= 8 * (-(-share // (8 * tilesQ)) + 1)
 
 
 def test_gemm_store_hint(L):
