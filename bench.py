@@ -30,11 +30,10 @@ BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA
 HBM_PEAK_GBS = 8000.0
 # HBM bytes per k_tmm launch of the default run (FP4 codes, batch 256): rocprofv3 --pmc FETCH_SIZE and
 # WRITE_SIZE passes summarised in profiles/k_tmm_conv_resnet18_b256.md, (2 * FETCH_SIZE + WRITE_SIZE) KiB
-# averaged over the 19 launches of a step.  Measured 2026-11-28 on the kernels of commit 6a61329 (the
-# conv's loads and stores have not changed since); a constant, not a live reading: the counters need the
-# profiler.  It only applies to the default format, batch and tile choice.
-MEASURED_TRAFFIC_BYTES_PER_LAUNCH = 109.3e6
-MEASURED_TRAFFIC_STAMP = "rocprofv3 FETCH_SIZE/WRITE_SIZE, 2026-11-28, kernels of commit 6a61329"
+# averaged over the 19 launches of a step.  Measured 2026-12-04 on the kernels of commit ccb24fd; a
+# constant, not a live reading: the counters need the profiler.  It only applies to the default format, batch and tile choice.
+MEASURED_TRAFFIC_BYTES_PER_LAUNCH = 109.4e6
+MEASURED_TRAFFIC_STAMP = "rocprofv3 FETCH_SIZE/WRITE_SIZE, 2026-12-04, kernels of commit ccb24fd"
 
 
 def main():

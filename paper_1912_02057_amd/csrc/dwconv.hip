@@ -381,9 +381,8 @@ __global__ __launch_bounds__(256) void k_dwconv3(DwConvArgs a)
 }
 
 // ---- 3 x 3, pad <= 1, stride 1 and 2: on the int8 matrix cores ----------------------------
-// Streaming: 1 byte read and 4 written per output.  The kernel above is held by its vector instructions, some 80 issue
-// slots per output (MobileNet's 13 layers, batch 256: 1085 us; here 732, at 3.5 to 4.0 TB/s).  Here the dot products go to
-// the matrix cores, idle otherwise: v_mfma_i32_16x16x64_i8 multiplies 16 pixels by 16 channels over K = 4 taps x
+// Streaming: 1 byte read and 4 written per output.  The kernel above is held by its vector instructions (MobileNet's 13
+// layers within its pass, batch 256: 1096 us; here 855, at 3.2 TB/s).  Here the dot products go to the matrix cores, idle otherwise: v_mfma_i32_16x16x64_i8 multiplies 16 pixels by 16 channels over K = 4 taps x
 // 16 channels, with filter codes on the diagonal of each tap's 16 x 16 block.  15 of 16 products are with
 // zeros, and still the nine taps of 256 outputs are 3 instructions of 16 cycles.
 //  * The output pixels of a tile are consecutive, so their inputs are one run of consecutive pixels (tap (0, 0) of the first
@@ -620,7 +619,7 @@ hipError_t launch_dwconv(const DwConvArgs& a, hipStream_t st)
         const size_t lds = (size_t)(b.run * rb + 16 + 16 * rb * 8);
         const int64_t slabs = (a.g.C + rb - 1) / rb;
         // four blocks per CU, all of them resident, each with an even share of the pixels: the set-up is paid once.  MobileNet's
-        // 13 layers at batch 256: 732 us, with two rounds of them 744, with three 767.  A wave takes 16 pixels at a time.
+        // 13 layers at batch 256, each in a loop of its own: 732 us, with two rounds of them 744, with three 767.  A wave takes 16 pixels at a time.
         // (8 blocks a slab at least, one per XCD, however many channels there are: at most 2^22 / 9)
         const int64_t most = (total + 63) / 64;
         int64_t nb = 1024 / slabs < most ? 1024 / slabs : most;
