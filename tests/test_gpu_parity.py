@@ -170,9 +170,10 @@ def test_pack_nchw_forms(shape):
 
 
 @pytest.mark.parametrize("shape", [(1, 64, 3000, 3000), (2, 64, 2900, 2900),      # offsets of 31 bits and more; two images, 32
-                                   (2, 37, 3840, 3844), (1, 130, 2900, 2900)])      # more
-def test_pack_nchw_large_images(shape):
-    """Images of 2 to 4.4 GB, where a block's offsets no longer fit 32 bits, against torch's comparisons."""
+                                   (2, 37, 3840, 3844), (1, 130, 2900, 2900),       # more
+                                   (90, 64, 440, 440)])                             # many images, 32-bit offsets within a block
+def test_pack_nchw_large_tensors(shape):
+    """Tensors of 2 to 4.5 GB, with offsets of a block that fit 32 bits and that do not, against torch's comparisons."""
     _say("pack_nchw large %s" % (shape,))
     g = torch.Generator(device=T.DEV)
     g.manual_seed(sum(shape))
@@ -1999,6 +2000,22 @@ def test_depthwise_3x3_thousands_of_channels(C, H, stride, batch):
                                          want_acc=True)
     assert (acc.cpu().numpy() == D).all()
     T.assert_y_close(yy.cpu().numpy(), y, "depthwise y")
+
+
+def test_depthwise_3x3_codes_beyond_2_gib():
+    """2.4 GB of codes: the same bits as image by image."""
+    N, C, H, W = 9200, 64, 64, 64
+    _say("depthwise 3x3 on %d x %d x %d x %d" % (N, C, H, W))
+    g = torch.Generator(device=T.DEV)
+    g.manual_seed(N)
+    ca = torch.randint(-1, 2, (N, H, W, C), generator=g, dtype=torch.int8, device=T.DEV)
+    cw = torch.zeros((C, 64), dtype=torch.int8, device=T.DEV)
+    cw[:, :9] = torch.randint(-1, 2, (C, 9), generator=g, dtype=torch.int8, device=T.DEV)
+    ep = B.Epilogue(1.1, 0.2, torch.rand(C, generator=g, device=T.DEV) + 0.5, torch.rand(C, generator=g, device=T.DEV) - 0.5, None, None, relu=True)
+    _, y = B.ternary_depthwise_conv2d(ca, cw, N, C, H, W, 3, 3, 1, 1, ep=ep)
+    for n in (0, N // 2, 8191, 8192, N - 1):
+        _, one = B.ternary_depthwise_conv2d(ca[n:n + 1].contiguous(), cw, 1, C, H, W, 3, 3, 1, 1, ep=ep)
+        assert torch.equal(y[n:n + 1], one)
 
 
 @pytest.mark.parametrize("fmt", [B.RTN_CODE_FP4, B.RTN_CODE_I8])
