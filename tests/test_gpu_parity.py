@@ -2020,7 +2020,7 @@ def test_depthwise_3x3_codes_beyond_2_gib():
 
 @pytest.mark.parametrize("fmt", [B.RTN_CODE_FP4, B.RTN_CODE_I8])
 @pytest.mark.parametrize("side,pad,batch,cfg", [
-    (3200, 0, 1, -1), (4097, 1, 1, 0), (4097, 1, 2, 1), (4097, 1, 3, -1),       # 0.65 and 1.07 GB of codes an image, tiles on two of them
+    (3200, 0, 1, -1), (4096, 0, 1, -1), (4097, 1, 1, 0), (4097, 1, 2, 1), (4097, 1, 3, -1),      # 0.65 and 1.07 GB of codes an image, tiles on two of them
     (5825, 0, 1, -1), (5825, 1, 1, 13), (5825, 1, 1, -1), (8257, 1, 1, 1)])     # 2.2 and 4.4 GB
 def test_conv_on_images_beyond_32_bit_offsets(side, pad, batch, cfg, fmt, tile_reset):
     """Windows far apart on images that 32-bit offsets do not span (a tile's own windows they do): padded, the first and the
