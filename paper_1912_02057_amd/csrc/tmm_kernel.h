@@ -170,10 +170,11 @@ __device__ __forceinline__ int halo_byte(int row, int q)
 // reserved and warns that a clobber of it is not honoured); it is safe because on this
 // target the compiler itself writes M0 only immediately before an instruction that
 // reads it, never across other code, so no value of its own lives in M0 here.
-// The wait states are these statements' own, too: gfx9 wants one between a scalar write of M0 and a load to LDS, and
-// five between a vector instruction's write of a scalar register (v_readfirstlane) and a load that reads it, and the
-// compiler does not look for either in here.  So there is one instruction between, and where the load has a scalar
-// operand it is a scalar copy of that, which reads any write and needs no wait itself.
+// The wait states are these statements' own, too: gfx9 wants one between a scalar write of M0 and a load to LDS, and the
+// compiler does not look for it in here.  Nor for the five between a vector instruction's write of a scalar register
+// (v_readfirstlane) and a load that reads it: scalar operands are kept in scalar registers, except where a kernel runs out
+// of those, which waits itself (dma_buf).  (A scalar copy of the operand instead of the s_nop would need no such care, but
+// the compiler puts a wait state of its own between two statements that write one register.)
 // OFF is added on the way to M0: loads that follow each other in LDS share one address.
 template <int OFF = 0>
 __device__ __forceinline__ void dma16(const void* gptr, unsigned lds_off)
@@ -196,19 +197,15 @@ __device__ __forceinline__ void dma4(const void* gptr, unsigned lds_off)
 template <int OFF = 0>
 __device__ __forceinline__ void dma16_base(const void* sbase, unsigned voff, unsigned lds_off)
 {
-    const void* base;
-    asm volatile("s_add_u32 m0, %1, %2\n\ts_mov_b64 %0, %4\n\tglobal_load_lds_dwordx4 %3, %0"
-                 : "=&s"(base)
-                 : "s"(__builtin_amdgcn_readfirstlane(lds_off)), "n"(OFF), "v"(voff), "s"(sbase)
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3" ::"s"(__builtin_amdgcn_readfirstlane(lds_off)), "n"(OFF),
+                 "v"(voff), "s"(sbase)
                  : "memory", "scc");
 }
 template <int OFF = 0>
 __device__ __forceinline__ void dma4_base(const void* sbase, unsigned voff, unsigned lds_off)
 {
-    const void* base;
-    asm volatile("s_add_u32 m0, %1, %2\n\ts_mov_b64 %0, %4\n\tglobal_load_lds_dword %3, %0"
-                 : "=&s"(base)
-                 : "s"(__builtin_amdgcn_readfirstlane(lds_off)), "n"(OFF), "v"(voff), "s"(sbase)
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, %3" ::"s"(__builtin_amdgcn_readfirstlane(lds_off)), "n"(OFF),
+                 "v"(voff), "s"(sbase)
                  : "memory", "scc");
 }
 
@@ -233,13 +230,12 @@ __device__ __forceinline__ v4i buffer_base(const int8_t* p)
     return v4i{(int)__builtin_amdgcn_readfirstlane((uint32_t)v), (int)(__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) & 0xffff),
                (int)kOutside, 0x00020000};
 }
-template <int OFF>
+// VECTOR: `soff` may come out of a vector register just before.
+template <int OFF, bool VECTOR = false>
 __device__ __forceinline__ void dma_buf(v4i rsrc, unsigned voff, unsigned soff, unsigned lds_off)
 {
-    unsigned off;
-    asm volatile("s_add_u32 m0, %1, %2\n\ts_mov_b32 %0, %5\n\tbuffer_load_dwordx4 %3, %4, %0 offen lds"
-                 : "=&s"(off)
-                 : "s"(__builtin_amdgcn_readfirstlane(lds_off)), "n"(OFF), "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff))
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop %5\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds" ::"s"(__builtin_amdgcn_readfirstlane(lds_off)),
+                 "n"(OFF), "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff)), "n"(VECTOR ? 4 : 0)
                  : "memory", "scc");
 }
 
@@ -598,11 +594,13 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
         }
         if (DT == 1) n_q.off = n_q.off == prm.wwrap ? 0u : n_q.off;
     };
+    // (the 256 x 256 conv tile: its offsets live in vector registers)
+    constexpr bool FULL_SGPRS = CONV && BP == 256 && BQ == 256;
     // the idx-th of the DPS direct loads of the step set up by issue_begin()
     auto issue_one = [&](auto index) {
         constexpr int idx = decltype(index)::value;
         if constexpr (idx < LP) {
-            dma_buf<4096 * idx>(rsrcP, offP[idx], is_kP, is_base);
+            dma_buf<4096 * idx, FULL_SGPRS>(rsrcP, offP[idx], is_kP, is_base);
         } else if constexpr (LQ != 0) {
             constexpr int j = idx - LP;
             if constexpr (CONV) {
@@ -610,7 +608,7 @@ __global__ __launch_bounds__(256, MINW) void k_tmm(TmmParams prm)
                 if constexpr (BIG)
                     dma16<BP * 64 + 4096 * j>(out < 0 ? zero_page : gQ[j] + is_kQ, is_base);
                 else
-                    dma_buf<BP * 64 + 4096 * j>(rsrcQ, offQ[j] | ((unsigned)out & kOutside), is_kQ, is_base);
+                    dma_buf<BP * 64 + 4096 * j, FULL_SGPRS>(rsrcQ, offQ[j] | ((unsigned)out & kOutside), is_kQ, is_base);
             } else {
                 dma_buf<BP * 64 + 4096 * j>(rsrcQ, offQ[j], is_kQ, is_base);
             }
